@@ -25,57 +25,105 @@ namespace hbl {
 namespace {
 
 constexpr int kSumBlock = 256;
-constexpr int kSumItems = 16;  // floats per thread per block
+constexpr int kSumItems = 16;       // floats per thread and chunk
+constexpr int kChunk = kSumBlock * kSumItems;
+constexpr int kSumGrid = 2048;      // most workgroups of the sum = most partial sums
 
-// Eq. 1: partial sums of |W| in fp64, one per workgroup, fixed order inside the workgroup.
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+
+// Floats [4q, 4q + 4) of W.  VEC: W is 16-byte aligned; else four 4-byte loads of the same floats.  Only whole quads.
+template <bool VEC>
+__device__ __forceinline__ f32x4 load_quad(const float* __restrict__ W, int64_t q) {
+    if constexpr (VEC) return reinterpret_cast<const f32x4*>(W)[q];
+    else return f32x4{W[4 * q], W[4 * q + 1], W[4 * q + 2], W[4 * q + 3]};
+}
+
+// Sum of one fp64 value per thread over the workgroup, in a fixed order; every thread gets it.  `red`: a double per wave.
+__device__ __forceinline__ double workgroup_sum(double s, double* red) {
+#pragma unroll
+    for (int sft = 1; sft < 64; sft <<= 1) s += __shfl_xor(s, sft, 64);
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = s;
+    __syncthreads();
+    double t = red[0];
+#pragma unroll
+    for (int w = 1; w < kSumBlock / 64; ++w) t += red[w];
+    return t;
+}
+
+// Eq. 1: partial sums of |W| in fp64, one per workgroup, in an order that depends on the sizes alone.  Bound by the
+// read of W: a thread keeps four 16-byte loads in flight and walks chunks of 4096 floats (4096 x 16384 weights: 46 us =
+// 5.8 TB/s; with 4-byte loads and a workgroup per chunk it was 80 us, and one more launch of 17 us added 16384 sums).
+template <bool VEC>
 __global__ __launch_bounds__(kSumBlock) void abs_sum_partial_kernel(const float* __restrict__ W, int64_t count,
                                                                     double* __restrict__ partial) {
     __shared__ double red[kSumBlock / 64];
-    const int64_t base = (int64_t)blockIdx.x * (kSumBlock * kSumItems);
     double s = 0.0;
+    const int64_t chunks = count / kChunk;
+    for (int64_t c = blockIdx.x; c < chunks; c += gridDim.x) {
+        f32x4 w[kSumItems / 4];
 #pragma unroll
-    for (int i = 0; i < kSumItems; ++i) {
-        const int64_t idx = base + (int64_t)i * kSumBlock + threadIdx.x;
-        if (idx < count) s += (double)fabsf(W[idx]);
-    }
+        for (int i = 0; i < kSumItems / 4; ++i) w[i] = load_quad<VEC>(W, c * (kChunk / 4) + i * kSumBlock + threadIdx.x);
 #pragma unroll
-    for (int sft = 1; sft < 64; sft <<= 1) s += __shfl_xor(s, sft, 64);
-    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = s;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        double t = red[0];
-        for (int w = 1; w < kSumBlock / 64; ++w) t += red[w];
-        partial[blockIdx.x] = t;
+        for (int i = 0; i < kSumItems / 4; ++i)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) s += (double)fabsf(w[i][e]);
     }
+    if (blockIdx.x == 0)   // the floats beyond the last whole chunk
+        for (int64_t i = chunks * kChunk + threadIdx.x; i < count; i += kSumBlock) s += (double)fabsf(W[i]);
+    s = workgroup_sum(s, red);
+    if (threadIdx.x == 0) partial[blockIdx.x] = s;
 }
 
-// Final reduction by one workgroup (fixed order), alpha = (float)(sum / count).
-__global__ __launch_bounds__(256) void abs_mean_final_kernel(const double* __restrict__ partial, int64_t nparts,
-                                                             int64_t count, float* __restrict__ alpha) {
-    __shared__ double red[4];
-    double s = 0.0;
-    for (int64_t i = threadIdx.x; i < nparts; i += 256) s += partial[i];
-#pragma unroll
-    for (int sft = 1; sft < 64; sft <<= 1) s += __shfl_xor(s, sft, 64);
-    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = s;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        const double t = ((red[0] + red[1]) + red[2]) + red[3];
-        *alpha = (float)(t / (double)count);
+// Code of one weight: RoundClip(w / denom, -1, 1).  For a normal denom the rounded quotient fl(w / denom) exceeds 1/2
+// exactly when w > denom / 2: the next float above denom / 2 already lies more than half an ulp(1/2) of quotient
+// above 1/2, and 1/2 itself rounds to the even 0.  So two compares stand for the IEEE division, the rounding and
+// the clip.  (denom tiny, zero, negative, infinite or NaN: `divide`, the formula itself.)
+__device__ __forceinline__ uint32_t ternary_code(float w, float denom, float half, bool divide) {
+    if (divide) {
+        const float r = fminf(fmaxf(rintf(w / denom), -1.0f), 1.0f);
+        return (uint32_t)(uint8_t)(int8_t)(int)r;
     }
+    return w > half ? 0x01u : (w < -half ? 0xFFu : 0x00u);
 }
 
-// Eq. 1-2: codes = RoundClip(W / (alpha + eps), -1, 1).
-__global__ __launch_bounds__(256) void ternarize_kernel(const float* __restrict__ W, int64_t count,
-                                                        const float* __restrict__ alpha, float eps,
-                                                        int8_t* __restrict__ codes) {
-    const float denom = *alpha + eps;
-    const int64_t stride = (int64_t)gridDim.x * 256;
-    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < count; i += stride) {
-        float r = rintf(W[i] / denom);
-        r = fminf(fmaxf(r, -1.0f), 1.0f);
-        codes[i] = (int8_t)(int)r;
+// Eq. 1-2: alpha = mean |W| from the partial sums (each workgroup adds all of them, in one fixed order, so no launch
+// of its own is needed; at most 16 KiB out of L2), then codes = RoundClip(W / (alpha + eps), -1, 1).  The chunks are
+// walked from the end: the memory-side cache still holds the last ones that the sum has read (1 % of the three
+// launches).  4096 x 16384 weights: 55 us = 6.1 TB/s; one weight per step with a division and a byte store was 85 us.
+// VEC: W is 16-byte and codes 4-byte aligned.
+template <bool VEC>
+__global__ __launch_bounds__(kSumBlock) void ternarize_kernel(const float* __restrict__ W, int64_t count,
+                                                              const double* __restrict__ partial, int nparts, float eps,
+                                                              float* __restrict__ alpha, int8_t* __restrict__ codes) {
+    __shared__ double red[kSumBlock / 64];
+    double s = 0.0;
+    for (int i = threadIdx.x; i < nparts; i += kSumBlock) s += partial[i];
+    const float mean = (float)(workgroup_sum(s, red) / (double)count);
+    if (blockIdx.x == 0 && threadIdx.x == 0) *alpha = mean;
+    const float denom = mean + eps, half = 0.5f * denom;
+    const bool divide = !(denom >= 0x1p-100f && denom <= 0x1p100f);   // uniform
+    const int64_t chunks = count / kChunk;
+    for (int64_t c = chunks - 1 - blockIdx.x; c >= 0; c -= gridDim.x) {
+        f32x4 w[kSumItems / 4];
+#pragma unroll
+        for (int i = 0; i < kSumItems / 4; ++i) w[i] = load_quad<VEC>(W, c * (kChunk / 4) + i * kSumBlock + threadIdx.x);
+#pragma unroll
+        for (int i = 0; i < kSumItems / 4; ++i) {
+            const int64_t q = c * (kChunk / 4) + i * kSumBlock + threadIdx.x;
+            uint32_t b[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) b[e] = ternary_code(w[i][e], denom, half, divide);
+            if constexpr (VEC) {
+                reinterpret_cast<uint32_t*>(codes)[q] = b[0] | (b[1] << 8) | (b[2] << 16) | (b[3] << 24);
+            } else {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) codes[4 * q + e] = (int8_t)b[e];
+            }
+        }
     }
+    if (blockIdx.x == gridDim.x - 1)
+        for (int64_t i = chunks * kChunk + threadIdx.x; i < count; i += kSumBlock)
+            codes[i] = (int8_t)ternary_code(W[i], denom, half, divide);
 }
 
 // dword d of the packed stream -> (row, first feature) of its 16 weights
@@ -109,46 +157,69 @@ __global__ __launch_bounds__(256) void unpack_kernel(const uint32_t* __restrict_
     *reinterpret_cast<uint4*>(codes + row * K + k0) = raw;
 }
 
-__global__ __launch_bounds__(256) void pack_kernel(const int8_t* __restrict__ codes, int64_t N, int64_t K,
-                                                      uint32_t* __restrict__ packed) {
-    const int64_t total = (N / 32) * (K / 128) * 256;  // dwords
-    const int64_t d = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (d >= total) return;
-    int64_t row, k0;
-    packed_dword_origin(d, N, &row, &k0);
-    const uint4 raw = *reinterpret_cast<const uint4*>(codes + row * K + k0);
-    const int8_t* c = reinterpret_cast<const int8_t*>(&raw);
-    uint32_t out = 0;
-#pragma unroll
-    for (int n = 0; n < 8; ++n) {
-        const int a = c[n], b = c[8 + n];
-        out |= (uint32_t)(a != 0) << (4 * n + 1);
-        out |= (uint32_t)(a < 0) << (4 * n + 3);
-        out |= (uint32_t)(b != 0) << (4 * n);
-        out |= (uint32_t)(b < 0) << (4 * n + 2);
-    }
-    packed[d] = out;
+// Four codes (one byte each) -> their four nibbles: magnitude (code != 0) at bit 1, sign (code < 0) at bit 3.
+__device__ __forceinline__ uint32_t weight_nibbles(uint32_t c) {
+    const uint32_t nonzero = (((c & 0x7F7F7F7Fu) + 0x7F7F7F7Fu) | c) & 0x80808080u;
+    uint32_t v = (nonzero >> 6) | ((c & 0x80808080u) >> 4);
+    v = (v | (v >> 4)) & 0x00FF00FFu;
+    return (v | (v >> 8)) & 0xFFFFu;
 }
 
-// Row sums of the ternary codes, sum_k c[o][k], one wave per output row.
-__global__ __launch_bounds__(256) void row_sum_kernel(const int8_t* __restrict__ codes, int64_t N, int64_t K,
-                                                      int32_t* __restrict__ row_sum) {
-    const int64_t row = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-    if (row >= N) return;
-    const int lane = threadIdx.x & 63;
-    int s = 0;
-    for (int64_t k = lane * 16; k < K; k += 64 * 16) {
-        const uint4 raw = *reinterpret_cast<const uint4*>(codes + row * K + k);
-        const int8_t* c = reinterpret_cast<const int8_t*>(&raw);
+// Packs eight output rows and adds up their codes.  A wave reads 8 rows x 128 features per load (eight whole
+// 128-byte lines), a lane's 16 codes are one packed dword, and the wave's store is two pieces of 128 bytes of the
+// tile; the waves of the workgroup take the K-blocks in turn.  The row sums sum_k c[o][k] come from the same read.
+// Bound by the read of the codes: 16 us for 4096 x 16384 (5.2 TB/s; 8 loads in flight measured the same); with
+// scattered 16-byte loads and a launch of its own for the row sums it was 22 + 13 us.
+constexpr int kPackRows = 8, kPackWaves = 8, kPackAhead = 4;   // rows per workgroup, most waves, loads in flight per wave
+__global__ __launch_bounds__(64 * kPackWaves) void pack_kernel(const int8_t* __restrict__ codes, int64_t N, int64_t K,
+                                                               uint32_t* __restrict__ packed,
+                                                               int32_t* __restrict__ row_sum) {
+    __shared__ int red[kPackWaves][kPackRows];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, waves = blockDim.x >> 6;
+    const int nkb = (int)(K / 128);
+    const int64_t row = (int64_t)blockIdx.x * kPackRows + (lane >> 3);
+    const int chunk = lane & 7;   // 16 features
+    // dword j of tile lane l covers features 64 (j >> 1) + 32 (l >> 5) + 16 (j & 1) + 0..15 of row l & 31
+    const int dword = ((int)(row & 31) + 32 * ((chunk >> 1) & 1)) * 4 + 2 * (chunk >> 2) + (chunk & 1);
+    const int8_t* src = codes + row * K + chunk * 16;
+    uint32_t* dst = packed + (row / 32) * 256 + dword;
+    const int64_t kb_stride = (N / 32) * 256;
+    int sum = 0;
+    for (int kb = wave; kb < nkb; kb += waves * kPackAhead) {
+        uint4 c[kPackAhead];
 #pragma unroll
-        for (int i = 0; i < 16; ++i) s += c[i];
+        for (int u = 0; u < kPackAhead; ++u) {
+            c[u] = make_uint4(0, 0, 0, 0);
+            if (kb + u * waves < nkb) c[u] = *reinterpret_cast<const uint4*>(src + (int64_t)(kb + u * waves) * 128);
+        }
+#pragma unroll
+        for (int u = 0; u < kPackAhead; ++u) {
+            sum = __builtin_amdgcn_sdot4((int)c[u].x, 0x01010101, sum, false);
+            sum = __builtin_amdgcn_sdot4((int)c[u].y, 0x01010101, sum, false);
+            sum = __builtin_amdgcn_sdot4((int)c[u].z, 0x01010101, sum, false);
+            sum = __builtin_amdgcn_sdot4((int)c[u].w, 0x01010101, sum, false);
+            // weights 0..7 of the dword at bits 1 and 3 of a nibble, weights 8..15 at bits 0 and 2
+            const uint32_t a = weight_nibbles(c[u].x) | (weight_nibbles(c[u].y) << 16);
+            const uint32_t b = weight_nibbles(c[u].z) | (weight_nibbles(c[u].w) << 16);
+            if (kb + u * waves < nkb) dst[(int64_t)(kb + u * waves) * kb_stride] = a | (b >> 1);
+        }
     }
 #pragma unroll
-    for (int sft = 1; sft < 64; sft <<= 1) s += __shfl_xor(s, sft, 64);
-    if (lane == 0) row_sum[row] = s;
+    for (int m = 1; m < 8; m <<= 1) sum += __shfl_xor(sum, m, 64);
+    if (chunk == 0) red[wave][lane >> 3] = sum;
+    __syncthreads();
+    if (threadIdx.x < kPackRows) {
+        int t = 0;
+        for (int w = 0; w < waves; ++w) t += red[w][threadIdx.x];
+        row_sum[(int64_t)blockIdx.x * kPackRows + threadIdx.x] = t;
+    }
 }
 
-int64_t sum_blocks(int64_t count) { return (count + kSumBlock * kSumItems - 1) / (kSumBlock * kSumItems); }
+// Workgroups (= partial sums) of the absolute sum.
+int64_t sum_blocks(int64_t count) {
+    const int64_t chunks = (count + kChunk - 1) / kChunk;
+    return chunks < kSumGrid ? chunks : kSumGrid;
+}
 
 }  // namespace
 
@@ -157,27 +228,24 @@ size_t ternarize_workspace_bytes(int64_t count) { return round_up((size_t)sum_bl
 int launch_ternarize(const float* W, int64_t count, float eps, int8_t* codes, float* alpha, void* workspace,
                      hipStream_t stream) {
     double* partial = static_cast<double*>(workspace);
-    const int64_t nb = sum_blocks(count);
-    launch_kernel("abs_sum_partial_kernel", abs_sum_partial_kernel, dim3((unsigned)nb), dim3(kSumBlock), 0, stream, W, count, partial);
-    int rc = after_launch();
+    const int nb = (int)sum_blocks(count);
+    // any float-aligned W and any codes pointer are taken; the wide accesses need 16 and 4 bytes
+    const bool wide_in = aligned16(W), wide = wide_in && (reinterpret_cast<uintptr_t>(codes) & 3u) == 0;
+    if (wide_in) launch_kernel("abs_sum_partial_kernel", abs_sum_partial_kernel<true>, dim3(nb), dim3(kSumBlock), 0, stream, W, count, partial);
+    else launch_kernel("abs_sum_partial_kernel", abs_sum_partial_kernel<false>, dim3(nb), dim3(kSumBlock), 0, stream, W, count, partial);
+    const int rc = after_launch();
     if (rc != HBL_OK) return rc;
-    launch_kernel("abs_mean_final_kernel", abs_mean_final_kernel, dim3(1), dim3(256), 0, stream, partial, nb, count, alpha);
-    rc = after_launch();
-    if (rc != HBL_OK) return rc;
-    int64_t blocks = (count + 255) / 256;
-    if (blocks > 16384) blocks = 16384;
-    launch_kernel("ternarize_kernel", ternarize_kernel, dim3((unsigned)blocks), dim3(256), 0, stream, W, count, alpha, eps, codes);
+    if (wide) launch_kernel("ternarize_kernel", ternarize_kernel<true>, dim3(nb), dim3(kSumBlock), 0, stream, W, count, partial, nb, eps, alpha, codes);
+    else launch_kernel("ternarize_kernel", ternarize_kernel<false>, dim3(nb), dim3(kSumBlock), 0, stream, W, count, partial, nb, eps, alpha, codes);
     return after_launch();
 }
 
 int launch_pack(const int8_t* codes, int64_t N, int64_t K, void* packed, hipStream_t stream) {
-    const int64_t total = (N / 32) * (K / 128) * 256;
-    launch_kernel("pack_kernel", pack_kernel, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, stream, codes, N, K,
-                  static_cast<uint32_t*>(packed));
-    int rc = after_launch();
-    if (rc != HBL_OK) return rc;
     int32_t* row_sum = reinterpret_cast<int32_t*>(static_cast<char*>(packed) + packed_tile_bytes(N, K));
-    launch_kernel("row_sum_kernel", row_sum_kernel, dim3((unsigned)((N + 3) / 4)), dim3(256), 0, stream, codes, N, K, row_sum);
+    const int64_t nkb = K / 128;
+    const int waves = nkb < kPackWaves ? (int)nkb : kPackWaves;
+    launch_kernel("pack_kernel", pack_kernel, dim3((unsigned)(N / kPackRows)), dim3(64 * waves), 0, stream, codes, N, K,
+                  static_cast<uint32_t*>(packed), row_sum);
     return after_launch();
 }
 

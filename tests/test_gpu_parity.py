@@ -127,6 +127,56 @@ def test_ternarize_odd_sizes_and_scale(hbl):
         assert np.array_equal(c_dev.cpu().numpy(), c_ref), shape
 
 
+@pytest.mark.parametrize("count,offset", [(4095, 0), (4096, 1), (4097, 0), (3 * 4096 + 5, 3), (2049 * 4096 + 3, 0),
+                                          (2050 * 4096, 2)])
+def test_ternarize_chunk_edges_and_alignment(hbl, count, offset):
+    """Chunks of 4096 weights: remainders, more chunks than the sum has workgroups, and weights / codes that start
+    off a 16-byte (4-byte) boundary, which take the narrow loads and stores."""
+    note(f"ternarize count={count} offset={offset}")
+    W = (np.random.default_rng(count).standard_normal(count) * 0.02).astype(np.float32)
+    c_ref, a_ref = O.ternarize_weights_absmean(W[None, :], EPS)
+    buf = torch.zeros(count + offset, device="cuda")
+    buf[offset:] = torch.from_numpy(W).cuda()
+    codes = torch.zeros(count + offset, dtype=torch.int8, device="cuda")
+    alpha = torch.zeros(1, device="cuda")
+    ws = torch.empty(hbl.lib().hbl_ternarize_workspace_bytes(1, count), dtype=torch.uint8, device="cuda")
+    rc = hbl.lib().hbl_ternarize_weights_absmean(buf.data_ptr() + 4 * offset, 1, count, EPS, codes.data_ptr() + offset,
+                                                 alpha.data_ptr(), ws.data_ptr(), ws.numel(), hbl._stream())
+    assert rc == 0
+    assert alpha.cpu().numpy()[0] == a_ref
+    assert np.array_equal(codes.cpu().numpy()[offset:], c_ref[0]) and not codes[:offset].any()
+
+
+@pytest.mark.parametrize("eps", [EPS, 0.0])
+@pytest.mark.parametrize("v", [1.0, 0.3, 1.7e-5, 3.1e33, 2e-40])
+def test_ternarize_codes_at_the_rounding_boundary(hbl, v, eps):
+    """Weights within a few ulps of (alpha + eps) / 2, where the code changes between 0 and +-1, and denominators too
+    small or too large for the compare form: the same codes as dividing, rounding and clipping."""
+    note(f"ternarize boundary v={v} eps={eps}")
+    v = np.float32(v)
+    w = np.float32(v / 3 + 2 * np.float64(eps) / 3)      # half of the tensor v, half w: (v + w) / 2 + eps = 2 w
+    for steps in range(-4, 5):
+        u = w
+        for _ in range(abs(steps)):
+            u = np.nextafter(u, np.float32(np.inf if steps > 0 else -np.inf), dtype=np.float32)
+        W = np.where(np.arange(512) % 2 == 0, v, u).astype(np.float32)
+        W[np.arange(512) % 3 == 0] *= -1
+        c_ref, a_ref = O.ternarize_weights_absmean(W[None, :], eps)
+        c_dev, a_dev = hbl.ternarize_weights_absmean(torch.from_numpy(W[None, :]).cuda(), eps)
+        assert a_dev.cpu().numpy()[0] == a_ref, steps
+        assert np.array_equal(c_dev.cpu().numpy(), c_ref), steps
+
+
+@pytest.mark.parametrize("N,K", [(32, 16384), (64, 4224), (2080, 1152)])
+def test_pack_k_block_rounds(hbl, N, K):
+    """128, 33 and 9 K-blocks: full and partial rounds of the waves that share a row group's K range."""
+    note(f"pack N={N} K={K}")
+    codes = torch.randint(-1, 2, (N, K), dtype=torch.int8, device="cuda")
+    packed = hbl.pack_ternary_2bit(codes)
+    assert torch.equal(packed[N * K // 4:].view(torch.int32), codes.to(torch.int32).sum(1, dtype=torch.int32))
+    assert torch.equal(hbl.unpack_ternary_2bit(packed, N, K), codes)
+
+
 # ------------------------------------------------------------------ activation front end
 ALL_K = [128, 256, 512, 1024, 2048, 4096, 8192, 16384]
 
