@@ -261,10 +261,10 @@ int hbl_gemm_i32(const int8_t* codes, int64_t T, int64_t K, const void* Wq_packe
  * The same contraction on the fp6 x fp4 prefill kernel, the one every INT4 forward call with T > 64 and
  * K >= 512 runs: acc[t][o] = sum_k q[t][k] * c[o][k] as int32 [T, N], read out of that kernel's fp32
  * accumulators (exact integers) with no dequantisation, in the launch configuration (workgroup tile,
- * K split over workgroups at mid-size batches) hbl_hbitlinear_forward takes for the same T, K, N.
+ * K cut over the waves of a workgroup at mid-size batches) hbl_hbitlinear_forward takes for the same T, K, N.
  *   code_records  [T, K] bytes of HBL_CODES_BF6 records as written by hbl_fwht_quant (K >= 512)
- *   workspace     device, >= hbl_workspace_bytes(T, K, N, 4), 256-byte aligned (holds the int32 partial
- *                 tiles when the K range is split; the code region of it is not touched)
+ *   workspace     device, >= hbl_workspace_bytes(T, K, N, 4), 256-byte aligned (not touched by the
+ *                 present kernels)
  */
 int hbl_gemm_i32_bf6(const void* code_records, int64_t T, int64_t K, const void* Wq_packed, int64_t N,
                      int32_t* acc, void* workspace, size_t workspace_bytes, void* stream);

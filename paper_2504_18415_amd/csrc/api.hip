@@ -131,7 +131,7 @@ int forward(const void* x, int x_dtype, int64_t T, int64_t K, const void* Wq_pac
     }
     // INT4 at prefill sizes: bf6 code records and the fp6 x fp4 matrix cores (exact, twice the int8 MFMA rate)
     if (code_form == kCodesBf6)
-        return launch_ternary_gemm_f6f4(ws.codes, T, K, Wq_packed, N, ws.s_dequant, w_scales, groups, y, s, ws.partial);
+        return launch_ternary_gemm_f6f4(ws.codes, T, K, Wq_packed, N, ws.s_dequant, w_scales, groups, y, s);
     return launch_ternary_gemm(ws.codes, code_form, T, K, Wq_packed, N, ws.s_dequant, w_scales, groups, y, nullptr,
                                ws.partial, s);
 }
@@ -453,13 +453,12 @@ int hbl_gemm_i32_bf6(const void* code_records, int64_t T, int64_t K, const void*
         (reinterpret_cast<uintptr_t>(workspace) & 255u) != 0)
         return HBL_E_ALIGN;
     if (workspace_bytes < hbl_workspace_bytes(T, K, N, 4)) return HBL_E_WORKSPACE;
-    const Workspace ws = carve_workspace(workspace, T, K, N);
     return launch_ternary_gemm_f6f4(static_cast<const int8_t*>(code_records), T, K, Wq_packed, N, nullptr, nullptr, 1,
-                                    nullptr, static_cast<hipStream_t>(stream), T > 64 ? ws.partial : nullptr, acc);
+                                    nullptr, static_cast<hipStream_t>(stream), acc);
 }
 
 int hbl_test_gemm_i32_tile(const void* codes, int code_form, int64_t T, int64_t K, const void* Wq_packed, int64_t N,
-                           int32_t* acc, int tile, void* partial, size_t partial_bytes, void* stream) {
+                           int32_t* acc, int tile, void* partial, size_t, void* stream) {
     if (code_form != HBL_CODES_INT8 && code_form != HBL_CODES_BF6) return HBL_E_BITS;
     if (tile < kTileSquare || tile > kTileSplitK) return HBL_E_SHAPE;
     int rc = check_gemm_shape(T, K, N, false);
@@ -468,17 +467,11 @@ int hbl_test_gemm_i32_tile(const void* codes, int code_form, int64_t T, int64_t 
     if (!codes || !Wq_packed || !acc) return HBL_E_NULL;
     if (!aligned16(codes) || !aligned16(Wq_packed) || !aligned16(acc) || !aligned16(partial)) return HBL_E_ALIGN;
     hipStream_t s = static_cast<hipStream_t>(stream);
-    if (tile == kTileSplitK) {
-        // the K cut the launcher will take: the forward's own for this shape, else 4 (or 2) slices
-        if (code_form != HBL_CODES_BF6) return HBL_E_SHAPE;
-        int split = prefill_split_k(T, K, N);
-        if (split == 1) split = (K / 128) % 4 == 0 ? 4 : ((K / 128) % 2 == 0 ? 2 : 1);
-        if (!partial || partial_bytes < (size_t)split * T * N * sizeof(int32_t)) return HBL_E_WORKSPACE;
-    }
+    if (tile == kTileSplitK && code_form != HBL_CODES_BF6) return HBL_E_SHAPE;
+    if (tile == kTileSplitK && !partial) return HBL_E_WORKSPACE;
     if (code_form == HBL_CODES_BF6)
         return launch_ternary_gemm_f6f4(static_cast<const int8_t*>(codes), T, K, Wq_packed, N, nullptr, nullptr, 1,
-                                        nullptr, s, tile == kTileSplitK ? static_cast<int32_t*>(partial) : nullptr, acc,
-                                        tile);
+                                        nullptr, s, acc, tile);
     return launch_ternary_gemm(static_cast<const int8_t*>(codes), 0, T, K, Wq_packed, N, nullptr, nullptr, 1, nullptr,
                                acc, nullptr, s, tile);
 }

@@ -29,7 +29,6 @@ namespace {
 
 using namespace gemm;
 typedef int v16i __attribute__((ext_vector_type(16)));
-typedef int v8i __attribute__((ext_vector_type(8)));
 typedef float v4f __attribute__((ext_vector_type(4)));
 typedef float v16f __attribute__((ext_vector_type(16)));
 
@@ -45,21 +44,6 @@ __device__ __forceinline__ void lds_dma16_first48(uint32_t lds_addr, const void*
         : "=&s"(saved)
         : "s"(lds_addr), "v"(voff), "s"(base)
         : "memory", "m0");
-}
-
-// Two packed dwords (32 weights) -> the four fp4 operand registers of a lane.
-__device__ __forceinline__ v8i fp4_operand(uint32_t p0, uint32_t p1) {
-    return v8i{(int)(p0 & 0xAAAAAAAAu), (int)((p0 << 1) & 0xAAAAAAAAu), (int)(p1 & 0xAAAAAAAAu),
-               (int)((p1 << 1) & 0xAAAAAAAAu), 0, 0, 0, 0};
-}
-
-typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-typedef float f32x2 __attribute__((ext_vector_type(2)));
-// y = bf16((acc * s_d) * alpha) for four consecutive features; acc holds exact integers.
-__device__ __forceinline__ uint2 dequant_quad_f32(float a0, float a1, float a2, float a3, float sd, float alpha) {
-    const bf16x2 lo = __builtin_convertvector((f32x2){(a0 * sd) * alpha, (a1 * sd) * alpha}, bf16x2);
-    const bf16x2 hi = __builtin_convertvector((f32x2){(a2 * sd) * alpha, (a3 * sd) * alpha}, bf16x2);
-    return make_uint2(__builtin_bit_cast(uint32_t, lo), __builtin_bit_cast(uint32_t, hi));
 }
 
 // NW = waves per workgroup.  Four everywhere except the streaming form on a single long-K problem with few row

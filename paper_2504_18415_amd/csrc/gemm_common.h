@@ -59,6 +59,10 @@ struct GemmArgs {
     int32_t* partial;
 };
 
+// The mid-size form of the fp6 x fp4 GEMM (mid_gemm.hip); a.y, or the raw sums where a.acc_out is set.
+bool mid_gemm_preferred(int64_t T, int64_t N);
+int launch_mid_gemm_f6f4(const GemmArgs& a, hipStream_t stream);
+
 // Second launch of a split-K GEMM (ternary_gemm.hip): adds the split_k int32 partial tiles and dequantises.
 int launch_splitk_reduce(const GemmArgs& a, hipStream_t stream);
 
@@ -115,6 +119,23 @@ __device__ __forceinline__ uint2 dequant_quad(v4i acc, float sd, float alpha, in
     if (code_offset != 0) ws = *reinterpret_cast<const v4i*>(w_row_sum);
     return dequant_quad_sums(acc, sd, alpha, code_offset, ws);
 }
+
+typedef int v8i __attribute__((ext_vector_type(8)));
+// Two packed dwords (32 weights) -> the four fp4 operand registers of a lane.
+__device__ __forceinline__ v8i fp4_operand(uint32_t p0, uint32_t p1) {
+    return v8i{(int)(p0 & 0xAAAAAAAAu), (int)((p0 << 1) & 0xAAAAAAAAu), (int)(p1 & 0xAAAAAAAAu),
+               (int)((p1 << 1) & 0xAAAAAAAAu), 0, 0, 0, 0};
+}
+
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+// y = bf16((acc * s_d) * alpha) for four consecutive features; acc holds exact integers.
+__device__ __forceinline__ uint2 dequant_quad_f32(float a0, float a1, float a2, float a3, float sd, float alpha) {
+    const bf16x2 lo = __builtin_convertvector((f32x2){(a0 * sd) * alpha, (a1 * sd) * alpha}, bf16x2);
+    const bf16x2 hi = __builtin_convertvector((f32x2){(a2 * sd) * alpha, (a3 * sd) * alpha}, bf16x2);
+    return make_uint2(__builtin_bit_cast(uint32_t, lo), __builtin_bit_cast(uint32_t, hi));
+}
+
 
 // WAVES_N x WAVES_T waves; each wave owns TN x TT MFMA tiles (32 features x 32 tokens each).
 // LDS stage = [BT tokens x 128 B codes, XOR-swizzled][BN/32 packed weight tiles x 1 KiB].

@@ -108,11 +108,11 @@ inline int decode_split_k(int64_t T, int64_t K, int64_t N) {
 
 // Layout of the forward workspace: codes (one byte per code [T,K], or the record image) | float s_dequant [T],
 // and | int32 partial [split_k][T][N] for T <= 64 or a split K range.
-// K split of the fp6 x fp4 prefill GEMM at mid-size batches: between 65 tokens and about a thousand a long-K
-// projection has too few output tiles (128 x 128) to give most CUs a workgroup, so the K range is cut until about
+// K split of the int8 prefill GEMM at mid-size batches (INT8 activations): between 65 tokens and about a thousand a
+// long-K projection has too few output tiles (128 x 128) to give most CUs a workgroup, so the K range is cut until about
 // 256 workgroups exist, each keeping at least 8 K-blocks of 128; the int32 partial tiles then take one more launch.
 // Only for K >= 8192: at K = 4096 the unsplit call is short already and the extra launch costs more than it saves
-// (measured: W_down at 96-512 tokens 48-52 us -> 26-45 us; K = 4096 projections 18-20 us -> 21-29 us).
+// (W_down at 96-512 tokens: 48-52 us -> 29-55 us).
 inline int prefill_split_k(int64_t T, int64_t K, int64_t N) {
     if (T <= 64 || K < 8192) return 1;
     const int64_t tiles = ((N + 127) / 128) * ((T + 127) / 128), nkb = K / 128;
@@ -188,7 +188,7 @@ int launch_fwht_only(const void* x, int x_dtype, int64_t T, int64_t K, void* out
 // Workgroup tiles of the two prefill GEMM kernels.  kTileAuto is the choice every forward call makes from the
 // shape; the others let the parity tests run a given tile on a shape of their own.
 constexpr int kTileAuto = -1, kTileSquare = 0 /*256 x 256*/, kTileSmall = 1 /*128 x 128*/,
-              kTileWide = 2 /*512 features x 128 tokens*/, kTileSplitK = 3 /*128 x 128, K cut over workgroups*/;
+              kTileWide = 2 /*512 features x 128 tokens*/, kTileSplitK = 3 /*mid-size form, K cut over the waves*/;
 
 // GEMM + epilogue. If acc_out != nullptr the raw int32 accumulators are written
 // (no scales, no code_sum needed); otherwise y (bf16) is written.
@@ -201,8 +201,7 @@ int launch_ternary_gemm(const int8_t* codes, int code_offset, int64_t T, int64_t
 // acc_out != nullptr: the raw accumulators as int32 [T, N] instead of y.
 int launch_ternary_gemm_f6f4(const int8_t* code_records, int64_t T, int64_t K, const void* packed, int64_t N,
                              const float* s_dequant, const float* w_scales, int64_t n_scale_groups, void* y_bf16,
-                             hipStream_t stream, int32_t* splitk_partial = nullptr, int32_t* acc_out = nullptr,
-                             int tile = kTileAuto);
+                             hipStream_t stream, int32_t* acc_out = nullptr, int tile = kTileAuto);
 
 // ---------------------------------------------------------------------------------------------
 // Grouped small-batch path: up to kMaxGroup independent projections (T <= 64 each) served by one

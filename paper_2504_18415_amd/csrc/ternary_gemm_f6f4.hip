@@ -23,15 +23,11 @@ namespace hbl {
 namespace {
 
 using namespace gemm;
-typedef int v8i __attribute__((ext_vector_type(8)));
 typedef float v16f __attribute__((ext_vector_type(16)));
 
-// SPLIT: workgroup (tile, ks) covers K-blocks [ks * nkb/split_k, (ks+1) * nkb/split_k) and leaves its accumulators,
-// converted to int32 (they are exact integers), in partial[ks][T][N] for the reduction launch.
 // RAW: the accumulators themselves leave the kernel, as int32 [T, N] (acc_out), with no dequantisation: the
-// export the parity tests compare with the integer contraction of Eq. 7 bit for bit.  With SPLIT the partial
-// tiles are int32 either way and the reduction launch writes their sum undequantised.
-template <int WAVES_N, int WAVES_T, int TN, int TT, int NSTAGE, bool SPLIT = false, bool RAW = false>
+// export the parity tests compare with the integer contraction of Eq. 7 bit for bit.
+template <int WAVES_N, int WAVES_T, int TN, int TT, int NSTAGE, bool RAW = false>
 __global__ __launch_bounds__(64 * WAVES_N * WAVES_T) void ternary_gemm_f6f4_kernel(const GemmArgs a) {
     constexpr int NW = WAVES_N * WAVES_T;
     constexpr int BN = WAVES_N * TN * 32;
@@ -57,21 +53,13 @@ __global__ __launch_bounds__(64 * WAVES_N * WAVES_T) void ternary_gemm_f6f4_kern
 
     // each XCD gets a contiguous run of tiles, feature tile fastest (workgroups are dealt round-robin)
     int wg = blockIdx.x;
-    int ks = 0;
     const int nwg = a.tiles_n * a.tiles_t;
-    if constexpr (SPLIT) {
-        ks = wg % a.split_k;
-        wg = wg / a.split_k;
-    } else {
-        if ((nwg & 7) == 0) wg = (wg & 7) * (nwg >> 3) + (wg >> 3);
-    }
+    if ((nwg & 7) == 0) wg = (wg & 7) * (nwg >> 3) + (wg >> 3);
     const int tile_n = wg % a.tiles_n;
     const int tile_t = wg / a.tiles_n;
     const int n0 = tile_n * BN;
     const int t0 = tile_t * BT;
-    const int nkb_total = a.K / kBK;
-    const int nkb = SPLIT ? nkb_total / a.split_k : nkb_total;   // K-blocks of this workgroup
-    const int kb0 = ks * nkb;
+    const int nkb = a.K / kBK;
 
     // (K-block-major tiles: a stage's BN/32 tiles of this workgroup are consecutive KiB)
     const size_t wstride = (size_t)(a.N / 32) * 1024;
@@ -81,14 +69,14 @@ __global__ __launch_bounds__(64 * WAVES_N * WAVES_T) void ternary_gemm_f6f4_kern
         int nt = n0 / 32 + wave + NW * m;
         const int nt_max = a.N / 32 - 1;
         nt = nt < nt_max ? nt : nt_max;
-        wbase[m] = reinterpret_cast<const char*>(a.packed) + (size_t)kb0 * wstride + (size_t)nt * 1024;
+        wbase[m] = reinterpret_cast<const char*>(a.packed) + (size_t)nt * 1024;
     }
     const uint32_t wlane = lane * 16;
     // codes: the stage's panel blocks (one per 128 tokens of the tile, 12 KiB each, contiguous in the record
     // image) are copied as they are, piece q = 1 KiB; piece q of this wave belongs to panel q / 12
     const char* xbase = reinterpret_cast<const char*>(a.codes) +
-                        ((size_t)(t0 / kPanelTokens) * nkb_total + kb0) * kRecordBlockBytes;
-    const size_t panel_stride = (size_t)nkb_total * kRecordBlockBytes;
+                        (size_t)(t0 / kPanelTokens) * nkb * kRecordBlockBytes;
+    const size_t panel_stride = (size_t)nkb * kRecordBlockBytes;
     const char* xpiece[XL];
 #pragma unroll
     for (int m = 0; m < XL; ++m) {
@@ -256,7 +244,7 @@ __global__ __launch_bounds__(64 * WAVES_N * WAVES_T) void ternary_gemm_f6f4_kern
     // (the epilogue's scales are requested first, so that their latency passes under the drain: behind the
     // scheduling fences of the epilogue every one of them would cost its whole round trip)
     float sd_of[TT], alpha_of[TN];
-    if (!RAW && !(SPLIT && a.split_k > 1)) {   // (the int32 forms have no scales: the pointers may be null)
+    if (!RAW) {   // (the int32 form has no scales: the pointers may be null)
 #pragma unroll
         for (int j = 0; j < TT; ++j) {
             const int t = t0 + (wt * TT + j) * 32 + (lane & 31);
@@ -271,25 +259,22 @@ __global__ __launch_bounds__(64 * WAVES_N * WAVES_T) void ternary_gemm_f6f4_kern
     }
     asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
 
-    if constexpr (SPLIT || RAW) {
-        if (RAW || a.split_k > 1) {   // int32 tiles, stored from where the accumulators are
-            int32_t* const out = (SPLIT && a.split_k > 1) ? a.partial + (size_t)ks * a.T * a.N : a.acc_out;
+    if constexpr (RAW) {   // int32 tiles, stored from where the accumulators are
 #pragma unroll
-            for (int i = 0; i < TN; ++i)
+        for (int i = 0; i < TN; ++i)
 #pragma unroll
-                for (int j = 0; j < TT; ++j) {
-                    __builtin_amdgcn_sched_barrier(0);   // one accumulator tile at a time (register pressure)
-                    const int t = t0 + (wt * TT + j) * 32 + (lane & 31);
+            for (int j = 0; j < TT; ++j) {
+                __builtin_amdgcn_sched_barrier(0);   // one accumulator tile at a time (register pressure)
+                const int t = t0 + (wt * TT + j) * 32 + (lane & 31);
 #pragma unroll
-                    for (int g = 0; g < 4; ++g) {
-                        const int n = n0 + (wn * TN + i) * 32 + 8 * g + 4 * (lane >> 5);
-                        const v4i o = {(int)acc[i][j][4 * g], (int)acc[i][j][4 * g + 1], (int)acc[i][j][4 * g + 2],
-                                       (int)acc[i][j][4 * g + 3]};
-                        if (t < a.T && n < a.N) *reinterpret_cast<v4i*>(out + (size_t)t * a.N + n) = o;
-                    }
+                for (int g = 0; g < 4; ++g) {
+                    const int n = n0 + (wn * TN + i) * 32 + 8 * g + 4 * (lane >> 5);
+                    const v4i o = {(int)acc[i][j][4 * g], (int)acc[i][j][4 * g + 1], (int)acc[i][j][4 * g + 2],
+                                   (int)acc[i][j][4 * g + 3]};
+                    if (t < a.T && n < a.N) *reinterpret_cast<v4i*>(a.acc_out + (size_t)t * a.N + n) = o;
                 }
-            return;
-        }
+            }
+        return;
     }
 
     // Epilogue.  A lane holds token (lane & 31) of a 32 x 32 tile, register quad g holding features
@@ -345,29 +330,26 @@ __global__ __launch_bounds__(64 * WAVES_N * WAVES_T) void ternary_gemm_f6f4_kern
     }
 }
 
-template <int WAVES_N, int WAVES_T, int TN, int TT, int NSTAGE, bool SPLIT = false, bool RAW = false>
+template <int WAVES_N, int WAVES_T, int TN, int TT, int NSTAGE, bool RAW = false>
 int launch_cfg(GemmArgs a, hipStream_t stream) {
     constexpr int BN = WAVES_N * TN * 32;
     constexpr int BT = WAVES_T * TT * 32;
     constexpr size_t lds = (size_t)NSTAGE * (BT * kRecordRowBytes + (BN / 32) * 1024);
     a.tiles_n = (a.N + BN - 1) / BN;
     a.tiles_t = (a.T + BT - 1) / BT;
-    if (!SPLIT) a.split_k = 1;
-    auto kern = ternary_gemm_f6f4_kernel<WAVES_N, WAVES_T, TN, TT, NSTAGE, SPLIT, RAW>;
+    auto kern = ternary_gemm_f6f4_kernel<WAVES_N, WAVES_T, TN, TT, NSTAGE, RAW>;
     static std::atomic<uint64_t> lds_allowed{0};   // per instantiation: devices already set up
     if (const int rc = allow_dynamic_lds(kern, lds, lds_allowed); rc != HBL_OK) return rc;
-    launch_kernel("ternary_gemm_f6f4_kernel", kern, dim3((unsigned)(a.tiles_n * a.tiles_t * a.split_k)), dim3(64 * WAVES_N * WAVES_T), lds,
+    launch_kernel("ternary_gemm_f6f4_kernel", kern, dim3((unsigned)(a.tiles_n * a.tiles_t)), dim3(64 * WAVES_N * WAVES_T), lds,
                        stream, a);
-    const int rc = after_launch();
-    if (rc != HBL_OK || a.split_k == 1) return rc;
-    return launch_splitk_reduce(a, stream);
+    return after_launch();
 }
 
 }  // namespace
 
 int launch_ternary_gemm_f6f4(const int8_t* code_records, int64_t T, int64_t K, const void* packed, int64_t N,
                              const float* s_dequant, const float* w_scales, int64_t n_scale_groups, void* y_bf16,
-                             hipStream_t stream, int32_t* splitk_partial, int32_t* acc_out, int tile) {
+                             hipStream_t stream, int32_t* acc_out, int tile) {
     if (T == 0) return HBL_OK;
     GemmArgs a = {};
     a.codes = code_records;
@@ -380,9 +362,8 @@ int launch_ternary_gemm_f6f4(const int8_t* code_records, int64_t T, int64_t K, c
     a.K = (int)K;
     a.N = (int)N;
     a.rows_per_group = n_scale_groups > 0 ? (int)(N / n_scale_groups) : (int)N;
-    a.split_k = splitk_partial ? prefill_split_k(T, K, N) : 1;
-    a.partial = splitk_partial;
     a.code_offset = 0;      // signed operands: no correction terms
+    // Too few tiles for the chip: the mid-size kernel, which cuts K over the waves of a workgroup.
     // Workgroup tile: 64 K outputs either way (the 256 accumulator registers of four waves).  512 features x 128
     // tokens moves 32 KB per 128-feature stage through L2 and LDS (16 KB of codes + 16 KB of packed weights) against
     // 40 KB for 256 x 256 (32 + 8): measured 4 % faster on the GEMM at N = 4096 and 12288, equal at N = 32768.  The
@@ -391,27 +372,17 @@ int launch_ternary_gemm_f6f4(const int8_t* code_records, int64_t T, int64_t K, c
     const int64_t tiles_sq = (int64_t)((N + 255) / 256) * ((T + 255) / 256);
     const int64_t tiles_wide = (int64_t)((N + 511) / 512) * ((T + 127) / 128);
     int cfg = tiles_sq >= 180 ? (tiles_wide <= tiles_sq ? kTileWide : kTileSquare) : kTileSmall;
-    if (a.split_k > 1) cfg = kTileSplitK;   // mid-size batch, long K
-    if (tile != kTileAuto) {                // parity tests name the tile themselves
-        cfg = tile;
-        if (cfg == kTileSplitK) {
-            if (!splitk_partial) return HBL_E_WORKSPACE;
-            // any power-of-two cut that leaves whole K-blocks; the forward's own choice when it has one
-            if (a.split_k == 1) a.split_k = (K / 128) % 4 == 0 ? 4 : ((K / 128) % 2 == 0 ? 2 : 1);
-        }
-    }
-    if (cfg == kTileSplitK && a.split_k <= 1) cfg = kTileSmall;   // nothing to cut: the same tile, unsplit
-    if (cfg != kTileSplitK) a.split_k = 1;
+    if (mid_gemm_preferred(T, N)) cfg = kTileSplitK;
+    if (tile != kTileAuto) cfg = tile;   // parity tests name the tile themselves
     const bool raw = acc_out != nullptr;
     switch (cfg) {
         case kTileSquare:   // 256 x 256, 2 x 2 waves of 128 x 128
-            return raw ? launch_cfg<2, 2, 4, 4, 3, false, true>(a, stream) : launch_cfg<2, 2, 4, 4, 3>(a, stream);
+            return raw ? launch_cfg<2, 2, 4, 4, 3, true>(a, stream) : launch_cfg<2, 2, 4, 4, 3>(a, stream);
         case kTileSmall:    // 128 x 128
-            return raw ? launch_cfg<2, 2, 2, 2, 4, false, true>(a, stream) : launch_cfg<2, 2, 2, 2, 4>(a, stream);
+            return raw ? launch_cfg<2, 2, 2, 2, 4, true>(a, stream) : launch_cfg<2, 2, 2, 2, 4>(a, stream);
         case kTileWide:     // 512 features x 128 tokens, 4 x 1 waves of 128 x 128
-            return raw ? launch_cfg<4, 1, 4, 4, 3, false, true>(a, stream) : launch_cfg<4, 1, 4, 4, 3>(a, stream);
-        case kTileSplitK:   // 128 x 128, K cut over workgroups, int32 partial tiles + reduction launch
-            return launch_cfg<2, 2, 2, 2, 4, true>(a, stream);
+            return raw ? launch_cfg<4, 1, 4, 4, 3, true>(a, stream) : launch_cfg<4, 1, 4, 4, 3>(a, stream);
+        case kTileSplitK: return launch_mid_gemm_f6f4(a, stream);
         default: return HBL_E_SHAPE;
     }
 }

@@ -579,6 +579,32 @@ def test_config4_wdown_swiglu_input(hbl):
     run_site(hbl, synth.shrink(site, T=200, N=96), 4)            # and every row of a reduced shape
 
 
+@pytest.mark.parametrize("T,K,N,groups", [
+    (65, 640, 32, 1), (100, 8320, 96, 1),         # up to 128 tiles of 64 x 64: 32-token tiles, 4 and 8 K groups
+    (300, 640, 3104, 1),                          # up to 256 tiles: one workgroup per CU
+    (70, 512, 10016, 1), (1000, 896, 1152, 3),    # up to 512: two per CU, weights / codes shared out over the XCDs
+])
+def test_mid_size_gemm_forms(hbl, T, K, N, groups):
+    """The mid-size fp6 x fp4 kernel in every form its rule picks, with ragged token and feature tiles and K-blocks that
+    do not divide over the K groups: accumulators against the exact integer product, bf16 outputs bit for bit."""
+    note(f"mid-size GEMM T={T} K={K} N={N}")
+    rng = np.random.default_rng(T + K + N)
+    q = rng.integers(-8, 8, (T, K)).astype(np.int8)
+    q[3], q[T - 1] = -8, 7
+    c = rng.integers(-1, 2, (N, K)).astype(np.int8)
+    c[1], c[N - 1] = 1, -1
+    packed = hbl.pack_ternary_2bit(torch.from_numpy(c).cuda())
+    rec = torch.from_numpy(encode_bf6_records(q.astype(np.int32)).view(np.int8)).cuda()
+    want = torch.from_numpy(q).cuda().double() @ torch.from_numpy(c).cuda().double().t()     # exact
+    assert torch.equal(hbl.gemm_i32_bf6(rec, packed, N, T, K).double(), want)
+    sd = torch.rand(T, device="cuda") + 0.5
+    alpha = torch.rand(groups, device="cuda") + 0.5
+    y = hbl.gemm_dequant_bf16(rec, sd, torch.zeros(T, dtype=torch.int32, device="cuda"), packed, N, alpha,
+                              code_offset=hbl.CODES_BF6, K=K)
+    ref = ((want.float() * sd[:, None]) * alpha.repeat_interleave(N // groups)[None, :]).to(torch.bfloat16)
+    assert torch.equal(y, ref)
+
+
 @pytest.mark.parametrize("T,K,N", [(300, 1024, 544), (129, 4096, 96), (513, 512, 1056)])
 def test_prefill_gemm_tiles_raw_accumulators(hbl, T, K, N):
     """Every workgroup tile of both prefill GEMM kernels (256 x 256, 128 x 128, 512 x 128, and the fp6 x fp4
