@@ -120,9 +120,9 @@ int forward(const void* x, int x_dtype, int64_t T, int64_t K, const void* Wq_pac
     rc = launch_fwht_quant(x, x_dtype, T, K, bits, eps, hadamard, ws.codes, ws.s_dequant, nullptr, code_form, s, ln_gain,
                            ln_eps);
     if (rc != HBL_OK) return rc;
-    // a small batch: the weight-streaming kernel (always on the record path; on the byte path unless the plain
+    // a small batch: the weight-streaming kernel (up to 16 tokens on the record path; on the byte path unless the plain
     // split-K pair suits the shape better)
-    if (T <= 64 && (code_form == kCodesBf6 || decode_stream_preferred(T, K, N))) {
+    if (code_form == kCodesBf6 ? T <= 16 : (T <= 64 && decode_stream_preferred(T, K, N))) {
         DecodeArgs da = {};
         da.n = 1;
         fill_decode_problem(da.p[0], ws, T, K, Wq_packed, N, w_scales, groups, bits, y);
@@ -314,7 +314,32 @@ int hbl_bitlinear_forward_grouped(const hbl_problem* problems, int n_problems, f
         base += region;
     }
     hipStream_t s = static_cast<hipStream_t>(stream);
-    const int rc = launch_quant_grouped(qa, problems[0].bits, problems[0].x_dtype, s);
+    int rc = launch_quant_grouped(qa, problems[0].bits, problems[0].x_dtype, s);
+    if (rc != HBL_OK) return rc;
+    if (!mid_group_preferred(da.p, da.n)) return launch_decode_gemm(da, s);
+    // the problems on the record path through the mid-size kernel, the others (rows shorter than 512, INT8
+    // activations) through the shared form of the weight-streaming kernel
+    MidArgs ma = {};
+    int rest = 0;
+    for (int i = 0; i < da.n; ++i) {
+        if (!da.p[i].f6) {
+            da.p[rest++] = da.p[i];
+            continue;
+        }
+        const DecodeProblem& d = da.p[i];
+        MidProblem& m = ma.p[ma.n++];
+        m.codes = d.codes;
+        m.packed = d.packed;
+        m.s_dequant = d.s_dequant;
+        m.w_scales = d.w_scales;
+        m.y = d.y;
+        m.T = d.T;
+        m.K = d.K;
+        m.N = d.N;
+        m.rows_per_group = d.rows_per_group;
+    }
+    da.n = rest;
+    rc = launch_mid_gemm_grouped(ma, s);
     if (rc != HBL_OK) return rc;
     return launch_decode_gemm(da, s);
 }

@@ -7,7 +7,7 @@
 // copies, D = 4 stages deep per wave.  Per problem one of two operand paths:
 //  - fp6 x fp4 (INT4 activations, K >= 512): codes from the record image (96 bytes per token and stage),
 //    weights to fp4 with 3 vector-ALU instructions per 16; two 16x16x128 MFMAs per tile for up to 16 tokens,
-//    two 32x32x64 per tile and 32 tokens above that.  fp32 accumulators hold exact integers.
+//    two 32x32x64 per tile above that.  fp32 accumulators hold exact integers.
 //  - int8 (INT8 activations, short rows): codes as bytes (128 per token and stage), weights to signed bytes
 //    (15 instructions per 16), four 32x32x32 MFMAs per tile and 32 tokens.
 //
@@ -15,7 +15,8 @@
 //  - streaming (T <= 16): a wave's code stage is private (8 or 16 rows), so the waves never meet at a
 //    barrier.  The K range of one row tile may be split over the 2 or 4 waves of a workgroup; their
 //    accumulators are added through LDS at the end (exact).
-//  - shared (T <= 64): the four waves take four row tiles over one K range and share the code stage
+//  - shared (17 to 64 tokens of bytes, 17 to 32 of records in a group too large for the mid-size kernel, mid_gemm.hip):
+//    the four waves take four row tiles over one K range and share the code stage
 //    (32 or 64 rows): one barrier per stage.  A K range split over workgroups leaves int32 slices in the
 //    workspace; the workgroup of a K range that finishes last (an arrival counter) adds the others' slices to
 //    its own accumulators and dequantises.  (A group with more split row groups than a slot has counters runs
@@ -59,11 +60,6 @@ __device__ __forceinline__ void decode_body(const DecodeProblem& p, const int w,
     constexpr int STAGE = XW + NW * 1024;             // + one packed weight tile per wave
     constexpr int XL = SHARE ? TT : RQ;               // code copies per wave per stage (8 rows each)
     constexpr int NACC = TT == 1 ? 2 : TT;
-    // PAIR (shared form, two token tiles, fp6 x fp4): a wave multiplies two weight tiles by one token tile instead of
-    // one weight tile by two token tiles - waves 2p and 2p + 1 share the weight tiles 2p, 2p + 1 of the stage and take
-    // token tile 0 and 1.  Same MFMAs, but 5 KiB of LDS operand reads per wave and stage instead of 7: at 33-64
-    // tokens the eight waves of a CU are bound by the LDS read rate (56 KiB per stage at 128 bytes per clock).
-    constexpr bool PAIR = SHARE && F6 && TT == 2;
     constexpr bool PAIRED = SHARE && TT == 2;   // two stages per wait and barrier (below)
     static_assert(D >= 3 && (ROWS & (ROWS - 1)) == 0, "pipeline depth / row count");
     static_assert(!SHARE || NW == 4, "the shared form is written for four waves");
@@ -86,9 +82,6 @@ __device__ __forceinline__ void decode_body(const DecodeProblem& p, const int w,
     const int nt_max = p.N / 32 - 1;
     const bool live = nt <= nt_max;          // a wave past the last row tile streams that tile again, writes nothing
     const int ntc = live ? nt : nt_max;
-    // accumulator a of this wave: weight tile and token tile
-    auto tile_of = [&](int a) { return PAIR ? 4 * (w >> kl) + 2 * (wave >> 1) + a : nt; };
-    auto tok_tile_of = [&](int a) { return PAIR ? (wave & 1) : a; };
     const int kb0 = ks * nkb;
 
     // packed tiles are stored K-block-major (tile (nt, kb) at (kb * N/32 + nt) KiB): at any moment the waves
@@ -199,7 +192,7 @@ __device__ __forceinline__ void decode_body(const DecodeProblem& p, const int w,
     // copies they would delay the stream.  (They return in order behind the D - 1 stages in flight, which
     // only makes the first waits below stricter than they need to be.)
     const bool write_partial = SHARE && p.ksplit > 1;
-    const bool writer = (PAIR ? tile_of(0) <= nt_max : live) && (SHARE || ks == 0);
+    const bool writer = live && (SHARE || ks == 0);
     constexpr bool TOK16 = F6 && !SHARE;     // the 16x16 accumulator layout: token = lane & 15
     float alpha[TT], sd[TT];
     v4i wsum[4];
@@ -210,9 +203,8 @@ __device__ __forceinline__ void decode_body(const DecodeProblem& p, const int w,
     if (writer) {   // (with a K range split over workgroups any of them may turn out to be the one that dequantises)
 #pragma unroll
         for (int j = 0; j < TT; ++j) {
-            const int tile = tile_of(j) <= nt_max ? tile_of(j) : nt_max;
-            alpha[j] = p.w_scales[(tile * 32) / p.rows_per_group];
-            const int t = TOK16 ? (lane & 15) : tok_tile_of(j) * 32 + (lane & 31);
+            alpha[j] = p.w_scales[(nt * 32) / p.rows_per_group];
+            const int t = TOK16 ? (lane & 15) : j * 32 + (lane & 31);
             if (t < p.T) sd[j] = p.s_dequant[t];
         }
         if (!F6 && p.code_offset != 0) {
@@ -256,26 +248,6 @@ __device__ __forceinline__ void decode_body(const DecodeProblem& p, const int w,
             for (int hf = 0; hf < 2; ++hf)
                 facc[hf] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(fp4_operand(wp[hf].x, wp[hf].y), xop, facc[hf],
                                                                             4 /*A: fp4*/, 3 /*B: bf6*/, 0, 0, 0, 0);
-        } else if constexpr (PAIR) {
-            v4i wpk[2];
-#pragma unroll
-            for (int i = 0; i < 2; ++i)
-                wpk[i] = *reinterpret_cast<const v4i*>(st + XW + (2 * (wave >> 1) + i) * 1024 + lane * 16);
-            v8i xop[2];
-            const char* rows = st + (wave & 1) * 32 * kRecordRowBytes;
-#pragma unroll
-            for (int s = 0; s < 2; ++s) {
-                const v4i lo = *reinterpret_cast<const v4i*>(rows + xo_lo[s]);
-                const int2 hi = *reinterpret_cast<const int2*>(rows + xo_hi[s]);
-                xop[s] = v8i{lo[0], lo[1], lo[2], lo[3], hi.x, hi.y, 0, 0};
-            }
-            copies();
-#pragma unroll
-            for (int s = 0; s < 2; ++s)
-#pragma unroll
-                for (int i = 0; i < 2; ++i)
-                    wacc[i] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(
-                        fp4_operand((uint32_t)wpk[i][2 * s], (uint32_t)wpk[i][2 * s + 1]), xop[s], wacc[i], 4, 3, 0, 0, 0, 0);
         } else {
             const v4i wpk = *reinterpret_cast<const v4i*>(st + XW + wave * 1024 + lane * 16);
             v8i xop[2][TT];
@@ -379,8 +351,8 @@ __device__ __forceinline__ void decode_body(const DecodeProblem& p, const int w,
         }
         return;
     }
-    // accumulator j (token tile j, or weight tile j of the wave's two in the pair form): lane holds token (lane & 31)
-    // of its token tile; register quad g holds features 8g + 4*(lane >> 5) + 0..3 of its weight tile
+    // accumulator j: lane holds token (lane & 31) of token tile j; register quad g holds features 8g + 4*(lane >> 5) + 0..3
+    // of the weight tile
     v4i tot[TT][4];
 #pragma unroll
     for (int j = 0; j < TT; ++j)
@@ -431,11 +403,11 @@ __device__ __forceinline__ void decode_body(const DecodeProblem& p, const int w,
     }
 #pragma unroll
     for (int j = 0; j < TT; ++j) {
-        const int t = tok_tile_of(j) * 32 + (lane & 31);
-        if (t >= p.T || tile_of(j) > nt_max) continue;
+        const int t = j * 32 + (lane & 31);
+        if (t >= p.T) continue;
 #pragma unroll
         for (int g = 0; g < 4; ++g) {
-            const int n = tile_of(j) * 32 + 8 * g + 4 * (lane >> 5);
+            const int n = nt * 32 + 8 * g + 4 * (lane >> 5);
             if constexpr (F6) {
                 *reinterpret_cast<uint2*>(p.y + (size_t)t * p.N + n) =
                     dequant_quad_f32((float)tot[j][g][0], (float)tot[j][g][1], (float)tot[j][g][2], (float)tot[j][g][3], sd[j], alpha[j]);
@@ -451,8 +423,13 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void decode_gemm_kernel(c
     extern __shared__ __attribute__((aligned(1024))) char lds[];
     const DecodeProblem p = args.p[group_index_of(args.wg_begin, args.n, (int)blockIdx.x)];
     const int w = (int)blockIdx.x - p.wg_begin;
-    if (p.f6) decode_body<SHARE, TT, RQ, D, NW, true>(p, w, lds, args.arrive);      // uniform over the workgroup
-    else decode_body<SHARE, TT, RQ, D, NW, false>(p, w, lds, args.arrive);
+    if constexpr (TT == 1) {   // (records beyond 32 tokens go to the mid-size kernel)
+        if (p.f6) {            // uniform over the workgroup
+            decode_body<SHARE, TT, RQ, D, NW, true>(p, w, lds, args.arrive);
+            return;
+        }
+    }
+    decode_body<SHARE, TT, RQ, D, NW, false>(p, w, lds, args.arrive);
 }
 
 // Arrival counters of the shared form's in-kernel reduction: one per group of four row tiles whose K range is split

@@ -59,10 +59,6 @@ struct GemmArgs {
     int32_t* partial;
 };
 
-// The mid-size form of the fp6 x fp4 GEMM (mid_gemm.hip); a.y, or the raw sums where a.acc_out is set.
-bool mid_gemm_preferred(int64_t T, int64_t N);
-int launch_mid_gemm_f6f4(const GemmArgs& a, hipStream_t stream);
-
 // Second launch of a split-K GEMM (ternary_gemm.hip): adds the split_k int32 partial tiles and dequantises.
 int launch_splitk_reduce(const GemmArgs& a, hipStream_t stream);
 

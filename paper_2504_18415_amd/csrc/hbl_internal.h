@@ -265,6 +265,30 @@ __host__ __device__ inline int group_index_of(const int* begin, int n, int wg) {
 int launch_decode_gemm(DecodeArgs& args, hipStream_t stream);
 // The launch plan launch_decode_gemm would use (K splits, grid sizes), without launching: host logic only.
 int decode_plan_for_tests(DecodeArgs& args, int* wgs, int* arrival_counters);
+// Mid-size form of the fp6 x fp4 GEMM (mid_gemm.hip): 17 tokens up to where the prefill kernel has tiles enough.
+struct MidProblem {
+    const int8_t* codes;       // record image of [T, K]
+    const uint32_t* packed;    // weight tiles
+    const float* s_dequant;    // [T]
+    const float* w_scales;     // [groups]
+    uint16_t* y;               // [T, N] bf16, or
+    int32_t* acc_out;          // [T, N] the raw sums (no scales needed)
+    int T, K, N;
+    int rows_per_group;
+    int tiles_n, tiles_t;      // (set by the launch)
+    int form, wg_begin;        // grouped launch: which of its two forms, first workgroup
+};
+struct MidArgs {
+    int n;
+    int wg_begin[kMaxGroup];   // = p[i].wg_begin
+    MidProblem p[kMaxGroup];
+};
+bool mid_gemm_preferred(int64_t T, int64_t N);
+int launch_mid_gemm_f6f4(const MidProblem& a, hipStream_t stream);
+// Whether a group's problems on the record path take that kernel (more than 16 tokens somewhere).
+bool mid_group_preferred(const DecodeProblem* p, int n);
+// Every problem needs T <= 64; reorders args.
+int launch_mid_gemm_grouped(MidArgs& args, hipStream_t stream);
 // Whether a single projection with T <= 16 is better served by the streaming form of that launch than
 // by the split-K pair of launch_ternary_gemm.
 bool decode_stream_preferred(int64_t T, int64_t K, int64_t N);

@@ -1,15 +1,17 @@
-// Mid-size form of the fp6 x fp4 ternary GEMM (INT4 activations): batches of 65 tokens up to where the prefill kernel has
+// Mid-size form of the fp6 x fp4 ternary GEMM (INT4 activations): batches of 17 tokens up to where the prefill kernel has
 // enough 128 x 128 tiles for the chip.  There the output is too small to give every CU a tile and a CU that walks a long K
 // range by itself is bound by the latency of one stage after another, so the K range is cut - over the waves of one
-// workgroup, not over workgroups: a workgroup of 2 * KG waves owns 64 features x 64 tokens, K group g takes the K-blocks
-// g, g + KG, ... and its two waves one token tile each (two 32 x 32 accumulator tiles per wave).  A pipeline stage is one
-// K-block per group: KG x (64 token rows of the record image + two packed weight tiles) = KG x 8 KiB, copied to LDS as
-// contiguous 1 KiB pieces.  The groups' accumulators (exact integers) are added through LDS at the end, on the way to
-// whole-line stores: no partial tiles in memory and no second launch.
-// Bound by the copies' trip through L2 (64 bytes per clock and CU) behind the start-up of the launch.  Whole call, against
-// 128 x 128 tiles with K cut over workgroups and a reduction launch (K >= 8192) or uncut: 300 tokens x 8192 -> 3072
-// 28.8 -> 19.4 us, 97 x 11008 -> 4096 26.6 -> 17.0, 200 x 8192 -> 2048 21.8 -> 13.4, 65 x 4096 -> 4096 16.3 -> 9.7,
-// 512 x 16384 -> 4096 40 -> 37, 4000 x 16384 -> 512 89 -> 79.
+// workgroup, not over workgroups: K group g of KG takes the K-blocks g, g + KG, ...  A pipeline stage is one K-block per
+// group (token rows of the record image and packed weight tiles), copied to LDS as contiguous 1 KiB pieces.  The groups'
+// accumulators (exact integers) are added through LDS at the end, on the way to whole-line stores: no partial tiles in
+// memory and no second launch.
+// Bound by the copies' trip through L2 and LDS (64 / 128 bytes per clock and CU) behind the start-up of the launch.  Whole
+// call, both launches, against what ran before: 128 x 128 tiles above 64 tokens, with K >= 8192 cut over workgroups and a
+// reduction launch: 300 tokens x 8192 -> 3072 28.8 -> 19.4 us, 97 x 11008 -> 4096 26.6 -> 17.0, 200 x 8192 -> 2048 21.8 ->
+// 13.4, 65 x 4096 -> 4096 16.3 -> 9.7, 512 x 16384 -> 4096 40 -> 37, 4000 x 16384 -> 512 89 -> 79.  The shared form of the
+// weight-streaming kernel up to 64: 64 x 16384 -> 4096 22.6 -> 14.4, 64 x 11008 -> 4096 23.7 -> 12.7, 17 x 4096 -> 4096
+// 10.6 -> 9.1, 32 x 4096 -> 32768 13.5 -> 12.1 us.  (Up to 16 tokens that kernel's streaming form is faster: 8 x 4096 ->
+// 4096 7.2 us against 9.0.)
 #include <atomic>
 
 #include "gemm_common.h"
@@ -20,47 +22,56 @@ namespace {
 using namespace gemm;
 typedef float v16f __attribute__((ext_vector_type(16)));
 
-constexpr int kMidN = 64;                     // features of a workgroup
-constexpr int kMidSumRow = kMidN * 4 + 16;    // bytes of a token's sums in the reduction area (padded)
+// A form: KG K groups, D stages of LDS, NF feature tiles and TB token tiles of 32.  NF = TB = 2: a group is two waves, each
+// multiplies both weight tiles by one token tile.  NF = 2, TB = 1: two waves, one weight tile each.  NF = TB = 1: one wave.
+template <int KG_, int D_, int NF_, int TB_>
+struct MidForm {
+    static constexpr int KG = KG_, D = D_, NF = NF_, TB = TB_;
+    static constexpr int BN = 32 * NF, BT = 32 * TB;
+    static constexpr int GW = NF;                                // waves per group
+    static constexpr int NI = NF * TB / GW;                      // 32 x 32 accumulator tiles per wave
+    static constexpr int THREADS = 64 * GW * KG;
+    static constexpr int CODES = BT * kRecordRowBytes;           // bytes of a K-block: code records, then weight tiles
+    static constexpr int BLOCK = CODES + NF * 1024;
+    static constexpr int STAGE = KG * BLOCK;
+    static constexpr int PIECES = BLOCK / 1024;                  // 1 KiB copies per group and stage
+    static constexpr int COPIES = (PIECES + GW - 1) / GW;        // ... of wave 0 of the group
+    static constexpr int SUMROW = BN * 4 + 16;                   // bytes of a token's sums in the reduction area (padded)
+    static constexpr int TPT = BN / 8;                           // threads per token at the store (8 features each)
+    static constexpr size_t STAGES_LDS = (size_t)D * STAGE, SUMS_LDS = (size_t)KG * BT * SUMROW;
+    static constexpr size_t LDS = STAGES_LDS > SUMS_LDS ? STAGES_LDS : SUMS_LDS;
+    static_assert(D >= 2 && D <= 4 && (NF == 1 || NF == 2 || NF == 4) && TB >= 1 && TB <= 2 && TB <= NF && LDS <= 160 * 1024, "form");
+    static constexpr int STORES = (BT * TPT + THREADS - 1) / THREADS;   // 16-byte stores per thread
+    static int64_t tiles_n(int64_t N) { return (N + BN - 1) / BN; }
+    static int64_t tiles_t(int64_t T) { return (T + BT - 1) / BT; }
+};
 
-// Bytes of one K-block of a workgroup's tile (TB token tiles of 32): code records, then two packed weight tiles.
-constexpr int mid_code_bytes(int tb) { return tb * 32 * kRecordRowBytes; }
-constexpr int mid_block_bytes(int tb) { return mid_code_bytes(tb) + (kMidN / 32) * 1024; }
-
-// KG: K groups of two waves, D: stages of LDS, TB: token tiles of 32.  With TB = 2 a wave multiplies both weight tiles by
-// token tile `half`; with TB = 1 weight tile `half` by the token tile.
-// RAW: the sums leave as int32 [T, N] (acc_out) without dequantisation.
-template <int KG, int D, int TB, bool RAW>
-__global__ __launch_bounds__(128 * KG) void mid_gemm_f6f4_kernel(const GemmArgs a) {
-    constexpr int CODES = mid_code_bytes(TB), BLOCK = mid_block_bytes(TB), STAGE = KG * BLOCK;
-    constexpr int BT = 32 * TB;
-    constexpr int PIECES = BLOCK / 1024, COPIES = (PIECES + 1) / 2;   // 1 KiB pieces; wave 0 of a group copies COPIES of them
-    constexpr int NI = TB;                                            // weight tiles (accumulators) per wave
-    static_assert(D >= 2 && D <= 4 && (TB == 1 || TB == 2), "stages / token tiles");
-    static_assert(KG * 128 >= BT * 8, "the store needs eight threads per token");
-    extern __shared__ __attribute__((aligned(1024))) char lds[];
-
+// Workgroup `wg` of the problem.  RAW: the sums leave as int32 [T, N] (acc_out) without dequantisation.
+template <typename F, bool RAW>
+__device__ __forceinline__ void mid_gemm_body(const MidProblem& a, int wg, char* lds) {
+    constexpr int KG = F::KG, D = F::D, TB = F::TB, BT = F::BT, CODES = F::CODES, BLOCK = F::BLOCK, STAGE = F::STAGE;
+    constexpr int GW = F::GW, PIECES = F::PIECES, COPIES = F::COPIES, NI = F::NI, SUMROW = F::SUMROW, TPT = F::TPT;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int group = wave >> 1, half = wave & 1;
+    const int group = wave / GW, half = wave % GW;
 
     // workgroups are dealt round-robin over the 8 XCDs: each XCD gets a contiguous run of tiles, ordered so that the larger
     // operand (codes 3/4 T K bytes, weights 1/4 N K) is shared out over the XCDs' L2s and the smaller one read by all
-    const int nwg = a.tiles_n * a.tiles_t, xcd = blockIdx.x & 7;
-    const int tile = xcd * (nwg >> 3) + (xcd < (nwg & 7) ? xcd : (nwg & 7)) + (blockIdx.x >> 3);
+    const int nwg = a.tiles_n * a.tiles_t, xcd = wg & 7;
+    const int tile = xcd * (nwg >> 3) + (xcd < (nwg & 7) ? xcd : (nwg & 7)) + (wg >> 3);
     const bool by_token = 3 * (int64_t)a.T > a.N;
-    const int n0 = (by_token ? tile % a.tiles_n : tile / a.tiles_t) * kMidN;
+    const int n0 = (by_token ? tile % a.tiles_n : tile / a.tiles_t) * F::BN;
     const int t0 = (by_token ? tile / a.tiles_n : tile % a.tiles_t) * BT;
     const int nkb = a.K / kBK, stages = (nkb + KG - 1) / KG;
 
-    // Copies of this wave: pieces half, half + 2, ... of its group's block (codes first, then weights).  A row tile past N
+    // Copies of this wave: pieces half, half + GW, ... of its group's block (codes first, then weights).  A row tile past N
     // re-reads the last one (never stored); the record image holds whole panels, so rows past T exist.
     const size_t wstride = (size_t)(a.N / 32) * 1024;
     const char* src[COPIES];
     size_t step[COPIES];
 #pragma unroll
     for (int m = 0; m < COPIES; ++m) {
-        const int piece = 2 * m + half;
+        const int piece = GW * m + half;
         if (piece < CODES / 1024) {
             src[m] = reinterpret_cast<const char*>(a.codes) + (size_t)(t0 / kPanelTokens) * nkb * kRecordBlockBytes +
                      (t0 % kPanelTokens) * kRecordRowBytes + piece * 1024;
@@ -79,12 +90,12 @@ __global__ __launch_bounds__(128 * KG) void mid_gemm_f6f4_kernel(const GemmArgs 
         kb = kb < nkb ? kb : nkb - 1;   // a group without a block in the last stage re-reads the last one
 #pragma unroll
         for (int m = 0; m < COPIES; ++m)
-            if (2 * m + 1 < PIECES || half == 0)
-                lds_dma16(lds0 + slot * STAGE + group * BLOCK + (2 * m + half) * 1024, src[m] + kb * step[m], voff);
+            if (GW * m + GW - 1 < PIECES || half < PIECES % GW)
+                lds_dma16(lds0 + slot * STAGE + group * BLOCK + (GW * m + half) * 1024, src[m] + kb * step[m], voff);
     };
     // waits until at most `later` (0, 1 or D - 2) stages of this wave's copies are in flight
     auto wait_stage = [&](int later) {
-        if (PIECES % 2 == 0 || half == 0) {
+        if (PIECES % GW == 0 || half < PIECES % GW) {
             if (later >= D - 2) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"((D - 2) * COPIES) : "memory");
             else if (later == 1) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(COPIES) : "memory");
             else asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
@@ -95,13 +106,18 @@ __global__ __launch_bounds__(128 * KG) void mid_gemm_f6f4_kernel(const GemmArgs 
         }
     };
 
-    // what the store needs, requested ahead of the stream: thread -> token tid / 8, features 8 (tid % 8) .. + 7
-    const int st = t0 + (tid >> 3), sn = n0 + (tid & 7) * 8;
-    const bool stores = tid < BT * 8 && st < a.T && sn < a.N;
-    float sd = 0.0f, alpha = 0.0f;
-    if (!RAW && stores) {
-        sd = a.s_dequant[st];
-        alpha = a.w_scales[sn / a.rows_per_group];
+    // what the stores need, requested ahead of the stream: unit u -> token u / TPT, features 8 (u % TPT) .. + 7
+    float sd[F::STORES], alpha[F::STORES];
+    auto unit_token = [&](int i) { return t0 + (tid + i * F::THREADS) / TPT; };
+    auto unit_feature = [&](int i) { return n0 + ((tid + i * F::THREADS) % TPT) * 8; };
+    auto unit_stores = [&](int i) { return tid + i * F::THREADS < BT * TPT && unit_token(i) < a.T && unit_feature(i) < a.N; };
+#pragma unroll
+    for (int i = 0; i < F::STORES; ++i) {
+        sd[i] = alpha[i] = 0.0f;
+        if (!RAW && unit_stores(i)) {
+            sd[i] = a.s_dequant[unit_token(i)];
+            alpha[i] = a.w_scales[unit_feature(i) / a.rows_per_group];
+        }
     }
 
 #pragma unroll
@@ -109,14 +125,14 @@ __global__ __launch_bounds__(128 * KG) void mid_gemm_f6f4_kernel(const GemmArgs 
         if (s < stages) issue(s, s);
 
     // operand offsets inside the group's block
-    const int row = (TB == 2 ? half * 32 : 0) + (lane & 31);
+    const int row = (TB == 2 ? (half & 1) * 32 : 0) + (lane & 31);
     int xo_lo[2], xo_hi[2];
 #pragma unroll
     for (int s = 0; s < 2; ++s) {
         xo_lo[s] = group * BLOCK + row * kRecordRowBytes + record_lo_offset(row, s, lane >> 5);
         xo_hi[s] = group * BLOCK + row * kRecordRowBytes + record_hi_offset(row, s, lane >> 5);
     }
-    const int wtile = TB == 2 ? 0 : half;   // first weight tile of this wave
+    const int wtile = TB == 1 ? half : half & ~1;   // first weight tile of this wave
     const int wo = group * BLOCK + CODES + wtile * 1024 + lane * 16;
 
     v16f acc[NI];
@@ -130,7 +146,7 @@ __global__ __launch_bounds__(128 * KG) void mid_gemm_f6f4_kernel(const GemmArgs 
         // stage s has landed once at most min(D - 2, stages - 1 - s) later stages of this wave are in flight; after the
         // barrier it is visible to every wave and the buffer of stage s - 1 is free
         wait_stage(stages - 1 - s);
-        asm volatile("s_barrier" ::: "memory");
+        if constexpr (GW > 1) asm volatile("s_barrier" ::: "memory");   // (a group of one wave shares its block with nobody)
         const char* base = lds + slot * STAGE;
         v4i w[NI];
         v8i x[2];
@@ -161,67 +177,145 @@ __global__ __launch_bounds__(128 * KG) void mid_gemm_f6f4_kernel(const GemmArgs 
     for (int i = 0; i < NI; ++i)
 #pragma unroll
         for (int g = 0; g < 4; ++g)
-            *reinterpret_cast<float4*>(lds + (group * BT + row) * kMidSumRow + (32 * (wtile + i) + 8 * g + 4 * (lane >> 5)) * 4) =
+            *reinterpret_cast<float4*>(lds + (group * BT + row) * SUMROW + (32 * (wtile + i) + 8 * g + 4 * (lane >> 5)) * 4) =
                 make_float4(acc[i][4 * g], acc[i][4 * g + 1], acc[i][4 * g + 2], acc[i][4 * g + 3]);
     __syncthreads();
-    if (!stores) return;
-    float v[8];
 #pragma unroll
-    for (int e = 0; e < 8; ++e) v[e] = 0.0f;
+    for (int i = 0; i < F::STORES; ++i) {
+        if (!unit_stores(i)) continue;
+        const int unit = tid + i * F::THREADS;
+        float v[8];
 #pragma unroll
-    for (int g = 0; g < KG; ++g)
+        for (int e = 0; e < 8; ++e) v[e] = 0.0f;
 #pragma unroll
-        for (int q = 0; q < 2; ++q) {
-            const float4 p = *reinterpret_cast<const float4*>(lds + (g * BT + (tid >> 3)) * kMidSumRow + (tid & 7) * 32 + q * 16);
-            v[4 * q] += p.x; v[4 * q + 1] += p.y; v[4 * q + 2] += p.z; v[4 * q + 3] += p.w;
+        for (int g = 0; g < KG; ++g)
+#pragma unroll
+            for (int q = 0; q < 2; ++q) {
+                const float4 p = *reinterpret_cast<const float4*>(lds + (g * BT + unit / TPT) * SUMROW + (unit % TPT) * 32 + q * 16);
+                v[4 * q] += p.x; v[4 * q + 1] += p.y; v[4 * q + 2] += p.z; v[4 * q + 3] += p.w;
+            }
+        const size_t at = (size_t)unit_token(i) * a.N + unit_feature(i);
+        if constexpr (RAW) {
+            v4i* dst = reinterpret_cast<v4i*>(a.acc_out + at);
+            dst[0] = v4i{(int)v[0], (int)v[1], (int)v[2], (int)v[3]};
+            dst[1] = v4i{(int)v[4], (int)v[5], (int)v[6], (int)v[7]};
+        } else {
+            const uint2 lo = dequant_quad_f32(v[0], v[1], v[2], v[3], sd[i], alpha[i]);
+            const uint2 hi = dequant_quad_f32(v[4], v[5], v[6], v[7], sd[i], alpha[i]);
+            store_y16(a.y + at, make_uint4(lo.x, lo.y, hi.x, hi.y));
         }
-    if constexpr (RAW) {
-        v4i* dst = reinterpret_cast<v4i*>(a.acc_out + (size_t)st * a.N + sn);
-        dst[0] = v4i{(int)v[0], (int)v[1], (int)v[2], (int)v[3]};
-        dst[1] = v4i{(int)v[4], (int)v[5], (int)v[6], (int)v[7]};
-    } else {
-        const uint2 lo = dequant_quad_f32(v[0], v[1], v[2], v[3], sd, alpha), hi = dequant_quad_f32(v[4], v[5], v[6], v[7], sd, alpha);
-        store_y16(a.y + (size_t)st * a.N + sn, make_uint4(lo.x, lo.y, hi.x, hi.y));
     }
 }
 
-template <int KG, int D, int TB, bool RAW>
-int launch_cfg(GemmArgs a, hipStream_t stream) {
-    constexpr size_t stages = (size_t)D * KG * mid_block_bytes(TB), sums = (size_t)KG * 32 * TB * kMidSumRow;
-    constexpr size_t lds = stages > sums ? stages : sums;
-    static_assert(lds <= 160 * 1024, "LDS of a CU");
-    a.tiles_n = (a.N + kMidN - 1) / kMidN;
-    a.tiles_t = (a.T + 32 * TB - 1) / (32 * TB);
-    auto kern = mid_gemm_f6f4_kernel<KG, D, TB, RAW>;
+template <typename F, bool RAW>
+__global__ __launch_bounds__(F::THREADS) void mid_gemm_f6f4_kernel(const MidProblem a) {
+    extern __shared__ __attribute__((aligned(1024))) char lds[];
+    mid_gemm_body<F, RAW>(a, blockIdx.x, lds);
+}
+
+// Several problems of at most 64 tokens in one grid: workgroup -> problem, and one of two forms by the problem.
+template <typename FA, typename FB>
+__global__ __launch_bounds__(FA::THREADS) void mid_gemm_grouped_kernel(const MidArgs args) {
+    static_assert(FA::THREADS == FB::THREADS, "one workgroup size");
+    extern __shared__ __attribute__((aligned(1024))) char lds[];
+    const MidProblem p = args.p[group_index_of(args.wg_begin, args.n, (int)blockIdx.x)];
+    const int wg = (int)blockIdx.x - p.wg_begin;
+    if (p.form == 0) mid_gemm_body<FA, false>(p, wg, lds);   // uniform over the workgroup
+    else mid_gemm_body<FB, false>(p, wg, lds);
+}
+
+template <typename F, bool RAW>
+int launch_cfg(MidProblem a, hipStream_t stream) {
+    a.tiles_n = (int)F::tiles_n(a.N);
+    a.tiles_t = (int)F::tiles_t(a.T);
+    auto kern = mid_gemm_f6f4_kernel<F, RAW>;
     static std::atomic<uint64_t> lds_allowed{0};   // per instantiation: devices already set up
-    if (const int rc = allow_dynamic_lds(kern, lds, lds_allowed); rc != HBL_OK) return rc;
-    launch_kernel("mid_gemm_f6f4_kernel", kern, dim3((unsigned)(a.tiles_n * a.tiles_t)), dim3(128 * KG), lds, stream, a);
+    if (const int rc = allow_dynamic_lds(kern, F::LDS, lds_allowed); rc != HBL_OK) return rc;
+    launch_kernel("mid_gemm_f6f4_kernel", kern, dim3((unsigned)(a.tiles_n * a.tiles_t)), dim3(F::THREADS), F::LDS, stream, a);
     return after_launch();
 }
 
 // 64 x 64 tiles of the output.  Up to 256 of them one workgroup per CU with three stages of LDS; up to 512 two per CU with
-// two stages each (K = 4096, 128 tokens x 12288: 15.4 -> 14.0 us per call; but 300 tokens x 8192 -> 3072, 240 tiles, 19.6 ->
+// two stages each (128 tokens, 4096 -> 12288: 15.4 -> 14.0 us per call; but 300 tokens, 8192 -> 3072, 240 tiles, 19.6 ->
 // 23.1 us).  Up to 128 the token tile is halved: half of the chip would idle; and a K range of 64 blocks and more goes to
 // eight groups (128 tokens, 16384 -> 4096: 22.0 -> 20.0 us, with four groups 21.5; but at K = 1024 6.6 with four, 7.3 with
-// eight).  Above 512 tiles the 128 x 128 tile of the prefill kernel is faster (256 tokens, 4096 -> 12288, 768 tiles:
-// 18.0 against 20.5 us).
-int64_t mid_tiles(int64_t T, int64_t N) { return ((N + kMidN - 1) / kMidN) * ((T + 63) / 64); }
+// eight), up to 64 tiles with one wave per group on 32 x 32 outputs (64 tokens, 16384 -> 4096: 18.5 -> 14.4 us).  Above 512
+// tiles the 128 x 128 tile of the prefill kernel is faster (256 tokens, 4096 -> 12288, 768 tiles: 18.0 against 20.5 us).
+int64_t mid_tiles(int64_t T, int64_t N) { return MidForm<4, 2, 2, 2>::tiles_n(N) * MidForm<4, 2, 2, 2>::tiles_t(T); }
+
+constexpr int64_t kMidResident = 512;   // workgroups of 8 waves and up to 80 KiB of LDS that the chip holds at once
 
 template <bool RAW>
-int launch_form(const GemmArgs& a, hipStream_t stream) {
+int launch_form(const MidProblem& a, hipStream_t stream) {
     const int64_t tiles = mid_tiles(a.T, a.N);
-    if (tiles <= 128) return a.K < 8192 ? launch_cfg<4, 4, 1, RAW>(a, stream) : launch_cfg<8, 3, 1, RAW>(a, stream);
-    if (tiles <= 256) return launch_cfg<4, 3, 2, RAW>(a, stream);
-    return launch_cfg<4, 2, 2, RAW>(a, stream);
+    if (2 * tiles <= 128 && a.K >= 8192) return launch_cfg<MidForm<8, 3, 1, 1>, RAW>(a, stream);
+    if (tiles <= 128) return a.K < 8192 ? launch_cfg<MidForm<4, 4, 2, 1>, RAW>(a, stream) : launch_cfg<MidForm<8, 3, 2, 1>, RAW>(a, stream);
+    if (a.T <= 32) return launch_cfg<MidForm<4, 3, 2, 1>, RAW>(a, stream);
+    if (tiles <= 256) return launch_cfg<MidForm<4, 3, 2, 2>, RAW>(a, stream);
+    return launch_cfg<MidForm<4, 2, 2, 2>, RAW>(a, stream);
+}
+
+template <typename FA, typename FB>
+int launch_grouped_forms(MidArgs& args, hipStream_t stream) {
+    int wgs = 0;
+    for (int i = 0; i < args.n; ++i) {
+        MidProblem& p = args.p[i];
+        p.tiles_n = (int)(p.form == 0 ? FA::tiles_n(p.N) : FB::tiles_n(p.N));
+        p.tiles_t = (int)(p.form == 0 ? FA::tiles_t(p.T) : FB::tiles_t(p.T));
+        p.wg_begin = args.wg_begin[i] = wgs;
+        wgs += p.tiles_n * p.tiles_t;
+    }
+    constexpr size_t lds = FA::LDS > FB::LDS ? FA::LDS : FB::LDS;
+    auto kern = mid_gemm_grouped_kernel<FA, FB>;
+    static std::atomic<uint64_t> lds_allowed{0};   // per instantiation: devices already set up
+    if (const int rc = allow_dynamic_lds(kern, lds, lds_allowed); rc != HBL_OK) return rc;
+    launch_kernel("mid_gemm_grouped_kernel", kern, dim3((unsigned)wgs), dim3(FA::THREADS), lds, stream, args);
+    return after_launch();
 }
 
 }  // namespace
 
-namespace gemm {
-bool mid_gemm_preferred(int64_t T, int64_t N) { return mid_tiles(T, N) <= 512; }
-int launch_mid_gemm_f6f4(const GemmArgs& a, hipStream_t stream) {
+bool mid_gemm_preferred(int64_t T, int64_t N) { return T <= 64 || mid_tiles(T, N) <= kMidResident; }
+
+int launch_mid_gemm_f6f4(const MidProblem& a, hipStream_t stream) {
     return a.acc_out ? launch_form<true>(a, stream) : launch_form<false>(a, stream);
 }
-}  // namespace gemm
+
+int launch_mid_gemm_grouped(MidArgs& args, hipStream_t stream) {
+    if (args.n <= 0) return HBL_OK;
+    // long K ranges first: their workgroups run longest
+    for (int i = 1; i < args.n; ++i)
+        for (int j = i; j > 0 && args.p[j].K > args.p[j - 1].K; --j) {
+            const MidProblem t = args.p[j];
+            args.p[j] = args.p[j - 1];
+            args.p[j - 1] = t;
+        }
+    // While everything is resident at once: small tiles.  Beyond that four weight tiles per code stage move fewer bytes (47
+    // tokens, four 7B projections, 832 tiles: 36.2 -> 30.5 us per layer), and a long K range takes more groups and smaller
+    // tiles so that it does not outlast the rest (with eight one-wave groups it is 640 workgroups: 36.5 us).
+    int max_t = 0;
+    int64_t tiles = 0;
+    for (int i = 0; i < args.n; ++i) {
+        max_t = args.p[i].T > max_t ? args.p[i].T : max_t;
+        tiles += mid_tiles(args.p[i].T, args.p[i].N);
+        args.p[i].form = args.p[i].K >= 8192 ? 1 : 0;
+    }
+    if (max_t <= 32) return launch_grouped_forms<MidForm<4, 3, 2, 1>, MidForm<8, 2, 1, 1>>(args, stream);
+    if (tiles <= kMidResident) return launch_grouped_forms<MidForm<4, 2, 2, 2>, MidForm<8, 2, 1, 1>>(args, stream);
+    return launch_grouped_forms<MidForm<2, 3, 4, 2>, MidForm<4, 3, 2, 1>>(args, stream);
+}
+
+// A group at 47 tokens: 2048 / 8192 projections 21.2 -> 14.7 us per layer against the shared form of the weight-streaming
+// kernel, 7B 31.8 -> 30.5; up to 32 tokens that form's 512 workgroups of four waves are the better one once the tiles do not
+// fit at once (7B, 20 tokens: 25.3 against 26.0 us per layer; 2048 / 8192, 24 tokens: 17.0 against 14.0).
+bool mid_group_preferred(const DecodeProblem* p, int n) {
+    int max_t = 0;
+    int64_t tiles = 0;
+    for (int i = 0; i < n; ++i) {
+        max_t = p[i].T > max_t ? p[i].T : max_t;
+        if (p[i].f6) tiles += mid_tiles(p[i].T, p[i].N);
+    }
+    return max_t > 32 || (max_t > 16 && tiles <= kMidResident);
+}
 
 }  // namespace hbl

@@ -382,7 +382,20 @@ int launch_ternary_gemm_f6f4(const int8_t* code_records, int64_t T, int64_t K, c
             return raw ? launch_cfg<2, 2, 2, 2, 4, true>(a, stream) : launch_cfg<2, 2, 2, 2, 4>(a, stream);
         case kTileWide:     // 512 features x 128 tokens, 4 x 1 waves of 128 x 128
             return raw ? launch_cfg<4, 1, 4, 4, 3, true>(a, stream) : launch_cfg<4, 1, 4, 4, 3>(a, stream);
-        case kTileSplitK: return launch_mid_gemm_f6f4(a, stream);
+        case kTileSplitK: {
+            MidProblem m = {};
+            m.codes = a.codes;
+            m.packed = a.packed;
+            m.s_dequant = a.s_dequant;
+            m.w_scales = a.w_scales;
+            m.y = a.y;
+            m.acc_out = a.acc_out;
+            m.T = a.T;
+            m.K = a.K;
+            m.N = a.N;
+            m.rows_per_group = a.rows_per_group;
+            return launch_mid_gemm_f6f4(m, stream);
+        }
         default: return HBL_E_SHAPE;
     }
 }

@@ -580,7 +580,9 @@ def test_config4_wdown_swiglu_input(hbl):
 
 
 @pytest.mark.parametrize("T,K,N,groups", [
-    (65, 640, 32, 1), (100, 8320, 96, 1),         # up to 128 tiles of 64 x 64: 32-token tiles, 4 and 8 K groups
+    (17, 8320, 96, 1), (64, 8192, 4128, 1),       # up to 64 tiles of 64 x 64, long K; one more than that
+    (65, 640, 32, 1), (100, 8320, 96, 1),         # up to 128 tiles: 32-token tiles, 4 groups; long K
+    (20, 640, 8224, 1),                           # more, but at most 32 tokens
     (300, 640, 3104, 1),                          # up to 256 tiles: one workgroup per CU
     (70, 512, 10016, 1), (1000, 896, 1152, 3),    # up to 512: two per CU, weights / codes shared out over the XCDs
 ])
@@ -603,6 +605,26 @@ def test_mid_size_gemm_forms(hbl, T, K, N, groups):
                               code_offset=hbl.CODES_BF6, K=K)
     ref = ((want.float() * sd[:, None]) * alpha.repeat_interleave(N // groups)[None, :]).to(torch.bfloat16)
     assert torch.equal(y, ref)
+
+
+@pytest.mark.parametrize("shapes", [
+    [(20, 640, 96), (17, 8320, 160), (5, 512, 32), (32, 256, 64)],            # at most 32 tokens, few tiles
+    [(40, 640, 96), (64, 8320, 160), (5, 512, 32), (33, 384, 64)],            # more tokens
+    [(33, 640, 16416), (64, 8320, 160), (40, 512, 16448), (50, 256, 64)],     # more tiles than workgroups fit at once
+    [(20, 640, 16416), (32, 8320, 160), (24, 512, 16448)],                    # ... at most 32 tokens
+], ids=["few", "more_tokens", "many_tiles", "many_tiles_32"])
+def test_grouped_forms_beyond_16_tokens(hbl, shapes):
+    """Groups beyond 16 tokens: every form of the grouped mid-size launch, rows shorter than 512 (bytes, another launch)
+    and small members beside it; each output bit for bit as the problem gives alone, which takes another form."""
+    note(f"grouped forms {shapes}")
+    g = torch.Generator(device="cuda").manual_seed(11)
+    items = []
+    for T, K, N in shapes:
+        codes = torch.randint(-1, 2, (N, K), dtype=torch.int8, device="cuda", generator=g)
+        x = torch.randn((T, K), device="cuda", generator=g).to(torch.bfloat16)
+        items.append((x, hbl.pack_ternary_2bit(codes), N, torch.rand(1, device="cuda", generator=g) + 0.5, 4, False, None))
+    for y, it in zip(hbl.bitlinear_forward_grouped(items, EPS), items):
+        assert torch.equal(y, hbl.plain_bitlinear_forward(it[0], it[1], it[2], it[3], 4, EPS)), it[0].shape
 
 
 @pytest.mark.parametrize("T,K,N", [(300, 1024, 544), (129, 4096, 96), (513, 512, 1056)])
