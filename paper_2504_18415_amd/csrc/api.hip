@@ -120,20 +120,17 @@ int forward(const void* x, int x_dtype, int64_t T, int64_t K, const void* Wq_pac
     rc = launch_fwht_quant(x, x_dtype, T, K, bits, eps, hadamard, ws.codes, ws.s_dequant, nullptr, code_form, s, ln_gain,
                            ln_eps);
     if (rc != HBL_OK) return rc;
-    // a small batch: the weight-streaming kernel (up to 16 tokens on the record path; on the byte path unless the plain
-    // split-K pair suits the shape better)
-    if (code_form == kCodesBf6 ? T <= 16 : (T <= 64 && decode_stream_preferred(T, K, N))) {
+    // up to 16 tokens: the weight-streaming kernel, unless its plan leaves long serial chains of tiles
+    if (decode_stream_preferred(T, K, N)) {
         DecodeArgs da = {};
         da.n = 1;
         fill_decode_problem(da.p[0], ws, T, K, Wq_packed, N, w_scales, groups, bits, y);
-        if (code_form != kCodesBf6) da.p[0].partial = nullptr;   // byte path: the streaming form only
         return launch_decode_gemm(da, s);
     }
     // INT4 at prefill sizes: bf6 code records and the fp6 x fp4 matrix cores (exact, twice the int8 MFMA rate)
     if (code_form == kCodesBf6)
         return launch_ternary_gemm_f6f4(ws.codes, T, K, Wq_packed, N, ws.s_dequant, w_scales, groups, y, s);
-    return launch_ternary_gemm(ws.codes, code_form, T, K, Wq_packed, N, ws.s_dequant, w_scales, groups, y, nullptr,
-                               ws.partial, s);
+    return launch_ternary_gemm(ws.codes, code_form, T, K, Wq_packed, N, ws.s_dequant, w_scales, groups, y, nullptr, s);
 }
 
 // Workspace region of one problem of a grouped call: large enough for the grouped launches (partials
@@ -316,32 +313,37 @@ int hbl_bitlinear_forward_grouped(const hbl_problem* problems, int n_problems, f
     hipStream_t s = static_cast<hipStream_t>(stream);
     int rc = launch_quant_grouped(qa, problems[0].bits, problems[0].x_dtype, s);
     if (rc != HBL_OK) return rc;
-    if (!mid_group_preferred(da.p, da.n)) return launch_decode_gemm(da, s);
-    // the problems on the record path through the mid-size kernel, the others (rows shorter than 512, INT8
-    // activations) through the shared form of the weight-streaming kernel
-    MidArgs ma = {};
-    int rest = 0;
-    for (int i = 0; i < da.n; ++i) {
-        if (!da.p[i].f6) {
-            da.p[rest++] = da.p[i];
+    if (tile_rows == 0) return launch_decode_gemm(da, s);   // at most 16 tokens everywhere
+    for (const bool records : {true, false}) {   // a launch of its own for the problems on either operand path
+        DecodeArgs part = {};
+        for (int i = 0; i < da.n; ++i)
+            if ((da.p[i].f6 != 0) == records) part.p[part.n++] = da.p[i];
+        if (part.n == 0) continue;
+        if (!mid_group_preferred(part.p, part.n, records)) {
+            rc = launch_decode_gemm(part, s);
+            if (rc != HBL_OK) return rc;
             continue;
         }
-        const DecodeProblem& d = da.p[i];
-        MidProblem& m = ma.p[ma.n++];
-        m.codes = d.codes;
-        m.packed = d.packed;
-        m.s_dequant = d.s_dequant;
-        m.w_scales = d.w_scales;
-        m.y = d.y;
-        m.T = d.T;
-        m.K = d.K;
-        m.N = d.N;
-        m.rows_per_group = d.rows_per_group;
+        MidArgs ma = {};
+        for (int i = 0; i < part.n; ++i) {
+            const DecodeProblem& d = part.p[i];
+            MidProblem& m = ma.p[ma.n++];
+            m.codes = d.codes;
+            m.packed = d.packed;
+            m.s_dequant = d.s_dequant;
+            m.w_scales = d.w_scales;
+            m.y = d.y;
+            m.T = d.T;
+            m.K = d.K;
+            m.N = d.N;
+            m.rows_per_group = d.rows_per_group;
+            m.code_offset = d.code_offset;
+            m.w_row_sum = d.w_row_sum;
+        }
+        rc = launch_mid_gemm_grouped(ma, records, s);
+        if (rc != HBL_OK) return rc;
     }
-    da.n = rest;
-    rc = launch_mid_gemm_grouped(ma, s);
-    if (rc != HBL_OK) return rc;
-    return launch_decode_gemm(da, s);
+    return HBL_OK;
 }
 
 int hbl_ln_bitlinear_forward(const void* x, int x_dtype, int64_t T, int64_t K, const float* ln_gain, float ln_eps,
@@ -463,7 +465,7 @@ int hbl_gemm_i32(const int8_t* codes, int64_t T, int64_t K, const void* Wq_packe
     if (T == 0) return HBL_OK;
     if (!codes || !Wq_packed || !acc) return HBL_E_NULL;
     if (!aligned16(codes) || !aligned16(Wq_packed) || !aligned16(acc)) return HBL_E_ALIGN;
-    return launch_ternary_gemm(codes, 0, T, K, Wq_packed, N, nullptr, nullptr, 1, nullptr, acc, nullptr,
+    return launch_ternary_gemm(codes, 0, T, K, Wq_packed, N, nullptr, nullptr, 1, nullptr, acc,
                                static_cast<hipStream_t>(stream));
 }
 
@@ -498,7 +500,7 @@ int hbl_test_gemm_i32_tile(const void* codes, int code_form, int64_t T, int64_t 
         return launch_ternary_gemm_f6f4(static_cast<const int8_t*>(codes), T, K, Wq_packed, N, nullptr, nullptr, 1,
                                         nullptr, s, acc, tile);
     return launch_ternary_gemm(static_cast<const int8_t*>(codes), 0, T, K, Wq_packed, N, nullptr, nullptr, 1, nullptr,
-                               acc, nullptr, s, tile);
+                               acc, s, tile);
 }
 
 int hbl_trace_begin(int max_launches) {
@@ -556,7 +558,7 @@ int hbl_gemm_dequant_bf16(const int8_t* codes, int code_offset, const float* s_d
         return launch_ternary_gemm_f6f4(codes, T, K, Wq_packed, N, s_dequant, w_scales, n_scale_groups, y,
                                         static_cast<hipStream_t>(stream));
     return launch_ternary_gemm(codes, code_offset, T, K, Wq_packed, N, s_dequant, w_scales, n_scale_groups, y, nullptr,
-                               nullptr, static_cast<hipStream_t>(stream));
+                               static_cast<hipStream_t>(stream));
 }
 
 }  // extern "C"

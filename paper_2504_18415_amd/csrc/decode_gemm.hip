@@ -1,4 +1,4 @@
-// Small-batch (decode) form of the ternary GEMM of Eq. 7: T <= 64 tokens, so the packed weights are
+// Small-batch (decode) form of the ternary GEMM of Eq. 7: T <= 16 tokens (32 in one case), so the packed weights are
 // read once from HBM and dominate the traffic, and the job is to keep as many weight tiles in flight as
 // the memory system needs.  One launch serves up to kMaxGroup independent projections.
 //
@@ -15,9 +15,8 @@
 //  - streaming (T <= 16): a wave's code stage is private (8 or 16 rows), so the waves never meet at a
 //    barrier.  The K range of one row tile may be split over the 2 or 4 waves of a workgroup; their
 //    accumulators are added through LDS at the end (exact).
-//  - shared (17 to 64 tokens of bytes, 17 to 32 of records in a group too large for the mid-size kernel, mid_gemm.hip):
-//    the four waves take four row tiles over one K range and share the code stage
-//    (32 or 64 rows): one barrier per stage.  A K range split over workgroups leaves int32 slices in the
+//  - shared (17 to 32 tokens of records in a group too large for the mid-size kernel, mid_gemm.hip): the four waves
+//    take four row tiles over one K range and share the code stage (32 rows): one barrier per stage.  A K range split over workgroups leaves int32 slices in the
 //    workspace; the workgroup of a K range that finishes last (an arrival counter) adds the others' slices to
 //    its own accumulators and dequantises.  (A group with more split row groups than a slot has counters runs
 //    without the split.)
@@ -51,18 +50,16 @@ __device__ __forceinline__ void lds_dma16_first48(uint32_t lds_addr, const void*
 // tiles (W_down alone): there 8 waves share a row tile's K range, which shortens each wave's serial chain of
 // tiles (128 workgroups cannot be made more without narrower row tiles).
 // F6: the problem's codes are bf6 records and the fp6 x fp4 matrix cores do the work.
-template <bool SHARE, int TT, int RQ, int D, int NW, bool F6>
+template <bool SHARE, int RQ, int D, int NW, bool F6>
 __device__ __forceinline__ void decode_body(const DecodeProblem& p, const int w, char* lds, unsigned int* p_arrive) {
-    constexpr int ROWS = SHARE ? TT * 32 : RQ * 8;    // token rows of one code stage
+    constexpr int ROWS = SHARE ? 32 : RQ * 8;         // token rows of one code stage
     constexpr int ROWB = F6 ? kRecordRowBytes : kBK;  // bytes of one token row of a stage
     constexpr int XB = ROWS * ROWB;                   // bytes of one code stage
     constexpr int XW = SHARE ? XB : NW * XB;          // code bytes per stage in the workgroup
     constexpr int STAGE = XW + NW * 1024;             // + one packed weight tile per wave
-    constexpr int XL = SHARE ? TT : RQ;               // code copies per wave per stage (8 rows each)
-    constexpr int NACC = TT == 1 ? 2 : TT;
-    constexpr bool PAIRED = SHARE && TT == 2;   // two stages per wait and barrier (below)
+    constexpr int XL = SHARE ? 1 : RQ;                // code copies per wave per stage (8 rows each)
     static_assert(D >= 3 && (ROWS & (ROWS - 1)) == 0, "pipeline depth / row count");
-    static_assert(!SHARE || NW == 4, "the shared form is written for four waves");
+    static_assert(!SHARE || (NW == 4 && F6), "the shared form is written for four waves and records");
     static_assert(NW * 4096 <= D * STAGE, "the in-workgroup reduction reuses the stage buffers");
 
     const int tid = threadIdx.x;
@@ -150,19 +147,17 @@ __device__ __forceinline__ void decode_body(const DecodeProblem& p, const int w,
         }
     }
 
-    v16i acc[NACC];          // int8 path
+    v16i acc[2];             // int8 path: two accumulators take turns so that consecutive MFMAs do not depend on each other
     v4f facc[2];             // fp6 x fp4, streaming: row halves 0..15, 16..31 of the tile
-    v16f wacc[TT];           // fp6 x fp4, shared: one 32 x 32 tile per token tile
+    v16f wacc;               // fp6 x fp4, shared
 #pragma unroll
-    for (int i = 0; i < NACC; ++i)
+    for (int i = 0; i < 2; ++i)
 #pragma unroll
         for (int r = 0; r < 16; ++r) acc[i][r] = 0;
 #pragma unroll
     for (int i = 0; i < 2; ++i) facc[i] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
-    for (int i = 0; i < TT; ++i)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) wacc[i][r] = 0.0f;
+    for (int r = 0; r < 16; ++r) wacc[r] = 0.0f;
 
     // Stage kb may be consumed once at most min(D - 2, nkb - 1 - kb) later stages are still in flight
     // (copies return in order).  Nothing is requested past the end of the K range, so the count
@@ -184,7 +179,7 @@ __device__ __forceinline__ void decode_body(const DecodeProblem& p, const int w,
     static_assert(D - 2 <= 6, "wait_stage covers up to 5 later stages below the steady state");
 
 #pragma unroll
-    for (int s = 0; s < (PAIRED ? D - 2 : D - 1); ++s)
+    for (int s = 0; s < D - 1; ++s)
         if (s < nkb) issue(s, s);
 
     // Epilogue operands, requested right behind the first stages: under a saturated memory system a load
@@ -194,19 +189,14 @@ __device__ __forceinline__ void decode_body(const DecodeProblem& p, const int w,
     const bool write_partial = SHARE && p.ksplit > 1;
     const bool writer = live && (SHARE || ks == 0);
     constexpr bool TOK16 = F6 && !SHARE;     // the 16x16 accumulator layout: token = lane & 15
-    float alpha[TT], sd[TT];
+    float alpha = 0.0f, sd = 0.0f;
     v4i wsum[4];
-#pragma unroll
-    for (int j = 0; j < TT; ++j) sd[j] = alpha[j] = 0.0f;
 #pragma unroll
     for (int g = 0; g < 4; ++g) wsum[g] = v4i{0, 0, 0, 0};
     if (writer) {   // (with a K range split over workgroups any of them may turn out to be the one that dequantises)
-#pragma unroll
-        for (int j = 0; j < TT; ++j) {
-            alpha[j] = p.w_scales[(nt * 32) / p.rows_per_group];
-            const int t = TOK16 ? (lane & 15) : j * 32 + (lane & 31);
-            if (t < p.T) sd[j] = p.s_dequant[t];
-        }
+        alpha = p.w_scales[(nt * 32) / p.rows_per_group];
+        const int t = lane & (TOK16 ? 15 : 31);
+        if (t < p.T) sd = p.s_dequant[t];
         if (!F6 && p.code_offset != 0) {
 #pragma unroll
             for (int g = 0; g < 4; ++g)
@@ -220,22 +210,13 @@ __device__ __forceinline__ void decode_body(const DecodeProblem& p, const int w,
     auto stage_work = [&](const char* st, auto&& copies) {
         if constexpr (!F6) {
             const v4i wpk = *reinterpret_cast<const v4i*>(st + XW + wave * 1024 + lane * 16);
-            v4i xop[4][TT];
+            v4i xop[4];
 #pragma unroll
-            for (int k4 = 0; k4 < 4; ++k4)
-#pragma unroll
-                for (int j = 0; j < TT; ++j) xop[k4][j] = *reinterpret_cast<const v4i*>(st + xarea + xoff[k4] + j * 32 * kBK);
+            for (int k4 = 0; k4 < 4; ++k4) xop[k4] = *reinterpret_cast<const v4i*>(st + xarea + xoff[k4]);
             copies();
 #pragma unroll
-            for (int k4 = 0; k4 < 4; ++k4) {
-                const v4i wop = expand_weights_i8((uint32_t)wpk[k4]);
-#pragma unroll
-                for (int j = 0; j < TT; ++j) {
-                    // TT == 1: two accumulators take turns so that consecutive MFMAs do not depend on each other
-                    const int ai = TT == 1 ? (k4 & 1) : j;
-                    acc[ai] = __builtin_amdgcn_mfma_i32_32x32x32_i8(wop, xop[k4][j], acc[ai], 0, 0, 0);
-                }
-            }
+            for (int k4 = 0; k4 < 4; ++k4)
+                acc[k4 & 1] = __builtin_amdgcn_mfma_i32_32x32x32_i8(expand_weights_i8((uint32_t)wpk[k4]), xop[k4], acc[k4 & 1], 0, 0, 0);
         } else if constexpr (!SHARE) {
             const v4i lo = *reinterpret_cast<const v4i*>(st + xarea + xo_lo[0]);
             const int2 hi = *reinterpret_cast<const int2*>(st + xarea + xo_hi[0]);
@@ -250,61 +231,32 @@ __device__ __forceinline__ void decode_body(const DecodeProblem& p, const int w,
                                                                             4 /*A: fp4*/, 3 /*B: bf6*/, 0, 0, 0, 0);
         } else {
             const v4i wpk = *reinterpret_cast<const v4i*>(st + XW + wave * 1024 + lane * 16);
-            v8i xop[2][TT];
-#pragma unroll
-            for (int s = 0; s < 2; ++s)
-#pragma unroll
-                for (int j = 0; j < TT; ++j) {
-                    const char* rows = st + j * 32 * kRecordRowBytes;
-                    const v4i lo = *reinterpret_cast<const v4i*>(rows + xo_lo[s]);
-                    const int2 hi = *reinterpret_cast<const int2*>(rows + xo_hi[s]);
-                    xop[s][j] = v8i{lo[0], lo[1], lo[2], lo[3], hi.x, hi.y, 0, 0};
-                }
-            copies();
+            v8i xop[2];
 #pragma unroll
             for (int s = 0; s < 2; ++s) {
-                const v8i wop = fp4_operand((uint32_t)wpk[2 * s], (uint32_t)wpk[2 * s + 1]);
-#pragma unroll
-                for (int j = 0; j < TT; ++j)
-                    wacc[j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(wop, xop[s][j], wacc[j], 4, 3, 0, 0, 0, 0);
+                const v4i lo = *reinterpret_cast<const v4i*>(st + xo_lo[s]);
+                const int2 hi = *reinterpret_cast<const int2*>(st + xo_hi[s]);
+                xop[s] = v8i{lo[0], lo[1], lo[2], lo[3], hi.x, hi.y, 0, 0};
             }
+            copies();
+#pragma unroll
+            for (int s = 0; s < 2; ++s)
+                wacc = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(fp4_operand((uint32_t)wpk[2 * s], (uint32_t)wpk[2 * s + 1]),
+                                                                       xop[s], wacc, 4, 3, 0, 0, 0, 0);
         }
     };
-    if constexpr (PAIRED) {
-        // Shared form with two token tiles: one wait and one barrier per two stages (with one token tile the deeper
-        // ring this needs costs more than the barriers: 25.3 against 24.7 us per layer at batch 32).  The prologue
-        // has requested stages 0 .. D - 3; at the barrier of a pair every wave is done reading the previous pair,
-        // whose two buffers take stages kb + D - 2 and kb + D - 1.
-        static_assert(D >= 6 && D % 2 == 0, "the paired loop keeps two pairs of stages in flight");
-        int slot = 0;
-        for (int kb = 0; kb < nkb; kb += 2) {
-            const int n2 = nkb - kb < 2 ? nkb - kb : 2;
-            const int issued = kb + D - 2 < nkb ? kb + D - 2 : nkb;
-            wait_stage(issued - kb - n2);
-            asm volatile("s_barrier" ::: "memory");
-            for (int u = 0; u < n2; ++u) {
-                const int ahead = kb + u + D - 2;
-                const int aslot = slot >= 2 ? slot - 2 : slot + D - 2;
-                stage_work(lds + slot * STAGE, [&]() {
-                    if (ahead < nkb) issue(ahead, aslot);
-                });
-                slot = slot + 1 == D ? 0 : slot + 1;
-            }
-        }
-    } else {
-        int slot = 0;
-        for (int kb = 0; kb < nkb; ++kb) {
-            // stage kb has landed (for every wave, if the code stage is shared); the buffer read in the previous
-            // iteration is free for stage kb + D - 1
-            wait_stage(nkb - 1 - kb);
-            if constexpr (SHARE) asm volatile("s_barrier" ::: "memory");
-            stage_work(lds + slot * STAGE, [&]() {
-                if (kb + D - 1 < nkb) issue(kb + D - 1, slot == 0 ? D - 1 : slot - 1);
-            });
-            slot = slot + 1 == D ? 0 : slot + 1;
-        }
+    int slot = 0;
+    for (int kb = 0; kb < nkb; ++kb) {
+        // stage kb has landed (for every wave, if the code stage is shared); the buffer read in the previous
+        // iteration is free for stage kb + D - 1
+        wait_stage(nkb - 1 - kb);
+        if constexpr (SHARE) asm volatile("s_barrier" ::: "memory");
+        stage_work(lds + slot * STAGE, [&]() {
+            if (kb + D - 1 < nkb) issue(kb + D - 1, slot == 0 ? D - 1 : slot - 1);
+        });
+        slot = slot + 1 == D ? 0 : slot + 1;
     }
-    if constexpr (!F6 && TT == 1) acc[0] += acc[1];
+    if constexpr (!F6) acc[0] += acc[1];
 
     if constexpr (!SHARE) {
         if (p.ksplit > 1) {   // uniform over the workgroup
@@ -347,37 +299,31 @@ __device__ __forceinline__ void decode_body(const DecodeProblem& p, const int w,
         for (int hf = 0; hf < 2; ++hf) {
             const int n = nt * 32 + 16 * hf + 4 * (lane >> 4);
             *reinterpret_cast<uint2*>(p.y + (size_t)t * p.N + n) =
-                dequant_quad_f32(facc[hf][0], facc[hf][1], facc[hf][2], facc[hf][3], sd[0], alpha[0]);
+                dequant_quad_f32(facc[hf][0], facc[hf][1], facc[hf][2], facc[hf][3], sd, alpha);
         }
         return;
     }
-    // accumulator j: lane holds token (lane & 31) of token tile j; register quad g holds features 8g + 4*(lane >> 5) + 0..3
-    // of the weight tile
-    v4i tot[TT][4];
+    // lane holds token (lane & 31); register quad g holds features 8g + 4*(lane >> 5) + 0..3 of the weight tile
+    v4i tot[4];
 #pragma unroll
-    for (int j = 0; j < TT; ++j)
+    for (int g = 0; g < 4; ++g)
 #pragma unroll
-        for (int g = 0; g < 4; ++g) {
-            if constexpr (F6) {
-#pragma unroll
-                for (int r = 0; r < 4; ++r) tot[j][g][r] = (int)wacc[j][4 * g + r];
-            } else {
-#pragma unroll
-                for (int r = 0; r < 4; ++r) tot[j][g][r] = acc[TT == 1 ? 0 : j][4 * g + r];
-            }
+        for (int r = 0; r < 4; ++r) {
+            if constexpr (F6) tot[g][r] = (int)wacc[4 * g + r];
+            else tot[g][r] = acc[0][4 * g + r];
         }
     if constexpr (SHARE) {
         if (write_partial) {   // uniform over the workgroup
             // This workgroup's slice of the K range, as int32 tiles (exact).  A slice is only ever read by a workgroup
-            // of the same shape, so it is kept as the lanes hold it - quad (j, g) of wave `wave` of slice k at v4i index (((k * groups + group) * 4 + wave) *
-            // 4 TT + 4 j + g) * 64 + lane: every store and load instruction moves 1 KiB of consecutive bytes.  The
+            // of the same shape, so it is kept as the lanes hold it - quad g of wave `wave` of slice k at v4i index
+            // (((k * groups + group) * 4 + wave) * 4 + g) * 64 + lane: every store and load instruction moves 1 KiB of consecutive bytes.  The
             // stores are device-scope (write-through): readable from the other XCDs without a write-back of this L2.
             const int groups = (p.N / 32 + 3) / 4;
             v4i* const frag = reinterpret_cast<v4i*>(p.partial);
-            auto frag_index = [&](int k, int q) { return ((((size_t)k * groups + (w >> kl)) * 4 + wave) * (4 * TT) + q) * 64 + lane; };
+            auto frag_index = [&](int k, int q) { return ((((size_t)k * groups + (w >> kl)) * 4 + wave) * 4 + q) * 64 + lane; };
 #pragma unroll
-            for (int q = 0; q < 4 * TT; ++q)
-                asm volatile("global_store_dwordx4 %0, %1, off sc1" ::"v"(frag + frag_index(ks, q)), "v"(tot[q >> 2][q & 3]) : "memory");
+            for (int q = 0; q < 4; ++q)
+                asm volatile("global_store_dwordx4 %0, %1, off sc1" ::"v"(frag + frag_index(ks, q)), "v"(tot[q]) : "memory");
             // Arrival: once a workgroup's stores have completed it counts itself in; the counter wraps at ksplit, so
             // the workgroup that brings it back to zero is the last of its K range and every slice is in memory.
             asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
@@ -390,46 +336,38 @@ __device__ __forceinline__ void decode_body(const DecodeProblem& p, const int w,
             for (int k = 0; k < p.ksplit; ++k) {
                 if (k == ks) continue;   // (uniform)
 #pragma unroll
-                for (int q = 0; q < 4 * TT; ++q) {
+                for (int q = 0; q < 4; ++q) {
                     const uint64_t* src = reinterpret_cast<const uint64_t*>(frag + frag_index(k, q));
                     const uint64_t lo = __hip_atomic_load(src, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                     const uint64_t hi = __hip_atomic_load(src + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                    tot[q >> 2][q & 3] += v4i{(int)(uint32_t)lo, (int)(uint32_t)(lo >> 32), (int)(uint32_t)hi, (int)(uint32_t)(hi >> 32)};
+                    tot[q] += v4i{(int)(uint32_t)lo, (int)(uint32_t)(lo >> 32), (int)(uint32_t)hi, (int)(uint32_t)(hi >> 32)};
                 }
             }
         } else if (!writer) {
             return;
         }
     }
+    const int t = lane & 31;
+    if (t >= p.T) return;
 #pragma unroll
-    for (int j = 0; j < TT; ++j) {
-        const int t = j * 32 + (lane & 31);
-        if (t >= p.T) continue;
-#pragma unroll
-        for (int g = 0; g < 4; ++g) {
-            const int n = nt * 32 + 8 * g + 4 * (lane >> 5);
-            if constexpr (F6) {
-                *reinterpret_cast<uint2*>(p.y + (size_t)t * p.N + n) =
-                    dequant_quad_f32((float)tot[j][g][0], (float)tot[j][g][1], (float)tot[j][g][2], (float)tot[j][g][3], sd[j], alpha[j]);
-            } else {
-                *reinterpret_cast<uint2*>(p.y + (size_t)t * p.N + n) = dequant_quad_sums(tot[j][g], sd[j], alpha[j], p.code_offset, wsum[g]);
-            }
-        }
+    for (int g = 0; g < 4; ++g) {
+        uint2* const dst = reinterpret_cast<uint2*>(p.y + (size_t)t * p.N + nt * 32 + 8 * g + 4 * (lane >> 5));
+        if constexpr (F6) *dst = dequant_quad_f32((float)tot[g][0], (float)tot[g][1], (float)tot[g][2], (float)tot[g][3], sd, alpha);
+        else *dst = dequant_quad_sums(tot[g], sd, alpha, p.code_offset, wsum[g]);
     }
 }
 
-template <bool SHARE, int TT, int RQ, int D, int NW = 4>
+template <bool SHARE, int RQ, int D, int NW = 4>
 __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void decode_gemm_kernel(const DecodeArgs args) {
     extern __shared__ __attribute__((aligned(1024))) char lds[];
     const DecodeProblem p = args.p[group_index_of(args.wg_begin, args.n, (int)blockIdx.x)];
     const int w = (int)blockIdx.x - p.wg_begin;
-    if constexpr (TT == 1) {   // (records beyond 32 tokens go to the mid-size kernel)
-        if (p.f6) {            // uniform over the workgroup
-            decode_body<SHARE, TT, RQ, D, NW, true>(p, w, lds, args.arrive);
-            return;
-        }
+    if constexpr (SHARE) {
+        decode_body<SHARE, RQ, D, NW, true>(p, w, lds, args.arrive);
+    } else {
+        if (p.f6) decode_body<SHARE, RQ, D, NW, true>(p, w, lds, args.arrive);      // uniform over the workgroup
+        else decode_body<SHARE, RQ, D, NW, false>(p, w, lds, args.arrive);
     }
-    decode_body<SHARE, TT, RQ, D, NW, false>(p, w, lds, args.arrive);
 }
 
 // Arrival counters of the shared form's in-kernel reduction: one per group of four row tiles whose K range is split
@@ -457,16 +395,16 @@ int next_arrive_slot(unsigned int** out) {
     return HBL_OK;
 }
 
-template <bool SHARE, int TT, int RQ, int D, int NW = 4>
+template <bool SHARE, int RQ, int D, int NW = 4>
 int launch_form(const DecodeArgs& planned, int wgs, int counters, hipStream_t stream) {
     DecodeArgs a = planned;
     a.arrive = nullptr;
     if (counters != 0) {   // some K range is split over workgroups
         if (const int rc = next_arrive_slot(&a.arrive); rc != HBL_OK) return rc;
     }
-    constexpr int ROWS = SHARE ? TT * 32 : RQ * 8;
+    constexpr int ROWS = SHARE ? 32 : RQ * 8;
     constexpr size_t lds = (size_t)D * ((SHARE ? 1 : NW) * ROWS * kBK + NW * 1024);
-    auto kern = decode_gemm_kernel<SHARE, TT, RQ, D, NW>;
+    auto kern = decode_gemm_kernel<SHARE, RQ, D, NW>;
     static std::atomic<uint64_t> lds_allowed{0};   // per instantiation: devices already set up
     if (const int rc = allow_dynamic_lds(kern, lds, lds_allowed); rc != HBL_OK) return rc;
     launch_kernel("decode_gemm_kernel", kern, dim3((unsigned)wgs), dim3(64 * NW), lds, stream, a);
@@ -561,7 +499,7 @@ bool decode_stream_preferred(int64_t T, int64_t K, int64_t N) {
     int wgs, counters;
     plan(a, false, &wgs, &counters);
     // a wave's tiles are a serial chain: few workgroups with long chains leave most of the chip idle
-    return (K / 128) / a.p[0].ksplit <= 16 || wgs >= 256;
+    return (K / 128) / a.p[0].ksplit <= 16 || wgs >= 192;
 }
 
 int decode_plan_for_tests(DecodeArgs& a, int* wgs, int* counters) {
@@ -581,20 +519,22 @@ int launch_decode_gemm(DecodeArgs& a, hipStream_t stream) {
     if (a.n <= 0) return HBL_OK;
     int max_t = 0;
     for (int i = 0; i < a.n; ++i) max_t = a.p[i].T > max_t ? a.p[i].T : max_t;
-    if (max_t > 64) return HBL_E_SHAPE;
+    if (max_t > 32) return HBL_E_SHAPE;   // (the mid-size kernel's)
+    if (max_t > 16)
+        for (int i = 0; i < a.n; ++i)
+            if (!a.p[i].f6) return HBL_E_SHAPE;
     int wgs, counters;
     if (const int nw = wide_waves(a, max_t); nw != 0) {
         plan_wide(a, nw, &wgs);
-        return max_t <= 8 ? launch_form<false, 1, 1, 4, 8>(a, wgs, 0, stream)
-                          : launch_form<false, 1, 2, 4, 8>(a, wgs, 0, stream);
+        return max_t <= 8 ? launch_form<false, 1, 4, 8>(a, wgs, 0, stream)
+                          : launch_form<false, 2, 4, 8>(a, wgs, 0, stream);
     }
     plan(a, max_t > 16, &wgs, &counters);
     // Stages in flight per wave: 4.  Shallow is best (3 to 8 measured): the memory-level parallelism comes from
     // the 2048 waves of a full grid, and deeper rings only cost LDS and queueing.
-    if (max_t <= 8) return launch_form<false, 1, 1, 4>(a, wgs, 0, stream);
-    if (max_t <= 16) return launch_form<false, 1, 2, 4>(a, wgs, 0, stream);
-    if (max_t <= 32) return launch_form<true, 1, 1, 4>(a, wgs, counters, stream);
-    return launch_form<true, 2, 1, 6>(a, wgs, counters, stream);
+    if (max_t <= 8) return launch_form<false, 1, 4>(a, wgs, 0, stream);
+    if (max_t <= 16) return launch_form<false, 2, 4>(a, wgs, 0, stream);
+    return launch_form<true, 1, 4>(a, wgs, counters, stream);
 }
 
 }  // namespace hbl

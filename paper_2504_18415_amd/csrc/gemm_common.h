@@ -53,14 +53,7 @@ struct GemmArgs {
     int T, K, N;
     int rows_per_group;
     int tiles_n, tiles_t;
-    // split-K (small T only): workgroup (tile, ks) covers K-blocks [ks*nkb/split_k, (ks+1)*nkb/split_k)
-    // and writes its int32 partial tile to partial[ks][T][N]; splitk_reduce_kernel finishes the job
-    int split_k;
-    int32_t* partial;
 };
-
-// Second launch of a split-K GEMM (ternary_gemm.hip): adds the split_k int32 partial tiles and dequantises.
-int launch_splitk_reduce(const GemmArgs& a, hipStream_t stream);
 
 // Packed weights (ternary_setup.hip): sign / magnitude bit pairs, 16 weights per dword, placed so that two
 // AND and one shift give fp4 operands.  For the int8 matrix cores the same dword is expanded into four
@@ -131,10 +124,6 @@ __device__ __forceinline__ uint2 dequant_quad_f32(float a0, float a1, float a2, 
     const bf16x2 hi = __builtin_convertvector((f32x2){(a2 * sd) * alpha, (a3 * sd) * alpha}, bf16x2);
     return make_uint2(__builtin_bit_cast(uint32_t, lo), __builtin_bit_cast(uint32_t, hi));
 }
-
-
-// WAVES_N x WAVES_T waves; each wave owns TN x TT MFMA tiles (32 features x 32 tokens each).
-// LDS stage = [BT tokens x 128 B codes, XOR-swizzled][BN/32 packed weight tiles x 1 KiB].
 
 }  // namespace gemm
 }  // namespace hbl

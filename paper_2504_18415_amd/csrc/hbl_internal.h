@@ -94,35 +94,23 @@ inline bool is_pow2(int64_t v) { return v > 0 && (v & (v - 1)) == 0; }
 inline bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 inline size_t round_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
-// Split-K factor of the small-T (decode) GEMM: split K only until there are enough workgroups (128
-// output rows each) to occupy the chip, and never below 4 K-blocks of 128 per workgroup.  Every
-// split costs a second launch (the reduction) and T*N*4 bytes of partials per slice.
-constexpr int kDecodeWgTarget = 192;
-inline int decode_split_k(int64_t T, int64_t K, int64_t N) {
-    if (T > 64 || T <= 0) return 1;
-    const int64_t nkb = K / 128, groups = (N + 127) / 128;
+// Slices of int32 partial sums that the forward workspace has room for.  One launch keeps such slices in memory: the shared
+// form of the weight-streaming kernel (17 to 32 tokens of a large group), at most kMaxDecodeSplit of them; the single calls
+// cut K inside a workgroup.  The sizes that callers are told for single calls stay what they were.
+constexpr int kMaxDecodeSplit = 4;
+inline int workspace_slices(int64_t T, int64_t K, int64_t N) {
+    const int64_t nkb = K / 128;
     int sk = 1;
-    while ((int64_t)sk * groups < kDecodeWgTarget && nkb % (sk * 2) == 0 && nkb / (sk * 2) >= 4) sk *= 2;
-    return sk;
-}
-
-// Layout of the forward workspace: codes (one byte per code [T,K], or the record image) | float s_dequant [T],
-// and | int32 partial [split_k][T][N] for T <= 64 or a split K range.
-// K split of the int8 prefill GEMM at mid-size batches (INT8 activations): between 65 tokens and about a thousand a
-// long-K projection has too few output tiles (128 x 128) to give most CUs a workgroup, so the K range is cut until about
-// 256 workgroups exist, each keeping at least 8 K-blocks of 128; the int32 partial tiles then take one more launch.
-// Only for K >= 8192: at K = 4096 the unsplit call is short already and the extra launch costs more than it saves
-// (W_down at 96-512 tokens: 48-52 us -> 29-55 us).
-inline int prefill_split_k(int64_t T, int64_t K, int64_t N) {
-    if (T <= 64 || K < 8192) return 1;
-    const int64_t tiles = ((N + 127) / 128) * ((T + 127) / 128), nkb = K / 128;
-    int sk = 1;
+    if (T <= 64) {
+        const int64_t groups = (N + 127) / 128;
+        while ((int64_t)sk * groups < 192 && nkb % (sk * 2) == 0 && nkb / (sk * 2) >= 4) sk *= 2;
+        return sk < kMaxDecodeSplit ? kMaxDecodeSplit : sk;
+    }
+    if (K < 8192) return 1;
+    const int64_t tiles = ((N + 127) / 128) * ((T + 127) / 128);
     while (sk < 8 && tiles * sk * 2 <= 256 && nkb % (sk * 2) == 0 && nkb / (sk * 2) >= 8) sk *= 2;
     return sk;
 }
-
-// Largest K split the small-batch streaming GEMM may choose (sizes the partial buffers).
-constexpr int kMaxDecodeSplit = 4;
 
 struct Workspace {
     int8_t* codes;
@@ -144,10 +132,7 @@ inline Workspace carve_workspace(void* base, int64_t T, int64_t K, int64_t N, bo
     w.s_dequant = reinterpret_cast<float*>(static_cast<char*>(base) + off);
     off += round_up(static_cast<size_t>(T) * sizeof(float), 256);
     w.partial = nullptr;
-    // small batches: room for the K split of either small-batch kernel pair (the streaming kernel's plan cuts a
-    // K range into at most kMaxDecodeSplit slices)
-    int split = T <= 64 ? decode_split_k(T, K, N) : prefill_split_k(T, K, N);
-    if (T <= 64 && split < kMaxDecodeSplit) split = kMaxDecodeSplit;
+    const int split = workspace_slices(T, K, N);
     if (with_partial && (T <= 64 || split > 1)) {
         w.partial = reinterpret_cast<int32_t*>(static_cast<char*>(base) + off);
         // (17 to 64 tokens: the small-batch kernel keeps its slices as whole tiles of 32 tokens x 128 features)
@@ -194,8 +179,7 @@ constexpr int kTileAuto = -1, kTileSquare = 0 /*256 x 256*/, kTileSmall = 1 /*12
 // (no scales, no code_sum needed); otherwise y (bf16) is written.
 int launch_ternary_gemm(const int8_t* codes, int code_offset, int64_t T, int64_t K, const void* packed, int64_t N,
                         const float* s_dequant, const float* w_scales,
-                        int64_t n_scale_groups, void* y_bf16, int32_t* acc_out, int32_t* splitk_partial,
-                        hipStream_t stream, int tile = kTileAuto);
+                        int64_t n_scale_groups, void* y_bf16, int32_t* acc_out, hipStream_t stream, int tile = kTileAuto);
 
 // GEMM + epilogue on the fp6 x fp4 matrix-core path: codes as bf6 records; exact, INT4 activations only.
 // acc_out != nullptr: the raw accumulators as int32 [T, N] instead of y.
@@ -267,7 +251,7 @@ int launch_decode_gemm(DecodeArgs& args, hipStream_t stream);
 int decode_plan_for_tests(DecodeArgs& args, int* wgs, int* arrival_counters);
 // Mid-size form of the fp6 x fp4 GEMM (mid_gemm.hip): 17 tokens up to where the prefill kernel has tiles enough.
 struct MidProblem {
-    const int8_t* codes;       // record image of [T, K]
+    const int8_t* codes;       // record image of [T, K], or bytes
     const uint32_t* packed;    // weight tiles
     const float* s_dequant;    // [T]
     const float* w_scales;     // [groups]
@@ -275,6 +259,8 @@ struct MidProblem {
     int32_t* acc_out;          // [T, N] the raw sums (no scales needed)
     int T, K, N;
     int rows_per_group;
+    int code_offset;           // bytes: stored code byte = q + code_offset
+    const int32_t* w_row_sum;  // bytes: [N]
     int tiles_n, tiles_t;      // (set by the launch)
     int form, wg_begin;        // grouped launch: which of its two forms, first workgroup
 };
@@ -284,13 +270,12 @@ struct MidArgs {
     MidProblem p[kMaxGroup];
 };
 bool mid_gemm_preferred(int64_t T, int64_t N);
-int launch_mid_gemm_f6f4(const MidProblem& a, hipStream_t stream);
-// Whether a group's problems on the record path take that kernel (more than 16 tokens somewhere).
-bool mid_group_preferred(const DecodeProblem* p, int n);
+int launch_mid_gemm(const MidProblem& a, bool records, hipStream_t stream);
+// Whether a group's problems of one operand path take that kernel (more than 16 tokens somewhere).
+bool mid_group_preferred(const DecodeProblem* p, int n, bool records);
 // Every problem needs T <= 64; reorders args.
-int launch_mid_gemm_grouped(MidArgs& args, hipStream_t stream);
-// Whether a single projection with T <= 16 is better served by the streaming form of that launch than
-// by the split-K pair of launch_ternary_gemm.
+int launch_mid_gemm_grouped(MidArgs& args, bool records, hipStream_t stream);
+// Whether a single projection is better served by the streaming form of that launch (T <= 16) than by the mid-size kernel.
 bool decode_stream_preferred(int64_t T, int64_t K, int64_t N);
 
 // Packed weight buffer: N*K/4 bytes of 2-bit tiles (one form, read by every GEMM kernel), then N int32 row sums

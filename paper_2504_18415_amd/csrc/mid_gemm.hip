@@ -1,5 +1,6 @@
-// Mid-size form of the fp6 x fp4 ternary GEMM (INT4 activations): batches of 17 tokens up to where the prefill kernel has
-// enough 128 x 128 tiles for the chip.  There the output is too small to give every CU a tile and a CU that walks a long K
+// Mid-size form of the ternary GEMM, on both operand paths (code records for the fp6 x fp4 matrix cores; bytes for the int8
+// ones: INT8 activations, rows shorter than 512): batches of 17 tokens up to where the prefill kernels have enough 128 x 128
+// tiles for the chip, and smaller ones where the weight-streaming kernel has few workgroups with long chains.  There the output is too small to give every CU a tile and a CU that walks a long K
 // range by itself is bound by the latency of one stage after another, so the K range is cut - over the waves of one
 // workgroup, not over workgroups: K group g of KG takes the K-blocks g, g + KG, ...  A pipeline stage is one K-block per
 // group (token rows of the record image and packed weight tiles), copied to LDS as contiguous 1 KiB pieces.  The groups'
@@ -11,8 +12,10 @@
 // 13.4, 65 x 4096 -> 4096 16.3 -> 9.7, 512 x 16384 -> 4096 40 -> 37, 4000 x 16384 -> 512 89 -> 79.  The shared form of the
 // weight-streaming kernel up to 64: 64 x 16384 -> 4096 22.6 -> 14.4, 64 x 11008 -> 4096 23.7 -> 12.7, 17 x 4096 -> 4096
 // 10.6 -> 9.1, 32 x 4096 -> 32768 13.5 -> 12.1 us.  (Up to 16 tokens that kernel's streaming form is faster: 8 x 4096 ->
-// 4096 7.2 us against 9.0.)
+// 4096 7.2 us against 9.0.)  INT8 activations: 64 x 16384 -> 4096 21.4 -> 15.2, 24 x 8192 -> 3072 13.2 -> 8.9, 97 x 11008 ->
+// 4096 35.1 -> 19.0, 128 x 4096 -> 4096 23.0 -> 10.6, 300 x 8192 -> 3072 32.4 -> 19.7 us.
 #include <atomic>
+#include <type_traits>
 
 #include "gemm_common.h"
 
@@ -21,17 +24,22 @@ namespace {
 
 using namespace gemm;
 typedef float v16f __attribute__((ext_vector_type(16)));
+typedef int v16i __attribute__((ext_vector_type(16)));
+typedef float v4f __attribute__((ext_vector_type(4)));
 
-// A form: KG K groups, D stages of LDS, NF feature tiles and TB token tiles of 32.  NF = TB = 2: a group is two waves, each
-// multiplies both weight tiles by one token tile.  NF = 2, TB = 1: two waves, one weight tile each.  NF = TB = 1: one wave.
-template <int KG_, int D_, int NF_, int TB_>
+// A form: KG K groups of NF waves, D stages of LDS, NF feature tiles and TB token tiles of 32.  TB = 1: each wave of a group
+// multiplies one weight tile by the token tile.  TB = 2, records: waves 2p, 2p + 1 multiply weight tiles 2p and 2p + 1 by one
+// token tile each (fewer LDS operand bytes); bytes (I8): a wave multiplies one weight tile by both token tiles (the weights'
+// expansion is the larger cost there).
+template <int KG_, int D_, int NF_, int TB_, bool I8_ = false>
 struct MidForm {
     static constexpr int KG = KG_, D = D_, NF = NF_, TB = TB_;
+    static constexpr bool I8 = I8_;
     static constexpr int BN = 32 * NF, BT = 32 * TB;
     static constexpr int GW = NF;                                // waves per group
     static constexpr int NI = NF * TB / GW;                      // 32 x 32 accumulator tiles per wave
     static constexpr int THREADS = 64 * GW * KG;
-    static constexpr int CODES = BT * kRecordRowBytes;           // bytes of a K-block: code records, then weight tiles
+    static constexpr int CODES = BT * (I8 ? kBK : kRecordRowBytes);   // bytes of a K-block: codes, then weight tiles
     static constexpr int BLOCK = CODES + NF * 1024;
     static constexpr int STAGE = KG * BLOCK;
     static constexpr int PIECES = BLOCK / 1024;                  // 1 KiB copies per group and stage
@@ -56,23 +64,32 @@ __device__ __forceinline__ void mid_gemm_body(const MidProblem& a, int wg, char*
     const int group = wave / GW, half = wave % GW;
 
     // workgroups are dealt round-robin over the 8 XCDs: each XCD gets a contiguous run of tiles, ordered so that the larger
-    // operand (codes 3/4 T K bytes, weights 1/4 N K) is shared out over the XCDs' L2s and the smaller one read by all
+    // operand (codes 3/4 T K or T K bytes, weights 1/4 N K) is shared out over the XCDs' L2s and the smaller one read by all
     const int nwg = a.tiles_n * a.tiles_t, xcd = wg & 7;
     const int tile = xcd * (nwg >> 3) + (xcd < (nwg & 7) ? xcd : (nwg & 7)) + (wg >> 3);
-    const bool by_token = 3 * (int64_t)a.T > a.N;
+    const bool by_token = (F::I8 ? 4 : 3) * (int64_t)a.T > a.N;
     const int n0 = (by_token ? tile % a.tiles_n : tile / a.tiles_t) * F::BN;
     const int t0 = (by_token ? tile / a.tiles_n : tile % a.tiles_t) * BT;
     const int nkb = a.K / kBK, stages = (nkb + KG - 1) / KG;
 
     // Copies of this wave: pieces half, half + GW, ... of its group's block (codes first, then weights).  A row tile past N
-    // re-reads the last one (never stored); the record image holds whole panels, so rows past T exist.
+    // re-reads the last one (never stored); the record image holds whole panels, so rows past T exist.  Bytes: piece q is
+    // token rows 8q .. 8q + 7, lane l -> row 8q + l/8, LDS slot l%8 of the row, 16-byte chunk (l%8) ^ ((row/2) % 8); rows past
+    // T re-read the last one.
     const size_t wstride = (size_t)(a.N / 32) * 1024;
     const char* src[COPIES];
     size_t step[COPIES];
+    uint32_t voff[COPIES];
 #pragma unroll
     for (int m = 0; m < COPIES; ++m) {
         const int piece = GW * m + half;
-        if (piece < CODES / 1024) {
+        voff[m] = lane * 16;
+        if (piece < CODES / 1024 && F::I8) {
+            const int r = 8 * piece + (lane >> 3), t = t0 + r < a.T ? r : a.T - 1 - t0;
+            src[m] = reinterpret_cast<const char*>(a.codes) + (size_t)t0 * a.K;
+            step[m] = kBK;
+            voff[m] = (uint32_t)t * (uint32_t)a.K + (((lane & 7) ^ ((r >> 1) & 7)) << 4);
+        } else if (piece < CODES / 1024) {
             src[m] = reinterpret_cast<const char*>(a.codes) + (size_t)(t0 / kPanelTokens) * nkb * kRecordBlockBytes +
                      (t0 % kPanelTokens) * kRecordRowBytes + piece * 1024;
             step[m] = kRecordBlockBytes;
@@ -84,14 +101,13 @@ __device__ __forceinline__ void mid_gemm_body(const MidProblem& a, int wg, char*
         }
     }
     const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)lds;
-    const uint32_t voff = lane * 16;
     auto issue = [&](int s, int slot) {
         int kb = s * KG + group;
         kb = kb < nkb ? kb : nkb - 1;   // a group without a block in the last stage re-reads the last one
 #pragma unroll
         for (int m = 0; m < COPIES; ++m)
             if (GW * m + GW - 1 < PIECES || half < PIECES % GW)
-                lds_dma16(lds0 + slot * STAGE + group * BLOCK + (GW * m + half) * 1024, src[m] + kb * step[m], voff);
+                lds_dma16(lds0 + slot * STAGE + group * BLOCK + (GW * m + half) * 1024, src[m] + kb * step[m], voff[m]);
     };
     // waits until at most `later` (0, 1 or D - 2) stages of this wave's copies are in flight
     auto wait_stage = [&](int later) {
@@ -124,22 +140,28 @@ __device__ __forceinline__ void mid_gemm_body(const MidProblem& a, int wg, char*
     for (int s = 0; s < D - 1; ++s)
         if (s < stages) issue(s, s);
 
-    // operand offsets inside the group's block
-    const int row = (TB == 2 ? (half & 1) * 32 : 0) + (lane & 31);
-    int xo_lo[2], xo_hi[2];
+    // operand offsets inside the group's block; accumulator i of this wave: weight tile, token tile
+    auto tile_of = [&](int i) { return TB == 1 || F::I8 ? half : (half & ~1) + i; };
+    auto token_tile_of = [&](int i) { return TB == 1 ? 0 : (F::I8 ? i : half & 1); };
+    const int row = token_tile_of(0) * 32 + (lane & 31);   // of accumulator 0
+    int xo_lo[2], xo_hi[2], xo_byte[4];
 #pragma unroll
-    for (int s = 0; s < 2; ++s) {
-        xo_lo[s] = group * BLOCK + row * kRecordRowBytes + record_lo_offset(row, s, lane >> 5);
-        xo_hi[s] = group * BLOCK + row * kRecordRowBytes + record_hi_offset(row, s, lane >> 5);
+    for (int k = 0; k < 2; ++k) {
+        xo_lo[k] = group * BLOCK + row * kRecordRowBytes + record_lo_offset(row, k, lane >> 5);
+        xo_hi[k] = group * BLOCK + row * kRecordRowBytes + record_hi_offset(row, k, lane >> 5);
     }
-    const int wtile = TB == 1 ? half : half & ~1;   // first weight tile of this wave
-    const int wo = group * BLOCK + CODES + wtile * 1024 + lane * 16;
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+        xo_byte[k] = group * BLOCK + row * kBK + ((code_chunk_of_dword(k, lane >> 5) ^ ((row >> 1) & 7)) << 4);
+    const int wo = group * BLOCK + CODES + tile_of(0) * 1024 + lane * 16;
 
-    v16f acc[NI];
+    typedef typename std::conditional<F::I8, v16i, v16f>::type acc_t;
+    typedef typename std::conditional<F::I8, v4i, v4f>::type sum_t;
+    acc_t acc[NI];
 #pragma unroll
     for (int i = 0; i < NI; ++i)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) acc[i][r] = 0.0f;
+        for (int r = 0; r < 16; ++r) acc[i][r] = 0;
 
     int slot = 0;
     for (int s = 0; s < stages; ++s) {
@@ -148,25 +170,44 @@ __device__ __forceinline__ void mid_gemm_body(const MidProblem& a, int wg, char*
         wait_stage(stages - 1 - s);
         if constexpr (GW > 1) asm volatile("s_barrier" ::: "memory");   // (a group of one wave shares its block with nobody)
         const char* base = lds + slot * STAGE;
-        v4i w[NI];
-        v8i x[2];
+        const bool live = s * KG + group < nkb;   // uniform
+        if constexpr (F::I8) {
+            const v4i w = *reinterpret_cast<const v4i*>(base + wo);
+            v4i x[4][NI];
 #pragma unroll
-        for (int i = 0; i < NI; ++i) w[i] = *reinterpret_cast<const v4i*>(base + wo + i * 1024);
+            for (int k = 0; k < 4; ++k)
 #pragma unroll
-        for (int k = 0; k < 2; ++k) {
-            const v4i lo = *reinterpret_cast<const v4i*>(base + xo_lo[k]);
-            const int2 hi = *reinterpret_cast<const int2*>(base + xo_hi[k]);
-            x[k] = v8i{lo[0], lo[1], lo[2], lo[3], hi.x, hi.y, 0, 0};
-        }
-        if (s + D - 1 < stages) issue(s + D - 1, slot == 0 ? D - 1 : slot - 1);
-        if (s * KG + group < nkb) {   // uniform
+                for (int i = 0; i < NI; ++i) x[k][i] = *reinterpret_cast<const v4i*>(base + xo_byte[k] + i * 32 * kBK);
+            if (s + D - 1 < stages) issue(s + D - 1, slot == 0 ? D - 1 : slot - 1);
+            if (live) {
 #pragma unroll
-            for (int k = 0; k < 2; ++k)
+                for (int k = 0; k < 4; ++k) {
+                    const v4i wop = expand_weights_i8((uint32_t)w[k]);
 #pragma unroll
-                for (int i = 0; i < NI; ++i)
-                    acc[i] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(
-                        fp4_operand((uint32_t)w[i][2 * k], (uint32_t)w[i][2 * k + 1]), x[k], acc[i], 4 /*A: fp4*/, 3 /*B: bf6*/,
-                        0, 0, 0, 0);
+                    for (int i = 0; i < NI; ++i) acc[i] = __builtin_amdgcn_mfma_i32_32x32x32_i8(wop, x[k][i], acc[i], 0, 0, 0);
+                }
+            }
+        } else {
+            v4i w[NI];
+            v8i x[2];
+#pragma unroll
+            for (int i = 0; i < NI; ++i) w[i] = *reinterpret_cast<const v4i*>(base + wo + i * 1024);
+#pragma unroll
+            for (int k = 0; k < 2; ++k) {
+                const v4i lo = *reinterpret_cast<const v4i*>(base + xo_lo[k]);
+                const int2 hi = *reinterpret_cast<const int2*>(base + xo_hi[k]);
+                x[k] = v8i{lo[0], lo[1], lo[2], lo[3], hi.x, hi.y, 0, 0};
+            }
+            if (s + D - 1 < stages) issue(s + D - 1, slot == 0 ? D - 1 : slot - 1);
+            if (live) {
+#pragma unroll
+                for (int k = 0; k < 2; ++k)
+#pragma unroll
+                    for (int i = 0; i < NI; ++i)
+                        acc[i] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(
+                            fp4_operand((uint32_t)w[i][2 * k], (uint32_t)w[i][2 * k + 1]), x[k], acc[i], 4 /*A: fp4*/,
+                            3 /*B: bf6*/, 0, 0, 0, 0);
+            }
         }
         slot = slot + 1 == D ? 0 : slot + 1;
     }
@@ -177,38 +218,39 @@ __device__ __forceinline__ void mid_gemm_body(const MidProblem& a, int wg, char*
     for (int i = 0; i < NI; ++i)
 #pragma unroll
         for (int g = 0; g < 4; ++g)
-            *reinterpret_cast<float4*>(lds + (group * BT + row) * SUMROW + (32 * (wtile + i) + 8 * g + 4 * (lane >> 5)) * 4) =
-                make_float4(acc[i][4 * g], acc[i][4 * g + 1], acc[i][4 * g + 2], acc[i][4 * g + 3]);
+            *reinterpret_cast<sum_t*>(lds + (group * BT + token_tile_of(i) * 32 + (lane & 31)) * SUMROW +
+                                      (32 * tile_of(i) + 8 * g + 4 * (lane >> 5)) * 4) =
+                sum_t{acc[i][4 * g], acc[i][4 * g + 1], acc[i][4 * g + 2], acc[i][4 * g + 3]};
     __syncthreads();
 #pragma unroll
     for (int i = 0; i < F::STORES; ++i) {
         if (!unit_stores(i)) continue;
         const int unit = tid + i * F::THREADS;
-        float v[8];
-#pragma unroll
-        for (int e = 0; e < 8; ++e) v[e] = 0.0f;
+        sum_t v[2] = {sum_t{0, 0, 0, 0}, sum_t{0, 0, 0, 0}};
 #pragma unroll
         for (int g = 0; g < KG; ++g)
 #pragma unroll
-            for (int q = 0; q < 2; ++q) {
-                const float4 p = *reinterpret_cast<const float4*>(lds + (g * BT + unit / TPT) * SUMROW + (unit % TPT) * 32 + q * 16);
-                v[4 * q] += p.x; v[4 * q + 1] += p.y; v[4 * q + 2] += p.z; v[4 * q + 3] += p.w;
-            }
+            for (int q = 0; q < 2; ++q)
+                v[q] += *reinterpret_cast<const sum_t*>(lds + (g * BT + unit / TPT) * SUMROW + (unit % TPT) * 32 + q * 16);
         const size_t at = (size_t)unit_token(i) * a.N + unit_feature(i);
         if constexpr (RAW) {
             v4i* dst = reinterpret_cast<v4i*>(a.acc_out + at);
-            dst[0] = v4i{(int)v[0], (int)v[1], (int)v[2], (int)v[3]};
-            dst[1] = v4i{(int)v[4], (int)v[5], (int)v[6], (int)v[7]};
+#pragma unroll
+            for (int q = 0; q < 2; ++q) dst[q] = v4i{(int)v[q][0], (int)v[q][1], (int)v[q][2], (int)v[q][3]};
         } else {
-            const uint2 lo = dequant_quad_f32(v[0], v[1], v[2], v[3], sd[i], alpha[i]);
-            const uint2 hi = dequant_quad_f32(v[4], v[5], v[6], v[7], sd[i], alpha[i]);
-            store_y16(a.y + at, make_uint4(lo.x, lo.y, hi.x, hi.y));
+            uint2 o[2];
+#pragma unroll
+            for (int q = 0; q < 2; ++q) {
+                if constexpr (F::I8) o[q] = dequant_quad(v[q], sd[i], alpha[i], a.code_offset, a.w_row_sum + unit_feature(i) + 4 * q);
+                else o[q] = dequant_quad_f32(v[q][0], v[q][1], v[q][2], v[q][3], sd[i], alpha[i]);
+            }
+            store_y16(a.y + at, make_uint4(o[0].x, o[0].y, o[1].x, o[1].y));
         }
     }
 }
 
 template <typename F, bool RAW>
-__global__ __launch_bounds__(F::THREADS) void mid_gemm_f6f4_kernel(const MidProblem a) {
+__global__ __launch_bounds__(F::THREADS) void mid_gemm_kernel(const MidProblem a) {
     extern __shared__ __attribute__((aligned(1024))) char lds[];
     mid_gemm_body<F, RAW>(a, blockIdx.x, lds);
 }
@@ -228,31 +270,31 @@ template <typename F, bool RAW>
 int launch_cfg(MidProblem a, hipStream_t stream) {
     a.tiles_n = (int)F::tiles_n(a.N);
     a.tiles_t = (int)F::tiles_t(a.T);
-    auto kern = mid_gemm_f6f4_kernel<F, RAW>;
+    auto kern = mid_gemm_kernel<F, RAW>;
     static std::atomic<uint64_t> lds_allowed{0};   // per instantiation: devices already set up
     if (const int rc = allow_dynamic_lds(kern, F::LDS, lds_allowed); rc != HBL_OK) return rc;
-    launch_kernel("mid_gemm_f6f4_kernel", kern, dim3((unsigned)(a.tiles_n * a.tiles_t)), dim3(F::THREADS), F::LDS, stream, a);
+    launch_kernel("mid_gemm_kernel", kern, dim3((unsigned)(a.tiles_n * a.tiles_t)), dim3(F::THREADS), F::LDS, stream, a);
     return after_launch();
 }
 
-// 64 x 64 tiles of the output.  Up to 256 of them one workgroup per CU with three stages of LDS; up to 512 two per CU with
-// two stages each (128 tokens, 4096 -> 12288: 15.4 -> 14.0 us per call; but 300 tokens, 8192 -> 3072, 240 tiles, 19.6 ->
-// 23.1 us).  Up to 128 the token tile is halved: half of the chip would idle; and a K range of 64 blocks and more goes to
-// eight groups (128 tokens, 16384 -> 4096: 22.0 -> 20.0 us, with four groups 21.5; but at K = 1024 6.6 with four, 7.3 with
-// eight), up to 64 tiles with one wave per group on 32 x 32 outputs (64 tokens, 16384 -> 4096: 18.5 -> 14.4 us).  Above 512
-// tiles the 128 x 128 tile of the prefill kernel is faster (256 tokens, 4096 -> 12288, 768 tiles: 18.0 against 20.5 us).
-int64_t mid_tiles(int64_t T, int64_t N) { return MidForm<4, 2, 2, 2>::tiles_n(N) * MidForm<4, 2, 2, 2>::tiles_t(T); }
-
+// Tiles of 64 x 64 outputs.  Up to 256 of them one workgroup per CU with three stages of LDS; up to 512 two per CU with two
+// stages each (128 tokens, 4096 -> 12288: 15.4 -> 14.0 us per call; but 300 tokens, 8192 -> 3072, 240 tiles, 19.6 -> 23.1 us).
+// Up to 128 the token tile is halved: half of the chip would idle; with a K range of 64 blocks and more eight groups (128
+// tokens, 16384 -> 4096: 22.0 -> 20.0 us, with four groups 21.5).  Where 32 x 32 outputs give at most one workgroup per CU and
+// each of eight one-wave groups at least one K-block, that form needs no barrier and half of the stages (64 tokens, 16384 ->
+// 4096: 18.5 -> 14.4 us; 32 x 4096 -> 4096 9.3 -> 7.6; 64 x 1024 -> 4096 6.3 -> 6.0).  Above 512 tiles the 128 x 128 tile of
+// the prefill kernel is faster (256 tokens, 4096 -> 12288, 768 tiles: 18.0 against 20.5 us).
 constexpr int64_t kMidResident = 512;   // workgroups of 8 waves and up to 80 KiB of LDS that the chip holds at once
 
-template <bool RAW>
+template <bool I8, bool RAW>
 int launch_form(const MidProblem& a, hipStream_t stream) {
     const int64_t tiles = mid_tiles(a.T, a.N);
-    if (2 * tiles <= 128 && a.K >= 8192) return launch_cfg<MidForm<8, 3, 1, 1>, RAW>(a, stream);
-    if (tiles <= 128) return a.K < 8192 ? launch_cfg<MidForm<4, 4, 2, 1>, RAW>(a, stream) : launch_cfg<MidForm<8, 3, 2, 1>, RAW>(a, stream);
-    if (a.T <= 32) return launch_cfg<MidForm<4, 3, 2, 1>, RAW>(a, stream);
-    if (tiles <= 256) return launch_cfg<MidForm<4, 3, 2, 2>, RAW>(a, stream);
-    return launch_cfg<MidForm<4, 2, 2, 2>, RAW>(a, stream);
+    using Narrow = MidForm<8, 3, 1, 1, I8>;
+    if (a.K >= 1024 && Narrow::tiles_n(a.N) * Narrow::tiles_t(a.T) <= 256) return launch_cfg<Narrow, RAW>(a, stream);
+    if (tiles <= 128) return a.K < 8192 ? launch_cfg<MidForm<4, 4, 2, 1, I8>, RAW>(a, stream) : launch_cfg<MidForm<8, 3, 2, 1, I8>, RAW>(a, stream);
+    if (a.T <= 32) return launch_cfg<MidForm<4, 3, 2, 1, I8>, RAW>(a, stream);
+    if (tiles <= 256) return launch_cfg<MidForm<4, 3, 2, 2, I8>, RAW>(a, stream);
+    return launch_cfg<MidForm<4, 2, 2, 2, I8>, RAW>(a, stream);
 }
 
 template <typename FA, typename FB>
@@ -273,15 +315,27 @@ int launch_grouped_forms(MidArgs& args, hipStream_t stream) {
     return after_launch();
 }
 
+template <bool I8>
+int launch_grouped(MidArgs& args, int max_t, int64_t tiles, hipStream_t stream) {
+    if (max_t <= 32 && (!I8 || tiles <= kMidResident))   // (more tiles of records than that stay with the shared form)
+        return launch_grouped_forms<MidForm<4, 3, 2, 1, I8>, MidForm<8, 2, 1, 1, I8>>(args, stream);
+    if constexpr (I8) {
+        if (max_t <= 32) return launch_grouped_forms<MidForm<2, 4, 4, 1, true>, MidForm<8, 2, 1, 1, true>>(args, stream);
+    }
+    if (tiles <= kMidResident) return launch_grouped_forms<MidForm<4, 2, 2, 2, I8>, MidForm<8, 2, 1, 1, I8>>(args, stream);
+    return launch_grouped_forms<MidForm<2, 3, 4, 2, I8>, MidForm<4, 3, 2, 1, I8>>(args, stream);
+}
+
 }  // namespace
 
 bool mid_gemm_preferred(int64_t T, int64_t N) { return T <= 64 || mid_tiles(T, N) <= kMidResident; }
 
-int launch_mid_gemm_f6f4(const MidProblem& a, hipStream_t stream) {
-    return a.acc_out ? launch_form<true>(a, stream) : launch_form<false>(a, stream);
+int launch_mid_gemm(const MidProblem& a, bool records, hipStream_t stream) {
+    if (records) return a.acc_out ? launch_form<false, true>(a, stream) : launch_form<false, false>(a, stream);
+    return a.acc_out ? launch_form<true, true>(a, stream) : launch_form<true, false>(a, stream);
 }
 
-int launch_mid_gemm_grouped(MidArgs& args, hipStream_t stream) {
+int launch_mid_gemm_grouped(MidArgs& args, bool records, hipStream_t stream) {
     if (args.n <= 0) return HBL_OK;
     // long K ranges first: their workgroups run longest
     for (int i = 1; i < args.n; ++i)
@@ -294,28 +348,28 @@ int launch_mid_gemm_grouped(MidArgs& args, hipStream_t stream) {
     // tokens, four 7B projections, 832 tiles: 36.2 -> 30.5 us per layer), and a long K range takes more groups and smaller
     // tiles so that it does not outlast the rest (with eight one-wave groups it is 640 workgroups: 36.5 us).
     int max_t = 0;
-    int64_t tiles = 0;
+    int64_t tiles = 0, narrow = 0;
     for (int i = 0; i < args.n; ++i) {
         max_t = args.p[i].T > max_t ? args.p[i].T : max_t;
         tiles += mid_tiles(args.p[i].T, args.p[i].N);
-        args.p[i].form = args.p[i].K >= 8192 ? 1 : 0;
+        narrow += MidForm<8, 2, 1, 1>::tiles_n(args.p[i].N) * MidForm<8, 2, 1, 1>::tiles_t(args.p[i].T);
     }
-    if (max_t <= 32) return launch_grouped_forms<MidForm<4, 3, 2, 1>, MidForm<8, 2, 1, 1>>(args, stream);
-    if (tiles <= kMidResident) return launch_grouped_forms<MidForm<4, 2, 2, 2>, MidForm<8, 2, 1, 1>>(args, stream);
-    return launch_grouped_forms<MidForm<2, 3, 4, 2>, MidForm<4, 3, 2, 1>>(args, stream);
+    for (int i = 0; i < args.n; ++i) args.p[i].form = args.p[i].K >= (narrow <= kMidResident ? 2048 : 8192) ? 1 : 0;
+    return records ? launch_grouped<false>(args, max_t, tiles, stream) : launch_grouped<true>(args, max_t, tiles, stream);
 }
 
 // A group at 47 tokens: 2048 / 8192 projections 21.2 -> 14.7 us per layer against the shared form of the weight-streaming
 // kernel, 7B 31.8 -> 30.5; up to 32 tokens that form's 512 workgroups of four waves are the better one once the tiles do not
 // fit at once (7B, 20 tokens: 25.3 against 26.0 us per layer; 2048 / 8192, 24 tokens: 17.0 against 14.0).
-bool mid_group_preferred(const DecodeProblem* p, int n) {
+// INT8 activations: 7B 20 tokens 27.2 -> 25.2, 64 tokens 36.8 -> 32, 2048 / 8192 40 tokens 24.4 -> 14.6.
+bool mid_group_preferred(const DecodeProblem* p, int n, bool records) {
     int max_t = 0;
     int64_t tiles = 0;
     for (int i = 0; i < n; ++i) {
         max_t = p[i].T > max_t ? p[i].T : max_t;
-        if (p[i].f6) tiles += mid_tiles(p[i].T, p[i].N);
+        tiles += mid_tiles(p[i].T, p[i].N);
     }
-    return max_t > 32 || (max_t > 16 && tiles <= kMidResident);
+    return max_t > 16 && (!records || max_t > 32 || tiles <= kMidResident);
 }
 
 }  // namespace hbl

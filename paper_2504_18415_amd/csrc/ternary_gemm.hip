@@ -23,9 +23,8 @@ namespace {
 using namespace gemm;
 typedef int v16i __attribute__((ext_vector_type(16)));
 
-// OCC = waves per SIMD the register budget must allow (2: two workgroups of 4 waves share a CU).
-template <int WAVES_N, int WAVES_T, int TN, int TT, int NSTAGE, bool RAW, bool SPLIT, int OCC>
-__global__ __launch_bounds__(64 * WAVES_N * WAVES_T, OCC) void ternary_gemm_kernel(const GemmArgs a) {
+template <int WAVES_N, int WAVES_T, int TN, int TT, int NSTAGE, bool RAW>
+__global__ __launch_bounds__(64 * WAVES_N * WAVES_T) void ternary_gemm_kernel(const GemmArgs a) {
     constexpr int NW = WAVES_N * WAVES_T;
     constexpr int BN = WAVES_N * TN * 32;
     constexpr int BT = WAVES_T * TT * 32;
@@ -33,14 +32,12 @@ __global__ __launch_bounds__(64 * WAVES_N * WAVES_T, OCC) void ternary_gemm_kern
     constexpr int WBYTES = (BN / 32) * 1024;       // packed weights per stage
     constexpr int STAGE = XBYTES + WBYTES;
     constexpr int XL = (BT / 8) / NW;              // global->LDS instructions per wave per stage: codes
-    constexpr int WL = (BN / 32 + NW - 1) / NW;    // ... and weights (waves beyond BN/32 tiles issue none)
+    constexpr int WL = (BN / 32) / NW;             // ... and weights
     static_assert((BT / 8) % NW == 0, "code loads must divide evenly over the waves");
-    static_assert((BN / 32) % NW == 0 || (BN / 32) < NW, "weight loads must divide evenly over the waves");
+    static_assert((BN / 32) % NW == 0, "weight loads must divide evenly over the waves");
     static_assert(NSTAGE >= 2, "need at least double buffering");
-    // loads of later stages that may stay in flight while stage kb is consumed (waves that issue fewer
-    // weight loads than WL simply wait for a little more than they must)
-    constexpr int WL_MIN = (BN / 32) >= NW ? WL : 0;
-    constexpr int PENDING = (NSTAGE - 2) * (XL + WL_MIN);
+    // loads of later stages that may stay in flight while stage kb is consumed
+    constexpr int PENDING = (NSTAGE - 2) * (XL + WL);
 
     extern __shared__ __attribute__((aligned(1024))) char lds[];
 
@@ -53,21 +50,13 @@ __global__ __launch_bounds__(64 * WAVES_N * WAVES_T, OCC) void ternary_gemm_kern
     // Workgroups are dealt round-robin over the 8 XCDs; give each XCD a contiguous run of tiles
     // (feature tile fastest) so that the workgroups sharing an activation panel share an L2.
     int wg = blockIdx.x;
-    int ks = 0;
     const int nwg = a.tiles_n * a.tiles_t;
-    if constexpr (SPLIT) {
-        ks = wg % a.split_k;
-        wg = wg / a.split_k;
-    } else {
-        if ((nwg & 7) == 0) wg = (wg & 7) * (nwg >> 3) + (wg >> 3);
-    }
+    if ((nwg & 7) == 0) wg = (wg & 7) * (nwg >> 3) + (wg >> 3);
     const int tile_n = wg % a.tiles_n;
     const int tile_t = wg / a.tiles_n;
     const int n0 = tile_n * BN;
     const int t0 = tile_t * BT;
-    const int nkb_total = a.K / kBK;
-    const int nkb = SPLIT ? nkb_total / a.split_k : nkb_total;   // K-blocks of this workgroup
-    const int kb_first = ks * nkb;
+    const int nkb = a.K / kBK;
 
     // Global -> LDS copies: wave-uniform 64-bit base (SGPR pair) + 32-bit per-lane offset, so that
     // advancing along K is scalar arithmetic only.
@@ -81,13 +70,13 @@ __global__ __launch_bounds__(64 * WAVES_N * WAVES_T, OCC) void ternary_gemm_kern
         int nt = n0 / 32 + wave + NW * m;
         const int nt_max = a.N / 32 - 1;
         nt = nt < nt_max ? nt : nt_max;
-        wbase[m] = reinterpret_cast<const char*>(a.packed) + (size_t)kb_first * wstride + (size_t)nt * 1024;
+        wbase[m] = reinterpret_cast<const char*>(a.packed) + (size_t)nt * 1024;
     }
     const uint32_t wlane = lane * 16;
     // activation codes: instruction q covers tokens 8q..8q+7, lane l -> token 8q + l/8, LDS slot l%8,
     // global 16-byte chunk (l%8) ^ ((token/2) % 8); rows past T are clamped to the last row.
     // (rows are 128 B = half of the 64 LDS banks: 16 consecutive rows then cover every bank group once)
-    const char* xbase = reinterpret_cast<const char*>(a.codes) + (size_t)t0 * a.K + (size_t)kb_first * kBK;
+    const char* xbase = reinterpret_cast<const char*>(a.codes) + (size_t)t0 * a.K;
     uint32_t xlane[XL];
 #pragma unroll
     for (int m = 0; m < XL; ++m) {
@@ -110,8 +99,7 @@ __global__ __launch_bounds__(64 * WAVES_N * WAVES_T, OCC) void ternary_gemm_kern
             lds_dma16(lds0 + slot * STAGE + q * 1024, xbase + (size_t)kbc * kBK, xlane[m]);
         } else {
             const int wtile = wave + NW * (m - XL);
-            if ((BN / 32) % NW == 0 || wtile < BN / 32)
-                lds_dma16(lds0 + slot * STAGE + XBYTES + wtile * 1024, wbase[m - XL] + (size_t)kbc * wstride, wlane);
+            lds_dma16(lds0 + slot * STAGE + XBYTES + wtile * 1024, wbase[m - XL] + (size_t)kbc * wstride, wlane);
         }
     };
     auto issue = [&](int kb, int slot) {
@@ -257,7 +245,7 @@ __global__ __launch_bounds__(64 * WAVES_N * WAVES_T, OCC) void ternary_gemm_kern
     // (the epilogue's scales are requested first, so that their latency passes under the drain: behind the
     // scheduling fences of the epilogue every one of them would cost its whole round trip)
     float sd_of[TT], alpha_of[TN];
-    if (!RAW && !(SPLIT && a.split_k > 1)) {   // (the int32 forms have no scales: the pointers may be null)
+    if (!RAW) {   // (the int32 form has no scales: the pointers may be null)
 #pragma unroll
         for (int j = 0; j < TT; ++j) {
             const int t = t0 + (wt * TT + j) * 32 + (lane & 31);
@@ -275,8 +263,7 @@ __global__ __launch_bounds__(64 * WAVES_N * WAVES_T, OCC) void ternary_gemm_kern
     asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
 
     // epilogue: lane holds token t = ..+(lane&31); register quad g holds features 8g + 4*(lane>>5) + 0..3
-    const bool write_partial = SPLIT && a.split_k > 1;
-    if (RAW || write_partial) {   // int32 tiles (debug export / split-K partials): stored from where they are
+    if constexpr (RAW) {   // int32 tiles (debug export): stored from where they are
 #pragma unroll
         for (int j = 0; j < TT; ++j) {
             const int t = t0 + (wt * TT + j) * 32 + (lane & 31);
@@ -294,14 +281,11 @@ __global__ __launch_bounds__(64 * WAVES_N * WAVES_T, OCC) void ternary_gemm_kern
                     v4i o;
 #pragma unroll
                     for (int r = 0; r < 4; ++r) o[r] = acc[i][j][4 * g + r];
-                    if constexpr (RAW) *reinterpret_cast<v4i*>(a.acc_out + (size_t)t * a.N + n) = o;
-                    else *reinterpret_cast<v4i*>(a.partial + ((size_t)ks * a.T + t) * a.N + n) = o;
+                    *reinterpret_cast<v4i*>(a.acc_out + (size_t)t * a.N + n) = o;
                 }
             }
         }
-        return;
-    }
-    if constexpr (!RAW) {
+    } else {
         // bf16 output.  Stored from the accumulator layout, every instruction would touch 32 token rows
         // with 16 bytes each, and the output burst at the end of each round of workgroups is bound by the
         // number of such partial-line writes.  So the dequantised tiles go through the wave's share of the
@@ -354,86 +338,36 @@ __global__ __launch_bounds__(64 * WAVES_N * WAVES_T, OCC) void ternary_gemm_kern
     }
 }
 
-// Second half of the split-K path: y[t][n..n+3] from the split_k int32 partial tiles, summed in fixed
-// order (integer, so exact) and passed through the same dequantising epilogue.  A separate launch: the
-// kernel boundary is what makes the partials of workgroups on other XCDs visible.
-__global__ __launch_bounds__(256) void splitk_reduce_kernel(const GemmArgs a) {
-    const int quads = a.N / 4;
-    const int64_t total = (int64_t)a.T * quads;
-    for (int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x; idx < total; idx += (int64_t)gridDim.x * 256) {
-        const int t = (int)(idx / quads);
-        const int n = (int)(idx % quads) * 4;
-        v4i sum = {0, 0, 0, 0};
-        for (int k = 0; k < a.split_k; ++k)
-            sum += *reinterpret_cast<const v4i*>(a.partial + ((size_t)k * a.T + t) * a.N + n);
-        if (a.acc_out) {   // raw export: the integer sum itself
-            *reinterpret_cast<v4i*>(a.acc_out + (size_t)t * a.N + n) = sum;
-            continue;
-        }
-        *reinterpret_cast<uint2*>(a.y + (size_t)t * a.N + n) =
-            dequant_quad(sum, a.s_dequant[t], a.w_scales[n / a.rows_per_group], a.code_offset, a.w_row_sum + n);
-    }
-}
-
-}  // namespace
-namespace gemm {
-int launch_splitk_reduce(const GemmArgs& a, hipStream_t stream) {
-    const int64_t quads = (int64_t)a.T * (a.N / 4);
-    int64_t blocks = (quads + 255) / 256;
-    if (blocks > 2048) blocks = 2048;
-    launch_kernel("splitk_reduce_kernel", splitk_reduce_kernel, dim3((unsigned)blocks), dim3(256), 0, stream, a);
-    return after_launch();
-}
-}  // namespace gemm
-namespace {
-
-template <int WAVES_N, int WAVES_T, int TN, int TT, int NSTAGE, bool RAW, bool SPLIT = false, int OCC = 1>
+template <int WAVES_N, int WAVES_T, int TN, int TT, int NSTAGE, bool RAW>
 int launch_cfg(GemmArgs a, hipStream_t stream) {
     constexpr int BN = WAVES_N * TN * 32;
     constexpr int BT = WAVES_T * TT * 32;
     constexpr size_t lds = (size_t)NSTAGE * (BT * kBK + (BN / 32) * 1024);
     a.tiles_n = (a.N + BN - 1) / BN;
     a.tiles_t = (a.T + BT - 1) / BT;
-    if (!SPLIT) a.split_k = 1;
-    auto kern = ternary_gemm_kernel<WAVES_N, WAVES_T, TN, TT, NSTAGE, RAW, SPLIT, OCC>;
+    auto kern = ternary_gemm_kernel<WAVES_N, WAVES_T, TN, TT, NSTAGE, RAW>;
     static std::atomic<uint64_t> lds_allowed{0};   // per instantiation: devices already set up
     if (const int rc = allow_dynamic_lds(kern, lds, lds_allowed); rc != HBL_OK) return rc;
-    launch_kernel("ternary_gemm_kernel", kern, dim3((unsigned)(a.tiles_n * a.tiles_t * a.split_k)), dim3(64 * WAVES_N * WAVES_T), lds,
+    launch_kernel("ternary_gemm_kernel", kern, dim3((unsigned)(a.tiles_n * a.tiles_t)), dim3(64 * WAVES_N * WAVES_T), lds,
                        stream, a);
-    int rc = after_launch();
-    if (rc != HBL_OK || !SPLIT || a.split_k == 1) return rc;
-    return launch_splitk_reduce(a, stream);
+    return after_launch();
 }
 
 template <bool RAW>
 int choose(const GemmArgs& a, hipStream_t stream, int tile) {
     const int64_t big_tiles = (int64_t)((a.N + 255) / 256) * ((a.T + 255) / 256);
-    int cfg;
-    if (a.T <= 64 && a.partial != nullptr && !RAW) cfg = a.T <= 32 ? 6 : 7;
-    else if (a.T > 64 && a.partial != nullptr && a.split_k > 1 && !RAW) cfg = 8;   // mid-size batch, long K
-    else if (a.T <= 32) cfg = 0;
-    else if (a.T <= 64) cfg = 1;
-    else if (big_tiles >= 200) {
+    int cfg = kTileSmall;
+    if (big_tiles >= 200) {
         // 512 features x 128 tokens moves 32 KB per stage (16 codes + 16 weights) against 40 KB for 256 x 256:
         // 1-3 % faster here (4 % on the fp6 x fp4 kernel); the square tile stays where the wide one pads more
         const int64_t wide_tiles = (int64_t)((a.N + 511) / 512) * ((a.T + 127) / 128);
-        cfg = wide_tiles <= big_tiles ? 4 : 3;
-    } else cfg = 2;
-    if (tile != kTileAuto && cfg < 6) {   // parity tests name the tile of the unsplit kernel themselves
-        if (tile == kTileSquare) cfg = 3;
-        else if (tile == kTileSmall) cfg = 2;
-        else if (tile == kTileWide) cfg = 4;
-        else return HBL_E_SHAPE;
+        cfg = wide_tiles <= big_tiles ? kTileWide : kTileSquare;
     }
+    if (tile != kTileAuto) cfg = tile;   // parity tests name the tile themselves
     switch (cfg) {
-        case 0: return launch_cfg<4, 1, 2, 1, 4, RAW>(a, stream);   // 256 features x 32 tokens, 4 waves
-        case 1: return launch_cfg<4, 1, 2, 2, 4, RAW>(a, stream);   // 256 x 64, 4 waves
-        case 2: return launch_cfg<2, 2, 2, 2, 4, RAW>(a, stream);   // 128 x 128, 4 waves
-        case 3: return launch_cfg<2, 2, 4, 4, 3, RAW>(a, stream);   // 256 x 256, 4 waves of 128 x 128
-        case 4: return launch_cfg<4, 1, 4, 4, 3, RAW>(a, stream);   // 512 features x 128 tokens, 4 waves of 128 x 128
-        case 6: if constexpr (!RAW) return launch_cfg<4, 1, 1, 1, 4, false, true>(a, stream);   // 128 x 32, split-K
-        case 7: if constexpr (!RAW) return launch_cfg<4, 1, 1, 2, 4, false, true>(a, stream);   // 128 x 64, split-K
-        case 8: if constexpr (!RAW) return launch_cfg<2, 2, 2, 2, 4, false, true>(a, stream);   // 128 x 128, split-K
+        case kTileSmall: return launch_cfg<2, 2, 2, 2, 4, RAW>(a, stream);    // 128 x 128, 4 waves
+        case kTileSquare: return launch_cfg<2, 2, 4, 4, 3, RAW>(a, stream);   // 256 x 256, 4 waves of 128 x 128
+        case kTileWide: return launch_cfg<4, 1, 4, 4, 3, RAW>(a, stream);     // 512 features x 128 tokens, 4 waves of 128 x 128
         default: return HBL_E_SHAPE;
     }
 }
@@ -442,8 +376,7 @@ int choose(const GemmArgs& a, hipStream_t stream, int tile) {
 
 int launch_ternary_gemm(const int8_t* codes, int code_offset, int64_t T, int64_t K, const void* packed, int64_t N,
                         const float* s_dequant, const float* w_scales,
-                        int64_t n_scale_groups, void* y_bf16, int32_t* acc_out, int32_t* splitk_partial,
-                        hipStream_t stream, int tile) {
+                        int64_t n_scale_groups, void* y_bf16, int32_t* acc_out, hipStream_t stream, int tile) {
     if (T == 0) return HBL_OK;
     GemmArgs a;
     a.codes = codes;
@@ -459,8 +392,22 @@ int launch_ternary_gemm(const int8_t* codes, int code_offset, int64_t T, int64_t
     a.N = (int)N;
     a.rows_per_group = n_scale_groups > 0 ? (int)(N / n_scale_groups) : (int)N;
     a.tiles_n = a.tiles_t = 0;
-    a.split_k = splitk_partial ? (T <= 64 ? decode_split_k(T, K, N) : prefill_split_k(T, K, N)) : 1;
-    a.partial = splitk_partial;
+    if (tile == kTileAuto && mid_gemm_preferred(T, N)) {   // too few tiles for the chip
+        MidProblem m = {};
+        m.codes = a.codes;
+        m.packed = a.packed;
+        m.s_dequant = a.s_dequant;
+        m.w_scales = a.w_scales;
+        m.y = a.y;
+        m.acc_out = a.acc_out;
+        m.T = a.T;
+        m.K = a.K;
+        m.N = a.N;
+        m.rows_per_group = a.rows_per_group;
+        m.code_offset = a.code_offset;
+        m.w_row_sum = a.w_row_sum;
+        return launch_mid_gemm(m, false, stream);
+    }
     return acc_out ? choose<true>(a, stream, tile) : choose<false>(a, stream, tile);
 }
 

@@ -394,7 +394,7 @@ int launch_ternary_gemm_f6f4(const int8_t* code_records, int64_t T, int64_t K, c
             m.K = a.K;
             m.N = a.N;
             m.rows_per_group = a.rows_per_group;
-            return launch_mid_gemm_f6f4(m, stream);
+            return launch_mid_gemm(m, true, stream);
         }
         default: return HBL_E_SHAPE;
     }

@@ -580,15 +580,16 @@ def test_config4_wdown_swiglu_input(hbl):
 
 
 @pytest.mark.parametrize("T,K,N,groups", [
-    (17, 8320, 96, 1), (64, 8192, 4128, 1),       # up to 64 tiles of 64 x 64, long K; one more than that
-    (65, 640, 32, 1), (100, 8320, 96, 1),         # up to 128 tiles: 32-token tiles, 4 groups; long K
+    (17, 8320, 96, 1), (64, 1152, 4096, 1),       # up to 256 tiles of 32 x 32, K >= 1024: one wave per K group
+    (64, 8192, 4128, 1), (65, 640, 32, 1),        # up to 128 tiles of 64 x 64: 32-token tiles, 8 and 4 K groups
     (20, 640, 8224, 1),                           # more, but at most 32 tokens
     (300, 640, 3104, 1),                          # up to 256 tiles: one workgroup per CU
     (70, 512, 10016, 1), (1000, 896, 1152, 3),    # up to 512: two per CU, weights / codes shared out over the XCDs
 ])
 def test_mid_size_gemm_forms(hbl, T, K, N, groups):
-    """The mid-size fp6 x fp4 kernel in every form its rule picks, with ragged token and feature tiles and K-blocks that
-    do not divide over the K groups: accumulators against the exact integer product, bf16 outputs bit for bit."""
+    """The mid-size kernel in every form its rule picks, on both operand paths (code records; bytes as they are and with
+    the INT4 offset), with ragged token and feature tiles and K-blocks that do not divide over the K groups: accumulators
+    against the exact integer product, bf16 outputs bit for bit."""
     note(f"mid-size GEMM T={T} K={K} N={N}")
     rng = np.random.default_rng(T + K + N)
     q = rng.integers(-8, 8, (T, K)).astype(np.int8)
@@ -601,10 +602,22 @@ def test_mid_size_gemm_forms(hbl, T, K, N, groups):
     assert torch.equal(hbl.gemm_i32_bf6(rec, packed, N, T, K).double(), want)
     sd = torch.rand(T, device="cuda") + 0.5
     alpha = torch.rand(groups, device="cuda") + 0.5
-    y = hbl.gemm_dequant_bf16(rec, sd, torch.zeros(T, dtype=torch.int32, device="cuda"), packed, N, alpha,
-                              code_offset=hbl.CODES_BF6, K=K)
-    ref = ((want.float() * sd[:, None]) * alpha.repeat_interleave(N // groups)[None, :]).to(torch.bfloat16)
-    assert torch.equal(y, ref)
+    unused = torch.zeros(T, dtype=torch.int32, device="cuda")
+
+    def outputs(acc):
+        return ((acc.float() * sd[:, None]) * alpha.repeat_interleave(N // groups)[None, :]).to(torch.bfloat16)
+
+    y = hbl.gemm_dequant_bf16(rec, sd, unused, packed, N, alpha, code_offset=hbl.CODES_BF6, K=K)
+    assert torch.equal(y, outputs(want))
+    y = hbl.gemm_dequant_bf16(torch.from_numpy(q + 8).cuda(), sd, unused, packed, N, alpha,
+                              code_offset=hbl.CODES_UINT4_PLUS8)
+    assert torch.equal(y, outputs(want))
+    q8 = rng.integers(-128, 128, (T, K)).astype(np.int8)
+    q8[3], q8[T - 1] = -128, 127
+    q8 = torch.from_numpy(q8).cuda()
+    want = q8.double() @ torch.from_numpy(c).cuda().double().t()
+    assert torch.equal(hbl.gemm_i32(q8, packed, N).double(), want)
+    assert torch.equal(hbl.gemm_dequant_bf16(q8, sd, unused, packed, N, alpha), outputs(want))
 
 
 @pytest.mark.parametrize("shapes", [
@@ -613,18 +626,19 @@ def test_mid_size_gemm_forms(hbl, T, K, N, groups):
     [(33, 640, 16416), (64, 8320, 160), (40, 512, 16448), (50, 256, 64)],     # more tiles than workgroups fit at once
     [(20, 640, 16416), (32, 8320, 160), (24, 512, 16448)],                    # ... at most 32 tokens
 ], ids=["few", "more_tokens", "many_tiles", "many_tiles_32"])
-def test_grouped_forms_beyond_16_tokens(hbl, shapes):
-    """Groups beyond 16 tokens: every form of the grouped mid-size launch, rows shorter than 512 (bytes, another launch)
-    and small members beside it; each output bit for bit as the problem gives alone, which takes another form."""
-    note(f"grouped forms {shapes}")
+@pytest.mark.parametrize("bits", [4, 8])
+def test_grouped_forms_beyond_16_tokens(hbl, shapes, bits):
+    """Groups beyond 16 tokens: every form of the grouped mid-size launch, rows shorter than 512 (bytes, a launch
+    beside that of the records) and small members; each output bit for bit as the problem gives alone, which takes another form."""
+    note(f"grouped forms bits={bits} {shapes}")
     g = torch.Generator(device="cuda").manual_seed(11)
     items = []
     for T, K, N in shapes:
         codes = torch.randint(-1, 2, (N, K), dtype=torch.int8, device="cuda", generator=g)
         x = torch.randn((T, K), device="cuda", generator=g).to(torch.bfloat16)
-        items.append((x, hbl.pack_ternary_2bit(codes), N, torch.rand(1, device="cuda", generator=g) + 0.5, 4, False, None))
+        items.append((x, hbl.pack_ternary_2bit(codes), N, torch.rand(1, device="cuda", generator=g) + 0.5, bits, False, None))
     for y, it in zip(hbl.bitlinear_forward_grouped(items, EPS), items):
-        assert torch.equal(y, hbl.plain_bitlinear_forward(it[0], it[1], it[2], it[3], 4, EPS)), it[0].shape
+        assert torch.equal(y, hbl.plain_bitlinear_forward(it[0], it[1], it[2], it[3], bits, EPS)), it[0].shape
 
 
 @pytest.mark.parametrize("T,K,N", [(300, 1024, 544), (129, 4096, 96), (513, 512, 1056)])
