@@ -1,11 +1,11 @@
 // Mid-size form of the ternary GEMM, on both operand paths (code records for the fp6 x fp4 matrix cores; bytes for the int8
 // ones: INT8 activations, rows shorter than 512): batches of 17 tokens up to where the prefill kernels have enough 128 x 128
-// tiles for the chip, and smaller ones where the weight-streaming kernel has few workgroups with long chains.  There the output is too small to give every CU a tile and a CU that walks a long K
-// range by itself is bound by the latency of one stage after another, so the K range is cut - over the waves of one
-// workgroup, not over workgroups: K group g of KG takes the K-blocks g, g + KG, ...  A pipeline stage is one K-block per
-// group (token rows of the record image and packed weight tiles), copied to LDS as contiguous 1 KiB pieces.  The groups'
-// accumulators (exact integers) are added through LDS at the end, on the way to whole-line stores: no partial tiles in
-// memory and no second launch.
+// tiles for the chip, and smaller ones where the weight-streaming kernel has few workgroups with long chains.
+// There the output is too small to give every CU a tile and a CU that walks a long K range by itself is bound by the latency
+// of one stage after another, so the K range is cut - over the waves of one workgroup, not over workgroups: K group g of KG
+// takes the K-blocks g, g + KG, ...  A pipeline stage is one K-block per group (code rows and packed weight tiles), copied to
+// LDS in 1 KiB pieces.  The groups' accumulators (exact integers) are added through LDS at the end, on the way to whole-line
+// stores: no partial tiles in memory and no second launch.
 // Bound by the copies' trip through L2 and LDS (64 / 128 bytes per clock and CU) behind the start-up of the launch.  Whole
 // call, both launches, against what ran before: 128 x 128 tiles above 64 tokens, with K >= 8192 cut over workgroups and a
 // reduction launch: 300 tokens x 8192 -> 3072 28.8 -> 19.4 us, 97 x 11008 -> 4096 26.6 -> 17.0, 200 x 8192 -> 2048 21.8 ->
@@ -284,6 +284,8 @@ int launch_cfg(MidProblem a, hipStream_t stream) {
 // each of eight one-wave groups at least one K-block, that form needs no barrier and half of the stages (64 tokens, 16384 ->
 // 4096: 18.5 -> 14.4 us; 32 x 4096 -> 4096 9.3 -> 7.6; 64 x 1024 -> 4096 6.3 -> 6.0).  Above 512 tiles the 128 x 128 tile of
 // the prefill kernel is faster (256 tokens, 4096 -> 12288, 768 tiles: 18.0 against 20.5 us).
+int64_t mid_tiles(int64_t T, int64_t N) { return MidForm<4, 2, 2, 2>::tiles_n(N) * MidForm<4, 2, 2, 2>::tiles_t(T); }
+
 constexpr int64_t kMidResident = 512;   // workgroups of 8 waves and up to 80 KiB of LDS that the chip holds at once
 
 template <bool I8, bool RAW>
