@@ -19,7 +19,7 @@ CSRC = os.path.join(PKG, "csrc")
 OBJ_DIR = os.path.join(CSRC, "_build")
 LIB = os.path.join(PKG, "libhbitlinear.so")
 SOURCES = ["api.hip", "fwht_quant.hip", "ternary_setup.hip", "ternary_gemm.hip", "ternary_gemm_f6f4.hip", "mid_gemm.hip",
-           "decode_gemm.hip", "kv_quant.hip"]
+           "decode_gemm.hip", "fused_small.hip", "kv_quant.hip"]
 
 HIPCC_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",

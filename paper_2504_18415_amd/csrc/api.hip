@@ -115,6 +115,8 @@ int forward(const void* x, int x_dtype, int64_t T, int64_t K, const void* Wq_pac
     if (T == 0) return HBL_OK;
     if (workspace_bytes < carve_workspace(nullptr, T, K, N, with_partial).bytes) return HBL_E_WORKSPACE;
     hipStream_t s = static_cast<hipStream_t>(stream);
+    if (!ln_gain && fused_small_preferred(T, K, N, x_dtype, bits, hadamard))
+        return launch_fused_small(x, x_dtype, T, K, Wq_packed, N, w_scales, groups, eps, hadamard, y, s);
     const Workspace ws = carve_workspace(workspace, T, K, N, with_partial);
     const int code_form = code_form_for(K, bits);
     rc = launch_fwht_quant(x, x_dtype, T, K, bits, eps, hadamard, ws.codes, ws.s_dequant, nullptr, code_form, s, ln_gain,

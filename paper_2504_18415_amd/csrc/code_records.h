@@ -40,12 +40,15 @@ __device__ __forceinline__ int record_hi_offset(int r, int s, int h) {
 
 // Store the 16 codes of features [16*quad, 16*quad + 16) of token t, given as 96 bits d0 | d1 << 32 | d2 << 64
 // (feature 16*quad + i at bits [6i, 6i+6)), into the record image of a [*, K] code buffer.
+// BLOCKB: bytes from one K-block of the row to the next.  (Other than kRecordBlockBytes: an image of a few rows, 96 bytes
+// each per K-block, in LDS.)
+template <int BLOCKB = kRecordBlockBytes>
 __device__ __forceinline__ void store_code_quad(int8_t* codes, int64_t t, int K, int quad, uint32_t d0, uint32_t d1,
                                                 uint32_t d2) {
     const int r = (int)(t & (kPanelTokens - 1));
     const int kb = quad >> 3, s = (quad >> 2) & 1, h = (quad >> 1) & 1;
     char* row = reinterpret_cast<char*>(codes) +
-                ((size_t)(t >> 7) * (size_t)(K >> 7) + (size_t)kb) * kRecordBlockBytes + r * kRecordRowBytes;
+                ((size_t)(t >> 7) * (size_t)(K >> 7) + (size_t)kb) * BLOCKB + r * kRecordRowBytes;
     char* lo = row + record_lo_offset(r, s, h);
     if ((quad & 1) == 0) {   // bits 0..95 of the record
         *reinterpret_cast<uint2*>(lo) = make_uint2(d0, d1);
@@ -59,12 +62,13 @@ __device__ __forceinline__ void store_code_quad(int8_t* codes, int64_t t, int K,
 // Store the 32 codes of features [32*rec, 32*rec + 32) of token t - a whole record, given as six dwords (feature
 // 32*rec + i at bits [6i, 6i+6)) - as its 16-byte and its 8-byte piece.  The row address is uniform over a
 // workgroup that works on one token and the rest is a 32-bit per-lane offset.
+template <int BLOCKB = kRecordBlockBytes>
 __device__ __forceinline__ void store_code_record(int8_t* codes, int64_t t, int K, int rec, uint32_t d0, uint32_t d1,
                                                   uint32_t d2, uint32_t d3, uint32_t d4, uint32_t d5) {
     const int r = (int)(t & (kPanelTokens - 1));
     const int kb = rec >> 2, s = (rec >> 1) & 1, h = rec & 1;
-    char* row = reinterpret_cast<char*>(codes) + (size_t)(t >> 7) * (size_t)(K >> 7) * kRecordBlockBytes + r * kRecordRowBytes;
-    const uint32_t blk = (uint32_t)kb * kRecordBlockBytes;
+    char* row = reinterpret_cast<char*>(codes) + (size_t)(t >> 7) * (size_t)(K >> 7) * BLOCKB + r * kRecordRowBytes;
+    const uint32_t blk = (uint32_t)kb * BLOCKB;
     *reinterpret_cast<uint4*>(row + (blk + (uint32_t)record_lo_offset(r, s, h))) = make_uint4(d0, d1, d2, d3);
     *reinterpret_cast<uint2*>(row + (blk + (uint32_t)record_hi_offset(r, s, h))) = make_uint2(d4, d5);
 }

@@ -187,6 +187,11 @@ int launch_ternary_gemm_f6f4(const int8_t* code_records, int64_t T, int64_t K, c
                              const float* s_dequant, const float* w_scales, int64_t n_scale_groups, void* y_bf16,
                              hipStream_t stream, int32_t* acc_out = nullptr, int tile = kTileAuto);
 
+// One-launch form for one to four tokens (fused_small.hip): INT4 activations, K >= 512, no norm.
+bool fused_small_preferred(int64_t T, int64_t K, int64_t N, int x_dtype, int bits, bool hadamard);
+int launch_fused_small(const void* x, int x_dtype, int64_t T, int64_t K, const void* packed, int64_t N, const float* w_scales,
+                       int64_t groups, float eps, bool hadamard, void* y, hipStream_t stream);
+
 // ---------------------------------------------------------------------------------------------
 // Grouped small-batch path: up to kMaxGroup independent projections (T <= 64 each) served by one
 // quantiser launch and one GEMM launch (a K range split over workgroups is reduced by the last of them to

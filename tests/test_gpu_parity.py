@@ -620,6 +620,36 @@ def test_mid_size_gemm_forms(hbl, T, K, N, groups):
     assert torch.equal(hbl.gemm_dequant_bf16(q8, sd, unused, packed, N, alpha), outputs(want))
 
 
+@pytest.mark.parametrize("T,K,N,groups,hadamard", [
+    (1, 640, 96, 1, False), (1, 4096, 24544, 1, False), (1, 4096, 32736, 3, False),   # 16, 32, 64 output rows a workgroup
+    (1, 11008, 288, 3, False), (2, 4096, 64, 1, False), (4, 1920, 96, 1, False),
+    (1, 512, 32, 1, True), (3, 1024, 96, 3, True), (4, 2048, 64, 2, True), (2, 2048, 24608, 1, True),
+    (1, 4096, 96, 1, True), (4, 4096, 64, 1, True), (1, 8192, 160, 1, True), (1, 16384, 96, 1, True),
+])
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+def test_one_launch_small_batches(hbl, T, K, N, groups, hadamard, dtype):
+    """One to four tokens in one launch: every row form, share of output rows and ragged edge, bit for bit what the two
+    stages give on their own (the quantiser's records, then a GEMM kernel on them)."""
+    note(f"one-launch form T={T} K={K} N={N} hadamard={hadamard} {dtype}")
+    g = torch.Generator(device="cuda").manual_seed(T + K + N)
+    codes = torch.randint(-1, 2, (N, K), dtype=torch.int8, device="cuda", generator=g)
+    x = torch.randn((T, K), device="cuda", generator=g)
+    x[:, 5] *= 40
+    x = x.to(dtype)
+    alpha = torch.rand(groups, device="cuda", generator=g) + 0.5
+    packed = hbl.pack_ternary_2bit(codes)
+    fn = hbl.hbitlinear_forward if hadamard else hbl.plain_bitlinear_forward
+    y = torch.full((T + 1, N), 7.0, dtype=torch.bfloat16, device="cuda")     # a row that stays as it is
+    with hbl.trace(4) as tr:
+        fn(x, packed, N, alpha, 4, EPS, y=y[:T])
+        torch.cuda.synchronize()
+    if dtype == torch.bfloat16 or N < 24600:     # (fp32 rows take more LDS: the two largest do not fit at once)
+        assert [name for name, _ in tr.launches] == ["fused_small_kernel"]
+    rec, sd, cs = hbl.fwht_quant(x, 4, hadamard, EPS, code_offset=hbl.CODES_BF6)
+    want = hbl.gemm_dequant_bf16(rec, sd, cs, packed, N, alpha, code_offset=hbl.CODES_BF6, K=K)
+    assert torch.equal(y[:T], want) and bool((y[T] == 7.0).all())
+
+
 @pytest.mark.parametrize("shapes", [
     [(20, 640, 96), (17, 8320, 160), (5, 512, 32), (32, 256, 64)],            # at most 32 tokens, few tiles
     [(40, 640, 96), (64, 8320, 160), (5, 512, 32), (33, 384, 64)],            # more tokens
