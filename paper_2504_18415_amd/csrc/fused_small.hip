@@ -122,9 +122,11 @@ __global__ __launch_bounds__(256) void fused_small_kernel(const FusedArgs a) {
     int8_t* const codes = reinterpret_cast<int8_t*>(lds + a.codes_off);
     const RowParams rp{a.eps, nullptr, 0.0f, 1};
     if constexpr (LOG2K == 0) {
-        for (int t = 0; t < a.T; ++t)
+        for (int t = 0; t < a.T; ++t) {
+            if (t != 0) __syncthreads();   // every wave is done with the previous row's partial sums
             quant_generic_body<4, BF16, MAXC, BLOCK>(0, tid, lds + t * (MAXC * 2048) * EB, K, codes + t * kRecordRowBytes, s_d + t,
-                                                           nullptr, rp, kCodesBf6);
+                                                     nullptr, rp, kCodesBf6);
+        }
     } else if constexpr (LOG2K < 12) {
         fwht_quant_body<LOG2K, 1, 4, BF16, true, BLOCK>(0, rtid, slot, codes + row * kRecordRowBytes, s_d + row, nullptr, rp, kCodesBf6);
     } else {

@@ -232,7 +232,7 @@ struct RowParams {
     float eps;
     const float* ln_gain;   // [K] fp32 or nullptr
     float ln_eps;
-    int few_rows;           // a launch of at most 64 rows: latency matters, not throughput (reduction form)
+    int few_rows;           // few rows per SIMD: a row's latency matters, not throughput (reduction form)
 };
 
 // r of the row from this thread's partial sum of squares `ss`: wave butterfly, then a fixed-order
@@ -476,9 +476,11 @@ __device__ __forceinline__ void fwht_quant_body(int64_t row, int tid, const void
         for (int e = 0; e < CH; ++e) {
             const float y = v[r][e] * gain;
             const float t = __builtin_amdgcn_fmed3f(y, lo, hi);
-            const uint32_t bits = as_u(t + magic);
-            isum += (int)bits;
-            packed[e / 4] |= (bits & 0xFFu) << (8 * (e % 4));
+            packed[e / 4] |= (as_u(t + magic) & 0xFFu) << (8 * (e % 4));
+        }
+        if (code_sum) {   // uniform, and off on the forward path: += the stored bytes
+#pragma unroll
+            for (int p = 0; p < (CH + 3) / 4; ++p) isum = __builtin_amdgcn_sdot4((int)packed[p], 0x01010101, isum, false);
         }
         int g;
         if (exchanged) {
@@ -499,19 +501,18 @@ __device__ __forceinline__ void fwht_quant_body(int64_t row, int tid, const void
             *reinterpret_cast<uint8_t*>(dst) = (uint8_t)packed[0];
         }
     }
-    isum = (int)((uint32_t)isum - (uint32_t)E * as_u(magic));  // remove the constant's bit pattern (mod 2^32)
-    isum = wave_sum(isum, few_rows);
-    if constexpr (W > 1) {
-        if (lane == 0) red_i[wave] = isum;
-        __syncthreads();
-        isum = 0;
+    if (code_sum) {
+        isum = wave_sum(isum - E * code_offset, few_rows);
+        if constexpr (W > 1) {
+            if (lane == 0) red_i[wave] = isum;
+            __syncthreads();
+            isum = 0;
 #pragma unroll
-        for (int w = 0; w < W; ++w) isum += red_i[w];
+            for (int w = 0; w < W; ++w) isum += red_i[w];
+        }
+        if (tid == 0) code_sum[row] = isum;
     }
-    if (tid == 0) {
-        s_dequant[row] = s_d;
-        if (code_sum) code_sum[row] = isum;
-    }
+    if (tid == 0) s_dequant[row] = s_d;
 }
 
 // Plain BitLinear front end for K that is not a power of two (K % 128 == 0, K <= 16384): the same
@@ -601,22 +602,24 @@ __device__ __forceinline__ void quant_generic_body(int64_t row, int tid, const v
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
                 const float t = __builtin_amdgcn_fmed3f(v[c][e] * gain, lo, hi);
-                const uint32_t bits = as_u(t + magic);
-                isum += (int)(bits - as_u(magic));
-                packed[e / 4] |= (bits & 0xFFu) << (8 * (e % 4));
+                packed[e / 4] |= (as_u(t + magic) & 0xFFu) << (8 * (e % 4));
+            }
+            if (code_sum) {   // uniform, and off on the forward path: += the stored bytes
+                isum = __builtin_amdgcn_sdot4((int)packed[0], 0x01010101, isum - 8 * code_offset, false);
+                isum = __builtin_amdgcn_sdot4((int)packed[1], 0x01010101, isum, false);
             }
             // K / 8 is a multiple of 16: the lanes of a quad are in or out of this branch together
             if (bf6) bf6_store_pair<BLOCKB>(codes, row, K, ch, bf6_pack4(packed[0]), bf6_pack4(packed[1]));
             else *reinterpret_cast<uint2*>(codes + row_off + (int64_t)ch * 8) = make_uint2(packed[0], packed[1]);
         }
     }
-    isum = wave_sum(isum, few_rows);
-    if (lane == 0) red_i[wave] = isum;
-    __syncthreads();
-    if (tid == 0) {
-        s_dequant[row] = s_d;
-        if (code_sum) code_sum[row] = red_i[0] + red_i[1] + red_i[2] + red_i[3];
+    if (code_sum) {
+        isum = wave_sum(isum, few_rows);
+        if (lane == 0) red_i[wave] = isum;
+        __syncthreads();
+        if (tid == 0) code_sum[row] = red_i[0] + red_i[1] + red_i[2] + red_i[3];
     }
+    if (tid == 0) s_dequant[row] = s_d;
 }
 
 // Large rows (K = 4096, 8192, 16384): every butterfly stage runs in registers.
