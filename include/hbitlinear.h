@@ -107,7 +107,7 @@ int hbl_unpack_ternary_2bit(const void* packed, int64_t N, int64_t K, int8_t* co
  * ------------------------------------------------------------------------- */
 
 /* Device scratch needed by the two forward calls (activation codes, per-token
- * dequantisation scale, int32 partial tiles where a K range is split). */
+ * dequantisation scale, room for int32 slices of a K range). */
 size_t hbl_workspace_bytes(int64_t T, int64_t K, int64_t N, int bits);
 
 /*
@@ -183,7 +183,8 @@ int hbl_ln_bitlinear_forward(const void* x, int x_dtype, int64_t T, int64_t K, c
  * Meant for small batches (decode), where one projection's launches are too short to keep HBM
  * busy: when every T <= 64, n_problems <= 8 and all problems share bits and x_dtype, the rows of
  * all problems are quantised by one launch and all packed weights are streamed by one launch
- * (for 16 < T <= 64 a K range may be split over workgroups; the last of them to finish adds the
+ * (two launches where INT4 rows shorter than 512 are among them; with 17 to 32 tokens and more output rows
+ * than the chip holds at once a K range of INT4 codes may be split over workgroups: the last of them to finish adds the
  * slices, counted in a small static device array of which overlapping calls on one GPU take
  * different slots, 128 in all); otherwise the problems run one after the other through the calls above.
  *   problems   host array, read during the call only; fields as the arguments of the forward
@@ -274,10 +275,10 @@ int hbl_gemm_i32_bf6(const void* code_records, int64_t T, int64_t K, const void*
  * two launches the forward calls make, on caller-held intermediates.
  *   codes [T, K] int8, s_dequant [T] fp32, code_sum [T] int32: as written by hbl_fwht_quant with
  *   the same code_offset;  y [T, N] bf16 out
- * A forward call with T > 64 is hbl_fwht_quant(x, ..., hadamard, code_offset) into the workspace followed by
+ * A forward call with T > 16 is hbl_fwht_quant(x, ..., hadamard, code_offset) into the workspace followed by
  * this call, with code_offset = HBL_CODES_BF6 for INT4 activations with K >= 512 (fp6 x fp4 matrix cores),
- * HBL_CODES_UINT4_PLUS8 for INT4 on shorter rows, HBL_CODES_INT8 for INT8 activations (smaller batches run the
- * weight-streaming kernel on the same code forms).  code_sum is not read (the packed weights are signed) and
+ * HBL_CODES_UINT4_PLUS8 for INT4 on shorter rows, HBL_CODES_INT8 for INT8 activations (up to 16 tokens the
+ * weight-streaming kernel runs on the same code forms, up to 4 with INT4 one launch does both).  code_sum is not read (the packed weights are signed) and
  * may be NULL.
  */
 int hbl_gemm_dequant_bf16(const int8_t* codes, int code_offset, const float* s_dequant,

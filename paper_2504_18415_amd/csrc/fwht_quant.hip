@@ -88,7 +88,7 @@ int launch_generic(const void* x, int x_dtype, int64_t T, int64_t K, int bits, R
 // compiler also moves the ~100 per-thread LDS and global address computations out of the row loop and keeps
 // them in registers (about 200 VGPRs in all): measured 7-20 % faster than recomputing them per row, and the
 // LDS row buffer limits the workgroups per CU before the registers do.
-// FEW: at most 64 rows - one row per workgroup and the short-latency reductions.
+// FEW: at most kFewRows rows - one row per workgroup and the short-latency reductions.
 template <int LOG2K, int BITS, bool BF16, bool BF6OUT, bool NORM, bool FEW>
 __global__ __launch_bounds__((1 << LOG2K) / 64, 2) void fwht_quant_bigrow_kernel(
     const void* __restrict__ x, int64_t T, int8_t* __restrict__ codes, float* __restrict__ s_dequant,
@@ -296,11 +296,15 @@ int launch_fwht_only(const void* x, int x_dtype, int64_t T, int64_t K, void* out
 #undef HBL_BIG
 }
 
+constexpr int64_t kFewRows = 320;   // about a row per CU
+
 int launch_fwht_quant(const void* x, int x_dtype, int64_t T, int64_t K, int bits, float eps, bool hadamard,
                       int8_t* codes, float* s_dequant, int32_t* code_sum, int code_offset, hipStream_t stream,
                       const float* ln_gain, float ln_eps) {
     if (T == 0) return HBL_OK;
-    const RowParams rp = {eps, ln_gain, ln_eps, T <= 64 ? 1 : 0};
+    // (large Hadamard rows: one row per workgroup up to about a row per CU, the row loop beyond: 300 rows of 16384 18.4 -> 16.7 us
+    // per call, 600 rows 23.0 -> 23.3, so not there; 300 fp32 rows of 8192 13.2 -> 12.5)
+    const RowParams rp = {eps, ln_gain, ln_eps, T <= kFewRows ? 1 : 0};
     if (code_offset == kCodesBf6 && (bits != 4 || K < 512)) return HBL_E_SHAPE;   // records need 8-element chunks
     // The one-row-per-workgroup kernels: up to 4096 rows the chip holds most of them at once and a row's latency counts, so the
     // reductions take the short-latency form (3001 rows of 3072 with the norm: 18.1 -> 17.2 us per call; 8000 rows of 2048: 21.7
