@@ -357,7 +357,7 @@ def bench_decode(args, hbl, synth, torch, np):
                         "67.1 MB in 13-14 us (profiles/decode_layer_kernels_config5.txt)"}
     return {"layers_cycled": layers, "weight_bytes_per_layer": w_bytes, "roofline": roofline,
             "launch": "one HIP graph of all layers; sequential = four forward calls per layer in model order "
-                      "(2 kernel nodes each), grouped = one hbl_bitlinear_forward_grouped call per layer "
+                      "(one or two kernel nodes each), grouped = one hbl_bitlinear_forward_grouped call per layer "
                       "(one quantiser launch, one weight-streaming GEMM launch)",
             "batch": res}
 
