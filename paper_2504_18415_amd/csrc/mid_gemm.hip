@@ -284,6 +284,8 @@ int launch_cfg(MidProblem a, hipStream_t stream) {
 // each of eight one-wave groups at least one K-block, that form needs no barrier and half of the stages (64 tokens, 16384 ->
 // 4096: 18.5 -> 14.4 us; 32 x 4096 -> 4096 9.3 -> 7.6; 64 x 1024 -> 4096 6.3 -> 6.0).  Above 512 tiles the 128 x 128 tile of
 // the prefill kernel is faster (256 tokens, 4096 -> 12288, 768 tiles: 18.0 against 20.5 us).
+// Up to 64 tokens there is no such tile: four weight tiles per code stage move fewer bytes (64 tokens, 4096 -> 131072: 47 -> 35
+// us, the shared streaming form took 41; INT8 at 20 tokens 38 -> 34, against 32).
 int64_t mid_tiles(int64_t T, int64_t N) { return MidForm<4, 2, 2, 2>::tiles_n(N) * MidForm<4, 2, 2, 2>::tiles_t(T); }
 
 constexpr int64_t kMidResident = 512;   // workgroups of 8 waves and up to 80 KiB of LDS that the chip holds at once
@@ -294,6 +296,8 @@ int launch_form(const MidProblem& a, hipStream_t stream) {
     using Narrow = MidForm<8, 3, 1, 1, I8>;
     if (a.K >= 1024 && Narrow::tiles_n(a.N) * Narrow::tiles_t(a.T) <= 256) return launch_cfg<Narrow, RAW>(a, stream);
     if (tiles <= 128) return a.K < 8192 ? launch_cfg<MidForm<4, 4, 2, 1, I8>, RAW>(a, stream) : launch_cfg<MidForm<8, 3, 2, 1, I8>, RAW>(a, stream);
+    if (tiles > kMidResident)   // at most 64 tokens
+        return a.T <= 32 ? launch_cfg<MidForm<2, 4, 4, 1, I8>, RAW>(a, stream) : launch_cfg<MidForm<2, 3, 4, 2, I8>, RAW>(a, stream);
     if (a.T <= 32) return launch_cfg<MidForm<4, 3, 2, 1, I8>, RAW>(a, stream);
     if (tiles <= 256) return launch_cfg<MidForm<4, 3, 2, 2, I8>, RAW>(a, stream);
     return launch_cfg<MidForm<4, 2, 2, 2, I8>, RAW>(a, stream);

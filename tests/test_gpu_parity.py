@@ -583,6 +583,7 @@ def test_config4_wdown_swiglu_input(hbl):
     (17, 8320, 96, 1), (64, 1152, 4096, 1),       # up to 256 tiles of 32 x 32, K >= 1024: one wave per K group
     (64, 8192, 4128, 1), (65, 640, 32, 1),        # up to 128 tiles of 64 x 64: 32-token tiles, 8 and 4 K groups
     (20, 640, 8224, 1),                           # more, but at most 32 tokens
+    (20, 640, 32800, 1), (40, 512, 32800, 1),     # at most 64 tokens, more tiles than fit at once
     (300, 640, 3104, 1),                          # up to 256 tiles: one workgroup per CU
     (70, 512, 10016, 1), (1000, 896, 1152, 3),    # up to 512: two per CU, weights / codes shared out over the XCDs
 ])
