@@ -103,6 +103,17 @@ void fill_decode_problem(DecodeProblem& dp, const Workspace& ws, int64_t T, int6
     dp.code_offset = dp.f6 ? 0 : small_code_offset(bits);
 }
 
+}  // namespace
+
+Route forward_route(int64_t T, int64_t K, int64_t N, int x_dtype, int bits, bool hadamard, bool norm) {
+    if (!norm && fused_small_preferred(T, K, N, x_dtype, bits, hadamard)) return Route::kFused;
+    // up to 16 tokens: the weight-streaming kernel, unless its plan leaves long serial chains of tiles
+    if (decode_stream_preferred(T, K, N)) return Route::kStream;
+    return mid_gemm_preferred(T, N) ? Route::kMid : Route::kPrefill;
+}
+
+namespace {
+
 // Form of the codes between the two launches of a forward call.
 int code_form_for(int64_t K, int bits) { return bf6_path_supported(K, bits) ? kCodesBf6 : small_code_offset(bits); }
 
@@ -115,21 +126,22 @@ int forward(const void* x, int x_dtype, int64_t T, int64_t K, const void* Wq_pac
     if (T == 0) return HBL_OK;
     if (workspace_bytes < carve_workspace(nullptr, T, K, N, with_partial).bytes) return HBL_E_WORKSPACE;
     hipStream_t s = static_cast<hipStream_t>(stream);
-    if (!ln_gain && fused_small_preferred(T, K, N, x_dtype, bits, hadamard))
+    const Route route = forward_route(T, K, N, x_dtype, bits, hadamard, ln_gain != nullptr);
+    if (route == Route::kFused)
         return launch_fused_small(x, x_dtype, T, K, Wq_packed, N, w_scales, groups, eps, hadamard, y, s);
     const Workspace ws = carve_workspace(workspace, T, K, N, with_partial);
     const int code_form = code_form_for(K, bits);
     rc = launch_fwht_quant(x, x_dtype, T, K, bits, eps, hadamard, ws.codes, ws.s_dequant, nullptr, code_form, s, ln_gain,
                            ln_eps);
     if (rc != HBL_OK) return rc;
-    // up to 16 tokens: the weight-streaming kernel, unless its plan leaves long serial chains of tiles
-    if (decode_stream_preferred(T, K, N)) {
+    if (route == Route::kStream) {
         DecodeArgs da = {};
         da.n = 1;
         fill_decode_problem(da.p[0], ws, T, K, Wq_packed, N, w_scales, groups, bits, y);
         return launch_decode_gemm(da, s);
     }
-    // INT4 at prefill sizes: bf6 code records and the fp6 x fp4 matrix cores (exact, twice the int8 MFMA rate)
+    // INT4: bf6 code records and the fp6 x fp4 matrix cores (exact, twice the int8 MFMA rate); either launch takes the
+    // mid-size kernel itself where the route says so
     if (code_form == kCodesBf6)
         return launch_ternary_gemm_f6f4(ws.codes, T, K, Wq_packed, N, ws.s_dequant, w_scales, groups, y, s);
     return launch_ternary_gemm(ws.codes, code_form, T, K, Wq_packed, N, ws.s_dequant, w_scales, groups, y, nullptr, s);
@@ -397,6 +409,15 @@ int hbl_test_grouped_plan(const hbl_problem* problems, int n_problems, int* kspl
     if (rc != HBL_OK) return rc;
     for (int i = 0; i < n_problems; ++i) ksplit[i] = da.p[i].ksplit;
     return HBL_OK;
+}
+
+int hbl_test_forward_route(int64_t T, int64_t K, int64_t N, int x_dtype, int bits, int hadamard, int norm) {
+    if (bits != 4 && bits != 8) return HBL_E_BITS;
+    if (x_dtype != HBL_F32 && x_dtype != HBL_BF16) return HBL_E_DTYPE;
+    const int rc = check_gemm_shape(T, K, N, hadamard != 0);
+    if (rc != HBL_OK) return rc;
+    if (T < 1) return HBL_E_SHAPE;
+    return (int)forward_route(T, K, N, x_dtype, bits, hadamard != 0, norm != 0);
 }
 
 size_t hbl_code_bytes(int64_t T, int64_t K, int code_form) {

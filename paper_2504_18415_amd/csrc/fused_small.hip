@@ -218,6 +218,31 @@ int launch_cfg(FusedArgs a, const FusedLayout& l, hipStream_t stream) {
     return after_launch();
 }
 
+// Most workgroups per CU at which one launch is no slower than two, for 16, 32 and 64 output rows a workgroup; 0: not at all.
+// Every workgroup quantises the rows for itself, so beyond one per CU that work is repeated side by side on the same SIMDs,
+// while the two launches do it once: what is saved, a launch of about 2 us, is spent again.  Time against the two launches
+// (both input types, 32 to 131072 output rows; by workgroups of 16 rows per CU):
+//   transformed rows: K = 512  1: 0.6  2: 0.7  4: 0.87  6: 1.02  8: 1.2;  1024  1: 0.6  3: 0.8  4: 0.94  5: 1.07  8: 1.4;
+//                     2048  1: 0.7  2: 0.85  3: 0.97  4: 1.17;  4096 and more  1: 0.75-0.85, LDS holds no more than two
+//   plain rows, one token: 512  1: 0.7  4: 0.84  8: 1.07;  1024 to 4096  1: 0.55  4: 0.8
+//   plain rows of several tokens are taken one after the other by the whole workgroup, whatever their length:
+//                     2 tokens, 512  1: 0.85  3: 0.99  4: 1.07;  2048  1: 0.7  3: 0.87  4: 0.99
+//                     3 tokens, 512  1: 0.95-1.02  2: 1.08;  1024  1: 0.85  2: 0.98  3: 1.07;  2560  1: 0.93  2: 1.02
+//                     4 tokens, 512  1: 1.1;  1024  1: 0.97  2: 1.12;  1536  1: 0.93  2: 1.04;  2048  1: 0.95  2: 1.07
+// 32 and 64 rows a workgroup start 0.05 and 0.1 higher (fewer wavefronts, longer sums) and rise in the same way.
+// (us: 4 x 512 -> 12288 plain 7.0 by one launch, 5.1 by two; 1 x 1024 -> 32768 transformed 8.8, 6.4; 1 x 2048 -> 16384
+// transformed 9.3 with 16 rows a workgroup, 7.0 with 32, 7.9 by two.)
+int most_workgroups_per_cu(int64_t T, int64_t K, bool hadamard, int rw) {
+    if (hadamard) return K <= 512 ? 4 : (K <= 1024 ? 3 : 2);
+    if (T == 1) return 4;
+    if (T == 2) return rw == 16 ? 3 : (K >= 1024 ? (rw == 32 ? 3 : 2) : (rw == 32 ? 2 : 1));
+    if (T == 3) {
+        if (rw == 16) return K >= 1024 && K <= 2048 ? 2 : 1;
+        return rw == 64 || K < 640 ? 0 : (K >= 1280 && K <= 2048 ? 2 : 1);
+    }
+    return rw == 64 ? 0 : (K >= (rw == 16 ? 1024 : 1536) ? 1 : 0);
+}
+
 struct FusedPlan {
     int log2k, maxc, rb, rw;   // rw = 0: not this kernel
     FusedLayout layout;
@@ -237,8 +262,9 @@ FusedPlan fused_plan(int64_t T, int64_t K, int64_t N, int x_dtype, bool hadamard
         if ((rw == 64 && (hadamard || K > 4096)) || (rw == 32 && K > 8192)) continue;
         const FusedLayout l = fused_layout(p.log2k, p.maxc, eb, (int)T, p.rb, K, rw);
         if (l.bytes > kCuLds - 1024) continue;
-        const int64_t wgs = (N + rw - 1) / rw, per_cu = (int64_t)(kCuLds / (l.bytes + 1024));
-        if (wgs > 256 * (per_cu < 8 ? per_cu : 8)) continue;
+        const int64_t wgs = (N + rw - 1) / rw, resident = (int64_t)(kCuLds / (l.bytes + 1024));
+        const int64_t most = most_workgroups_per_cu(T, K, hadamard, rw);
+        if (wgs > 256 * (resident < most ? resident : most)) continue;
         p.rw = rw;
         p.layout = l;
         break;

@@ -283,6 +283,15 @@ int launch_mid_gemm_grouped(MidArgs& args, bool records, hipStream_t stream);
 // Whether a single projection is better served by the streaming form of that launch (T <= 16) than by the mid-size kernel.
 bool decode_stream_preferred(int64_t T, int64_t K, int64_t N);
 
+// The kernel that a single forward call (T >= 1) ends in.
+enum class Route : int {
+    kFused = 0,     // fused_small.hip: quantiser and product in one launch
+    kStream = 1,    // decode_gemm.hip, after a quantiser launch (as the ones below)
+    kMid = 2,       // mid_gemm.hip
+    kPrefill = 3,   // ternary_gemm_f6f4.hip / ternary_gemm.hip
+};
+Route forward_route(int64_t T, int64_t K, int64_t N, int x_dtype, int bits, bool hadamard, bool norm);
+
 // Packed weight buffer: N*K/4 bytes of 2-bit tiles (one form, read by every GEMM kernel), then N int32 row sums
 // of the ternary codes.
 inline size_t packed_tile_bytes(int64_t N, int64_t K) { return (size_t)N * (size_t)K / 4; }

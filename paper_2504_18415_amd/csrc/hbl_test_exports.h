@@ -24,6 +24,13 @@ int hbl_test_grouped_plan(const hbl_problem* problems, int n_problems, int* kspl
                           int* arrival_counters, int* single_call_streams);
 
 /*
+ * Host only: the kernel that a single forward call of this shape ends in, as the dispatch picks it (norm != 0: with the
+ * RMS normalisation).  0: one launch for quantiser and product   1: weight streaming   2: mid-size   3: prefill;
+ * or a negative status.
+ */
+int hbl_test_forward_route(int64_t T, int64_t K, int64_t N, int x_dtype, int bits, int hadamard, int norm);
+
+/*
  * The integer contraction of Eq. 7 through one named workgroup tile of a prefill GEMM kernel (T > 64):
  * acc[t][o] = sum_k q[t][k] c[o][k] as int32 [T, N], on a shape of the caller's choice - the forward
  * calls pick the tile from the shape, so most tiles would otherwise be reachable at benchmark sizes only.

@@ -35,7 +35,8 @@ EXPORTS = [
     "hbl_code_bytes", "hbl_bitlinear_forward_small",
 ]
 # exports for the test suite only (csrc/hbl_test_exports.h)
-TEST_EXPORTS = ["hbl_test_grouped_plan", "hbl_test_gemm_i32_tile"]
+TEST_EXPORTS = ["hbl_test_grouped_plan", "hbl_test_gemm_i32_tile", "hbl_test_forward_route"]
+ROUTES = ("fused", "stream", "mid", "prefill")
 TILE_SQUARE, TILE_SMALL, TILE_WIDE, TILE_SPLIT_K = 0, 1, 2, 3
 
 _lib = None
@@ -95,6 +96,7 @@ def lib():
         ip = ctypes.POINTER(ci)
         L.hbl_test_grouped_plan.argtypes = [ctypes.POINTER(Problem), ci, ip, ip, ip, ip]
         L.hbl_test_gemm_i32_tile.argtypes = [vp, ci, i64, i64, vp, i64, vp, ci, vp, sz, vp]
+        L.hbl_test_forward_route.argtypes = [i64, i64, i64, ci, ci, ci, ci]
         L.hbl_gemm_i32_bf6.argtypes = [vp, i64, i64, vp, i64, vp, vp, sz, vp]
         L.hbl_bitlinear_forward_small.argtypes = [vp, ci, i64, i64, vp, i64, vp, i64, ci, f32, ci, vp, vp]
         L.hbl_code_bytes.restype = sz
@@ -465,6 +467,15 @@ def grouped_plan(shapes):
     wgs, counters = ctypes.c_int(0), ctypes.c_int(0)
     _check(lib().hbl_test_grouped_plan(arr, n, ks, ctypes.byref(wgs), ctypes.byref(counters), st), "grouped_plan")
     return list(ks), wgs.value, counters.value, [bool(v) for v in st]
+
+
+def forward_route(T: int, K: int, N: int, bits: int = 4, hadamard: bool = True, x_dtype: int = BF16,
+                  norm: bool = False) -> str:
+    """Host-only: which kernel a single forward call of this shape ends in (one of ``ROUTES``)."""
+    rc = lib().hbl_test_forward_route(T, K, N, x_dtype, bits, int(bool(hadamard)), int(bool(norm)))
+    if rc < 0:
+        raise HblError(rc, "forward_route")
+    return ROUTES[rc]
 
 
 def kv_quant_absmax(x: torch.Tensor, bits: int, eps: float = EPS, packed: Optional[torch.Tensor] = None,

@@ -185,6 +185,24 @@ def test_small_batch_launch_plan(L):
         hbl.grouped_plan([(4, 4096 + 128, 4096, True)])
 
 
+def test_one_launch_only_where_it_is_no_slower(L):
+    """One launch for one to four tokens repeats the quantisation in every workgroup: it is taken up to as many workgroups
+    per CU as measured no slower than two launches, not wherever it fits the chip at once."""
+    from paper_2504_18415_amd import hbl
+    fused = lambda T, K, N, had, dt=hbl.BF16: hbl.forward_route(T, K, N, 4, had, dt) == "fused"
+    for N in (96, 4096, 12288):                                    # the projections of a decode step, batch 1
+        assert fused(1, 4096, min(N, 8192), True) and fused(1, 4096, N, False) and fused(1, 1024, N, False)
+    assert fused(1, 16384, 4096, True) and fused(1, 4096, 32768, False) and fused(4, 2048, 4096, True)
+    for T, K, N, had in [(1, 1024, 32768, True), (2, 512, 65536, True), (4, 2048, 32768, True), (1, 512, 131072, False),
+                         (2, 640, 32768, False), (3, 512, 12288, False), (3, 1024, 32768, False), (4, 512, 32, False),
+                         (4, 640, 12288, False), (4, 1024, 8192, False), (4, 2048, 12288, False)]:
+        for dt in (hbl.BF16, hbl.F32):
+            assert not fused(T, K, N, had, dt), (T, K, N, had, dt)   # 1.05 to 1.6 times the two launches
+    assert hbl.forward_route(1, 4096, 4096, 8) == "stream" and hbl.forward_route(1, 4096, 4096, 4, norm=True) == "stream"
+    with pytest.raises(hbl.HblError):
+        hbl.forward_route(0, 4096, 4096)
+
+
 def test_kv_quant_argument_errors_before_any_launch(L):
     from paper_2504_18415_amd import hbl
     E = {n: getattr(hbl, n) for n in ("E_NULL", "E_SHAPE", "E_BITS", "E_DTYPE", "E_ALIGN")}
