@@ -161,7 +161,7 @@ __device__ __forceinline__ void decode_body(const DecodeProblem& p, const int w,
 
     // Stage kb may be consumed once at most min(D - 2, nkb - 1 - kb) later stages are still in flight
     // (copies return in order).  Nothing is requested past the end of the K range, so the count
-    // shrinks over the last D - 2 stages: those take the switch.
+    // shrinks over the last D - 2 stages.
     auto wait_stage = [&](int later) {
         if (later >= D - 2) {
             asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"((D - 2) * (XL + 1)) : "memory");
@@ -245,15 +245,26 @@ __device__ __forceinline__ void decode_body(const DecodeProblem& p, const int w,
                                                                        xop[s], wacc, 4, 3, 0, 0, 0, 0);
         }
     };
-    int slot = 0;
-    for (int kb = 0; kb < nkb; ++kb) {
-        // stage kb has landed (for every wave, if the code stage is shared); the buffer read in the previous
-        // iteration is free for stage kb + D - 1
-        wait_stage(nkb - 1 - kb);
+    // Stage kb has landed (for every wave, if the code stage is shared); the buffer read in the previous iteration is free
+    // for stage kb + D - 1.  The last D - 1 stages, which request nothing and wait for fewer copies, stand apart, one by one:
+    // with few workgroups a wave has its SIMD to itself and walks its stages one after another, so every branch of the
+    // steady loop is waited for.  In one loop, three or four branches each, the time even hung on where the compiler had put
+    // it: GEMM launch alone, 3 tokens x 16256 -> 24576 records 21.8 to 23.6 us, now 20.0; 3 x 11008 -> 12288 9.5 to 10.0, now
+    // 8.3; INT8 8 x 16128 -> 24576 25.2 to 26.4, now 23.6; groups of INT8 projections at 8 tokens, 2048 / 8192 8.2 to 8.4,
+    // now 7.6, 7B 15.5 to 16.0, now 14.8.
+    int slot = 0, kb = 0;
+    for (; kb < nkb - (D - 1); ++kb) {
+        wait_stage(D - 2);
         if constexpr (SHARE) asm volatile("s_barrier" ::: "memory");
-        stage_work(lds + slot * STAGE, [&]() {
-            if (kb + D - 1 < nkb) issue(kb + D - 1, slot == 0 ? D - 1 : slot - 1);
-        });
+        stage_work(lds + slot * STAGE, [&]() { issue(kb + D - 1, slot == 0 ? D - 1 : slot - 1); });
+        slot = slot + 1 == D ? 0 : slot + 1;
+    }
+#pragma unroll
+    for (int later = D - 2; later >= 0; --later) {
+        if (nkb <= later) continue;   // (uniform)
+        wait_stage(later);
+        if constexpr (SHARE) asm volatile("s_barrier" ::: "memory");
+        stage_work(lds + slot * STAGE, []() {});
         slot = slot + 1 == D ? 0 : slot + 1;
     }
     if constexpr (!F6) acc[0] += acc[1];

@@ -836,12 +836,12 @@ def test_grouped_ragged_mix(hbl, bits, x_dtype):
 
 
 @pytest.mark.parametrize("bits", [4, 8])
-@pytest.mark.parametrize("T", [33, 48, 64])
-def test_grouped_two_token_tiles_short_and_odd_k(hbl, bits, T):
-    """33-64 tokens take the shared form with two token tiles, which waits and synchronises once per two
-    K-blocks and, on the fp6 x fp4 path, gives a wave two row tiles of weights: K ranges of 1, 3, 4, 5 and 9
-    blocks (shorter than the copy ring, odd tails) and row-tile counts that leave a wave one or no live tile."""
-    note(f"grouped two token tiles bits={bits} T={T}")
+@pytest.mark.parametrize("T", [5, 16, 33, 48, 64])
+def test_grouped_short_and_odd_k(hbl, bits, T):
+    """K ranges of 1, 3, 4, 5 and 9 blocks: shorter than the copy ring of the weight-streaming kernel (up to 16 tokens),
+    as long, and with odd tails there and over the K groups of the mid-size kernel (33 to 64 tokens); row-tile counts that
+    leave a wave one or no live tile."""
+    note(f"grouped short and odd K bits={bits} T={T}")
     common = dict(outlier_frac=0.01, outlier_scale=30.0)
     sites = [
         synth.Site("p_k128", T, 128, 32, hadamard=True, seed=61, **common),
