@@ -108,7 +108,7 @@ void fill_decode_problem(DecodeProblem& dp, const Workspace& ws, int64_t T, int6
 Route forward_route(int64_t T, int64_t K, int64_t N, int x_dtype, int bits, bool hadamard, bool norm) {
     if (!norm && fused_small_preferred(T, K, N, x_dtype, bits, hadamard)) return Route::kFused;
     // up to 16 tokens: the weight-streaming kernel, unless its plan leaves long serial chains of tiles
-    if (decode_stream_preferred(T, K, N)) return Route::kStream;
+    if (decode_stream_preferred(T, K, N, bf6_path_supported(K, bits))) return Route::kStream;
     return mid_gemm_preferred(T, N) ? Route::kMid : Route::kPrefill;
 }
 
@@ -403,7 +403,7 @@ int hbl_test_grouped_plan(const hbl_problem* problems, int n_problems, int* kspl
         dp.K = (int)q.K;
         dp.N = (int)q.N;
         dp.partial = &dummy_partial;   // the grouped call always brings a partial buffer
-        single_call_streams[i] = decode_stream_preferred(q.T, q.K, q.N) ? 1 : 0;
+        single_call_streams[i] = decode_stream_preferred(q.T, q.K, q.N, q.K >= 512) ? 1 : 0;
     }
     const int rc = decode_plan_for_tests(da, gemm_workgroups, arrival_counters);
     if (rc != HBL_OK) return rc;

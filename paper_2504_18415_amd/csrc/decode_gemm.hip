@@ -499,7 +499,11 @@ void plan_wide(DecodeArgs& a, int nw, int* wgs_out) {
 
 }  // namespace
 
-bool decode_stream_preferred(int64_t T, int64_t K, int64_t N) {
+// A wave's tiles are a serial chain: few workgroups with long chains leave most of the chip idle, and there the mid-size
+// kernel cuts K further.  Call time by that kernel against this one, 1 to 16 tokens, chains of more than 16 tiles: records,
+// up to 128 workgroups 0.75 (K in one piece) and 0.92 (in two), from there on 1.08 and 1.18 (3 x 11008 -> 10240: 16.4 us,
+// 12.9 here); bytes, up to 128 workgroups 0.5 to 0.7, up to 192 0.91 and 1.02.
+bool decode_stream_preferred(int64_t T, int64_t K, int64_t N, bool records) {
     if (T <= 0 || T > 16) return false;
     DecodeArgs a = {};
     a.n = 1;
@@ -509,8 +513,7 @@ bool decode_stream_preferred(int64_t T, int64_t K, int64_t N) {
     if (wide_waves(a, (int)T) != 0) return true;
     int wgs, counters;
     plan(a, false, &wgs, &counters);
-    // a wave's tiles are a serial chain: few workgroups with long chains leave most of the chip idle
-    return (K / 128) / a.p[0].ksplit <= 16 || wgs >= 192;
+    return (K / 128) / a.p[0].ksplit <= 16 || wgs > (records ? 128 : 191);
 }
 
 int decode_plan_for_tests(DecodeArgs& a, int* wgs, int* counters) {

@@ -281,7 +281,7 @@ bool mid_group_preferred(const DecodeProblem* p, int n, bool records);
 // Every problem needs T <= 64; reorders args.
 int launch_mid_gemm_grouped(MidArgs& args, bool records, hipStream_t stream);
 // Whether a single projection is better served by the streaming form of that launch (T <= 16) than by the mid-size kernel.
-bool decode_stream_preferred(int64_t T, int64_t K, int64_t N);
+bool decode_stream_preferred(int64_t T, int64_t K, int64_t N, bool records);
 
 // The kernel that a single forward call (T >= 1) ends in.
 enum class Route : int {

@@ -203,6 +203,17 @@ def test_one_launch_only_where_it_is_no_slower(L):
         hbl.forward_route(0, 4096, 4096)
 
 
+def test_single_calls_of_up_to_16_tokens_stream_or_not(L):
+    """Long K ranges that few waves share: the mid-size kernel up to 128 workgroups of the streaming one, where it is the
+    faster; beyond them records stream, bytes from 192 on."""
+    from paper_2504_18415_amd import hbl
+    route = lambda K, N, bits: hbl.forward_route(8, K, N, bits, hadamard=False)
+    assert route(11008, 8192, 4) == "mid" and route(11008, 8224, 4) == "stream"      # 86 K-blocks: two pieces
+    assert route(16256, 16384, 4) == "mid" and route(16256, 16512, 4) == "stream"    # 127: one
+    assert route(16256, 24448, 8) == "mid" and route(16256, 24576, 8) == "stream"
+    assert route(4096, 4096, 4) == route(4096, 4096, 8) == "stream" and route(16384, 4096, 4) == "stream"
+
+
 def test_kv_quant_argument_errors_before_any_launch(L):
     from paper_2504_18415_amd import hbl
     E = {n: getattr(hbl, n) for n in ("E_NULL", "E_SHAPE", "E_BITS", "E_DTYPE", "E_ALIGN")}
