@@ -109,7 +109,8 @@ Route forward_route(int64_t T, int64_t K, int64_t N, int x_dtype, int bits, bool
     if (!norm && fused_small_preferred(T, K, N, x_dtype, bits, hadamard)) return Route::kFused;
     // up to 16 tokens: the weight-streaming kernel, unless its plan leaves long serial chains of tiles
     if (decode_stream_preferred(T, K, N, bf6_path_supported(K, bits))) return Route::kStream;
-    return mid_gemm_preferred(T, N) ? Route::kMid : Route::kPrefill;
+    if (bf6_path_supported(K, bits) && decode_shared_preferred(T, K, N)) return Route::kStream;
+    return mid_gemm_preferred(T, K, N, bf6_path_supported(K, bits)) ? Route::kMid : Route::kPrefill;
 }
 
 namespace {

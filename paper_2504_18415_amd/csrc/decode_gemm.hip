@@ -516,6 +516,14 @@ bool decode_stream_preferred(int64_t T, int64_t K, int64_t N, bool records) {
     return (K / 128) / a.p[0].ksplit <= 16 || wgs > (records ? 128 : 191);
 }
 
+// Against the mid-size kernel, 17 to 32 tokens: this form reads each code stage once per four weight tiles too and has no
+// sums to add up, but its waves meet at a barrier per K-block.  Call time here against there: up to 32768 output rows 1.0
+// at K = 512 to 1024, up to 1.2 above; beyond them K = 512 0.82 to 0.97, 2048 0.92 to 0.97, 4096 0.95 to 1.0, 5504 0.94 to
+// 0.98, and where the K range is split over workgroups 11008 0.91 up to 45056 rows, 8192 0.94 to 1.0; above that 1.05 to 1.6.
+bool decode_shared_preferred(int64_t T, int64_t K, int64_t N) {
+    return T > 16 && T <= 32 && N > 32768 && (K < 8192 || (K < 12288 && N <= 45056));
+}
+
 int decode_plan_for_tests(DecodeArgs& a, int* wgs, int* counters) {
     int max_t = 0;
     for (int i = 0; i < a.n; ++i) max_t = a.p[i].T > max_t ? a.p[i].T : max_t;

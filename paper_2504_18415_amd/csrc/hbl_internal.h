@@ -173,7 +173,8 @@ int launch_fwht_only(const void* x, int x_dtype, int64_t T, int64_t K, void* out
 // Workgroup tiles of the two prefill GEMM kernels.  kTileAuto is the choice every forward call makes from the
 // shape; the others let the parity tests run a given tile on a shape of their own.
 constexpr int kTileAuto = -1, kTileSquare = 0 /*256 x 256*/, kTileSmall = 1 /*128 x 128*/,
-              kTileWide = 2 /*512 features x 128 tokens*/, kTileSplitK = 3 /*mid-size form, K cut over the waves*/;
+              kTileWide = 2 /*512 features x 128 tokens*/, kTileSplitK = 3 /*mid-size form, K cut over the waves*/,
+              kTileFewTokens = 4 /*bytes, at most 64 tokens*/;
 
 // GEMM + epilogue. If acc_out != nullptr the raw int32 accumulators are written
 // (no scales, no code_sum needed); otherwise y (bf16) is written.
@@ -274,7 +275,7 @@ struct MidArgs {
     int wg_begin[kMaxGroup];   // = p[i].wg_begin
     MidProblem p[kMaxGroup];
 };
-bool mid_gemm_preferred(int64_t T, int64_t N);
+bool mid_gemm_preferred(int64_t T, int64_t K, int64_t N, bool records);
 int launch_mid_gemm(const MidProblem& a, bool records, hipStream_t stream);
 // Whether a group's problems of one operand path take that kernel (more than 16 tokens somewhere).
 bool mid_group_preferred(const DecodeProblem* p, int n, bool records);
@@ -282,6 +283,8 @@ bool mid_group_preferred(const DecodeProblem* p, int n, bool records);
 int launch_mid_gemm_grouped(MidArgs& args, bool records, hipStream_t stream);
 // Whether a single projection is better served by the streaming form of that launch (T <= 16) than by the mid-size kernel.
 bool decode_stream_preferred(int64_t T, int64_t K, int64_t N, bool records);
+// ... and by its shared form (17 to 32 tokens of records).
+bool decode_shared_preferred(int64_t T, int64_t K, int64_t N);
 
 // The kernel that a single forward call (T >= 1) ends in.
 enum class Route : int {

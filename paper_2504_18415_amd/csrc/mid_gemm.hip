@@ -12,7 +12,7 @@
 // 13.4, 65 x 4096 -> 4096 16.3 -> 9.7, 512 x 16384 -> 4096 40 -> 37, 4000 x 16384 -> 512 89 -> 79.  The shared form of the
 // weight-streaming kernel up to 64: 64 x 16384 -> 4096 22.6 -> 14.4, 64 x 11008 -> 4096 23.7 -> 12.7, 17 x 4096 -> 4096
 // 10.6 -> 9.1, 32 x 4096 -> 32768 13.5 -> 12.1 us.  (Up to 16 tokens that kernel's streaming form is faster: 8 x 4096 ->
-// 4096 7.2 us against 9.0.)  INT8 activations: 64 x 16384 -> 4096 21.4 -> 15.2, 24 x 8192 -> 3072 13.2 -> 8.9, 97 x 11008 ->
+// 4096 7.2 us against 9.0; and its shared form up to 32 where there are many output rows: decode_shared_preferred.)  INT8 activations: 64 x 16384 -> 4096 21.4 -> 15.2, 24 x 8192 -> 3072 13.2 -> 8.9, 97 x 11008 ->
 // 4096 35.1 -> 19.0, 128 x 4096 -> 4096 23.0 -> 10.6, 300 x 8192 -> 3072 32.4 -> 19.7 us.
 #include <atomic>
 #include <type_traits>
@@ -285,7 +285,11 @@ int launch_cfg(MidProblem a, hipStream_t stream) {
 // 4096: 18.5 -> 14.4 us; 32 x 4096 -> 4096 9.3 -> 7.6; 64 x 1024 -> 4096 6.3 -> 6.0).  Above 512 tiles the 128 x 128 tile of
 // the prefill kernel is faster (256 tokens, 4096 -> 12288, 768 tiles: 18.0 against 20.5 us).
 // Up to 64 tokens there is no such tile: four weight tiles per code stage move fewer bytes (64 tokens, 4096 -> 131072: 47 -> 35
-// us, the shared streaming form took 41; INT8 at 20 tokens 38 -> 34, against 32).
+// us).  At most 32 tokens get three stages of LDS, so that three workgroups share a CU (with four stages, two: INT8 17 x 4096
+// -> 131072 33.5 -> 32.1 us, INT4 24 x 16384 -> 65536 49.3 -> 48.3).  The same form with one stage less from 257 tiles on where
+// K is at most 1024: with one or two stages per K group, what counts is how many workgroups start at once (24 x 512 -> 32768
+// INT4 6.8 -> 6.3, 17 x 512 -> 32768 INT8 6.5 -> 6.2; 64 x 256 -> 24576 7.3 -> 6.5 us; at K = 2048 1.0 to 1.06, at 8192 1.07 to
+// 1.25 times the time).
 int64_t mid_tiles(int64_t T, int64_t N) { return MidForm<4, 2, 2, 2>::tiles_n(N) * MidForm<4, 2, 2, 2>::tiles_t(T); }
 
 constexpr int64_t kMidResident = 512;   // workgroups of 8 waves and up to 80 KiB of LDS that the chip holds at once
@@ -296,8 +300,10 @@ int launch_form(const MidProblem& a, hipStream_t stream) {
     using Narrow = MidForm<8, 3, 1, 1, I8>;
     if (a.K >= 1024 && Narrow::tiles_n(a.N) * Narrow::tiles_t(a.T) <= 256) return launch_cfg<Narrow, RAW>(a, stream);
     if (tiles <= 128) return a.K < 8192 ? launch_cfg<MidForm<4, 4, 2, 1, I8>, RAW>(a, stream) : launch_cfg<MidForm<8, 3, 2, 1, I8>, RAW>(a, stream);
-    if (tiles > kMidResident)   // at most 64 tokens
-        return a.T <= 32 ? launch_cfg<MidForm<2, 4, 4, 1, I8>, RAW>(a, stream) : launch_cfg<MidForm<2, 3, 4, 2, I8>, RAW>(a, stream);
+    const bool many = tiles > kMidResident, short_rows = a.T <= 64 && a.K <= 1024 && tiles > 256;   // (many: at most 64 tokens)
+    if (a.T <= 32 && (many || short_rows)) return launch_cfg<MidForm<2, 3, 4, 1, I8>, RAW>(a, stream);
+    if (many) return launch_cfg<MidForm<2, 3, 4, 2, I8>, RAW>(a, stream);
+    if (short_rows) return launch_cfg<MidForm<2, 2, 4, 2, I8>, RAW>(a, stream);
     if (a.T <= 32) return launch_cfg<MidForm<4, 3, 2, 1, I8>, RAW>(a, stream);
     if (tiles <= 256) return launch_cfg<MidForm<4, 3, 2, 2, I8>, RAW>(a, stream);
     return launch_cfg<MidForm<4, 2, 2, 2, I8>, RAW>(a, stream);
@@ -334,7 +340,14 @@ int launch_grouped(MidArgs& args, int max_t, int64_t tiles, hipStream_t stream) 
 
 }  // namespace
 
-bool mid_gemm_preferred(int64_t T, int64_t N) { return T <= 64 || mid_tiles(T, N) <= kMidResident; }
+// Up to 64 tokens, beyond 512 tiles, rows of at most 1024 bytes: a workgroup has at most eight K-blocks and nothing is gained
+// by cutting them over its waves; the int8 kernel's tiles of 128 features by 32 or 64 tokens are up to 1.2 times as fast (20 x
+// 128 -> 131072 7.4 us against 8.7, 64 x 384 -> 98304 9.1 against 10.3; from K = 1536 on they are 1.0 to 1.1 times as slow, and
+// above 32 tokens already from K = 512 on up to 65536 output rows).
+bool mid_gemm_preferred(int64_t T, int64_t K, int64_t N, bool records) {
+    if (mid_tiles(T, N) <= kMidResident) return true;
+    return T <= 64 && (records || K > (T <= 32 || N > 65536 ? 1024 : 384));
+}
 
 int launch_mid_gemm(const MidProblem& a, bool records, hipStream_t stream) {
     if (records) return a.acc_out ? launch_form<false, true>(a, stream) : launch_form<false, false>(a, stream);

@@ -363,8 +363,11 @@ int choose(const GemmArgs& a, hipStream_t stream, int tile) {
         const int64_t wide_tiles = (int64_t)((a.N + 511) / 512) * ((a.T + 127) / 128);
         cfg = wide_tiles <= big_tiles ? kTileWide : kTileSquare;
     }
+    if (a.T <= 64) cfg = kTileFewTokens;
     if (tile != kTileAuto) cfg = tile;   // parity tests name the tile themselves
     switch (cfg) {
+        case kTileFewTokens:   // 128 features x 32 or 64 tokens, 4 waves of one feature tile
+            return a.T <= 32 ? launch_cfg<4, 1, 1, 1, 4, RAW>(a, stream) : launch_cfg<4, 1, 1, 2, 4, RAW>(a, stream);
         case kTileSmall: return launch_cfg<2, 2, 2, 2, 4, RAW>(a, stream);    // 128 x 128, 4 waves
         case kTileSquare: return launch_cfg<2, 2, 4, 4, 3, RAW>(a, stream);   // 256 x 256, 4 waves of 128 x 128
         case kTileWide: return launch_cfg<4, 1, 4, 4, 3, RAW>(a, stream);     // 512 features x 128 tokens, 4 waves of 128 x 128
@@ -392,7 +395,7 @@ int launch_ternary_gemm(const int8_t* codes, int code_offset, int64_t T, int64_t
     a.N = (int)N;
     a.rows_per_group = n_scale_groups > 0 ? (int)(N / n_scale_groups) : (int)N;
     a.tiles_n = a.tiles_t = 0;
-    if (tile == kTileAuto && mid_gemm_preferred(T, N)) {   // too few tiles for the chip
+    if (tile == kTileAuto && mid_gemm_preferred(T, K, N, false)) {   // too few tiles for the chip
         MidProblem m = {};
         m.codes = a.codes;
         m.packed = a.packed;

@@ -214,6 +214,23 @@ def test_single_calls_of_up_to_16_tokens_stream_or_not(L):
     assert route(4096, 4096, 4) == route(4096, 4096, 8) == "stream" and route(16384, 4096, 4) == "stream"
 
 
+def test_routes_of_17_to_64_tokens_against_many_output_rows(L):
+    """More than 512 tiles of 64 x 64: records of up to 32 tokens stream in the shared form where it is the faster, short rows
+    of bytes take the int8 kernel's narrow tiles; everything else is the mid-size kernel's."""
+    from paper_2504_18415_amd import hbl
+    route = lambda T, K, N, bits: hbl.forward_route(T, K, N, bits, hadamard=False)
+    for T in (17, 32):
+        assert route(T, 512, 32768, 4) == "mid" and route(T, 512, 32800, 4) == "stream"
+        assert route(T, 8064, 131072, 4) == "stream" and route(T, 8192, 45056, 4) == "stream"
+        assert route(T, 8192, 45088, 4) == "mid" and route(T, 12288, 40960, 4) == "mid"
+    for T in (17, 32, 33, 64):
+        for K, bits in ((128, 8), (384, 8), (384, 4)):
+            assert route(T, K, 32768, bits) == "mid" and route(T, K, 32800, bits) == "prefill"
+        assert route(T, 512, 65536, 8) == ("prefill" if T <= 32 else "mid") and route(T, 1024, 65568, 8) == "prefill"
+        assert route(T, 1152, 32800, 8) == "mid"
+    assert route(33, 512, 131072, 4) == route(64, 4096, 131072, 4) == "mid"
+
+
 def test_kv_quant_argument_errors_before_any_launch(L):
     from paper_2504_18415_amd import hbl
     E = {n: getattr(hbl, n) for n in ("E_NULL", "E_SHAPE", "E_BITS", "E_DTYPE", "E_ALIGN")}

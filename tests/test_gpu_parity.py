@@ -583,7 +583,9 @@ def test_config4_wdown_swiglu_input(hbl):
     (17, 8320, 96, 1), (64, 1152, 4096, 1),       # up to 256 tiles of 32 x 32, K >= 1024: one wave per K group
     (64, 8192, 4128, 1), (65, 640, 32, 1),        # up to 128 tiles of 64 x 64: 32-token tiles, 8 and 4 K groups
     (20, 640, 8224, 1),                           # more, but at most 32 tokens
-    (20, 640, 32800, 1), (40, 512, 32800, 1),     # at most 64 tokens, more tiles than fit at once
+    (20, 640, 16416, 1), (64, 640, 16448, 1),     # short rows, more than 256 tiles
+    (20, 1152, 32800, 1), (40, 1152, 32800, 1),   # at most 64 tokens, more tiles than fit at once
+    (20, 640, 32800, 1), (40, 512, 32800, 1),     # ... where short rows of bytes take the int8 kernel's narrow tiles
     (300, 640, 3104, 1),                          # up to 256 tiles: one workgroup per CU
     (70, 512, 10016, 1), (1000, 896, 1152, 3),    # up to 512: two per CU, weights / codes shared out over the XCDs
 ])
@@ -619,6 +621,50 @@ def test_mid_size_gemm_forms(hbl, T, K, N, groups):
     want = q8.double() @ torch.from_numpy(c).cuda().double().t()
     assert torch.equal(hbl.gemm_i32(q8, packed, N).double(), want)
     assert torch.equal(hbl.gemm_dequant_bf16(q8, sd, unused, packed, N, alpha), outputs(want))
+
+
+@pytest.mark.parametrize("T,K,N,groups", [(17, 128, 32800, 1), (32, 384, 33120, 3), (33, 1024, 65600, 1), (64, 256, 32928, 3)])
+def test_int8_narrow_tiles(hbl, T, K, N, groups):
+    """Up to 64 tokens of short rows against very many output rows: 128 features by 32 or 64 tokens of the int8 kernel, ragged
+    in both, K ranges shorter than its ring of stages; sums against the exact integer product, bf16 outputs bit for bit."""
+    note(f"int8 narrow tiles T={T} K={K} N={N}")
+    g = torch.Generator(device="cuda").manual_seed(T + K)
+    c = torch.randint(-1, 2, (N, K), dtype=torch.int8, device="cuda", generator=g)
+    packed = hbl.pack_ternary_2bit(c)
+    sd = torch.rand(T, device="cuda", generator=g) + 0.5
+    alpha = torch.rand(groups, device="cuda", generator=g) + 0.5
+    unused = torch.zeros(T, dtype=torch.int32, device="cuda")
+    for lo, hi, offset in ((-128, 128, hbl.CODES_INT8), (-8, 8, hbl.CODES_UINT4_PLUS8)):
+        q = torch.randint(lo, hi, (T, K), dtype=torch.int8, device="cuda", generator=g)
+        q[3], q[T - 1] = lo, hi - 1
+        acc = q.double() @ c.double().t()                                   # exact
+        if offset == 0:
+            assert torch.equal(hbl.gemm_i32(q, packed, N).double(), acc)
+        want = ((acc.float() * sd[:, None]) * alpha.repeat_interleave(N // groups)[None, :]).to(torch.bfloat16)
+        assert torch.equal(hbl.gemm_dequant_bf16(q + offset, sd, unused, packed, N, alpha, code_offset=offset), want)
+
+
+@pytest.mark.parametrize("T,K,N", [(17, 640, 32800), (24, 11008, 32800), (32, 8192, 33024)])
+def test_17_to_32_tokens_stream_against_many_rows(hbl, T, K, N):
+    """The shared form of the weight-streaming kernel behind a single call: K in one piece and cut over workgroups (whose last
+    one adds the slices), row tiles that leave a wave none; bit for bit what the two stages give on their own, which take the
+    mid-size kernel, call after call, with a workspace and without (there K stays in one piece)."""
+    note(f"shared form, single call T={T} K={K} N={N}")
+    g = torch.Generator(device="cuda").manual_seed(T + K)
+    packed = hbl.pack_ternary_2bit(torch.randint(-1, 2, (N, K), dtype=torch.int8, device="cuda", generator=g))
+    alpha = torch.rand(1, device="cuda", generator=g) + 0.5
+    for _ in range(3):
+        x = torch.randn((T, K), device="cuda", generator=g).to(torch.bfloat16)
+        with hbl.trace(4) as tr:
+            y = hbl.plain_bitlinear_forward(x, packed, N, alpha, 4, EPS)
+            torch.cuda.synchronize()
+        assert tr.launches[-1][0] == "decode_gemm_kernel"
+        rec, sd, cs = hbl.fwht_quant(x, 4, False, EPS, code_offset=hbl.CODES_BF6)
+        want = hbl.gemm_dequant_bf16(rec, sd, cs, packed, N, alpha, code_offset=hbl.CODES_BF6, K=K)
+        assert torch.equal(y, want)
+        y = torch.empty_like(y)
+        hbl.bitlinear_forward_small(x, packed, N, alpha, y, bits=4, hadamard=False, eps=EPS)
+        assert torch.equal(y, want)
 
 
 @pytest.mark.parametrize("T,K,N,groups,hadamard", [
