@@ -364,8 +364,10 @@ int launch_mid_gemm_grouped(MidArgs& args, bool records, hipStream_t stream) {
             args.p[j - 1] = t;
         }
     // While everything is resident at once: small tiles.  Beyond that four weight tiles per code stage move fewer bytes (47
-    // tokens, four 7B projections, 832 tiles: 36.2 -> 30.5 us per layer), and a long K range takes more groups and smaller
-    // tiles so that it does not outlast the rest (with eight one-wave groups it is 640 workgroups: 36.5 us).
+    // tokens, four 7B projections, 832 tiles: 36.2 -> 30.5 us per layer), and a K range much longer than the others' takes more
+    // groups and smaller tiles so that it does not outlast them (with eight one-wave groups it is 640 workgroups: 36.5 us).  Not
+    // so where all are long: 33 to 64 tokens, two projections 8192 -> 16384, 36 us with the smaller tiles, 23 without; three
+    // 8192 -> 8192 28 and 22.
     int max_t = 0;
     int64_t tiles = 0, narrow = 0;
     for (int i = 0; i < args.n; ++i) {
@@ -373,7 +375,9 @@ int launch_mid_gemm_grouped(MidArgs& args, bool records, hipStream_t stream) {
         tiles += mid_tiles(args.p[i].T, args.p[i].N);
         narrow += MidForm<8, 2, 1, 1>::tiles_n(args.p[i].N) * MidForm<8, 2, 1, 1>::tiles_t(args.p[i].T);
     }
-    for (int i = 0; i < args.n; ++i) args.p[i].form = args.p[i].K >= (narrow <= kMidResident ? 2048 : 8192) ? 1 : 0;
+    const int shortest = args.p[args.n - 1].K;
+    for (int i = 0; i < args.n; ++i)
+        args.p[i].form = narrow <= kMidResident ? args.p[i].K >= 2048 : args.p[i].K >= 8192 && args.p[i].K >= 2 * shortest;
     return records ? launch_grouped<false>(args, max_t, tiles, stream) : launch_grouped<true>(args, max_t, tiles, stream);
 }
 

@@ -703,7 +703,9 @@ def test_one_launch_small_batches(hbl, T, K, N, groups, hadamard, dtype):
     [(40, 640, 96), (64, 8320, 160), (5, 512, 32), (33, 384, 64)],            # more tokens
     [(33, 640, 16416), (64, 8320, 160), (40, 512, 16448), (50, 256, 64)],     # more tiles than workgroups fit at once
     [(20, 640, 16416), (32, 8320, 160), (24, 512, 16448)],                    # ... at most 32 tokens
-], ids=["few", "more_tokens", "many_tiles", "many_tiles_32"])
+    [(40, 8192, 8224), (64, 8320, 8256)],                                     # long rows only
+    [(40, 8192, 16416), (33, 8320, 16416)],
+], ids=["few", "more_tokens", "many_tiles", "many_tiles_32", "long", "long_many"])
 @pytest.mark.parametrize("bits", [4, 8])
 def test_grouped_forms_beyond_16_tokens(hbl, shapes, bits):
     """Groups beyond 16 tokens: every form of the grouped mid-size launch, rows shorter than 512 (bytes, a launch
