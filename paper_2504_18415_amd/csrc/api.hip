@@ -326,39 +326,27 @@ int hbl_bitlinear_forward_grouped(const hbl_problem* problems, int n_problems, f
         base += region;
     }
     hipStream_t s = static_cast<hipStream_t>(stream);
-    int rc = launch_quant_grouped(qa, problems[0].bits, problems[0].x_dtype, s);
+    const int rc = launch_quant_grouped(qa, problems[0].bits, problems[0].x_dtype, s);
     if (rc != HBL_OK) return rc;
-    if (tile_rows == 0) return launch_decode_gemm(da, s);   // at most 16 tokens everywhere
-    for (const bool records : {true, false}) {   // a launch of its own for the problems on either operand path
-        DecodeArgs part = {};
-        for (int i = 0; i < da.n; ++i)
-            if ((da.p[i].f6 != 0) == records) part.p[part.n++] = da.p[i];
-        if (part.n == 0) continue;
-        if (!mid_group_preferred(part.p, part.n, records)) {
-            rc = launch_decode_gemm(part, s);
-            if (rc != HBL_OK) return rc;
-            continue;
-        }
-        MidArgs ma = {};
-        for (int i = 0; i < part.n; ++i) {
-            const DecodeProblem& d = part.p[i];
-            MidProblem& m = ma.p[ma.n++];
-            m.codes = d.codes;
-            m.packed = d.packed;
-            m.s_dequant = d.s_dequant;
-            m.w_scales = d.w_scales;
-            m.y = d.y;
-            m.T = d.T;
-            m.K = d.K;
-            m.N = d.N;
-            m.rows_per_group = d.rows_per_group;
-            m.code_offset = d.code_offset;
-            m.w_row_sum = d.w_row_sum;
-        }
-        rc = launch_mid_gemm_grouped(ma, records, s);
-        if (rc != HBL_OK) return rc;
+    if (!mid_group_preferred(da.p, da.n)) return launch_decode_gemm(da, s);
+    MidArgs ma = {};
+    for (int i = 0; i < da.n; ++i) {
+        const DecodeProblem& d = da.p[i];
+        MidProblem& m = ma.p[ma.n++];
+        m.codes = d.codes;
+        m.packed = d.packed;
+        m.s_dequant = d.s_dequant;
+        m.w_scales = d.w_scales;
+        m.y = d.y;
+        m.T = d.T;
+        m.K = d.K;
+        m.N = d.N;
+        m.rows_per_group = d.rows_per_group;
+        m.code_offset = d.code_offset;
+        m.w_row_sum = d.w_row_sum;
+        m.bytes = d.f6 == 0;
     }
-    return HBL_OK;
+    return launch_mid_gemm_grouped(ma, s);
 }
 
 int hbl_ln_bitlinear_forward(const void* x, int x_dtype, int64_t T, int64_t K, const float* ln_gain, float ln_eps,

@@ -267,6 +267,7 @@ struct MidProblem {
     int rows_per_group;
     int code_offset;           // bytes: stored code byte = q + code_offset
     const int32_t* w_row_sum;  // bytes: [N]
+    int bytes;                 // codes are bytes (read by grouped launches)
     int tiles_n, tiles_t;      // (set by the launch)
     int form, wg_begin;        // grouped launch: which of its two forms, first workgroup
 };
@@ -277,10 +278,10 @@ struct MidArgs {
 };
 bool mid_gemm_preferred(int64_t T, int64_t K, int64_t N, bool records);
 int launch_mid_gemm(const MidProblem& a, bool records, hipStream_t stream);
-// Whether a group's problems of one operand path take that kernel (more than 16 tokens somewhere).
-bool mid_group_preferred(const DecodeProblem* p, int n, bool records);
+// Whether a group takes that kernel (more than 16 tokens somewhere).
+bool mid_group_preferred(const DecodeProblem* p, int n);
 // Every problem needs T <= 64; reorders args.
-int launch_mid_gemm_grouped(MidArgs& args, bool records, hipStream_t stream);
+int launch_mid_gemm_grouped(MidArgs& args, hipStream_t stream);
 // Whether a single projection is better served by the streaming form of that launch (T <= 16) than by the mid-size kernel.
 bool decode_stream_preferred(int64_t T, int64_t K, int64_t N, bool records);
 // ... and by its shared form (17 to 32 tokens of records).

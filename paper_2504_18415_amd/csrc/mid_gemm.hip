@@ -354,7 +354,7 @@ int launch_mid_gemm(const MidProblem& a, bool records, hipStream_t stream) {
     return a.acc_out ? launch_form<true, true>(a, stream) : launch_form<true, false>(a, stream);
 }
 
-int launch_mid_gemm_grouped(MidArgs& args, bool records, hipStream_t stream) {
+int launch_mid_gemm_grouped(MidArgs& args, hipStream_t stream) {
     if (args.n <= 0) return HBL_OK;
     // long K ranges first: their workgroups run longest
     for (int i = 1; i < args.n; ++i)
@@ -363,36 +363,47 @@ int launch_mid_gemm_grouped(MidArgs& args, bool records, hipStream_t stream) {
             args.p[j] = args.p[j - 1];
             args.p[j - 1] = t;
         }
+    int max_t = 0, bytes = 0;
+    int64_t tiles = 0, narrow = 0;
+    for (int i = 0; i < args.n; ++i) {
+        max_t = args.p[i].T > max_t ? args.p[i].T : max_t;
+        bytes += args.p[i].bytes != 0;
+        tiles += mid_tiles(args.p[i].T, args.p[i].N);
+        narrow += MidForm<8, 2, 1, 1>::tiles_n(args.p[i].N) * MidForm<8, 2, 1, 1>::tiles_t(args.p[i].T);
+    }
+    if (bytes != 0 && bytes != args.n) {
+        // Records and bytes: one launch with a form for either.  Two launches cost 2 to 3 us more (24 tokens, 256 -> 4096 and 512
+        // -> 2048: 9.5 us, 6.4 as one; 47 tokens, 384 / 1536 four projections 12.2, 7.8).
+        for (int i = 0; i < args.n; ++i) args.p[i].form = args.p[i].bytes != 0;
+        if (narrow <= kMidResident) return launch_grouped_forms<MidForm<8, 2, 1, 1, false>, MidForm<8, 2, 1, 1, true>>(args, stream);
+        return max_t <= 32 ? launch_grouped_forms<MidForm<4, 3, 2, 1, false>, MidForm<4, 3, 2, 1, true>>(args, stream)
+                           : launch_grouped_forms<MidForm<4, 2, 2, 2, false>, MidForm<4, 2, 2, 2, true>>(args, stream);
+    }
     // While everything is resident at once: small tiles.  Beyond that four weight tiles per code stage move fewer bytes (47
     // tokens, four 7B projections, 832 tiles: 36.2 -> 30.5 us per layer), and a K range much longer than the others' takes more
     // groups and smaller tiles so that it does not outlast them (with eight one-wave groups it is 640 workgroups: 36.5 us).  Not
     // so where all are long: 33 to 64 tokens, two projections 8192 -> 16384, 36 us with the smaller tiles, 23 without; three
     // 8192 -> 8192 28 and 22.
-    int max_t = 0;
-    int64_t tiles = 0, narrow = 0;
-    for (int i = 0; i < args.n; ++i) {
-        max_t = args.p[i].T > max_t ? args.p[i].T : max_t;
-        tiles += mid_tiles(args.p[i].T, args.p[i].N);
-        narrow += MidForm<8, 2, 1, 1>::tiles_n(args.p[i].N) * MidForm<8, 2, 1, 1>::tiles_t(args.p[i].T);
-    }
     const int shortest = args.p[args.n - 1].K;
     for (int i = 0; i < args.n; ++i)
         args.p[i].form = narrow <= kMidResident ? args.p[i].K >= 2048 : args.p[i].K >= 8192 && args.p[i].K >= 2 * shortest;
-    return records ? launch_grouped<false>(args, max_t, tiles, stream) : launch_grouped<true>(args, max_t, tiles, stream);
+    return bytes == 0 ? launch_grouped<false>(args, max_t, tiles, stream) : launch_grouped<true>(args, max_t, tiles, stream);
 }
 
 // A group at 47 tokens: 2048 / 8192 projections 21.2 -> 14.7 us per layer against the shared form of the weight-streaming
 // kernel, 7B 31.8 -> 30.5; up to 32 tokens that form's 512 workgroups of four waves are the better one once the tiles do not
 // fit at once (7B, 20 tokens: 25.3 against 26.0 us per layer; 2048 / 8192, 24 tokens: 17.0 against 14.0).
 // INT8 activations: 7B 20 tokens 27.2 -> 25.2, 64 tokens 36.8 -> 32, 2048 / 8192 40 tokens 24.4 -> 14.6.
-bool mid_group_preferred(const DecodeProblem* p, int n, bool records) {
-    int max_t = 0;
+bool mid_group_preferred(const DecodeProblem* p, int n) {
+    int max_t = 0, records = 0;
     int64_t tiles = 0;
     for (int i = 0; i < n; ++i) {
         max_t = p[i].T > max_t ? p[i].T : max_t;
+        records += p[i].f6 != 0;
         tiles += mid_tiles(p[i].T, p[i].N);
     }
-    return max_t > 16 && (!records || max_t > 32 || tiles <= kMidResident);
+    if (max_t <= 16) return false;
+    return max_t > 32 || tiles <= kMidResident || records != n;   // (the shared form takes records only)
 }
 
 }  // namespace hbl

@@ -703,13 +703,17 @@ def test_one_launch_small_batches(hbl, T, K, N, groups, hadamard, dtype):
     [(40, 640, 96), (64, 8320, 160), (5, 512, 32), (33, 384, 64)],            # more tokens
     [(33, 640, 16416), (64, 8320, 160), (40, 512, 16448), (50, 256, 64)],     # more tiles than workgroups fit at once
     [(20, 640, 16416), (32, 8320, 160), (24, 512, 16448)],                    # ... at most 32 tokens
+    [(20, 640, 96), (17, 8320, 160), (5, 512, 32)],                           # no rows shorter than 512: one kind of codes
+    [(40, 640, 96), (64, 8320, 160), (5, 1152, 32)],
+    [(33, 640, 16416), (64, 8320, 160), (40, 1152, 16448)],
     [(40, 8192, 8224), (64, 8320, 8256)],                                     # long rows only
     [(40, 8192, 16416), (33, 8320, 16416)],
-], ids=["few", "more_tokens", "many_tiles", "many_tiles_32", "long", "long_many"])
+], ids=["few", "more_tokens", "many_tiles", "many_tiles_32", "one_kind_few", "one_kind_more", "one_kind_many", "long", "long_many"])
 @pytest.mark.parametrize("bits", [4, 8])
 def test_grouped_forms_beyond_16_tokens(hbl, shapes, bits):
-    """Groups beyond 16 tokens: every form of the grouped mid-size launch, rows shorter than 512 (bytes, a launch
-    beside that of the records) and small members; each output bit for bit as the problem gives alone, which takes another form."""
+    """Groups beyond 16 tokens: every form of the grouped mid-size launch and of the shared streaming one, rows shorter than 512
+    (bytes beside the records of a launch) and small members, always two launches in all; each output bit for bit as the
+    problem gives alone, which takes another form."""
     note(f"grouped forms bits={bits} {shapes}")
     g = torch.Generator(device="cuda").manual_seed(11)
     items = []
@@ -717,7 +721,11 @@ def test_grouped_forms_beyond_16_tokens(hbl, shapes, bits):
         codes = torch.randint(-1, 2, (N, K), dtype=torch.int8, device="cuda", generator=g)
         x = torch.randn((T, K), device="cuda", generator=g).to(torch.bfloat16)
         items.append((x, hbl.pack_ternary_2bit(codes), N, torch.rand(1, device="cuda", generator=g) + 0.5, bits, False, None))
-    for y, it in zip(hbl.bitlinear_forward_grouped(items, EPS), items):
+    with hbl.trace(4) as tr:
+        ys = hbl.bitlinear_forward_grouped(items, EPS)
+        torch.cuda.synchronize()
+    assert len(tr.launches) == 2
+    for y, it in zip(ys, items):
         assert torch.equal(y, hbl.plain_bitlinear_forward(it[0], it[1], it[2], it[3], bits, EPS)), it[0].shape
 
 
