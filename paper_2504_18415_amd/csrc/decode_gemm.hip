@@ -1,4 +1,4 @@
-// Small-batch (decode) form of the ternary GEMM of Eq. 7: T <= 16 tokens (32 in one case), so the packed weights are
+// Small-batch (decode) form of the ternary GEMM of Eq. 7: T <= 16 tokens (32 in the shared form), so the packed weights are
 // read once from HBM and dominate the traffic, and the job is to keep as many weight tiles in flight as
 // the memory system needs.  One launch serves up to kMaxGroup independent projections.
 //
@@ -15,11 +15,11 @@
 //  - streaming (T <= 16): a wave's code stage is private (8 or 16 rows), so the waves never meet at a
 //    barrier.  The K range of one row tile may be split over the 2 or 4 waves of a workgroup; their
 //    accumulators are added through LDS at the end (exact).
-//  - shared (17 to 32 tokens of records in a group too large for the mid-size kernel, mid_gemm.hip): the four waves
-//    take four row tiles over one K range and share the code stage (32 rows): one barrier per stage.  A K range split over workgroups leaves int32 slices in the
-//    workspace; the workgroup of a K range that finishes last (an arrival counter) adds the others' slices to
-//    its own accumulators and dequantises.  (A group with more split row groups than a slot has counters runs
-//    without the split.)
+//  - shared (17 to 32 tokens, where there are too many output rows for the mid-size kernel, mid_gemm.hip; a launch of
+//    records or of bytes): the four waves take four row tiles over one K range and share the code stage (32 rows): one
+//    barrier per stage.  A K range split over workgroups leaves int32 slices in the workspace; the workgroup of a K range
+//    that finishes last (an arrival counter) adds the others' slices to its own accumulators and dequantises.  (A group
+//    with more split row groups than a slot has counters runs without the split.)
 #include <atomic>
 
 #include "gemm_common.h"
@@ -59,7 +59,7 @@ __device__ __forceinline__ void decode_body(const DecodeProblem& p, const int w,
     constexpr int STAGE = XW + NW * 1024;             // + one packed weight tile per wave
     constexpr int XL = SHARE ? 1 : RQ;                // code copies per wave per stage (8 rows each)
     static_assert(D >= 3 && (ROWS & (ROWS - 1)) == 0, "pipeline depth / row count");
-    static_assert(!SHARE || (NW == 4 && F6), "the shared form is written for four waves and records");
+    static_assert(!SHARE || NW == 4, "the shared form is written for four waves");
     static_assert(NW * 4096 <= D * STAGE, "the in-workgroup reduction reuses the stage buffers");
 
     const int tid = threadIdx.x;
@@ -368,13 +368,14 @@ __device__ __forceinline__ void decode_body(const DecodeProblem& p, const int w,
     }
 }
 
-template <bool SHARE, int RQ, int D, int NW = 4>
+// BYTES (shared form): the problems' codes are bytes, else records.  (A streaming launch takes either, problem by problem.)
+template <bool SHARE, int RQ, int D, int NW, bool BYTES>
 __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void decode_gemm_kernel(const DecodeArgs args) {
     extern __shared__ __attribute__((aligned(1024))) char lds[];
     const DecodeProblem p = args.p[group_index_of(args.wg_begin, args.n, (int)blockIdx.x)];
     const int w = (int)blockIdx.x - p.wg_begin;
     if constexpr (SHARE) {
-        decode_body<SHARE, RQ, D, NW, true>(p, w, lds, args.arrive);
+        decode_body<SHARE, RQ, D, NW, !BYTES>(p, w, lds, args.arrive);
     } else {
         if (p.f6) decode_body<SHARE, RQ, D, NW, true>(p, w, lds, args.arrive);      // uniform over the workgroup
         else decode_body<SHARE, RQ, D, NW, false>(p, w, lds, args.arrive);
@@ -406,7 +407,7 @@ int next_arrive_slot(unsigned int** out) {
     return HBL_OK;
 }
 
-template <bool SHARE, int RQ, int D, int NW = 4>
+template <bool SHARE, int RQ, int D, int NW = 4, bool BYTES = false>
 int launch_form(const DecodeArgs& planned, int wgs, int counters, hipStream_t stream) {
     DecodeArgs a = planned;
     a.arrive = nullptr;
@@ -415,7 +416,7 @@ int launch_form(const DecodeArgs& planned, int wgs, int counters, hipStream_t st
     }
     constexpr int ROWS = SHARE ? 32 : RQ * 8;
     constexpr size_t lds = (size_t)D * ((SHARE ? 1 : NW) * ROWS * kBK + NW * 1024);
-    auto kern = decode_gemm_kernel<SHARE, RQ, D, NW>;
+    auto kern = decode_gemm_kernel<SHARE, RQ, D, NW, BYTES>;
     static std::atomic<uint64_t> lds_allowed{0};   // per instantiation: devices already set up
     if (const int rc = allow_dynamic_lds(kern, lds, lds_allowed); rc != HBL_OK) return rc;
     launch_kernel("decode_gemm_kernel", kern, dim3((unsigned)wgs), dim3(64 * NW), lds, stream, a);
@@ -542,9 +543,9 @@ int launch_decode_gemm(DecodeArgs& a, hipStream_t stream) {
     int max_t = 0;
     for (int i = 0; i < a.n; ++i) max_t = a.p[i].T > max_t ? a.p[i].T : max_t;
     if (max_t > 32) return HBL_E_SHAPE;   // (the mid-size kernel's)
-    if (max_t > 16)
-        for (int i = 0; i < a.n; ++i)
-            if (!a.p[i].f6) return HBL_E_SHAPE;
+    int records = 0;
+    for (int i = 0; i < a.n; ++i) records += a.p[i].f6 != 0;
+    if (max_t > 16 && records != 0 && records != a.n) return HBL_E_SHAPE;
     int wgs, counters;
     if (const int nw = wide_waves(a, max_t); nw != 0) {
         plan_wide(a, nw, &wgs);
@@ -556,7 +557,7 @@ int launch_decode_gemm(DecodeArgs& a, hipStream_t stream) {
     // the 2048 waves of a full grid, and deeper rings only cost LDS and queueing.
     if (max_t <= 8) return launch_form<false, 1, 4>(a, wgs, 0, stream);
     if (max_t <= 16) return launch_form<false, 2, 4>(a, wgs, 0, stream);
-    return launch_form<true, 1, 4>(a, wgs, counters, stream);
+    return records != 0 ? launch_form<true, 1, 4>(a, wgs, counters, stream) : launch_form<true, 1, 4, 4, true>(a, wgs, counters, stream);
 }
 
 }  // namespace hbl

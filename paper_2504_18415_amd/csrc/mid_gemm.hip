@@ -262,8 +262,8 @@ __global__ __launch_bounds__(FA::THREADS) void mid_gemm_grouped_kernel(const Mid
     extern __shared__ __attribute__((aligned(1024))) char lds[];
     const MidProblem p = args.p[group_index_of(args.wg_begin, args.n, (int)blockIdx.x)];
     const int wg = (int)blockIdx.x - p.wg_begin;
-    if (p.form == 0) mid_gemm_body<FA, false>(p, wg, lds);   // uniform over the workgroup
-    else mid_gemm_body<FB, false>(p, wg, lds);
+    if (std::is_same<FA, FB>::value || p.form == 0) mid_gemm_body<FA, false>(p, wg, lds);   // uniform over the workgroup
+    else if constexpr (!std::is_same<FA, FB>::value) mid_gemm_body<FB, false>(p, wg, lds);
 }
 
 template <typename F, bool RAW>
@@ -327,14 +327,22 @@ int launch_grouped_forms(MidArgs& args, hipStream_t stream) {
     return after_launch();
 }
 
+// Short rows, more than 256 tiles: as for single calls.  (Four projections 256 -> 8192, 47 tokens 8.6 -> 7.9 us; 512 -> 8192 at
+// 17 tokens 7.5 -> 6.9.)  A kernel of one form alone where the group needs no other: its LDS is that form's.
+template <typename F>
+int launch_grouped_one(MidArgs& args, hipStream_t stream) { return launch_grouped_forms<F, F>(args, stream); }
+
 template <bool I8>
-int launch_grouped(MidArgs& args, int max_t, int64_t tiles, hipStream_t stream) {
-    if (max_t <= 32 && (!I8 || tiles <= kMidResident))   // (more tiles of records than that stay with the shared form)
+int launch_grouped(MidArgs& args, int max_t, int64_t tiles, bool any_long, hipStream_t stream) {
+    const bool few = max_t <= 32, fits = tiles <= kMidResident, short_rows = args.p[0].K <= 1024 && tiles > 256;
+    if (short_rows) return few ? launch_grouped_one<MidForm<2, 3, 4, 1, I8>>(args, stream) : launch_grouped_one<MidForm<2, 2, 4, 2, I8>>(args, stream);
+    if (few && fits)   // (more tiles of records than that stay with the shared form)
         return launch_grouped_forms<MidForm<4, 3, 2, 1, I8>, MidForm<8, 2, 1, 1, I8>>(args, stream);
     if constexpr (I8) {
-        if (max_t <= 32) return launch_grouped_forms<MidForm<2, 4, 4, 1, true>, MidForm<8, 2, 1, 1, true>>(args, stream);
+        if (few) return any_long ? launch_grouped_forms<MidForm<2, 3, 4, 1, true>, MidForm<8, 2, 1, 1, true>>(args, stream)
+                                 : launch_grouped_one<MidForm<2, 3, 4, 1, true>>(args, stream);
     }
-    if (tiles <= kMidResident) return launch_grouped_forms<MidForm<4, 2, 2, 2, I8>, MidForm<8, 2, 1, 1, I8>>(args, stream);
+    if (fits) return launch_grouped_forms<MidForm<4, 2, 2, 2, I8>, MidForm<8, 2, 1, 1, I8>>(args, stream);
     return launch_grouped_forms<MidForm<2, 3, 4, 2, I8>, MidForm<4, 3, 2, 1, I8>>(args, stream);
 }
 
@@ -385,25 +393,33 @@ int launch_mid_gemm_grouped(MidArgs& args, hipStream_t stream) {
     // so where all are long: 33 to 64 tokens, two projections 8192 -> 16384, 36 us with the smaller tiles, 23 without; three
     // 8192 -> 8192 28 and 22.
     const int shortest = args.p[args.n - 1].K;
-    for (int i = 0; i < args.n; ++i)
-        args.p[i].form = narrow <= kMidResident ? args.p[i].K >= 2048 : args.p[i].K >= 8192 && args.p[i].K >= 2 * shortest;
-    return bytes == 0 ? launch_grouped<false>(args, max_t, tiles, stream) : launch_grouped<true>(args, max_t, tiles, stream);
+    bool any_long = false;
+    for (int i = 0; i < args.n; ++i) {
+        MidProblem& p = args.p[i];
+        p.form = narrow <= kMidResident ? p.K >= 2048 : p.K >= 8192 && p.K >= 2 * shortest;
+        any_long = any_long || p.form != 0;
+    }
+    return bytes == 0 ? launch_grouped<false>(args, max_t, tiles, any_long, stream) : launch_grouped<true>(args, max_t, tiles, any_long, stream);
 }
 
 // A group at 47 tokens: 2048 / 8192 projections 21.2 -> 14.7 us per layer against the shared form of the weight-streaming
 // kernel, 7B 31.8 -> 30.5; up to 32 tokens that form's 512 workgroups of four waves are the better one once the tiles do not
 // fit at once (7B, 20 tokens: 25.3 against 26.0 us per layer; 2048 / 8192, 24 tokens: 17.0 against 14.0).
-// INT8 activations: 7B 20 tokens 27.2 -> 25.2, 64 tokens 36.8 -> 32, 2048 / 8192 40 tokens 24.4 -> 14.6.
+// INT8 activations: 7B 20 tokens 27.2 -> 25.2, 64 tokens 36.8 -> 32, 2048 / 8192 40 tokens 24.4 -> 14.6; but rows of at most
+// 1024 bytes, up to 32 tokens, that do not fit at once are faster in the shared form: four projections 256 -> 24576, 17 tokens
+// 7.4 us against 8.6, 1024 -> 16384 9.0 against 10.4.
 bool mid_group_preferred(const DecodeProblem* p, int n) {
-    int max_t = 0, records = 0;
+    int max_t = 0, max_k = 0, records = 0;
     int64_t tiles = 0;
     for (int i = 0; i < n; ++i) {
         max_t = p[i].T > max_t ? p[i].T : max_t;
+        max_k = p[i].K > max_k ? p[i].K : max_k;
         records += p[i].f6 != 0;
         tiles += mid_tiles(p[i].T, p[i].N);
     }
     if (max_t <= 16) return false;
-    return max_t > 32 || tiles <= kMidResident || records != n;   // (the shared form takes records only)
+    if (records != 0 && records != n) return true;   // (the shared form takes one kind)
+    return max_t > 32 || tiles <= kMidResident || (records == 0 && max_k > 1024);
 }
 
 }  // namespace hbl

@@ -708,7 +708,12 @@ def test_one_launch_small_batches(hbl, T, K, N, groups, hadamard, dtype):
     [(33, 640, 16416), (64, 8320, 160), (40, 1152, 16448)],
     [(40, 8192, 8224), (64, 8320, 8256)],                                     # long rows only
     [(40, 8192, 16416), (33, 8320, 16416)],
-], ids=["few", "more_tokens", "many_tiles", "many_tiles_32", "one_kind_few", "one_kind_more", "one_kind_many", "long", "long_many"])
+    [(20, 640, 8224), (24, 512, 8256)],                                       # short rows, more than 256 tiles
+    [(40, 640, 8224), (64, 512, 8256)],
+    [(20, 640, 16416), (32, 1024, 16448)],                                    # ... more than 512
+    [(20, 1152, 16416), (32, 1280, 16448)],
+], ids=["few", "more_tokens", "many_tiles", "many_tiles_32", "one_kind_few", "one_kind_more", "one_kind_many", "long", "long_many",
+        "short", "short_64", "short_many", "longer_many"])
 @pytest.mark.parametrize("bits", [4, 8])
 def test_grouped_forms_beyond_16_tokens(hbl, shapes, bits):
     """Groups beyond 16 tokens: every form of the grouped mid-size launch and of the shared streaming one, rows shorter than 512
