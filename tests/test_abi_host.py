@@ -149,6 +149,20 @@ def test_binding_fails_loudly_without_library(monkeypatch, tmp_path):
         hbl.lib()
 
 
+def test_outputs_are_plain_tensors_whatever_the_input_is():
+    """Outputs and workspaces that the binding allocates: plain tensors, also for a Parameter or another subclass."""
+    torch = pytest.importorskip("torch")
+    from paper_2504_18415_amd import hbl
+
+    class Tagged(torch.Tensor):
+        pass
+
+    x = torch.zeros((2, 4))
+    for t in (x, torch.nn.Parameter(x), x.as_subclass(Tagged)):
+        y = hbl._empty(t, (3, 5), torch.bfloat16)
+        assert type(y) is torch.Tensor and y.shape == (3, 5) and y.dtype == torch.bfloat16 and not y.requires_grad
+
+
 def test_small_batch_launch_plan(L):
     """Host logic of the decode path: K splits and grid sizes for the 7B layer and a few odd shapes."""
     from paper_2504_18415_amd import hbl
