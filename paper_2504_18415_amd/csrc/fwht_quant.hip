@@ -16,7 +16,8 @@
 //   [e: log2 CH in-thread][lane: 6][r: log2 R in-thread chunks][wave: log2 W]
 // so that every global access is one contiguous CH-element piece per lane and
 // the stage order e -> lane -> r -> wave is ascending.  The wave stages swap
-// the wave bits with the low r bits through LDS once, then run in registers.#include <atomic>
+// the wave bits with the low r bits through LDS once, then run in registers.
+#include <atomic>
 
 #include "quant_bodies.h"
 
