@@ -376,14 +376,15 @@ int hbl_ln_fwht_quant(const void* x, int x_dtype, int64_t T, int64_t K, const fl
                              static_cast<hipStream_t>(stream), ln_gain, ln_eps);
 }
 
-int hbl_test_grouped_plan(const hbl_problem* problems, int n_problems, int* ksplit, int* gemm_workgroups,
-                           int* arrival_counters, int* single_call_streams) {
-    if (!problems || !ksplit || !gemm_workgroups || !arrival_counters || !single_call_streams) return HBL_E_NULL;
+int hbl_test_grouped_plan(const hbl_problem* problems, int n_problems, int* route, int* ksplit, int* gemm_workgroups,
+                           int* arrival_counters) {
+    if (!problems || !route || !ksplit || !gemm_workgroups || !arrival_counters) return HBL_E_NULL;
     if (n_problems < 1 || n_problems > kMaxGroup) return HBL_E_SHAPE;
     DecodeArgs da = {};
     static int32_t dummy_partial;
     for (int i = 0; i < n_problems; ++i) {
         const hbl_problem& q = problems[i];
+        if ((q.bits != 4 && q.bits != 8) || q.bits != problems[0].bits) return HBL_E_BITS;
         if (q.T < 1 || q.T > 64) return HBL_E_SHAPE;
         const int rc = check_gemm_shape(q.T, q.K, q.N, q.hadamard != 0);
         if (rc != HBL_OK) return rc;
@@ -391,9 +392,13 @@ int hbl_test_grouped_plan(const hbl_problem* problems, int n_problems, int* kspl
         dp.T = (int)q.T;
         dp.K = (int)q.K;
         dp.N = (int)q.N;
+        dp.f6 = bf6_path_supported(q.K, q.bits) ? 1 : 0;
         dp.partial = &dummy_partial;   // the grouped call always brings a partial buffer
-        single_call_streams[i] = decode_stream_preferred(q.T, q.K, q.N, q.K >= 512) ? 1 : 0;
+        ksplit[i] = 0;
     }
+    *gemm_workgroups = *arrival_counters = 0;
+    *route = (int)(mid_group_preferred(da.p, da.n) ? Route::kMid : Route::kStream);
+    if (*route == (int)Route::kMid) return HBL_OK;
     const int rc = decode_plan_for_tests(da, gemm_workgroups, arrival_counters);
     if (rc != HBL_OK) return rc;
     for (int i = 0; i < n_problems; ++i) ksplit[i] = da.p[i].ksplit;

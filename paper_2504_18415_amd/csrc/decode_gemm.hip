@@ -528,7 +528,7 @@ bool decode_shared_preferred(int64_t T, int64_t K, int64_t N) {
 int decode_plan_for_tests(DecodeArgs& a, int* wgs, int* counters) {
     int max_t = 0;
     for (int i = 0; i < a.n; ++i) max_t = a.p[i].T > max_t ? a.p[i].T : max_t;
-    if (a.n <= 0 || max_t > 64) return HBL_E_SHAPE;
+    if (a.n <= 0 || max_t > 32) return HBL_E_SHAPE;
     if (const int nw = wide_waves(a, max_t); nw != 0) {
         plan_wide(a, nw, wgs);
         *counters = 0;

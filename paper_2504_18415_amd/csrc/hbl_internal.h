@@ -251,11 +251,11 @@ __host__ __device__ inline int group_index_of(const int* begin, int n, int wg) {
         if (i < n && wg >= begin[i]) idx = i;
     return idx;
 }
-// Fills ksplit / wg_begin / arrive_begin and launches.  Every problem needs T <= 64.
+// Fills ksplit / wg_begin / arrive_begin and launches.  Every problem needs T <= 32, and above 16 tokens one form of codes.
 int launch_decode_gemm(DecodeArgs& args, hipStream_t stream);
 // The launch plan launch_decode_gemm would use (K splits, grid sizes), without launching: host logic only.
 int decode_plan_for_tests(DecodeArgs& args, int* wgs, int* arrival_counters);
-// Mid-size form of the fp6 x fp4 GEMM (mid_gemm.hip): 17 tokens up to where the prefill kernel has tiles enough.
+// Mid-size form of the GEMM on both operand paths (mid_gemm.hip): 17 tokens up to where the prefill kernels have tiles enough.
 struct MidProblem {
     const int8_t* codes;       // record image of [T, K], or bytes
     const uint32_t* packed;    // weight tiles

@@ -12,16 +12,16 @@ extern "C" {
 #endif
 
 /*
- * Host only (no launch, no device access): the plan the small-batch GEMM launch of a grouped call would
- * use for these problems (every T in 1..64, n_problems <= 8; only T, K, N and hadamard are read).
- *   ksplit[i]              K slices per 32-row weight tile of problem i (inside a workgroup when every
- *                          T <= 16, over workgroups otherwise - the last of them to finish adds the slices)
- *   gemm_workgroups        grid size of the GEMM launch
- *   arrival_counters       groups of four row tiles whose K range is split over workgroups (0 = none)
- *   single_call_streams[i] 1 if a single forward call on problem i uses the weight-streaming kernel
+ * Host only (no launch, no device access): the GEMM launch a grouped call would make for these problems (every T in
+ * 1..64, one bit width, n_problems <= 8; only T, K, N, bits and hadamard are read).
+ *   route             1: weight streaming   2: mid-size (as in hbl_test_forward_route)
+ *   ksplit[i]         weight streaming: K slices per 32-row weight tile of problem i (inside a workgroup when every
+ *                     T <= 16, over workgroups otherwise - the last of them to finish adds the slices); else 0
+ *   gemm_workgroups   weight streaming: grid size; else 0
+ *   arrival_counters  groups of four row tiles whose K range is split over workgroups (0 = none)
  */
-int hbl_test_grouped_plan(const hbl_problem* problems, int n_problems, int* ksplit, int* gemm_workgroups,
-                          int* arrival_counters, int* single_call_streams);
+int hbl_test_grouped_plan(const hbl_problem* problems, int n_problems, int* route, int* ksplit, int* gemm_workgroups,
+                          int* arrival_counters);
 
 /*
  * Host only: the kernel that a single forward call of this shape ends in, as the dispatch picks it (norm != 0: with the

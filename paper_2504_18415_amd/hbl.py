@@ -464,17 +464,17 @@ def ln_fwht_quant(x: torch.Tensor, ln_gain: torch.Tensor, ln_eps: float, bits: i
     return codes, sd, cs
 
 
-def grouped_plan(shapes):
-    """Host-only: launch plan of the small-batch GEMM for [(T, K, N, hadamard), ...] ->
-    (ksplit list, gemm workgroups, arrival counters = groups of four row tiles whose K range is split over
-    workgroups and reduced by the last of them, list of "single call streams" flags)."""
+def grouped_plan(shapes, bits: int = 4):
+    """Host-only: the GEMM launch of a grouped call for [(T, K, N, hadamard), ...] -> (one of ``ROUTES``, ksplit list,
+    workgroups, arrival counters = groups of four row tiles whose K range is split over workgroups and reduced by the
+    last of them); the plan itself only where the weight-streaming kernel takes the group, else zeros."""
     n = len(shapes)
-    arr = (Problem * n)(*[Problem(0, BF16, 4, int(bool(h)), 0, T, K, N, 0, 0, 1, 0) for (T, K, N, h) in shapes])
+    arr = (Problem * n)(*[Problem(0, BF16, bits, int(bool(h)), 0, T, K, N, 0, 0, 1, 0) for (T, K, N, h) in shapes])
     ks = (ctypes.c_int * n)()
-    st = (ctypes.c_int * n)()
-    wgs, counters = ctypes.c_int(0), ctypes.c_int(0)
-    _check(lib().hbl_test_grouped_plan(arr, n, ks, ctypes.byref(wgs), ctypes.byref(counters), st), "grouped_plan")
-    return list(ks), wgs.value, counters.value, [bool(v) for v in st]
+    route, wgs, counters = ctypes.c_int(0), ctypes.c_int(0), ctypes.c_int(0)
+    _check(lib().hbl_test_grouped_plan(arr, n, ctypes.byref(route), ks, ctypes.byref(wgs), ctypes.byref(counters)),
+           "grouped_plan")
+    return ROUTES[route.value], list(ks), wgs.value, counters.value
 
 
 def forward_route(T: int, K: int, N: int, bits: int = 4, hadamard: bool = True, x_dtype: int = BF16,

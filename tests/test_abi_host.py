@@ -164,35 +164,32 @@ def test_outputs_are_plain_tensors_whatever_the_input_is():
 
 
 def test_small_batch_launch_plan(L):
-    """Host logic of the decode path: K splits and grid sizes for the 7B layer and a few odd shapes."""
+    """Host logic of the decode path as the calls take it: kernel, K splits and grid sizes for the 7B layer and a few odd
+    shapes."""
     from paper_2504_18415_amd import hbl
-    layer = lambda B: [(B, 4096, 12288, False), (B, 4096, 4096, True), (B, 4096, 32768, False), (B, 16384, 4096, True)]
+    layer = lambda B, h=4096, m=16384: [(B, h, 3 * h, False), (B, h, h, True), (B, h, 2 * m, False), (B, m, h, True)]
     # batch <= 16: streaming form; 2048 wave-units of 32 weight tiles = 512 workgroups = two per CU, no reduction
     for B in (1, 8, 16):
-        ks, wgs, red, single = hbl.grouped_plan(layer(B))
-        assert ks == [1, 1, 1, 4] and wgs == 96 + 32 + 256 + 128 and red == 0
-        assert single == [True, True, True, True]
-    # batch > 16: shared form; only the K = 16384 problem is split, over workgroups: one arrival counter per group
-    # of four row tiles of it
-    ks, wgs, red, single = hbl.grouped_plan(layer(64))
-    assert ks == [1, 1, 1, 4] and wgs == 512 and red == 4096 // 128 and single == [False] * 4
+        for bits in (4, 8):
+            assert hbl.grouped_plan(layer(B), bits) == ("stream", [1, 1, 1, 4], 96 + 32 + 256 + 128, 0)
+    # 17 to 32 tokens of records, more tiles than fit at once: shared form; only the K = 16384 problem is split, over
+    # workgroups: one arrival counter per group of four row tiles of it
+    assert hbl.grouped_plan(layer(32)) == ("stream", [1, 1, 1, 4], 512, 4096 // 128)
+    # everything else above 16 tokens is the mid-size kernel's: more tokens, INT8, fewer tiles
+    for shapes, bits in ((layer(33), 4), (layer(64), 4), (layer(32), 8), (layer(24, 2048, 8192), 4), ([(32, 16384, 4096, True)], 4),
+                         ([(40, 8192, 160, True)], 4), ([(20, 256, 32768, True), (20, 512, 32768, True)], 4)):
+        assert hbl.grouped_plan(shapes, bits) == ("mid", [0] * len(shapes), 0, 0)
+    # ... but for short rows of bytes that do not fit at once
+    assert hbl.grouped_plan([(32, 1024, 16448, True), (17, 512, 16448, True)], 8) == ("stream", [1, 1], 2 * 129, 0)
     # a single small problem is split down to 8 tiles per wave to reach more CUs
-    ks, wgs, red, _ = hbl.grouped_plan([(4, 4096, 4096, True)])
-    assert ks == [4] and wgs == 128 and red == 0
+    assert hbl.grouped_plan([(4, 4096, 4096, True)]) == ("stream", [4], 128, 0)
     # W_down alone: 128 row tiles and 128 K blocks - the 8 waves of a wider workgroup share a row tile's K range
-    ks, wgs, red, single = hbl.grouped_plan([(8, 16384, 4096, True)])
-    assert ks == [8] and wgs == 128 and red == 0 and single == [True]
-    ks, wgs, red, single = hbl.grouped_plan([(16, 16384, 4096, True)])
-    assert ks == [8] and wgs == 128 and red == 0 and single == [True]
-    ks, wgs, red, single = hbl.grouped_plan([(32, 16384, 4096, True)])   # shared form: split over workgroups
-    assert ks == [4] and wgs == 128 and red == 32 and single == [False]
-    ks, wgs, red, _ = hbl.grouped_plan([(4, 128, 96, False)])        # one K block: nothing to split
-    assert ks == [1] and wgs == 1 and red == 0
-    ks, wgs, red, _ = hbl.grouped_plan([(40, 8192, 160, True)])      # shared form, few rows: split over workgroups
-    assert ks == [4] and wgs == 2 * 4 and red == 2
-    # more split row groups than a slot has arrival counters: the group runs without the split
-    ks, wgs, red, _ = hbl.grouped_plan([(40, 8192, 128 * 2049, True)])
-    assert ks == [1] and wgs == 2049 and red == 0
+    for T in (8, 16):
+        assert hbl.grouped_plan([(T, 16384, 4096, True)]) == ("stream", [8], 128, 0)
+    assert hbl.grouped_plan([(4, 128, 96, False)]) == ("stream", [1], 1, 0)        # one K block: nothing to split
+    # as many split row groups as a slot has arrival counters; with more the group runs without the split
+    assert hbl.grouped_plan([(32, 8192, 128 * 2048, True)]) == ("stream", [2], 2 * 2048, 2048)
+    assert hbl.grouped_plan([(32, 8192, 128 * 2049, True)]) == ("stream", [1], 2049, 0)
     with pytest.raises(hbl.HblError):
         hbl.grouped_plan([(65, 4096, 4096, True)])
     with pytest.raises(hbl.HblError):
