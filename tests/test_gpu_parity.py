@@ -765,6 +765,30 @@ def test_prefill_gemm_tiles_raw_accumulators(hbl, T, K, N):
     assert np.array_equal(hbl.gemm_i32_bf6(rec, packed, N, T, K).cpu().numpy(), want)      # the forward's own choice
 
 
+@pytest.mark.parametrize("T,N,groups", [
+    (1000, 2208, 3),      # 560 tiles of 64 x 64, 36 of 256 x 256: 128 x 128
+    (3001, 4128, 3),      # 204 of 256 x 256, 216 of 512 x 128: the square tile
+    (3001, 4576, 11),     # 216 of either: 512 features x 128 tokens
+])
+@pytest.mark.parametrize("bits,K", [(4, 640), (8, 640), (4, 384)])
+def test_prefill_tiles_bf16_outputs(hbl, T, N, groups, bits, K):
+    """The prefill kernels behind a forward call with ragged token and feature tiles and several scale groups - code records,
+    bytes, and bytes with the INT4 offset that the row sums take out: every output bit for bit as the exact product of
+    the codes, scaled and rounded, gives it."""
+    note(f"prefill tiles, bf16 outputs T={T} N={N} K={K} bits={bits}")
+    assert hbl.forward_route(T, K, N, bits, hadamard=False) == "prefill"
+    g = torch.Generator(device="cuda").manual_seed(T + N + K)
+    c = torch.randint(-1, 2, (N, K), dtype=torch.int8, device="cuda", generator=g)
+    x = torch.randn((T, K), device="cuda", generator=g)
+    x[:, 7] *= 30
+    alpha = torch.rand(groups, device="cuda", generator=g) + 0.5
+    y = hbl.plain_bitlinear_forward(x.to(torch.bfloat16), hbl.pack_ternary_2bit(c), N, alpha, bits, EPS)
+    codes, sd, _ = hbl.fwht_quant(x.to(torch.bfloat16), bits, False, EPS)
+    acc = codes.double() @ c.double().t()                                       # exact
+    want = ((acc.float() * sd[:, None]) * alpha.repeat_interleave(N // groups)[None, :]).to(torch.bfloat16)
+    assert torch.equal(y, want)
+
+
 def test_f6f4_raw_accumulators_extreme_and_split_k_shapes(hbl):
     """|acc| = 8 * 16384 = 2^17 out of the fp6 x fp4 kernel as an integer, and the mid-size-batch shapes on
     which the forward call itself cuts K (8, 4 and 2 slices): raw accumulators against the oracle."""
@@ -992,6 +1016,31 @@ def test_ln_quantiser_rows_walked_by_resident_workgroups(hbl, K, T, dtype):
     c, sd, cs = hbl.ln_fwht_quant(xd, gd, 1e-6, 4, True, EPS, code_offset=8)
     assert np.array_equal(c.cpu().numpy().astype(np.int32) - 8, c4.astype(np.int32))
     assert np.array_equal(sd.cpu().numpy(), s4) and np.array_equal(cs.cpu().numpy(), c4.astype(np.int32).sum(1))
+
+
+@pytest.mark.parametrize("K,hadamard", [(256, True), (2048, True), (640, False), (3072, False), (4096, False)])
+@pytest.mark.parametrize("norm", [False, True])
+def test_one_row_per_workgroup_quantisers_beyond_4096_rows(hbl, K, hadamard, norm):
+    """Above 4096 rows the one-row-per-workgroup quantisers take the other form of their reductions: codes, scales and code
+    sums of all rows against the oracle, both bit widths, byte and record forms, with the norm and without."""
+    T = 4099
+    note(f"quantiser T={T} K={K} hadamard={hadamard} norm={norm}")
+    site = synth.Site("a", T, K, 32, hadamard=hadamard, outlier_frac=0.01, outlier_scale=30.0, seed=K + T)
+    x = synth.make_x(site)
+    g = ln_gain_for(K, K + T)
+    xr, xd, gd = (O.rmsnorm(x, g, 1e-6) if norm else x), dev_x(x), torch.from_numpy(g).cuda()
+    for bits, form in ((8, 0), (4, 8), (4, hbl.CODES_BF6)):
+        if form == hbl.CODES_BF6 and K < 512:
+            continue
+        c_ref, s_ref = O.fwht_quant(xr, bits, hadamard=hadamard, eps=EPS)
+        codes, sd, cs = (hbl.ln_fwht_quant(xd, gd, 1e-6, bits, hadamard, EPS, code_offset=form) if norm
+                         else hbl.fwht_quant(xd, bits, hadamard, EPS, code_offset=form))
+        if form == hbl.CODES_BF6:
+            assert np.array_equal(record_bits(codes.cpu().numpy(), T, K), record_bits(encode_bf6_records(c_ref.astype(np.int32)), T, K))
+        else:
+            assert np.array_equal(codes.cpu().numpy().astype(np.int32) - form, c_ref.astype(np.int32))
+        assert np.array_equal(sd.cpu().numpy(), s_ref)
+        assert np.array_equal(cs.cpu().numpy(), c_ref.astype(np.int32).sum(1))
 
 
 def ln_gain_for(K, seed):
