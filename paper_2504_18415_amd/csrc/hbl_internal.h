@@ -173,7 +173,7 @@ int launch_fwht_only(const void* x, int x_dtype, int64_t T, int64_t K, void* out
 // Workgroup tiles of the two prefill GEMM kernels.  kTileAuto is the choice every forward call makes from the
 // shape; the others let the parity tests run a given tile on a shape of their own.
 constexpr int kTileAuto = -1, kTileSquare = 0 /*256 x 256*/, kTileSmall = 1 /*128 x 128*/,
-              kTileWide = 2 /*512 features x 128 tokens*/, kTileSplitK = 3 /*mid-size form, K cut over the waves*/,
+              kTileWide = 2 /*512 features x 128 tokens*/, kTileMid = 3 /*mid-size kernel, K cut over the waves*/,
               kTileFewTokens = 4 /*bytes, at most 64 tokens*/;
 
 // GEMM + epilogue. If acc_out != nullptr the raw int32 accumulators are written

@@ -37,11 +37,10 @@ int hbl_test_forward_route(int64_t T, int64_t K, int64_t N, int x_dtype, int bit
  *   code_form  HBL_CODES_INT8 (int8 matrix-core kernel, codes [T, K] bytes) or HBL_CODES_BF6 (fp6 x fp4
  *              kernel, code records; K >= 512)
  *   tile       0: 256 x 256   1: 128 x 128   2: 512 features x 128 tokens
- *              3: the mid-size form, K cut over the waves of a workgroup (HBL_CODES_BF6 only)
- *   partial    tile 3: non-NULL, 16-byte aligned (its form keeps no partial tiles in memory); else may be NULL
+ *              3: the mid-size kernel, K cut over the waves of a workgroup (HBL_CODES_BF6 only)
  */
 int hbl_test_gemm_i32_tile(const void* codes, int code_form, int64_t T, int64_t K, const void* Wq_packed,
-                           int64_t N, int32_t* acc, int tile, void* partial, size_t partial_bytes, void* stream);
+                           int64_t N, int32_t* acc, int tile, void* stream);
 
 #ifdef __cplusplus
 }

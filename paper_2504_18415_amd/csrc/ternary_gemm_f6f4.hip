@@ -372,7 +372,7 @@ int launch_ternary_gemm_f6f4(const int8_t* code_records, int64_t T, int64_t K, c
     const int64_t tiles_sq = (int64_t)((N + 255) / 256) * ((T + 255) / 256);
     const int64_t tiles_wide = (int64_t)((N + 511) / 512) * ((T + 127) / 128);
     int cfg = tiles_sq >= 180 ? (tiles_wide <= tiles_sq ? kTileWide : kTileSquare) : kTileSmall;
-    if (mid_gemm_preferred(T, K, N, true)) cfg = kTileSplitK;
+    if (mid_gemm_preferred(T, K, N, true)) cfg = kTileMid;
     if (tile != kTileAuto) cfg = tile;   // parity tests name the tile themselves
     const bool raw = acc_out != nullptr;
     switch (cfg) {
@@ -382,7 +382,7 @@ int launch_ternary_gemm_f6f4(const int8_t* code_records, int64_t T, int64_t K, c
             return raw ? launch_cfg<2, 2, 2, 2, 4, true>(a, stream) : launch_cfg<2, 2, 2, 2, 4>(a, stream);
         case kTileWide:     // 512 features x 128 tokens, 4 x 1 waves of 128 x 128
             return raw ? launch_cfg<4, 1, 4, 4, 3, true>(a, stream) : launch_cfg<4, 1, 4, 4, 3>(a, stream);
-        case kTileSplitK: {
+        case kTileMid: {
             MidProblem m = {};
             m.codes = a.codes;
             m.packed = a.packed;

@@ -37,7 +37,7 @@ EXPORTS = [
 # exports for the test suite only (csrc/hbl_test_exports.h)
 TEST_EXPORTS = ["hbl_test_grouped_plan", "hbl_test_gemm_i32_tile", "hbl_test_forward_route"]
 ROUTES = ("fused", "stream", "mid", "prefill")
-TILE_SQUARE, TILE_SMALL, TILE_WIDE, TILE_SPLIT_K = 0, 1, 2, 3
+TILE_SQUARE, TILE_SMALL, TILE_WIDE, TILE_MID = 0, 1, 2, 3
 
 _lib = None
 
@@ -95,7 +95,7 @@ def lib():
         L.hbl_kv_dequant.argtypes = [vp, vp, i64, i64, ci, vp, ci, vp]
         ip = ctypes.POINTER(ci)
         L.hbl_test_grouped_plan.argtypes = [ctypes.POINTER(Problem), ci, ip, ip, ip, ip]
-        L.hbl_test_gemm_i32_tile.argtypes = [vp, ci, i64, i64, vp, i64, vp, ci, vp, sz, vp]
+        L.hbl_test_gemm_i32_tile.argtypes = [vp, ci, i64, i64, vp, i64, vp, ci, vp]
         L.hbl_test_forward_route.argtypes = [i64, i64, i64, ci, ci, ci, ci]
         L.hbl_gemm_i32_bf6.argtypes = [vp, i64, i64, vp, i64, vp, vp, sz, vp]
         L.hbl_bitlinear_forward_small.argtypes = [vp, ci, i64, i64, vp, i64, vp, i64, ci, f32, ci, vp, vp]
@@ -204,7 +204,7 @@ def alloc_workspace(T: int, K: int, N: int, bits: int, device="cuda") -> torch.T
 
 
 def _empty(x: torch.Tensor, shape, dtype: torch.dtype) -> torch.Tensor:
-    """A new plain tensor on x's device.  (``new_empty`` needs no device look-up, 0.5 us of a small call each, but gives a
+    """A new plain tensor on x's device.  (``new_empty`` takes 1.5 us where ``torch.empty(device=...)`` takes 1.7, but gives a
     subclass of ``torch.Tensor`` its own kind.)"""
     if type(x) is torch.Tensor:
         return x.new_empty(shape, dtype=dtype)
@@ -318,9 +318,8 @@ def gemm_i32_tile_for_tests(codes: torch.Tensor, code_form: int, Wq_packed: torc
         T, K = codes.shape
     _check_projection(T, K, N, Wq_packed, torch.empty(1), None)
     acc = torch.empty((T, N), dtype=torch.int32, device=codes.device)
-    partial = torch.empty(8 * T * N * 4 if tile == TILE_SPLIT_K else 16, dtype=torch.uint8, device=codes.device)
     _check(lib().hbl_test_gemm_i32_tile(_ptr(codes), code_form, T, K, _ptr(Wq_packed), N, _ptr(acc), tile,
-                                        _ptr(partial), partial.numel(), _stream()), "test_gemm_i32_tile")
+                                        _stream()), "test_gemm_i32_tile")
     return acc
 
 

@@ -480,7 +480,7 @@ def run_site(hbl, site, bits, sample_rows=None):
     y = fn(xd, packed, site.N, al_d, bits, EPS)
     codes, sd, cs = hbl.fwht_quant(xd, bits, site.hadamard, EPS)
     acc = hbl.gemm_i32(codes, packed, site.N)
-    # the forward call above ran the fp6 x fp4 kernel if INT4, T > 64, K >= 512: that kernel's own accumulators,
+    # the forward call above ran on the fp6 x fp4 matrix cores if INT4, T > 64, K >= 512: that kernel's own accumulators,
     # from the code records it reads, in the launch configuration the forward call takes for this shape
     acc6 = None
     if bits == 4 and site.T > 64 and site.K >= 512:
@@ -532,12 +532,11 @@ def test_configs_3_4_reduced_shapes(hbl, T, K, N):
 
 @pytest.mark.parametrize("T,K,N", [(300, 16384, 1056), (130, 8192, 2048), (513, 16384, 416)])
 def test_mid_size_batch_split_k(hbl, T, K, N):
-    """Between 65 tokens and about a thousand a long-K projection has few output tiles: the fp6 x fp4 GEMM then
-    splits K over workgroups and a reduction launch adds the int32 partial tiles.  Ragged T and N, splits of 8, 4
-    and 2; every output against the oracle."""
-    note(f"mid-size batch split-K T={T} K={K} N={N}")
+    """Between 65 tokens and about a thousand a long-K projection has few output tiles: the mid-size kernel then takes it
+    and cuts K over the waves of a workgroup.  Ragged T and N, 8 and 4 K groups; every output against the oracle."""
+    note(f"mid-size batch, K cut over waves T={T} K={K} N={N}")
     run_site(hbl, synth.shrink(synth.config_sites(4)[1], T=T, K=K, N=N), 4)
-    run_site(hbl, synth.shrink(synth.config_sites(4)[1], T=T, K=K, N=N), 8)     # the int8 kernel's split form
+    run_site(hbl, synth.shrink(synth.config_sites(4)[1], T=T, K=K, N=N), 8)     # the same on bytes
 
 
 def panel_rows(T, seed, panel=128):
@@ -736,8 +735,7 @@ def test_grouped_forms_beyond_16_tokens(hbl, shapes, bits):
 
 @pytest.mark.parametrize("T,K,N", [(300, 1024, 544), (129, 4096, 96), (513, 512, 1056)])
 def test_prefill_gemm_tiles_raw_accumulators(hbl, T, K, N):
-    """Every workgroup tile of both prefill GEMM kernels (256 x 256, 128 x 128, 512 x 128, and the fp6 x fp4
-    kernel's K cut over workgroups) on ragged shapes: the int32 accumulators, read straight out of the
+    """Every workgroup tile of both prefill GEMM kernels (256 x 256, 128 x 128, 512 x 128) and the mid-size kernel on ragged shapes: the int32 accumulators, read straight out of the
     kernel, against the oracle's integer contraction - every element, bit for bit."""
     note(f"prefill GEMM tiles, raw accumulators T={T} K={K} N={N}")
     rng = np.random.default_rng(T + K + N)
@@ -751,7 +749,7 @@ def test_prefill_gemm_tiles_raw_accumulators(hbl, T, K, N):
     packed = hbl.pack_ternary_2bit(torch.from_numpy(c).cuda())
     rec = torch.from_numpy(encode_bf6_records(q.astype(np.int32)).view(np.int8)).cuda()
     qd = torch.from_numpy(q).cuda()
-    for tile in (hbl.TILE_SQUARE, hbl.TILE_SMALL, hbl.TILE_WIDE, hbl.TILE_SPLIT_K):
+    for tile in (hbl.TILE_SQUARE, hbl.TILE_SMALL, hbl.TILE_WIDE, hbl.TILE_MID):
         got = hbl.gemm_i32_tile_for_tests(rec, hbl.CODES_BF6, packed, N, tile, T=T, K=K).cpu().numpy()
         assert np.array_equal(got, want), f"fp6 x fp4 kernel, tile {tile}"
     q8 = rng.integers(-128, 128, (T, K)).astype(np.int8)
@@ -790,8 +788,8 @@ def test_prefill_tiles_bf16_outputs(hbl, T, N, groups, bits, K):
 
 
 def test_f6f4_raw_accumulators_extreme_and_split_k_shapes(hbl):
-    """|acc| = 8 * 16384 = 2^17 out of the fp6 x fp4 kernel as an integer, and the mid-size-batch shapes on
-    which the forward call itself cuts K (8, 4 and 2 slices): raw accumulators against the oracle."""
+    """|acc| = 8 * 16384 = 2^17 out of the fp6 x fp4 matrix cores as an integer, on mid-size batches for which the forward
+    call cuts K over the waves of a workgroup (8 and 4 K groups): raw accumulators against the oracle."""
     note("f6f4 raw accumulators: extremes and the forward's own K cuts")
     rng = np.random.default_rng(17)
     for T, K, N in [(130, 16384, 64), (300, 16384, 1056), (130, 8192, 2048), (513, 16384, 416)]:
@@ -806,8 +804,8 @@ def test_f6f4_raw_accumulators_extreme_and_split_k_shapes(hbl):
         packed = hbl.pack_ternary_2bit(torch.from_numpy(c).cuda())
         rec = torch.from_numpy(encode_bf6_records(q.astype(np.int32)).view(np.int8)).cuda()
         assert np.array_equal(hbl.gemm_i32_bf6(rec, packed, N, T, K).cpu().numpy(), want), (T, K, N)
-        got = hbl.gemm_i32_tile_for_tests(rec, hbl.CODES_BF6, packed, N, hbl.TILE_SPLIT_K, T=T, K=K).cpu().numpy()
-        assert np.array_equal(got, want), (T, K, N, "split-K tile")
+        got = hbl.gemm_i32_tile_for_tests(rec, hbl.CODES_BF6, packed, N, hbl.TILE_MID, T=T, K=K).cpu().numpy()
+        assert np.array_equal(got, want), (T, K, N, "named tile")
 
 
 @pytest.mark.parametrize("T,K,N,groups,bits,hadamard", [
@@ -815,9 +813,9 @@ def test_f6f4_raw_accumulators_extreme_and_split_k_shapes(hbl):
     (17, 8192, 288, 1, 4, True), (64, 640, 96, 1, 8, False), (5, 16384, 64, 2, 4, True),
 ])
 def test_small_batch_split_k_path(hbl, T, K, N, groups, bits, hadamard):
-    """T <= 64 takes the split-K kernel pair (partial tiles + reduction): ragged T, N not a multiple of the
-    128-row workgroup tile, several scale groups, both code widths."""
-    note(f"split-K T={T} K={K} N={N} groups={groups} bits={bits} hadamard={hadamard}")
+    """Single calls of up to 64 tokens - one launch, weight streaming or the mid-size kernel - with ragged T, row counts that
+    are no multiple of a workgroup's tile, several scale groups, both code widths."""
+    note(f"small batch T={T} K={K} N={N} groups={groups} bits={bits} hadamard={hadamard}")
     site = synth.Site("s", T, K, N, hadamard=hadamard, groups=groups, outlier_frac=0.01, outlier_scale=30.0,
                       seed=T + K + N)
     rate, exact = run_site(hbl, site, bits)

@@ -41,8 +41,8 @@ def problem(hbl, name, T, K, N, hadamard, groups, seed, dtype=synth.BF16):
 
 
 def test_no_alloc_forward_matches_workspace_forward(hbl):
-    # a large problem first (split K range: partial tiles in the scratch), then smaller ones that reuse its
-    # scratch while the old contents are still there, then the large one again
+    # a large problem first, then smaller ones that reuse its scratch while the old contents are still there, then the large
+    # one again
     cases = [("a", 64, 16384, 1056, True, 1, 4, 101), ("b", 5, 4096, 288, False, 3, 4, 102),
              ("c", 33, 2048, 96, True, 1, 8, 103), ("d", 1, 512, 32, True, 1, 4, 104),
              ("a2", 64, 16384, 1056, True, 1, 4, 101), ("e", 16, 4096, 12288, False, 3, 4, 105)]
