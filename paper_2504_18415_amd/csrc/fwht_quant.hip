@@ -297,20 +297,23 @@ int launch_fwht_only(const void* x, int x_dtype, int64_t T, int64_t K, void* out
 #undef HBL_BIG
 }
 
-constexpr int64_t kFewRows = 320;   // about a row per CU
+// Large Hadamard rows: up to here one row per workgroup with the short-latency reductions, the row loop beyond.  Time of the
+// former against the latter (both input types and widths, with the norm and without): up to 320 rows 0.79 to 1.01 at every K.
+// K = 16384, of which two workgroups share a CU, 0.81 to 1.03 up to 512 rows, INT4 codes 1.01 to 1.11 from 576 on; K = 8192 0.85 to
+// 1.01 up to 1024 rows, 1.00 to 1.07 at 1536; K = 4096 0.94 to 1.00 up to 1536.  One line for all, below the first loss.
+constexpr int64_t kFewRows = 320;
+// The one-row-per-workgroup kernels: the short-latency form of the reductions up to here, the six shuffle rounds beyond.  Against
+// the latter: up to 4096 rows 0.85 to 1.01 (transformed rows of 2048 1.04 at 4096); at 5120 to 16384 rows still 0.82 to 1.00
+// for most lengths, but 0.98 to 1.04 for transformed rows of 1024 and 2048.
+constexpr int64_t kShortReductionRows = 4096;
 
 int launch_fwht_quant(const void* x, int x_dtype, int64_t T, int64_t K, int bits, float eps, bool hadamard,
                       int8_t* codes, float* s_dequant, int32_t* code_sum, int code_offset, hipStream_t stream,
                       const float* ln_gain, float ln_eps) {
     if (T == 0) return HBL_OK;
-    // (large Hadamard rows: one row per workgroup up to about a row per CU, the row loop beyond: 300 rows of 16384 18.4 -> 16.7 us
-    // per call, 600 rows 23.0 -> 23.3, so not there; 300 fp32 rows of 8192 13.2 -> 12.5)
     const RowParams rp = {eps, ln_gain, ln_eps, T <= kFewRows ? 1 : 0};
     if (code_offset == kCodesBf6 && (bits != 4 || K < 512)) return HBL_E_SHAPE;   // records need 8-element chunks
-    // The one-row-per-workgroup kernels: up to 4096 rows the chip holds most of them at once and a row's latency counts, so the
-    // reductions take the short-latency form (3001 rows of 3072 with the norm: 18.1 -> 17.2 us per call; 8000 rows of 2048: 21.7
-    // -> 22.0, so not there).
-    const RowParams row_rp = {eps, ln_gain, ln_eps, T <= 4096 ? 1 : 0};
+    const RowParams row_rp = {eps, ln_gain, ln_eps, T <= kShortReductionRows ? 1 : 0};
     if (!hadamard && !is_pow2(K)) return launch_generic(x, x_dtype, T, K, bits, row_rp, codes, s_dequant, code_sum, code_offset, stream);
     if (hadamard) {
         if (K == 4096) return dispatch_bigrow<12>(x, x_dtype, T, bits, rp, codes, s_dequant, code_sum, code_offset, stream);
