@@ -149,18 +149,22 @@ def test_binding_fails_loudly_without_library(monkeypatch, tmp_path):
         hbl.lib()
 
 
-def test_outputs_are_plain_tensors_whatever_the_input_is():
-    """Outputs and workspaces that the binding allocates: plain tensors, also for a Parameter or another subclass."""
+def test_outputs_are_plain_tensors_whatever_the_input_is(L, monkeypatch):
+    """Outputs that the binding allocates: plain tensors, also for a Parameter or another subclass."""
     torch = pytest.importorskip("torch")
     from paper_2504_18415_amd import hbl
 
     class Tagged(torch.Tensor):
         pass
 
-    x = torch.zeros((2, 4))
+    monkeypatch.setattr(hbl, "_dev_check", lambda *tensors: None)
+    monkeypatch.setattr(hbl, "_stream", lambda: 0)
+    x, packed = torch.zeros((2, 128)), torch.zeros(32 * 128 // 4 + 4 * 32, dtype=torch.uint8)
     for t in (x, torch.nn.Parameter(x), x.as_subclass(Tagged)):
-        y = hbl._empty(t, (3, 5), torch.bfloat16)
-        assert type(y) is torch.Tensor and y.shape == (3, 5) and y.dtype == torch.bfloat16 and not y.requires_grad
+        sizes = []
+        y = hbl._forward(lambda *args: sizes.append(args[-2]) or 0, "stub", t, packed, 32, torch.ones(1), 4, 1e-5, None, None)
+        assert type(y) is torch.Tensor and y.shape == (2, 32) and y.dtype == torch.bfloat16 and not y.requires_grad
+        assert sizes == [hbl.workspace_bytes(2, 128, 32, 4)]
 
 
 def test_small_batch_launch_plan(L):
