@@ -140,7 +140,7 @@ def bench_prefill(args, hbl, synth, torch, np):
         "launches_per_step": launches_per_step, "ms_fwht_quant": t_quant, "ms_gemm": t_gemm,
         "tops_end_to_end": ops / (ms_per_step * 1e-3) / 1e12,
         "tops_gemm": ops / (t_gemm * 1e-3) / 1e12,
-        # bytes the quantiser launch moves: bf16 in, code records out (0.75 byte per feature + padding, as stored), scales
+        # bytes the quantiser launch moves: bf16 in, code records out (0.75 byte per feature, as stored), scales
         "fwht_quant_bytes": 2.0 * T * K + hbl.code_bytes(T, K, hbl.CODES_BF6) + 4.0 * T,
         "int8_activations": {"ms_per_step": ms_int8, "TOPS": ops / (ms_int8 * 1e-3) / 1e12,
                              "frac_int8_mfma_peak": ops / (ms_int8 * 1e-3) / 1e12 / INT8_MFMA_PEAK_TOPS},
@@ -358,7 +358,7 @@ def bench_decode(args, hbl, synth, torch, np):
     return {"layers_cycled": layers, "weight_bytes_per_layer": w_bytes, "roofline": roofline,
             "launch": "one HIP graph of all layers; sequential = four forward calls per layer in model order "
                       "(one or two kernel nodes each), grouped = one hbl_bitlinear_forward_grouped call per layer "
-                      "(one quantiser launch, one weight-streaming GEMM launch)",
+                      "(one quantiser launch, one GEMM launch: weight streaming, from 33 tokens on the mid-size kernel)",
             "batch": res}
 
 

@@ -107,7 +107,7 @@ int hbl_unpack_ternary_2bit(const void* packed, int64_t N, int64_t K, int8_t* co
  * ------------------------------------------------------------------------- */
 
 /* Device scratch needed by the two forward calls (activation codes, per-token
- * dequantisation scale, room for int32 slices of a K range). */
+ * dequantisation scale, room for int32 slices of a K range, which only some calls of 17 to 32 tokens write). */
 size_t hbl_workspace_bytes(int64_t T, int64_t K, int64_t N, int bits);
 
 /*
@@ -127,6 +127,8 @@ size_t hbl_workspace_bytes(int64_t T, int64_t K, int64_t N, int bits);
  *              N/n_scale_groups must be a multiple of 32.
  *   y          [T, N] bf16 out; must not overlap x or the workspace
  *   workspace  at least hbl_workspace_bytes(T, K, N, bits), 256-byte aligned
+ * INT4 with 17 to 32 tokens, 8192 <= K < 12288 and more than 32768 output rows: the K range may be split over
+ * workgroups, counted as described at hbl_bitlinear_forward_grouped.
  */
 int hbl_hbitlinear_forward(const void* x, int x_dtype, int64_t T, int64_t K, const void* Wq_packed,
                            int64_t N, const float* w_scales, int64_t n_scale_groups, int bits,
@@ -182,10 +184,12 @@ int hbl_ln_bitlinear_forward(const void* x, int x_dtype, int64_t T, int64_t K, c
  * bit-identical to hbl_hbitlinear_forward / hbl_plain_bitlinear_forward on that problem alone.
  * Meant for small batches (decode), where one projection's launches are too short to keep HBM
  * busy: when every T <= 64, n_problems <= 8 and all problems share bits and x_dtype, the rows of
- * all problems are quantised by one launch and all packed weights are streamed by one launch
- * (with 17 to 32 tokens and more output rows than the chip holds at once a K range may be split over
- * workgroups: the last of them to finish adds the slices, counted in a small static device array of
- * which overlapping calls on one GPU take different slots, 128 in all); otherwise the problems run one after the other through the calls above.
+ * all problems are quantised by one launch and multiplied by one launch, also where short rows (bytes)
+ * and long ones (records) meet in a group.  With 17 to 32 tokens and more output rows than the chip holds
+ * at once a K range may be split over workgroups: the last of them to finish adds the slices, counted in a
+ * small static device array.  Calls take its 128 slots in turn, so overlapping calls on one GPU count in
+ * different ones; a call captured into a graph keeps the slot of its capture.  Otherwise the problems run
+ * one after the other through the calls above.
  *   problems   host array, read during the call only; fields as the arguments of the forward
  *              calls above (hadamard != 0 selects H-BitLinear, eps is shared)
  *   workspace  device, >= hbl_grouped_workspace_bytes(problems, n_problems), 256-byte aligned
@@ -258,10 +262,12 @@ int hbl_gemm_i32(const int8_t* codes, int64_t T, int64_t K, const void* Wq_packe
                  int32_t* acc, void* stream);
 
 /*
- * The same contraction on the fp6 x fp4 prefill kernel, the one every INT4 forward call with T > 64 and
- * K >= 512 runs: acc[t][o] = sum_k q[t][k] * c[o][k] as int32 [T, N], read out of that kernel's fp32
- * accumulators (exact integers) with no dequantisation, in the launch configuration (workgroup tile,
- * K cut over the waves of a workgroup at mid-size batches) hbl_hbitlinear_forward takes for the same T, K, N.
+ * The same contraction on the fp6 x fp4 matrix cores: acc[t][o] = sum_k q[t][k] * c[o][k] as int32 [T, N],
+ * read out of the kernel's fp32 accumulators (exact integers) with no dequantisation.  From 17 tokens on it
+ * runs the kernel and launch configuration (prefill kernel and workgroup tile, or the mid-size kernel with K
+ * cut over the waves of a workgroup) that hbl_hbitlinear_forward takes for the same T, K, N at bits = 4; up
+ * to 16 tokens, and with 17 to 32 where the forward call streams a large weight matrix, the forward call
+ * runs other kernels and this one the mid-size kernel.
  *   code_records  [T, K] bytes of HBL_CODES_BF6 records as written by hbl_fwht_quant (K >= 512)
  *   workspace     device, >= hbl_workspace_bytes(T, K, N, 4), 256-byte aligned (not touched by the
  *                 present kernels)
@@ -274,11 +280,12 @@ int hbl_gemm_i32_bf6(const void* code_records, int64_t T, int64_t K, const void*
  * two launches the forward calls make, on caller-held intermediates.
  *   codes [T, K] int8, s_dequant [T] fp32, code_sum [T] int32: as written by hbl_fwht_quant with
  *   the same code_offset;  y [T, N] bf16 out
- * A forward call with T > 16 is hbl_fwht_quant(x, ..., hadamard, code_offset) into the workspace followed by
+ * A forward call with T > 32 is hbl_fwht_quant(x, ..., hadamard, code_offset) into the workspace followed by
  * this call, with code_offset = HBL_CODES_BF6 for INT4 activations with K >= 512 (fp6 x fp4 matrix cores),
- * HBL_CODES_UINT4_PLUS8 for INT4 on shorter rows, HBL_CODES_INT8 for INT8 activations (up to 16 tokens the
- * weight-streaming kernel runs on the same code forms, up to 4 with INT4 one launch does both).  code_sum is not read (the packed weights are signed) and
- * may be NULL.
+ * HBL_CODES_UINT4_PLUS8 for INT4 on shorter rows, HBL_CODES_INT8 for INT8 activations.  Smaller batches give
+ * the same results, some by other kernels on the same code forms: up to 32 tokens the weight-streaming
+ * kernel, up to 4 with INT4 one launch for both steps.  code_sum is not read (the packed weights are
+ * signed) and may be NULL.
  */
 int hbl_gemm_dequant_bf16(const int8_t* codes, int code_offset, const float* s_dequant,
                           const int32_t* code_sum, int64_t T, int64_t K, const void* Wq_packed, int64_t N,

@@ -148,14 +148,14 @@ int forward(const void* x, int x_dtype, int64_t T, int64_t K, const void* Wq_pac
     return launch_ternary_gemm(ws.codes, code_form, T, K, Wq_packed, N, ws.s_dequant, w_scales, groups, y, nullptr, s);
 }
 
-// Workspace region of one problem of a grouped call: large enough for the grouped launches (partials
-// for the largest K split they may choose) and for the stand-alone forward call.
+// Workspace region of one problem of a grouped call: large enough for the grouped launches (slices for the
+// largest K split of the shared form) and for the stand-alone forward call.
 size_t group_region_bytes(const hbl_problem& q, int tile_rows) {
     if (q.T <= 0 || q.K <= 0 || q.N <= 0) return 256;
     return carve_workspace(nullptr, q.T, q.K, q.N, true, tile_rows).bytes;
 }
-// Token rows of the slices the small-batch kernel keeps for a group: set by the largest member that takes that
-// kernel (0: at most 16 tokens everywhere, no slices).
+// Token rows of the slices in a group's regions, set by its largest member of at most 64 tokens (0: at most 16 tokens
+// everywhere, no slices).  The shared form writes 32; 64 is room that no launch uses, in sizes that callers hold.
 int group_tile_rows(const hbl_problem* problems, int n) {
     int64_t max_t = 0;
     for (int i = 0; i < n; ++i)

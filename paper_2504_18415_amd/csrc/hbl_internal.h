@@ -94,9 +94,10 @@ inline bool is_pow2(int64_t v) { return v > 0 && (v & (v - 1)) == 0; }
 inline bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 inline size_t round_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
-// Slices of int32 partial sums that the forward workspace has room for.  One launch keeps such slices in memory: the shared
-// form of the weight-streaming kernel (17 to 32 tokens of a large group), at most kMaxDecodeSplit of them; the single calls
-// cut K inside a workgroup.  The sizes that callers are told for single calls stay what they were.
+// Slices of int32 partial sums that the forward workspace has room for.  One launch keeps such slices in memory, at most
+// kMaxDecodeSplit of them: the shared form of the weight-streaming kernel, 17 to 32 tokens (groups that the mid-size kernel does
+// not take; single calls of records with more than 32768 output rows and 8192 <= K < 12288).  Every other launch cuts K inside
+// a workgroup and leaves the room unused; callers hold workspaces of the sizes told here, so these do not depend on the route.
 constexpr int kMaxDecodeSplit = 4;
 inline int workspace_slices(int64_t T, int64_t K, int64_t N) {
     const int64_t nkb = K / 128;
@@ -228,7 +229,7 @@ struct DecodeProblem {
     const int32_t* w_row_sum;  // [N]
     const float* w_scales;     // [groups]
     uint16_t* y;               // [T, N] bf16
-    int32_t* partial;          // [ksplit][T][N] when the K range is split over workgroups, else unused
+    int32_t* partial;          // the slices (whole tiles of 32 tokens x 128 rows) when the K range is split over workgroups, else unused
     int T, K, N;
     int rows_per_group;
     int code_offset;           // int8 path: stored code byte = q + code_offset

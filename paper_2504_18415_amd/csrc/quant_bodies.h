@@ -111,7 +111,8 @@ __device__ __forceinline__ float wave_max_dpp(float m) {
 }
 // Form 2, six xor-shuffle rounds through the LDS crossbar: long dependent latency but no vector-ALU work.
 // A launch that keeps every SIMD busy with other waves runs faster with these (5 % on 8192 rows of 16384); a
-// launch of a few rows runs faster with form 1 (1.5 us per decode layer).  `few_rows` is uniform.
+// launch of a few rows runs faster with form 1 (1.5 us per decode layer; the limits: launch_fwht_quant).
+// `few_rows` is uniform.
 __device__ __forceinline__ double wave_sum(double s, int few_rows) {
     if (few_rows) return wave_sum_dpp(s);
 #pragma unroll

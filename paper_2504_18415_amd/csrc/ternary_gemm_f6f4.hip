@@ -365,8 +365,8 @@ int launch_ternary_gemm_f6f4(const int8_t* code_records, int64_t T, int64_t K, c
     a.code_offset = 0;      // signed operands: no correction terms
     // Too few tiles for the chip: the mid-size kernel, which cuts K over the waves of a workgroup.
     // Workgroup tile: 64 K outputs either way (the 256 accumulator registers of four waves).  512 features x 128
-    // tokens moves 32 KB per 128-feature stage through L2 and LDS (16 KB of codes + 16 KB of packed weights) against
-    // 40 KB for 256 x 256 (32 + 8): measured 4 % faster on the GEMM at N = 4096 and 12288, equal at N = 32768.  The
+    // tokens moves 28 KB per 128-feature stage through L2 and LDS (12 KB of codes + 16 KB of packed weights) against
+    // 32 KB for 256 x 256 (24 + 8): measured 4 % faster on the GEMM at N = 4096 and 12288, equal at N = 32768.  The
     // square tile stays for shapes the wide one pads more; below ~180 tiles (256 CUs) the small tile takes over
     // (192 big tiles measured 8 % faster than 768 tiles of 128 x 128).
     const int64_t tiles_sq = (int64_t)((N + 255) / 256) * ((T + 255) / 256);
