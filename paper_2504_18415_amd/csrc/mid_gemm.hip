@@ -7,13 +7,13 @@
 // LDS in 1 KiB pieces.  The groups' accumulators (exact integers) are added through LDS at the end, on the way to whole-line
 // stores: no partial tiles in memory and no second launch.
 // Bound by the copies' trip through L2 and LDS (64 / 128 bytes per clock and CU) behind the start-up of the launch.  Whole
-// call, both launches, against what ran before: 128 x 128 tiles above 64 tokens, with K >= 8192 cut over workgroups and a
-// reduction launch: 300 tokens x 8192 -> 3072 28.8 -> 19.4 us, 97 x 11008 -> 4096 26.6 -> 17.0, 200 x 8192 -> 2048 21.8 ->
-// 13.4, 65 x 4096 -> 4096 16.3 -> 9.7, 512 x 16384 -> 4096 40 -> 37, 4000 x 16384 -> 512 89 -> 79.  The shared form of the
-// weight-streaming kernel up to 64: 64 x 16384 -> 4096 22.6 -> 14.4, 64 x 11008 -> 4096 23.7 -> 12.7, 17 x 4096 -> 4096
-// 10.6 -> 9.1, 32 x 4096 -> 32768 13.5 -> 12.1 us.  (Up to 16 tokens that kernel's streaming form is faster: 8 x 4096 ->
-// 4096 7.2 us against 9.0; and its shared form up to 32 where there are many output rows: decode_shared_preferred.)  INT8 activations: 64 x 16384 -> 4096 21.4 -> 15.2, 24 x 8192 -> 3072 13.2 -> 8.9, 97 x 11008 ->
-// 4096 35.1 -> 19.0, 128 x 4096 -> 4096 23.0 -> 10.6, 300 x 8192 -> 3072 32.4 -> 19.7 us.
+// call, both launches (transformed where K is a power of two), against what it replaced: 128 x 128 tiles above 64 tokens, with
+// K >= 8192 cut over workgroups and a reduction launch: 300 tokens x 8192 -> 3072 27.9 -> 18.2 us, 97 x 11008 -> 4096 25.6 ->
+// 15.8, 200 x 8192 -> 2048 23.8 -> 15.2, 65 x 4096 -> 4096 17.4 -> 10.7, 512 x 16384 -> 4096 45.5 -> 42.2, 4000 x 16384 -> 512
+// 95.8 -> 84.1.  The shared form of the weight-streaming kernel up to 64: 64 x 16384 -> 4096 23.6 -> 15.1, 64 x 11008 -> 4096
+// 22.6 -> 11.9, 17 x 4096 -> 4096 12.0 -> 8.9, 32 x 4096 -> 32768 14.9 -> 13.4 (beyond that many rows: decode_shared_preferred).
+// INT8 activations: 64 x 16384 -> 4096 24.4 -> 16.9, 24 x 8192 -> 3072 15.2 -> 11.2, 97 x 11008 -> 4096 33.7 -> 16.8, 128 x
+// 4096 -> 4096 24.4 -> 11.9, 300 x 8192 -> 3072 34.9 -> 22.1 us.
 #include <atomic>
 #include <type_traits>
 
