@@ -19,7 +19,7 @@
 // the wave bits with the low r bits through LDS once, then run in registers.
 #include <atomic>
 
-#include "quant_bodies.h"
+#include "large_rows.h"
 
 namespace hbl {
 namespace {
@@ -83,82 +83,53 @@ int launch_generic(const void* x, int x_dtype, int64_t T, int64_t K, int bits, R
 
 // ---------------------------------------------------------------------------------------------
 
-// Each workgroup walks rows blockIdx.x, blockIdx.x + gridDim.x, ...; the grid is sized to what the chip holds
-// at once (the LDS row buffer allows only a few workgroups per CU), and the next row's loads are issued
-// under the tail of the current row's arithmetic so that their latency is not exposed once per row.  The
-// compiler also moves the ~100 per-thread LDS and global address computations out of the row loop and keeps
-// them in registers (about 200 VGPRs in all): measured 7-20 % faster than recomputing them per row, and the
-// LDS row buffer limits the workgroups per CU before the registers do.
-// FEW: at most kFewRows rows - one row per workgroup and the short-latency reductions.
-template <int LOG2K, int BITS, bool BF16, bool BF6OUT, bool NORM, bool FEW>
-__global__ __launch_bounds__((1 << LOG2K) / 64, 2) void fwht_quant_bigrow_kernel(
-    const void* __restrict__ x, int64_t T, int8_t* __restrict__ codes, float* __restrict__ s_dequant,
+// Rows of 8192 and 16384: 16 values per thread up to here, 32 beyond.  While every row has a CU to itself, twice the waves finish
+// it sooner, although one or two more stages run between lanes (64 rows, INT4 records: 8192 4.3 -> 4.0 us, 16384 5.35 ->
+// 5.25); from 257 rows on the fewer instructions count (257 rows of 16384 with the norm 9.4 -> 8.9; 512 of 8192 5.9 -> 5.8).
+constexpr int64_t kSixteenValueRows = 256;
+
+// Transformed rows of 2048 features and more (large_rows.h): one row per workgroup.
+template <int LOG2K, int R, int BITS, bool BF16, bool BF6OUT, bool NORM>
+__global__ __launch_bounds__((1 << LOG2K) >> R) void fwht_quant_bigrow_kernel(
+    const void* __restrict__ x, int64_t first_row, int8_t* __restrict__ codes, float* __restrict__ s_dequant,
     int32_t* __restrict__ code_sum, RowParams rp, int code_offset) {
-    int64_t row = blockIdx.x;
-    BigRowRaw<BF16> cur;
     extern __shared__ __attribute__((aligned(16))) float row_lds[];   // K floats
-    if constexpr (FEW && kRowThroughLds<LOG2K, BF16>) {
-        bigrow_load_lds<LOG2K, BF16>(x, row, threadIdx.x, reinterpret_cast<char*>(row_lds), cur);
-    } else {
-        bigrow_load<LOG2K, BF16>(x, row, threadIdx.x, cur);
-    }
-    if constexpr (BITS == 0 || FEW) {   // (transform only: the row loop would cost it registers it lacks)
-        fwht_quant_bigrow_body<LOG2K, BITS, BF16, BF6OUT, NORM>(row, threadIdx.x, cur, row_lds, codes, s_dequant, code_sum, rp,
-                                                                code_offset);
-        return;
-    }
-    for (;;) {
-        const int64_t next = row + gridDim.x;
-        BigRowRaw<BF16> ahead;
-        const uint32_t tid = threadIdx.x;
-        fwht_quant_bigrow_body<LOG2K, BITS, BF16, BF6OUT, NORM, true>(
-            row, tid, cur, row_lds, codes, s_dequant, code_sum, rp, code_offset,
-            [&]() { if (next < T) bigrow_load<LOG2K, BF16>(x, next, tid, ahead); });
-        if (next >= T) break;
-        cur = ahead;
-        row = next;
-    }
+    const int64_t row = first_row + blockIdx.x;
+    LargeRowRaw<R, BF16> raw;
+    large_row_load<LOG2K, R, BF16>(x, row, threadIdx.x, raw);
+    large_row_body<LOG2K, R, BITS, BF16, BF6OUT, NORM>(row, threadIdx.x, raw, row_lds, codes, s_dequant, code_sum, rp, code_offset);
 }
 
-template <int LOG2K, int BITS, bool BF16, bool BF6OUT, bool NORM, bool FEW>
+template <int LOG2K, int R, int BITS, bool BF16, bool BF6OUT, bool NORM>
 int launch_bigrow_form(const void* x, int64_t T, int8_t* codes, float* s_dequant, int32_t* code_sum, RowParams rp,
-                       int code_offset, hipStream_t stream);
+                       int code_offset, hipStream_t stream) {
+    using L = LargeRow<LOG2K, R>;
+    constexpr size_t lds = sizeof(float) * L::K;
+    auto kern = fwht_quant_bigrow_kernel<LOG2K, R, BITS, BF16, BF6OUT, NORM>;
+    static std::atomic<uint64_t> lds_allowed{0};   // per instantiation: devices already set up
+    if (const int rc = allow_dynamic_lds(kern, lds, lds_allowed); rc != HBL_OK) return rc;
+    constexpr int64_t most = (int64_t)1 << 22;   // rows per launch: a grid has fewer than 2^32 threads
+    for (int64_t first = 0; first < T; first += most)
+        launch_kernel("fwht_quant_bigrow_kernel", kern, dim3((unsigned)(T - first < most ? T - first : most)), dim3(L::NT), lds, stream,
+                      x, first, codes, s_dequant, code_sum, rp, code_offset);
+    return after_launch();
+}
 
 template <int LOG2K, int BITS, bool BF16, bool BF6OUT = false>
 int launch_bigrow(const void* x, int64_t T, int8_t* codes, float* s_dequant, int32_t* code_sum, RowParams rp,
                   int code_offset, hipStream_t stream) {
-    if constexpr (BITS != 0) {
-        const bool norm = rp.ln_gain != nullptr;
-        if (rp.few_rows)
-            return norm ? launch_bigrow_form<LOG2K, BITS, BF16, BF6OUT, true, true>(x, T, codes, s_dequant, code_sum, rp,
-                                                                                    code_offset, stream)
-                        : launch_bigrow_form<LOG2K, BITS, BF16, BF6OUT, false, true>(x, T, codes, s_dequant, code_sum, rp,
-                                                                                     code_offset, stream);
-        if (norm)
-            return launch_bigrow_form<LOG2K, BITS, BF16, BF6OUT, true, false>(x, T, codes, s_dequant, code_sum, rp,
-                                                                              code_offset, stream);
+    auto launch = [&](auto r_tag) {
+        constexpr int R = decltype(r_tag)::value;
+        if constexpr (BITS != 0) {
+            if (rp.ln_gain != nullptr)
+                return launch_bigrow_form<LOG2K, R, BITS, BF16, BF6OUT, true>(x, T, codes, s_dequant, code_sum, rp, code_offset, stream);
+        }
+        return launch_bigrow_form<LOG2K, R, BITS, BF16, BF6OUT, false>(x, T, codes, s_dequant, code_sum, rp, code_offset, stream);
+    };
+    if constexpr (LOG2K >= 13) {
+        if (T > kSixteenValueRows) return launch(std::integral_constant<int, 5>{});
     }
-    return launch_bigrow_form<LOG2K, BITS, BF16, BF6OUT, false, false>(x, T, codes, s_dequant, code_sum, rp, code_offset,
-                                                                       stream);
-}
-
-template <int LOG2K, int BITS, bool BF16, bool BF6OUT, bool NORM, bool FEW>
-int launch_bigrow_form(const void* x, int64_t T, int8_t* codes, float* s_dequant, int32_t* code_sum, RowParams rp,
-                       int code_offset, hipStream_t stream) {
-    constexpr int K = 1 << LOG2K;
-    constexpr size_t lds = sizeof(float) * K;
-    auto kern = fwht_quant_bigrow_kernel<LOG2K, BITS, BF16, BF6OUT, NORM, FEW>;
-    static std::atomic<uint64_t> lds_allowed{0};   // per instantiation: devices already set up
-    if (const int rc = allow_dynamic_lds(kern, lds, lds_allowed); rc != HBL_OK) return rc;
-    int grid = (int)T;   // one row per workgroup ...
-    if constexpr (BITS != 0 && !FEW) {   // ... or as many workgroups as the chip holds at once, walking the rows
-        static std::atomic<int> resident[64];
-        if (const int rc = resident_workgroups(kern, K / 64, lds, resident, &grid); rc != HBL_OK) return rc;
-        if ((int64_t)grid > T) grid = (int)T;
-    }
-    launch_kernel("fwht_quant_bigrow_kernel", kern, dim3((unsigned)grid), dim3(K / 64), lds, stream, x, T, codes, s_dequant, code_sum, rp,
-                       code_offset);
-    return after_launch();
+    return launch(std::integral_constant<int, 4>{});
 }
 
 template <int LOG2K>
@@ -174,8 +145,7 @@ int dispatch_bigrow(const void* x, int x_dtype, int64_t T, int bits, RowParams r
               : launch_bigrow<LOG2K, 4, false>(x, T, codes, s_dequant, code_sum, rp, code_offset, stream);
 }
 
-// WITH_H = false: rows of 4096 and more, whose transform belongs to the all-register kernel above - only the
-// plain quantiser is compiled from this body for them.
+// WITH_H = false: rows of 2048 and more, whose transform belongs to the kernel above - only the plain quantiser is compiled from this body for them.
 template <int LOG2K, int W, bool WITH_H = true>
 int dispatch(const void* x, int x_dtype, int64_t T, int bits, RowParams rp, bool hadamard, int8_t* codes,
              float* s_dequant, int32_t* code_sum, int code_offset, hipStream_t stream) {
@@ -280,14 +250,14 @@ int launch_fwht_only(const void* x, int x_dtype, int64_t T, int64_t K, void* out
                   : launch_one<L2K, 1, 0, false, true>(x, T, o, nullptr, nullptr, RowParams{0.0f, nullptr, 0.0f, 0}, out_dtype, stream);
 #define HBL_BIG(L2K)                                                                                             \
     case 1 << L2K:                                                                                               \
-        return bf ? launch_bigrow<L2K, 0, true, false>(x, T, o, nullptr, nullptr, RowParams{0.0f, nullptr, 0.0f, 0}, out_dtype, stream)       \
-                  : launch_bigrow<L2K, 0, false, false>(x, T, o, nullptr, nullptr, RowParams{0.0f, nullptr, 0.0f, 0}, out_dtype, stream);
+        return bf ? launch_bigrow<L2K, 0, true>(x, T, o, nullptr, nullptr, RowParams{0.0f, nullptr, 0.0f, 0}, out_dtype, stream)        \
+                  : launch_bigrow<L2K, 0, false>(x, T, o, nullptr, nullptr, RowParams{0.0f, nullptr, 0.0f, 0}, out_dtype, stream);
     switch (K) {
         HBL_SMALL(7)
         HBL_SMALL(8)
         HBL_SMALL(9)
         HBL_SMALL(10)
-        HBL_SMALL(11)
+        HBL_BIG(11)
         HBL_BIG(12)
         HBL_BIG(13)
         HBL_BIG(14)
@@ -297,38 +267,33 @@ int launch_fwht_only(const void* x, int x_dtype, int64_t T, int64_t K, void* out
 #undef HBL_BIG
 }
 
-// Large Hadamard rows: up to here one row per workgroup with the short-latency reductions, the row loop beyond.  Time of the
-// former against the latter (both input types and widths, with the norm and without): up to 320 rows 0.79 to 1.01 at every K.
-// K = 16384, of which two workgroups share a CU, 0.81 to 1.03 up to 512 rows, INT4 codes 1.01 to 1.11 from 576 on; K = 8192 0.85 to
-// 1.01 up to 1024 rows, 1.00 to 1.07 at 1536; K = 4096 0.94 to 1.00 up to 1536.  One line for all, below the first loss.
-constexpr int64_t kFewRows = 320;
-// The one-row-per-workgroup kernels: the short-latency form of the reductions up to here, the six shuffle rounds beyond.  Against
-// the latter: up to 4096 rows 0.85 to 1.01 (transformed rows of 2048 1.04 at 4096); at 5120 to 16384 rows still 0.82 to 1.00
-// for most lengths, but 0.98 to 1.04 for transformed rows of 1024 and 2048.
+// The kernels of one wave or more per row (transformed rows of up to 1024, plain rows): the short-latency form of the reductions
+// up to here, the six shuffle rounds beyond.  Against the latter: up to 4096 rows 0.85 to 1.01; at 5120 to 16384 rows still
+// 0.82 to 1.00 for most lengths, but 0.98 to 1.04 for transformed rows of 1024.
 constexpr int64_t kShortReductionRows = 4096;
 
 int launch_fwht_quant(const void* x, int x_dtype, int64_t T, int64_t K, int bits, float eps, bool hadamard,
                       int8_t* codes, float* s_dequant, int32_t* code_sum, int code_offset, hipStream_t stream,
                       const float* ln_gain, float ln_eps) {
     if (T == 0) return HBL_OK;
-    const RowParams rp = {eps, ln_gain, ln_eps, T <= kFewRows ? 1 : 0};
     if (code_offset == kCodesBf6 && (bits != 4 || K < 512)) return HBL_E_SHAPE;   // records need 8-element chunks
-    const RowParams row_rp = {eps, ln_gain, ln_eps, T <= kShortReductionRows ? 1 : 0};
-    if (!hadamard && !is_pow2(K)) return launch_generic(x, x_dtype, T, K, bits, row_rp, codes, s_dequant, code_sum, code_offset, stream);
+    const RowParams rp = {eps, ln_gain, ln_eps, T <= kShortReductionRows ? 1 : 0};
+    if (!hadamard && !is_pow2(K)) return launch_generic(x, x_dtype, T, K, bits, rp, codes, s_dequant, code_sum, code_offset, stream);
     if (hadamard) {
+        if (K == 2048) return dispatch_bigrow<11>(x, x_dtype, T, bits, rp, codes, s_dequant, code_sum, code_offset, stream);
         if (K == 4096) return dispatch_bigrow<12>(x, x_dtype, T, bits, rp, codes, s_dequant, code_sum, code_offset, stream);
         if (K == 8192) return dispatch_bigrow<13>(x, x_dtype, T, bits, rp, codes, s_dequant, code_sum, code_offset, stream);
         if (K == 16384) return dispatch_bigrow<14>(x, x_dtype, T, bits, rp, codes, s_dequant, code_sum, code_offset, stream);
     }
     switch (K) {
-        case 128:   return dispatch<7, 1>(x, x_dtype, T, bits, row_rp, hadamard, codes, s_dequant, code_sum, code_offset, stream);
-        case 256:   return dispatch<8, 1>(x, x_dtype, T, bits, row_rp, hadamard, codes, s_dequant, code_sum, code_offset, stream);
-        case 512:   return dispatch<9, 1>(x, x_dtype, T, bits, row_rp, hadamard, codes, s_dequant, code_sum, code_offset, stream);
-        case 1024:  return dispatch<10, 1>(x, x_dtype, T, bits, row_rp, hadamard, codes, s_dequant, code_sum, code_offset, stream);
-        case 2048:  return dispatch<11, 1>(x, x_dtype, T, bits, row_rp, hadamard, codes, s_dequant, code_sum, code_offset, stream);
-        case 4096:  return dispatch<12, 2, false>(x, x_dtype, T, bits, row_rp, hadamard, codes, s_dequant, code_sum, code_offset, stream);
-        case 8192:  return dispatch<13, 4, false>(x, x_dtype, T, bits, row_rp, hadamard, codes, s_dequant, code_sum, code_offset, stream);
-        case 16384: return dispatch<14, 4, false>(x, x_dtype, T, bits, row_rp, hadamard, codes, s_dequant, code_sum, code_offset, stream);
+        case 128:   return dispatch<7, 1>(x, x_dtype, T, bits, rp, hadamard, codes, s_dequant, code_sum, code_offset, stream);
+        case 256:   return dispatch<8, 1>(x, x_dtype, T, bits, rp, hadamard, codes, s_dequant, code_sum, code_offset, stream);
+        case 512:   return dispatch<9, 1>(x, x_dtype, T, bits, rp, hadamard, codes, s_dequant, code_sum, code_offset, stream);
+        case 1024:  return dispatch<10, 1>(x, x_dtype, T, bits, rp, hadamard, codes, s_dequant, code_sum, code_offset, stream);
+        case 2048:  return dispatch<11, 1, false>(x, x_dtype, T, bits, rp, hadamard, codes, s_dequant, code_sum, code_offset, stream);
+        case 4096:  return dispatch<12, 2, false>(x, x_dtype, T, bits, rp, hadamard, codes, s_dequant, code_sum, code_offset, stream);
+        case 8192:  return dispatch<13, 4, false>(x, x_dtype, T, bits, rp, hadamard, codes, s_dequant, code_sum, code_offset, stream);
+        case 16384: return dispatch<14, 4, false>(x, x_dtype, T, bits, rp, hadamard, codes, s_dequant, code_sum, code_offset, stream);
         default:    return HBL_E_SHAPE;
     }
 }

@@ -252,6 +252,14 @@ __device__ __forceinline__ float rms_factor(double ss, double* red, int lane, in
     return (float)(1.0 / sqrt(ss / (double)K + (double)ln_eps));
 }
 
+// Outputs of the transform alone leave with the non-temporal hint: written once and not read by the kernel, they need not
+// stay in L2 until the launch ends and has to write them back.  4096 rows of 4096, bf16 -> fp32, 16.0 -> 14.0 us; 2048 of 2048
+// fp32 6.0 -> 4.9.
+__device__ __forceinline__ void store_stream16(void* dst, uint4 val) {
+    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+    __builtin_nontemporal_store((u32x4){val.x, val.y, val.z, val.w}, reinterpret_cast<u32x4*>(dst));
+}
+
 // Transform-only output (BITS == 0 in the bodies below): N consecutive values of x_r as fp32 or, rounded
 // to nearest even, as bf16.
 template <int N>
@@ -270,7 +278,7 @@ __device__ __forceinline__ void store_xr(void* out, int out_dtype, int64_t elem,
         else {
 #pragma unroll
             for (int i = 0; i < N / 8; ++i)
-                reinterpret_cast<uint4*>(dst)[i] = make_uint4(h[4 * i], h[4 * i + 1], h[4 * i + 2], h[4 * i + 3]);
+                store_stream16(reinterpret_cast<uint4*>(dst) + i, make_uint4(h[4 * i], h[4 * i + 1], h[4 * i + 2], h[4 * i + 3]));
         }
     } else {
         float* dst = static_cast<float*>(out) + elem;
@@ -278,7 +286,7 @@ __device__ __forceinline__ void store_xr(void* out, int out_dtype, int64_t elem,
         else {
 #pragma unroll
             for (int i = 0; i < N / 4; ++i)
-                reinterpret_cast<float4*>(dst)[i] = make_float4(v[4 * i], v[4 * i + 1], v[4 * i + 2], v[4 * i + 3]);
+                store_stream16(reinterpret_cast<float4*>(dst) + i, make_uint4(as_u(v[4 * i]), as_u(v[4 * i + 1]), as_u(v[4 * i + 2]), as_u(v[4 * i + 3])));
         }
     }
 }

@@ -1016,6 +1016,33 @@ def test_ln_quantiser_rows_walked_by_resident_workgroups(hbl, K, T, dtype):
     assert np.array_equal(sd.cpu().numpy(), s4) and np.array_equal(cs.cpu().numpy(), c4.astype(np.int32).sum(1))
 
 
+@pytest.mark.parametrize("K,T", [(2048, 300), (4096, 3), (8192, 256), (8192, 257), (16384, 256), (16384, 257)])
+@pytest.mark.parametrize("dtype", [synth.BF16, synth.F32])
+def test_large_rows_on_both_sides_of_the_split(hbl, K, T, dtype):
+    """Transformed rows of 2048 features and more, 16 and 32 values per thread (the line is at 256 rows of 8192 and 16384): codes
+    in every form with the norm and without, and the transform alone.  One row is constant, so that all but one of its
+    transformed values cancel: they are +0 in the oracle's order, and no byte of the outputs depends on a sign carried by a lane."""
+    note(f"large rows K={K} T={T} {dtype}")
+    site = synth.Site("a", T, K, 32, hadamard=True, x_dtype=dtype, outlier_frac=0.01, outlier_scale=30.0, seed=7 * K + T)
+    x = synth.make_x(site)
+    x[1] = x[1, 5]
+    g = ln_gain_for(K, T)
+    xd, gd = dev_x(x), torch.from_numpy(g).cuda()
+    for norm in (False, True):
+        xn = O.rmsnorm(x, g, 1e-6) if norm else x
+        for bits, form in ((4, hbl.CODES_BF6), (4, 8), (8, 0)):
+            want, s = O.fwht_quant(xn, bits, hadamard=True, eps=EPS)
+            c, sd, cs = hbl.ln_fwht_quant(xd, gd, 1e-6, bits, True, EPS, code_offset=form) if norm else \
+                hbl.fwht_quant(xd, bits, True, EPS, code_offset=form)
+            assert np.array_equal(sd.cpu().numpy(), s) and np.array_equal(cs.cpu().numpy(), want.astype(np.int32).sum(1))
+            if form == hbl.CODES_BF6:
+                assert np.array_equal(record_bits(c.cpu().numpy(), T, K), record_bits(encode_bf6_records(want.astype(np.int32)), T, K))
+            else:
+                assert np.array_equal(c.cpu().numpy().astype(np.int32) - form, want.astype(np.int32))
+    assert np.array_equal(hbl.fwht(xd).cpu().numpy().view(np.uint32), O.hadamard_backward(x).view(np.uint32))
+    assert np.array_equal(host_bf16_bits(hbl.fwht(xd, out_dtype=torch.bfloat16)), O.hadamard_backward(x, out_bf16=True))
+
+
 @pytest.mark.parametrize("K,hadamard", [(256, True), (2048, True), (640, False), (3072, False), (4096, False)])
 @pytest.mark.parametrize("norm", [False, True])
 def test_one_row_per_workgroup_quantisers_beyond_4096_rows(hbl, K, hadamard, norm):
