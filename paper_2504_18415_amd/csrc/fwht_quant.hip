@@ -164,43 +164,46 @@ int dispatch(const void* x, int x_dtype, int64_t T, int bits, RowParams rp, bool
               : launch_one<LOG2K, W, 4, false, false>(x, T, codes, s_dequant, code_sum, rp, code_offset, stream);
 }
 
-// Rows of several projections in one grid (small-batch path): workgroup -> (problem, row), then the
-// body the stand-alone launch would run for that problem.  A body that needs fewer than 256 threads
-// runs on the first waves only; the other waves end at once, and a workgroup barrier waits only for
-// waves that have not ended.
+// Rows of several projections in one grid (small-batch path): workgroup -> (problem, row), then the body the stand-alone launch
+// would run for that problem (16 values per thread for large transformed rows).  A body that needs fewer threads than the
+// workgroup has runs on the first waves only; the other waves end at once, and a workgroup barrier waits only for waves
+// that have not ended.
+constexpr int grouped_row_threads(int64_t K, bool hadamard) {
+    return K <= 4096 ? 256 : (hadamard && K == 8192 ? 512 : 1024);
+}
+
 template <int BITS, bool BF16>
-__global__ __launch_bounds__(256) void quant_grouped_kernel(const QuantGroupArgs a) {
+__global__ __launch_bounds__(1024) void quant_grouped_kernel(const QuantGroupArgs a) {
     extern __shared__ __attribute__((aligned(16))) float row_lds[];
     const QuantProblem p = a.p[group_index_of(a.row_begin, a.n, (int)blockIdx.x)];
     const int64_t row = (int)blockIdx.x - p.row_begin;
     const int tid = threadIdx.x;
+    const RowParams rp{a.eps, p.ln_gain, p.ln_eps, 1};
     if (!p.hadamard) {
-        quant_generic_body<BITS, BF16>(row, tid, p.x, p.K, p.codes, p.s_dequant, p.code_sum, RowParams{a.eps, p.ln_gain, p.ln_eps, 1}, p.code_offset);
+        if (p.K > 4096) {
+            quant_generic_body<BITS, BF16, 2, kRecordBlockBytes, 16>(row, tid, p.x, p.K, p.codes, p.s_dequant, p.code_sum, rp, p.code_offset);
+        } else if (tid < 256) {
+            quant_generic_body<BITS, BF16, 2>(row, tid, p.x, p.K, p.codes, p.s_dequant, p.code_sum, rp, p.code_offset);
+        }
         return;
     }
 #define HBL_SMALL_ROW(L2K)                                                                                    \
     case 1 << L2K:                                                                                            \
         if (tid < 64)                                                                                         \
-            fwht_quant_body<L2K, 1, BITS, BF16, true>(row, tid, p.x, p.codes, p.s_dequant, p.code_sum, RowParams{a.eps, p.ln_gain, p.ln_eps, 1}, \
-                                                      p.code_offset);                                         \
+            fwht_quant_body<L2K, 1, BITS, BF16, true>(row, tid, p.x, p.codes, p.s_dequant, p.code_sum, rp, p.code_offset); \
         return;
 #define HBL_BIG_ROW(L2K)                                                                                      \
     case 1 << L2K:                                                                                            \
-        if (tid < (1 << L2K) / 64) {                                                                          \
-            BigRowRaw<BF16> raw;                                                                              \
-            if constexpr (kRowThroughLds<L2K, BF16>)                                                          \
-                bigrow_load_lds<L2K, BF16>(p.x, row, tid, reinterpret_cast<char*>(row_lds), raw);             \
-            else                                                                                              \
-                bigrow_load<L2K, BF16>(p.x, row, tid, raw);                                                       \
-            const RowParams rp{a.eps, p.ln_gain, p.ln_eps, 1};                                                \
+        if (tid < LargeRow<L2K, 4>::NT) {                                                                     \
+            LargeRowRaw<4, BF16> raw;                                                                         \
+            large_row_load<L2K, 4, BF16>(p.x, row, tid, raw);                                                 \
             if constexpr (BITS == 4) {                                                                        \
                 if (p.code_offset == kCodesBf6) {                                                             \
-                    fwht_quant_bigrow_body<L2K, 4, BF16, true, true>(row, tid, raw, row_lds, p.codes, p.s_dequant, p.code_sum, rp, 8); \
+                    large_row_body<L2K, 4, 4, BF16, true, true>(row, tid, raw, row_lds, p.codes, p.s_dequant, p.code_sum, rp, 8); \
                     return;                                                                                   \
                 }                                                                                             \
             }                                                                                                 \
-            fwht_quant_bigrow_body<L2K, BITS, BF16, false, true>(row, tid, raw, row_lds, p.codes, p.s_dequant, p.code_sum, rp, \
-                                                                 p.code_offset);                              \
+            large_row_body<L2K, 4, BITS, BF16, false, true>(row, tid, raw, row_lds, p.codes, p.s_dequant, p.code_sum, rp, p.code_offset); \
         }                                                                                                     \
         return;
     switch (p.K) {
@@ -208,7 +211,7 @@ __global__ __launch_bounds__(256) void quant_grouped_kernel(const QuantGroupArgs
         HBL_SMALL_ROW(8)
         HBL_SMALL_ROW(9)
         HBL_SMALL_ROW(10)
-        HBL_SMALL_ROW(11)
+        HBL_BIG_ROW(11)
         HBL_BIG_ROW(12)
         HBL_BIG_ROW(13)
         HBL_BIG_ROW(14)
@@ -223,17 +226,19 @@ __global__ __launch_bounds__(256) void quant_grouped_kernel(const QuantGroupArgs
 int launch_quant_grouped(const QuantGroupArgs& args, int bits, int x_dtype, hipStream_t stream) {
     int rows = 0;
     size_t lds = 0;
+    int threads = 256;
     for (int i = 0; i < args.n; ++i) {
-        rows += args.p[i].T;
-        if (args.p[i].hadamard && args.p[i].K >= 4096 && sizeof(float) * (size_t)args.p[i].K > lds)
-            lds = sizeof(float) * (size_t)args.p[i].K;
+        const QuantProblem& p = args.p[i];
+        rows += p.T;
+        if (p.hadamard && p.K >= 2048 && sizeof(float) * (size_t)p.K > lds) lds = sizeof(float) * (size_t)p.K;
+        if (grouped_row_threads(p.K, p.hadamard != 0) > threads) threads = grouped_row_threads(p.K, p.hadamard != 0);
     }
     if (rows == 0) return HBL_OK;
     const bool bf = x_dtype == HBL_BF16;
     auto launch = [&](auto kern) -> int {
         static std::atomic<uint64_t> lds_allowed{0};   // per instantiation: devices already set up
         if (const int rc = allow_dynamic_lds(kern, 64 * 1024, lds_allowed); rc != HBL_OK) return rc;
-        launch_kernel("quant_grouped_kernel", kern, dim3((unsigned)rows), dim3(256), lds, stream, args);
+        launch_kernel("quant_grouped_kernel", kern, dim3((unsigned)rows), dim3((unsigned)threads), lds, stream, args);
         return after_launch();
     };
     if (bits == 8) return bf ? launch(quant_grouped_kernel<8, true>) : launch(quant_grouped_kernel<8, false>);

@@ -525,24 +525,25 @@ __device__ __forceinline__ void fwht_quant_body(int64_t row, int tid, const void
 }
 
 // Plain BitLinear front end for K that is not a power of two (K % 128 == 0, K <= 16384): the same
-// quantiser with the row held as up to 8 chunks of 8 elements per thread of a 256-thread workgroup.
-// MAXC = chunk slots per thread (K <= 2048 * MAXC): the launcher picks the smallest that covers the row, so
+// quantiser with the row held as chunks of 8 elements by the threads of NW waves.
+// MAXC = chunk slots per thread (K <= 512 * NW * MAXC): the launcher picks the smallest that covers the row, so
 // that short rows do not walk empty slots; every MAXC performs the same arithmetic in the same order.
-template <int BITS, bool BF16, int MAXC = 8, int BLOCKB = kRecordBlockBytes>
+template <int BITS, bool BF16, int MAXC = 8, int BLOCKB = kRecordBlockBytes, int NW = 4>
 __device__ __forceinline__ void quant_generic_body(int64_t row, int tid, const void* __restrict__ x, int K,
                                                    int8_t* __restrict__ codes, float* __restrict__ s_dequant,
                                                    int32_t* __restrict__ code_sum, RowParams rp, int code_offset) {
     const int few_rows = rp.few_rows;
-    __shared__ double red_d[4];
-    __shared__ float red_f[4];
-    __shared__ int red_i[4];
+    constexpr int NT = 64 * NW;
+    __shared__ double red_d[NW];
+    __shared__ float red_f[NW];
+    __shared__ int red_i[NW];
     const int lane = tid & 63, wave = tid >> 6;
     const int64_t row_off = row * K;
     const int nchunks = K / 8;
     float v[MAXC][8];
 #pragma unroll
     for (int c = 0; c < MAXC; ++c) {
-        const int ch = c * 256 + tid;
+        const int ch = c * NT + tid;
         if (ch < nchunks) {
             load_chunk<8, BF16>(x, row_off + (int64_t)ch * 8, v[c]);
         } else {
@@ -551,16 +552,16 @@ __device__ __forceinline__ void quant_generic_body(int64_t row, int tid, const v
         }
     }
     if (rp.ln_gain) {   // uniform: RMS normalisation of the row (chunks past the row hold zeros)
-        __shared__ double red_n[4];
+        __shared__ double red_n[NW];
         double ss = 0.0;
 #pragma unroll
         for (int c = 0; c < MAXC; ++c)
 #pragma unroll
             for (int e = 0; e < 8; ++e) ss += (double)v[c][e] * (double)v[c][e];
-        const float rn = rms_factor<4>(ss, red_n, lane, wave, K, rp.ln_eps, few_rows);
+        const float rn = rms_factor<NW>(ss, red_n, lane, wave, K, rp.ln_eps, few_rows);
 #pragma unroll
         for (int c = 0; c < MAXC; ++c) {
-            const int ch = c * 256 + tid;
+            const int ch = c * NT + tid;
             if (ch < nchunks) {
                 float gv[8];
                 load_chunk<8, false>(rp.ln_gain, (int64_t)ch * 8, gv);
@@ -579,7 +580,9 @@ __device__ __forceinline__ void quant_generic_body(int64_t row, int tid, const v
         m = wave_max(m, few_rows);
         if (lane == 0) red_f[wave] = m;
         __syncthreads();
-        m = fmaxf(fmaxf(red_f[0], red_f[1]), fmaxf(red_f[2], red_f[3]));
+        m = red_f[0];
+#pragma unroll
+        for (int w = 1; w < NW; ++w) m = fmaxf(m, red_f[w]);
         gain = 127.0f / (m + rp.eps);
         s_d = m / 127.0f;
     } else {
@@ -591,7 +594,9 @@ __device__ __forceinline__ void quant_generic_body(int64_t row, int tid, const v
         s = wave_sum(s, few_rows);
         if (lane == 0) red_d[wave] = s;
         __syncthreads();
-        s = ((red_d[0] + red_d[1]) + red_d[2]) + red_d[3];
+        s = red_d[0];
+#pragma unroll
+        for (int w = 1; w < NW; ++w) s += red_d[w];
         const float beta = (float)(s / (double)K);
         gain = kRoot7 / (beta + rp.eps);
         s_d = beta / kRoot7;
@@ -605,7 +610,7 @@ __device__ __forceinline__ void quant_generic_body(int64_t row, int tid, const v
     int isum = 0;
 #pragma unroll
     for (int c = 0; c < MAXC; ++c) {
-        const int ch = c * 256 + tid;
+        const int ch = c * NT + tid;
         if (ch < nchunks) {
             uint32_t packed[2] = {0u, 0u};
 #pragma unroll
@@ -626,7 +631,12 @@ __device__ __forceinline__ void quant_generic_body(int64_t row, int tid, const v
         isum = wave_sum(isum, few_rows);
         if (lane == 0) red_i[wave] = isum;
         __syncthreads();
-        if (tid == 0) code_sum[row] = red_i[0] + red_i[1] + red_i[2] + red_i[3];
+        if (tid == 0) {
+            isum = 0;
+#pragma unroll
+            for (int w = 0; w < NW; ++w) isum += red_i[w];
+            code_sum[row] = isum;
+        }
     }
     if (tid == 0) s_dequant[row] = s_d;
 }

@@ -919,6 +919,17 @@ def test_grouped_ragged_mix(hbl, bits, x_dtype):
 
 
 @pytest.mark.parametrize("bits", [4, 8])
+@pytest.mark.parametrize("lengths", [((4096, False), (4096, True)), ((4224, False), (2048, True), (128, True)),
+                                     ((8192, False), (8320, False), (8192, True)), ((16384, False), (16256, False), (1024, True))])
+def test_grouped_quantiser_workgroup_sizes(hbl, bits, lengths):
+    """Rows of one launch that need 64 to 1024 threads, with 16 waves for the plain rows above 4096 features."""
+    note(f"grouped quantiser sizes bits={bits} {lengths}")
+    sites = [synth.Site(f"g{K}_{i}", 2 + i, K, 64, hadamard=h, seed=50 + i, outlier_frac=0.01, outlier_scale=30.0)
+             for i, (K, h) in enumerate(lengths)]
+    run_group(hbl, sites, [bits] * len(sites))
+
+
+@pytest.mark.parametrize("bits", [4, 8])
 @pytest.mark.parametrize("T", [5, 16, 33, 48, 64])
 def test_grouped_short_and_odd_k(hbl, bits, T):
     """K ranges of 1, 3, 4, 5 and 9 blocks: shorter than the copy ring of the weight-streaming kernel (up to 16 tokens),
