@@ -9,7 +9,7 @@
 // for another one.
 #include <atomic>
 
-#include "quant_bodies.h"
+#include "large_rows.h"
 
 namespace hbl {
 namespace {
@@ -47,11 +47,27 @@ __device__ __forceinline__ void wait_copies(int n) {
         default: asm volatile("s_waitcnt vmcnt(32)" ::: "memory"); break;
     }
 }
+// ... of exactly N.
+template <int N>
+__device__ __forceinline__ void wait_copies() {
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
+}
 
-// LOG2K: Hadamard rows of 2^LOG2K (9..14); 0: plain rows of up to 2048 * MAXC.  RB: most tokens.  RW: output rows per
+// Waves of a workgroup and log2 of the values per thread of a large row (large_rows.h).  Several rows are worked on side by
+// side: plain ones by PW waves each, transformed ones of 512 and 1024 by one wave each, larger ones by K / 1024 (16384: 8).
+constexpr int fused_values(int log2k) { return log2k == 14 ? 5 : 4; }
+constexpr int fused_row_waves(int log2k, int pw) { return log2k == 0 ? pw : log2k < 11 ? 1 : (1 << log2k) >> (6 + fused_values(log2k)); }
+constexpr int fused_waves(int log2k, int pw, int rb) {
+    const int n = fused_row_waves(log2k, pw) * rb;
+    return n < 4 ? 4 : n;
+}
+
+// LOG2K: Hadamard rows of 2^LOG2K (9..14); 0: plain rows of up to 1024 * PW features.  RB: most tokens.  RW: output rows per
 // workgroup.
-template <int LOG2K, int MAXC, bool BF16, int RB, int RW>
-__global__ __launch_bounds__(256) void fused_small_kernel(const FusedArgs a) {
+template <int LOG2K, int PW, bool BF16, int RB, int RW>
+__global__ __launch_bounds__(64 * fused_waves(LOG2K, PW, RB)) void fused_small_kernel(const FusedArgs a) {
+    constexpr int WAVES = fused_waves(LOG2K, PW, RB), R = fused_values(LOG2K);
+    constexpr bool LARGE = LOG2K >= 11;
     extern __shared__ __attribute__((aligned(1024))) char lds[];
     __shared__ float s_d[kFusedRows];
     constexpr int EB = BF16 ? 2 : 4;
@@ -67,40 +83,40 @@ __global__ __launch_bounds__(256) void fused_small_kernel(const FusedArgs a) {
     const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)lds;
 
     // 1. the rows' copies: each wave those that its own threads read back below
-    constexpr int ROW_WAVES = LOG2K == 0 ? 4 : (LOG2K <= 12 ? 1 : (LOG2K == 13 ? 2 : 4));   // waves that share a row
-    const int sub = wave / ROW_WAVES;                        // Hadamard: row slot of this wave
+    constexpr int ROW_WAVES = fused_row_waves(LOG2K, PW), SLOTS = WAVES / ROW_WAVES;
+    const int sub = wave / ROW_WAVES;                        // row slot of this wave
     const int row = sub < a.T ? sub : a.T - 1;               // (a slot past the last token repeats that one)
     const uint32_t rtid = tid - sub * ROW_WAVES * 64;
-    char* const slot = lds + (LOG2K >= 12 ? sub * (4 << LOG2K) : sub * (EB << (LOG2K ? LOG2K : 9)));
+    char* const slot = lds + sub * (LOG2K == 0 ? PW * 1024 * EB : LARGE ? 4 << LOG2K : EB << LOG2K);
     if constexpr (LOG2K == 0) {
-        for (int t = 0; t < a.T; ++t)
-            for (int c = 0; c * 256 < K / 8; ++c) {          // thread tid reads chunk c * 256 + tid (8 elements)
-                const int first = c * 256 + wave * 64;
-                if (first >= K / 8) continue;
-                const char* src = static_cast<const char*>(a.x) + ((size_t)t * K + (size_t)first * 8) * EB;
+        const char* src = static_cast<const char*>(a.x) + (size_t)row * K * EB;
+        for (int c = 0; c * PW * 64 < K / 8; ++c) {          // thread rtid reads chunk c * PW * 64 + rtid (8 elements)
+            const int first = c * PW * 64 + (wave % ROW_WAVES) * 64;
+            if (first >= K / 8) continue;
 #pragma unroll
-                for (int q = 0; q < EB / 2; ++q) {           // 64 chunks of 16 or 32 bytes; none past the row
-                    const uint32_t off = q * 1024 + lane * 16;
-                    const uint32_t most = (uint32_t)(K / 8 - first) * 8 * EB - 16;
-                    lds_dma16(lds0 + (t * (MAXC * 2048) + first * 8) * EB + q * 1024, src, off < most ? off : most);
-                }
+            for (int q = 0; q < EB / 2; ++q) {               // 64 chunks of 16 or 32 bytes; none past the row
+                const uint32_t off = q * 1024 + lane * 16;
+                const uint32_t most = (uint32_t)(K / 8 - first) * 8 * EB - 16;
+                lds_dma16((uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)slot + first * 8 * EB + q * 1024,
+                          src + (size_t)first * 8 * EB, off < most ? off : most);
             }
-    } else if constexpr (LOG2K < 12) {
+        }
+    } else if constexpr (!LARGE) {
         const char* src = static_cast<const char*>(a.x) + ((size_t)row * K) * EB;
 #pragma unroll
         for (int q = 0; q < (EB << LOG2K) / 1024; ++q)
             lds_dma16((uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)slot + q * 1024, src + q * 1024, lane * 16);
     } else {
-        bigrow_copy<LOG2K, BF16>(a.x, row, rtid, slot);
+        large_row_copy<LOG2K, R, BF16>(a.x, row, rtid, slot);
     }
 
-    // 2. this workgroup's weights, unit wave, wave + 4, ...; tiles past N re-read the last one (never stored)
+    // 2. this workgroup's weights, unit wave, wave + WAVES, ...; tiles past N re-read the last one (never stored)
     const size_t wstride = (size_t)(a.N / 32) * 1024;
     const int tile0 = RW == 16 ? blockIdx.x >> 1 : blockIdx.x * (RW / 32);
     const int tile_last = a.N / 32 - 1;
     const uint32_t wlds = lds0 + a.weights_off;
     int copies = 0;
-    for (int u = wave; u < units; u += 4) {
+    for (int u = wave; u < units; u += WAVES) {
         if constexpr (RW == 16) {
             // lanes 0-31 K-block 2u, lanes 32-63 the next one: of a tile the lanes of rows 16 h .. 16 h + 15, both halves
             const int kb = 2 * u, next = kb + 1 < nkb ? 1 : 0;
@@ -116,24 +132,22 @@ __global__ __launch_bounds__(256) void fused_small_kernel(const FusedArgs a) {
         }
         copies += CPU_;
     }
-    wait_copies(copies < 32 ? copies : 32);   // the rows have landed; the weights may be on their way
+    // the rows have landed; the weights may be on their way
+    if constexpr (LOG2K != 0 && ((1 << LOG2K) / 128 / KBU) % WAVES == 0) wait_copies<(1 << LOG2K) / 128 / KBU / WAVES * CPU_>();
+    else wait_copies(copies < 32 ? copies : 32);
 
     // 3. transform and quantise into the record image
     int8_t* const codes = reinterpret_cast<int8_t*>(lds + a.codes_off);
     const RowParams rp{a.eps, nullptr, 0.0f, 1};
     if constexpr (LOG2K == 0) {
-        for (int t = 0; t < a.T; ++t) {
-            if (t != 0) __syncthreads();   // every wave is done with the previous row's partial sums
-            quant_generic_body<4, BF16, MAXC, BLOCK>(0, tid, lds + t * (MAXC * 2048) * EB, K, codes + t * kRecordRowBytes, s_d + t,
-                                                     nullptr, rp, kCodesBf6);
-        }
-    } else if constexpr (LOG2K < 12) {
+        quant_generic_body<4, BF16, 2, BLOCK, PW, SLOTS>(0, rtid, slot, K, codes + row * kRecordRowBytes, s_d + row, nullptr, rp, kCodesBf6, sub);
+    } else if constexpr (!LARGE) {
         fwht_quant_body<LOG2K, 1, 4, BF16, true, BLOCK>(0, rtid, slot, codes + row * kRecordRowBytes, s_d + row, nullptr, rp, kCodesBf6);
     } else {
-        BigRowRaw<BF16> raw;
-        bigrow_read<LOG2K, BF16>(rtid, slot, raw);
-        fwht_quant_bigrow_body<LOG2K, 4, BF16, true, false, false, BLOCK>(
-            0, rtid, raw, reinterpret_cast<float*>(slot), codes + row * kRecordRowBytes, s_d + row, nullptr, rp, 8);
+        LargeRowRaw<R, BF16> raw;
+        large_row_read<LOG2K, R, BF16>(rtid, slot, raw);
+        large_row_body<LOG2K, R, 4, BF16, true, false, BLOCK, SLOTS>(
+            0, rtid, raw, reinterpret_cast<float*>(slot), codes + row * kRecordRowBytes, s_d + row, nullptr, rp, 8, sub);
     }
     __syncthreads();
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // a wave multiplies the weights that it copied itself
@@ -146,7 +160,7 @@ __global__ __launch_bounds__(256) void fused_small_kernel(const FusedArgs a) {
     v4f acc[NH];
 #pragma unroll
     for (int h = 0; h < NH; ++h) acc[h] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
-    for (int u = wave; u < units; u += 4)
+    for (int u = wave; u < units; u += WAVES)
 #pragma unroll
         for (int k = 0; k < KBU; ++k) {
             const int kb = u * KBU + k;
@@ -164,7 +178,7 @@ __global__ __launch_bounds__(256) void fused_small_kernel(const FusedArgs a) {
             }
         }
 
-    // 5. the four waves' sums (exact integers) through LDS, then bf16: wave 0 holds 4 features of token lane & 15 per half
+    // 5. the waves' sums (exact integers) through LDS, then bf16: wave 0 holds 4 features of token lane & 15 per half
     __syncthreads();
     v4f* red = reinterpret_cast<v4f*>(lds);
     if (wave != 0) {
@@ -178,7 +192,7 @@ __global__ __launch_bounds__(256) void fused_small_kernel(const FusedArgs a) {
     for (int h = 0; h < NH; ++h) {
         v4f v = acc[h];
 #pragma unroll
-        for (int w = 0; w < 3; ++w) v += red[(w * NH + h) * 64 + lane];
+        for (int w = 0; w < WAVES - 1; ++w) v += red[(w * NH + h) * 64 + lane];
         const int n0 = RW == 16 ? blockIdx.x * 16 : blockIdx.x * RW + h * 16;
         if (n0 < a.N)
             *reinterpret_cast<uint2*>(a.y + (size_t)r * a.N + n0 + 4 * g) =
@@ -192,59 +206,63 @@ constexpr size_t kCuLds = 160 * 1024;
 struct FusedLayout {
     size_t codes_off, weights_off, bytes;
 };
-FusedLayout fused_layout(int log2k, int maxc, int eb, int T, int rb, int64_t K, int rw) {
+FusedLayout fused_layout(int log2k, int pw, int eb, int rb, int64_t K, int rw) {
     FusedLayout l;
-    size_t rows;
-    if (log2k == 0) rows = (size_t)T * maxc * 2048 * eb;
-    else if (log2k < 12) rows = (size_t)4 * K * eb;                                  // four row slots, as loaded
-    else rows = (size_t)(log2k == 12 ? 4 : log2k == 13 ? 2 : 1) * K * sizeof(float); // row slots of K floats
+    const int waves = fused_waves(log2k, pw, rb);
+    const size_t slots = waves / fused_row_waves(log2k, pw);
+    const size_t rows = slots * (log2k == 0 ? (size_t)pw * 1024 * eb : log2k < 11 ? (size_t)K * eb : (size_t)K * sizeof(float));
     const size_t nkb = (size_t)K / 128, per = rw == 16 ? 512 : (size_t)rw * 32;
     l.codes_off = round_up(rows, 1024);
     l.weights_off = l.codes_off + round_up(nkb * rb * kRecordRowBytes, 1024);
     l.bytes = l.weights_off + (nkb + (rw == 16 ? nkb & 1 : 0)) * per;
-    const size_t sums = (size_t)3 * (rw / 16) * 1024;
+    const size_t sums = (size_t)(waves - 1) * (rw / 16) * 1024;
     if (l.bytes < sums) l.bytes = sums;
     return l;
 }
 
-template <int LOG2K, int MAXC, bool BF16, int RB, int RW>
+template <int LOG2K, int PW, bool BF16, int RB, int RW>
 int launch_cfg(FusedArgs a, const FusedLayout& l, hipStream_t stream) {
     a.codes_off = (uint32_t)l.codes_off;
     a.weights_off = (uint32_t)l.weights_off;
-    auto kern = fused_small_kernel<LOG2K, MAXC, BF16, RB, RW>;
+    auto kern = fused_small_kernel<LOG2K, PW, BF16, RB, RW>;
     static std::atomic<uint64_t> lds_allowed{0};   // per instantiation: devices already set up
     if (const int rc = allow_dynamic_lds(kern, kCuLds - 1024, lds_allowed); rc != HBL_OK) return rc;
-    launch_kernel("fused_small_kernel", kern, dim3((unsigned)((a.N + RW - 1) / RW)), dim3(256), l.bytes, stream, a);
+    launch_kernel("fused_small_kernel", kern, dim3((unsigned)((a.N + RW - 1) / RW)), dim3(64 * fused_waves(LOG2K, PW, RB)), l.bytes, stream, a);
     return after_launch();
 }
 
 // Most workgroups per CU at which one launch is no slower than two, for 16, 32 and 64 output rows a workgroup; 0: not at all.
 // Every workgroup quantises the rows for itself, so beyond one per CU that work is repeated side by side on the same SIMDs,
 // while the two launches do it once: what is saved, a launch of about 2 us, is spent again.  Time against the two launches
-// (both input types, 32 to 131072 output rows; by workgroups of 16 rows per CU):
-//   transformed rows: K = 512  1: 0.6  2: 0.7  4: 0.87  6: 1.02  8: 1.2;  1024  1: 0.6  3: 0.8  4: 0.94  5: 1.07  8: 1.4;
-//                     2048  1: 0.7  2: 0.85  3: 0.97  4: 1.17;  4096 and more  1: 0.75-0.85, LDS holds no more than two
-//   plain rows, one token: 512  1: 0.7  4: 0.84  8: 1.07;  1024 to 4096  1: 0.55  4: 0.8
-//   plain rows of several tokens are taken one after the other by the whole workgroup, whatever their length:
-//                     2 tokens, 512  1: 0.85  3: 0.99  4: 1.07;  2048  1: 0.7  3: 0.87  4: 0.99
-//                     3 tokens, 512  1: 0.95-1.02  2: 1.08;  1024  1: 0.85  2: 0.98  3: 1.07;  2560  1: 0.93  2: 1.02
-//                     4 tokens, 512  1: 1.1;  1024  1: 0.97  2: 1.12;  1536  1: 0.93  2: 1.04;  2048  1: 0.95  2: 1.07
-// 32 and 64 rows a workgroup start 0.05 and 0.1 higher (fewer wavefronts, longer sums) and rise in the same way.
-// (us: 4 x 512 -> 12288 plain 7.0 by one launch, 5.1 by two; 1 x 1024 -> 32768 transformed 8.8, 6.4; 1 x 2048 -> 16384
-// transformed 9.3 with 16 rows a workgroup, 7.0 with 32, 7.9 by two.)
+// (bf16 rows, 256 to 32768 output rows; fp32 within 0.03):
+//   16 rows, at most one per CU: 0.56-0.85 for one and two tokens, 0.61-0.85 for three, 0.61-0.97 for four
+//   between one and two per CU 32 rows are as good or better: 1 x 8192 -> 8192 0.72 (16 rows: 0.91), 2 x 2048 -> 12288 0.80
+//     (0.87), 3 x 2048 -> 8192 0.76 (0.90), 4 plain x 2048 -> 8192 0.81 (0.99)
+//   32 rows per CU, transformed:  K = 512  3: 0.83  4: 0.95;  1024  3: 0.92  4: 1.10;  2048  one or two tokens 3: 0.97  4: 1.12, three
+//     2: 0.97  3: 1.09, four 1: 0.81  1.5: 0.97-1.18;  4096  one token 3: 0.94, two 1: 0.78  1.5: 0.97, three 1: 0.91, four 1: 1.02;
+//     8192  1: 0.72-0.96
+//   32 rows, plain:  one token 3: 0.78-0.87 and 4: 0.83-0.99 (64 rows: 0.79-0.94);  two tokens 1: 0.66-0.80  1.5: 0.76-0.92 (64 rows:
+//     0.75-0.91);  three 1: 0.70-0.89  2: 0.92-1.04 (512: 1.12);  four 1: 0.81-0.91  1.5: 1.04-1.20
+//   64 rows, plain:  two tokens 1: 0.75-0.91  2: 0.88-0.98 (512: 1.07);  three 1.5: 1.09-1.32;  four 1: 1.06-1.31
+// Four plain rows of at most 512 features (0.89-0.95), and 32 rows for four of at most 1024 (0.82-0.87), are left to the two
+// launches: less than a microsecond, and more than one workgroup per CU is a loss from there on.
+// (1 x 4096 -> 4096 transformed 6.3 us by two launches, 4.3 by one; 1 x 16384 -> 4096 9.9 and 7.5; 4 x 2048 -> 2048 6.3 and 4.6.)
 int most_workgroups_per_cu(int64_t T, int64_t K, bool hadamard, int rw) {
-    if (hadamard) return K <= 512 ? 4 : (K <= 1024 ? 3 : 2);
-    if (T == 1) return 4;
-    if (T == 2) return rw == 16 ? 3 : (K >= 1024 ? (rw == 32 ? 3 : 2) : (rw == 32 ? 2 : 1));
-    if (T == 3) {
-        if (rw == 16) return K >= 1024 && K <= 2048 ? 2 : 1;
-        return rw == 64 || K < 640 ? 0 : (K >= 1280 && K <= 2048 ? 2 : 1);
+    if (rw == 16) return hadamard || T < 4 || K > 512 ? 1 : 0;
+    if (rw == 64) return T == 1 ? 4 : (T == 2 ? (K < 1024 ? 1 : 2) : 0);   // (plain rows only)
+    if (!hadamard) {
+        if (T == 1) return K <= 4096 ? 3 : 1;
+        if (T == 3) return K >= 1024 ? 2 : 1;
+        return T == 2 || K > 1024 ? 1 : 0;
     }
-    return rw == 64 ? 0 : (K >= (rw == 16 ? 1024 : 1536) ? 1 : 0);
+    if (K <= 1024) return K <= 512 ? 4 : 3;
+    if (K <= 2048) return T <= 2 ? 3 : (T == 3 ? 2 : 1);
+    if (K <= 4096) return T == 1 ? 3 : (T <= 3 ? 1 : 0);
+    return 1;
 }
 
 struct FusedPlan {
-    int log2k, maxc, rb, rw;   // rw = 0: not this kernel
+    int log2k, pw, rb, rw;   // rw = 0: not this kernel
     FusedLayout layout;
 };
 FusedPlan fused_plan(int64_t T, int64_t K, int64_t N, int x_dtype, bool hadamard) {
@@ -253,14 +271,13 @@ FusedPlan fused_plan(int64_t T, int64_t K, int64_t N, int x_dtype, bool hadamard
     if (hadamard) {
         while ((1 << p.log2k) < K) ++p.log2k;
     } else {
-        p.maxc = K <= 4096 ? 2 : 8;
+        p.pw = K <= 4096 ? 4 : 16;
     }
-    // the rows of K <= 4096 are transformed side by side, one per wave; larger and plain ones take the whole workgroup in turn
-    if (T > kFusedRows || (T > 1 && (hadamard ? K >= 8192 : T * K > 8192))) return p;
-    p.rb = T == 1 ? 1 : kFusedRows;
+    if (T > kFusedRows || (T > 1 && K > (hadamard && T == 2 ? 8192 : 4096))) return p;
+    p.rb = T == 1 ? 1 : (fused_row_waves(p.log2k, p.pw) > 1 ? (int)T : kFusedRows);
     for (const int rw : {16, 32, 64}) {
         if ((rw == 64 && (hadamard || K > 4096)) || (rw == 32 && K > 8192)) continue;
-        const FusedLayout l = fused_layout(p.log2k, p.maxc, eb, (int)T, p.rb, K, rw);
+        const FusedLayout l = fused_layout(p.log2k, p.pw, eb, p.rb, K, rw);
         if (l.bytes > kCuLds - 1024) continue;
         const int64_t wgs = (N + rw - 1) / rw, resident = (int64_t)(kCuLds / (l.bytes + 1024));
         const int64_t most = most_workgroups_per_cu(T, K, hadamard, rw);
@@ -272,29 +289,35 @@ FusedPlan fused_plan(int64_t T, int64_t K, int64_t N, int x_dtype, bool hadamard
     return p;
 }
 
-template <int LOG2K, int MAXC, bool BF16, int RB>
+template <int LOG2K, int PW, bool BF16, int RB>
 int launch_rows(const FusedArgs& a, const FusedPlan& p, hipStream_t stream) {
-    if (p.rw == 16) return launch_cfg<LOG2K, MAXC, BF16, RB, 16>(a, p.layout, stream);
+    if (p.rw == 16) return launch_cfg<LOG2K, PW, BF16, RB, 16>(a, p.layout, stream);
     if constexpr (LOG2K < 14) {
-        if (p.rw == 32) return launch_cfg<LOG2K, MAXC, BF16, RB, 32>(a, p.layout, stream);
+        if (p.rw == 32) return launch_cfg<LOG2K, PW, BF16, RB, 32>(a, p.layout, stream);
     }
-    if constexpr (LOG2K == 0 && MAXC == 2) {
-        if (p.rw == 64) return launch_cfg<LOG2K, MAXC, BF16, RB, 64>(a, p.layout, stream);
+    if constexpr (LOG2K == 0 && PW == 4) {
+        if (p.rw == 64) return launch_cfg<LOG2K, PW, BF16, RB, 64>(a, p.layout, stream);
     }
     return HBL_E_SHAPE;
 }
-template <int LOG2K, int MAXC, bool BF16>
+template <int LOG2K, int PW, bool BF16>
 int launch_tokens(const FusedArgs& a, const FusedPlan& p, hipStream_t stream) {
-    if constexpr (LOG2K < 13 && MAXC < 8) {
-        if (p.rb != 1) return launch_rows<LOG2K, MAXC, BF16, kFusedRows>(a, p, stream);
+    if constexpr (PW == 4 || (LOG2K >= 11 && LOG2K <= 13)) {
+        if (p.rb == 2) return launch_rows<LOG2K, PW, BF16, 2>(a, p, stream);
     }
-    return p.rb == 1 ? launch_rows<LOG2K, MAXC, BF16, 1>(a, p, stream) : HBL_E_SHAPE;
+    if constexpr (PW == 4 || LOG2K == 11 || LOG2K == 12) {
+        if (p.rb == 3) return launch_rows<LOG2K, PW, BF16, 3>(a, p, stream);
+    }
+    if constexpr (LOG2K < 13 && PW < 16) {
+        if (p.rb == kFusedRows) return launch_rows<LOG2K, PW, BF16, kFusedRows>(a, p, stream);
+    }
+    return p.rb == 1 ? launch_rows<LOG2K, PW, BF16, 1>(a, p, stream) : HBL_E_SHAPE;
 }
 
 template <bool BF16>
 int launch_kind(const FusedArgs& a, const FusedPlan& p, hipStream_t stream) {
     switch (p.log2k) {
-        case 0: return p.maxc == 2 ? launch_tokens<0, 2, BF16>(a, p, stream) : launch_tokens<0, 8, BF16>(a, p, stream);
+        case 0: return p.pw == 4 ? launch_tokens<0, 4, BF16>(a, p, stream) : launch_tokens<0, 16, BF16>(a, p, stream);
         case 9: return launch_tokens<9, 0, BF16>(a, p, stream);
         case 10: return launch_tokens<10, 0, BF16>(a, p, stream);
         case 11: return launch_tokens<11, 0, BF16>(a, p, stream);

@@ -73,20 +73,47 @@ __device__ __forceinline__ void large_row_load(const void* __restrict__ x, int64
             raw.q[c * Q + i] = *reinterpret_cast<const uint4*>(base + first + c * 128 * (BF16 ? 2 : 4) + i * 16);
 }
 
+// The same through LDS, for a caller that has its row copied there (global -> LDS copies, one wave at a time, each the elements
+// of its own threads: nobody else reads them) into the row buffer, where the wave later writes its floats.
+template <int LOG2K, int R, bool BF16>
+__device__ __forceinline__ void large_row_copy(const void* __restrict__ x, int64_t row, uint32_t tid, char* row_buffer) {
+    using L = LargeRow<LOG2K, R>;
+    constexpr int EB = BF16 ? 2 : 4;
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const char* src = static_cast<const char*>(x) + (row * L::K + wave * L::WAVE_FLOATS) * EB;
+    const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)(row_buffer + wave * L::WAVE_FLOATS * 4);
+#pragma unroll
+    for (int i = 0; i < L::WAVE_FLOATS * EB / 1024; ++i) gemm::lds_dma16(lds0 + i * 1024, src + i * 1024, (tid & 63) * 16);
+}
+template <int LOG2K, int R, bool BF16>
+__device__ __forceinline__ void large_row_read(uint32_t tid, const char* row_buffer, LargeRowRaw<R, BF16>& raw) {
+    using L = LargeRow<LOG2K, R>;
+    constexpr int Q = LargeRowRaw<R, BF16>::Q, EB = BF16 ? 2 : 4;
+    const char* part = row_buffer + __builtin_amdgcn_readfirstlane(tid >> 6) * L::WAVE_FLOATS * 4;
+#pragma unroll
+    for (int c = 0; c < L::CHUNKS; ++c)
+#pragma unroll
+        for (int i = 0; i < Q; ++i) raw.q[c * Q + i] = *reinterpret_cast<const uint4*>(part + L::in_wave(tid, c) * EB + i * 16);
+}
+
 // BF6OUT (INT4 only): records (code_records.h) instead of one byte per code.  NORM: compiled with the RMS-normalisation prologue
 // (taken when rp.ln_gain is set).  BITS = 0: the transform alone; `codes` is the output array and `code_offset` its element type.
-// row_lds: K floats.
-template <int LOG2K, int R, int BITS, bool BF16, bool BF6OUT, bool NORM, int BLOCKB = kRecordBlockBytes>
+// row_lds: K floats.  GROUPS: rows that a workgroup works on side by side, this one by its threads [group * NT, (group + 1) * NT)
+// (tid counts from the first of them).
+template <int LOG2K, int R, int BITS, bool BF16, bool BF6OUT, bool NORM, int BLOCKB = kRecordBlockBytes, int GROUPS = 1>
 __device__ __forceinline__ void large_row_body(int64_t row, uint32_t tid, const LargeRowRaw<R, BF16>& raw, float* row_lds,
                                                int8_t* __restrict__ codes, float* __restrict__ s_dequant,
-                                               int32_t* __restrict__ code_sum, RowParams rp, int code_offset) {
+                                               int32_t* __restrict__ code_sum, RowParams rp, int code_offset, int group = 0) {
     using L = LargeRow<LOG2K, R>;
     constexpr int few_rows = 1;
     constexpr int K = L::K, E = L::E, NT = L::NT, W = L::W, CHUNKS = L::CHUNKS, RS = L::RS;
     static_assert(!BF6OUT || BITS == 4, "records carry INT4 codes only");
-    __shared__ double red_d[W];
-    __shared__ float red_f[W];
-    __shared__ int red_i[W];
+    __shared__ double red_ds[GROUPS][W];
+    __shared__ float red_fs[GROUPS][W];
+    __shared__ int red_is[GROUPS][W];
+    double* const red_d = red_ds[GROUPS == 1 ? 0 : group];
+    float* const red_f = red_fs[GROUPS == 1 ? 0 : group];
+    int* const red_i = red_is[GROUPS == 1 ? 0 : group];
     const int lane = tid & 63, wave = tid >> 6;
     const uint32_t pos = L::position(tid);
     const uint32_t first = L::in_wave(tid, 0) + wave * L::WAVE_FLOATS;
@@ -111,13 +138,13 @@ __device__ __forceinline__ void large_row_body(int64_t row, uint32_t tid, const 
     }
 
     if (NORM && rp.ln_gain) {   // uniform: RMS normalisation ahead of the transform
-        __shared__ double red_n[W];
+        __shared__ double red_n[GROUPS][W];
         double ss = 0.0;
 #pragma unroll
         for (int c = 0; c < CHUNKS; ++c)
 #pragma unroll
             for (int e = 0; e < 8; ++e) ss += (double)a[c][e] * (double)a[c][e];
-        const float rn = rms_factor<W>(ss, red_n, lane, wave, K, rp.ln_eps, few_rows);
+        const float rn = rms_factor<W>(ss, red_n[GROUPS == 1 ? 0 : group], lane, wave, K, rp.ln_eps, few_rows);
 #pragma unroll
         for (int c = 0; c < CHUNKS; ++c) {
             float g[8];

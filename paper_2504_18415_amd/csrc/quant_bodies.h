@@ -133,7 +133,7 @@ __device__ __forceinline__ float wave_max(float m, int few_rows) {
 }
 
 // Butterfly between lanes in one multiply-add per element (lane_butterfly4): v <- partner * c + v, c = -1 on the
-// lane whose index bit is set.  That lane then holds the negative of the reference's a - b; see the large-row body
+// lane whose index bit is set.  That lane then holds the negative of the reference's a - b; see large_rows.h
 // for why a lane may simply carry that sign until the values meet their 1/sqrt(K) factor.
 template <int CTRL, int R, int CH>
 __device__ __forceinline__ void lane_stage_fma(float (&v)[R][CH], bool upper) {
@@ -527,16 +527,20 @@ __device__ __forceinline__ void fwht_quant_body(int64_t row, int tid, const void
 // Plain BitLinear front end for K that is not a power of two (K % 128 == 0, K <= 16384): the same
 // quantiser with the row held as chunks of 8 elements by the threads of NW waves.
 // MAXC = chunk slots per thread (K <= 512 * NW * MAXC): the launcher picks the smallest that covers the row, so
-// that short rows do not walk empty slots; every MAXC performs the same arithmetic in the same order.
-template <int BITS, bool BF16, int MAXC = 8, int BLOCKB = kRecordBlockBytes, int NW = 4>
+// that short rows do not walk empty slots; every MAXC performs the same arithmetic in the same order.  GROUPS: rows that a
+// workgroup works on side by side, this one by the NW waves of `group`.
+template <int BITS, bool BF16, int MAXC = 8, int BLOCKB = kRecordBlockBytes, int NW = 4, int GROUPS = 1>
 __device__ __forceinline__ void quant_generic_body(int64_t row, int tid, const void* __restrict__ x, int K,
                                                    int8_t* __restrict__ codes, float* __restrict__ s_dequant,
-                                                   int32_t* __restrict__ code_sum, RowParams rp, int code_offset) {
+                                                   int32_t* __restrict__ code_sum, RowParams rp, int code_offset, int group = 0) {
     const int few_rows = rp.few_rows;
     constexpr int NT = 64 * NW;
-    __shared__ double red_d[NW];
-    __shared__ float red_f[NW];
-    __shared__ int red_i[NW];
+    __shared__ double red_ds[GROUPS][NW];
+    __shared__ float red_fs[GROUPS][NW];
+    __shared__ int red_is[GROUPS][NW];
+    double* const red_d = red_ds[GROUPS == 1 ? 0 : group];
+    float* const red_f = red_fs[GROUPS == 1 ? 0 : group];
+    int* const red_i = red_is[GROUPS == 1 ? 0 : group];
     const int lane = tid & 63, wave = tid >> 6;
     const int64_t row_off = row * K;
     const int nchunks = K / 8;
@@ -552,13 +556,13 @@ __device__ __forceinline__ void quant_generic_body(int64_t row, int tid, const v
         }
     }
     if (rp.ln_gain) {   // uniform: RMS normalisation of the row (chunks past the row hold zeros)
-        __shared__ double red_n[NW];
+        __shared__ double red_n[GROUPS][NW];
         double ss = 0.0;
 #pragma unroll
         for (int c = 0; c < MAXC; ++c)
 #pragma unroll
             for (int e = 0; e < 8; ++e) ss += (double)v[c][e] * (double)v[c][e];
-        const float rn = rms_factor<NW>(ss, red_n, lane, wave, K, rp.ln_eps, few_rows);
+        const float rn = rms_factor<NW>(ss, red_n[GROUPS == 1 ? 0 : group], lane, wave, K, rp.ln_eps, few_rows);
 #pragma unroll
         for (int c = 0; c < MAXC; ++c) {
             const int ch = c * NT + tid;
@@ -637,438 +641,6 @@ __device__ __forceinline__ void quant_generic_body(int64_t row, int tid, const v
             for (int w = 0; w < NW; ++w) isum += red_i[w];
             code_sum[row] = isum;
         }
-    }
-    if (tid == 0) s_dequant[row] = s_d;
-}
-
-// Large rows (K = 4096, 8192, 16384): every butterfly stage runs in registers.
-//
-// A thread holds 64 values = 16 float4 "chunks"; a chunk is 4 consecutive elements (index bits 0-1)
-// and the chunk number j carries four more index bits.  Two or three register layouts, with the row exchanged through
-// LDS between them (one float per element, 16-byte accesses, XOR-swizzled so that both sides are conflict
-// free), and four stages between lanes in the middle:
-//   layout A: j = index bits 2-5,   thread = bits 6..m-1   stages 0-5   (64 contiguous elements / thread)
-//   K = 16384: index bits 6-9 are the low four bits of A's thread number: stages 6-9 run lane to lane (below)
-//   K < 16384: layout B: j = index bits 6-9, thread = bits 2-5, 10.. stages 6-9, after an exchange of its own
-//   layout C: j = index bits 10..   (+ finished low bits when m < 14)   stages 10..m-1
-// Stage order stays ascending, so every value equals the one the reference order produces.
-// In float4 units (q = index >> 2) every layout is q = q_t(thread) ^ q_j(j) with disjoint bit sets,
-// and the swizzle q ^ ((q >> 4) & 15) is linear over xor: an LDS address is one xor of a per-thread
-// base with a compile-time constant.
-//
-// Lane stages.  The butterfly on a lane bit is one instruction per element: v <- partner * c + v with the
-// partner read through a DPP lane permutation and c = +1 where the bit is 0 (a + b) and -1 where it is 1
-// (b - a): the product is exact and the sum rounds once, so the lower lane holds the reference's a + b and
-// the upper lane the negative of its a - b.  Negation commutes with every later rounding, so a lane simply
-// carries the sign (-1)^(number of its index bits 6-9 that are set); in layout C those bits belong to the
-// thread number, all 64 values of a thread share the sign, the butterflies among them keep it, and it
-// leaves through the factor the values are multiplied with anyway (1/sqrt(K) or the quantiser's gain).
-// DPP offers xor 1, xor 2 (quad permutes), xor 7 (half-row mirror) and xor 8 (row rotation by 8) inside a row
-// of 16 lanes, so the thread that takes segment t of layout A is lane t ^ (3 if bit 2 of t is set): flipping
-// index bit 8 (bit 2 of t) then flips lane bits 0-2 together.
-//
-// Layout C at K = 4096 and 8192 has chunk bits to spare (16 chunks, 4 or 8 of them needed for the unfinished index
-// bits).  LINEAR: the spare bits are the highest finished ones, so consecutive lanes hold consecutive chunks and a
-// store instruction writes whole lines (always so at K = 16384).  Else they are the lowest: a thread holds 2 or 4
-// neighbouring chunks.  The transform alone stores 8 or 16 bytes per chunk and is bound by those stores: 4096 rows of
-// 4096, bf16 -> fp32, 29.4 -> 18.7 us (5.4 TB/s) with LINEAR.  The INT4 quantiser measures 0-2 % faster with it; INT8
-// codes (4 bytes per chunk) 1-3 % slower at K = 8192, so they keep the other form.
-template <int LOG2K, int LAYOUT, bool LINEAR = true>
-struct BigRowLayout {
-    static constexpr int M = LOG2K;
-    __host__ __device__ static constexpr uint32_t qj(int j) {
-        if (LAYOUT == 0) return (uint32_t)j;
-        if (LAYOUT == 1) return (uint32_t)j << 4;
-        if (M == 14) return (uint32_t)j << 8;
-        if (M == 13) return ((uint32_t)(j & 7) << 8) | ((uint32_t)(j >> 3) << (LINEAR ? 7 : 0));
-        return ((uint32_t)(j & 3) << 8) | ((uint32_t)(j >> 2) << (LINEAR ? 6 : 0));   // M == 12
-    }
-    __device__ static uint32_t qt(uint32_t tid) {
-        if (LAYOUT == 0) return tid << 4;
-        if (LAYOUT == 1) return (tid & 15u) | ((tid >> 4) << 8);
-        return LINEAR ? tid : tid << (14 - M);
-    }
-    // number of chunk bits that are unfinished index bits in this layout (stages to run on j)
-    static constexpr int stages() { return LAYOUT < 2 ? 4 : M - 10; }
-};
-__host__ __device__ constexpr uint32_t swz16(uint32_t q) { return q ^ ((q >> 4) & 15u); }
-
-// BF6OUT (INT4 only): instead of one byte per code, write the form the fp6 x fp4 GEMM reads - per 32
-// consecutive features a 24-byte record of bf6 (e3m2) values, feature i at bits [6i, 6i+6), placed in the
-// record image of code_records.h; every integer in [-8, 7] is exact in that format.
-// NORM: compiled with the RMS-normalisation prologue (taken when rp.ln_gain is set).  A template switch
-// rather than the run-time test alone: the prologue's presence changes the register allocation of the
-// whole body, and the plain prefill path should not pay for it.
-// One row's input as loaded, layout A: 64 contiguous elements per thread (8 or 16 16-byte loads).
-template <bool BF16>
-struct BigRowRaw {
-    uint4 q[BF16 ? 8 : 16];
-};
-// Whether stages 6-9 run between lanes (one exchange through LDS) or in registers after an exchange of their
-// own (two exchanges).  With the four waves of a K = 16384 row an exchange costs two workgroup barriers and the
-// lane form is 5-6 % faster; the one or two waves of a K = 4096 / 8192 row exchange cheaply, and there the lane
-// form measured 3 % / 7 % slower (a DPP multiply-add issues more slowly than an add).
-template <int LOG2K>
-constexpr bool kLaneStages = LOG2K >= 14;
-// Segment of layout A (64 contiguous elements) that thread `tid` holds; its own inverse.
-template <int LOG2K>
-__device__ __forceinline__ uint32_t bigrow_segment(uint32_t tid) {
-    return kLaneStages<LOG2K> ? tid ^ (((tid >> 2) & 1u) * 3u) : tid;
-}
-template <int LOG2K, bool BF16>
-__device__ __forceinline__ void bigrow_load(const void* __restrict__ x, int64_t row, uint32_t tid, BigRowRaw<BF16>& raw) {
-    constexpr int K = 1 << LOG2K;
-    const int64_t first = row * (int64_t)K + bigrow_segment<LOG2K>(tid) * 64;
-    const uint4* src = BF16 ? reinterpret_cast<const uint4*>(static_cast<const uint16_t*>(x) + first)
-                            : reinterpret_cast<const uint4*>(static_cast<const float*>(x) + first);
-#pragma unroll
-    for (int i = 0; i < (BF16 ? 8 : 16); ++i) raw.q[i] = src[i];
-}
-
-// The same through LDS, for a row that a workgroup has to itself: there the row's latency counts, and a load whose lanes
-// are 128 or 256 bytes apart takes one step of the address path per lane.  Each wave copies the segments of its own
-// threads as contiguous KiB pieces into its own part of the (still empty) row buffer - where it later writes its floats -
-// and reads them back; inside a segment the 16-byte chunks are permuted so that the lanes of a read hit different banks.
-// Grouped call, 8 tokens, four 7B projections: 21.6 -> 21.2 us per layer; 64 rows of 16384 fp32 with the norm 17.3 -> 16.6
-// us per call.  A row of 4096 bf16 is one wave and 8 KiB: 8.3 -> 8.5 us there, so it keeps the direct loads.
-template <int LOG2K, bool BF16>
-constexpr bool kRowThroughLds = LOG2K >= 14 || (LOG2K == 13 && !BF16);
-template <int LOG2K, bool BF16>
-__device__ __forceinline__ void bigrow_copy(const void* __restrict__ x, int64_t row, uint32_t tid, char* row_buffer) {
-    constexpr int K = 1 << LOG2K;
-    constexpr int CH = BF16 ? 8 : 16;         // 16-byte chunks of a segment of 64 elements
-    const uint32_t lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const char* src = static_cast<const char*>(x) + (row * K + wave * 4096) * (BF16 ? 2 : 4);
-    // a wave's part: 64 segments of 64 floats
-    const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)(row_buffer + wave * 16384);
-#pragma unroll
-    for (int i = 0; i < CH; ++i) {
-        const uint32_t pos = i * 64 + lane;   // chunk pos of the part holds chunk (pos % CH) ^ (segment % CH)
-        gemm::lds_dma16(lds0 + i * 1024, src, (pos ^ ((pos / CH) & (CH - 1))) * 16);
-    }
-}
-template <int LOG2K, bool BF16>
-__device__ __forceinline__ void bigrow_read(uint32_t tid, const char* row_buffer, BigRowRaw<BF16>& raw) {
-    constexpr int CH = BF16 ? 8 : 16;
-    const uint32_t seg = bigrow_segment<LOG2K>(tid) & 63;
-    const char* part = row_buffer + __builtin_amdgcn_readfirstlane(tid >> 6) * 16384 + seg * CH * 16;
-#pragma unroll
-    for (int i = 0; i < CH; ++i) raw.q[i] = *reinterpret_cast<const uint4*>(part + ((i ^ (seg & (CH - 1))) << 4));
-}
-template <int LOG2K, bool BF16>
-__device__ __forceinline__ void bigrow_load_lds(const void* __restrict__ x, int64_t row, uint32_t tid, char* row_buffer,
-                                                BigRowRaw<BF16>& raw) {
-    bigrow_copy<LOG2K, BF16>(x, row, tid, row_buffer);
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    bigrow_read<LOG2K, BF16>(tid, row_buffer, raw);
-}
-
-// `before_tail` is called once, by every thread, after the last exchange through LDS and ahead of the last
-// butterfly stages, the row statistics and the quantiser: the place from which a caller that walks several
-// rows starts the loads of its next row (few registers are live there besides the row itself).
-struct NoPrefetch {
-    __device__ void operator()() const {}
-};
-// ROWLOOP: the caller runs this body for one row after another, so the row buffer still has readers from
-// the previous row until every thread has passed a barrier.
-template <int LOG2K, int BITS, bool BF16, bool BF6OUT, bool NORM, bool ROWLOOP = false, int BLOCKB = kRecordBlockBytes,
-          typename BeforeTail = NoPrefetch>
-__device__ __forceinline__ void fwht_quant_bigrow_body(int64_t row, uint32_t tid, const BigRowRaw<BF16>& raw, float* row_lds,
-                                                       int8_t* __restrict__ codes, float* __restrict__ s_dequant,
-                                                       int32_t* __restrict__ code_sum, RowParams rp, int code_offset,
-                                                       BeforeTail before_tail = BeforeTail{}) {
-    constexpr int few_rows = ROWLOOP ? 0 : 1;   // the row loop is the throughput form
-    constexpr int K = 1 << LOG2K;
-    constexpr int NT = K / 64;
-    constexpr int W = NT / 64;
-    using LA = BigRowLayout<LOG2K, 0>;
-    using LB = BigRowLayout<LOG2K, 1>;
-    using LC = BigRowLayout<LOG2K, 2, BITS != 8>;
-    // row_lds: K floats of LDS
-    __shared__ double red_d[W];
-    __shared__ float red_f[W];
-    __shared__ int red_i[W];
-
-    const int lane = tid & 63, wave = tid >> 6;
-    const int64_t row_off = row * (int64_t)K;
-
-    float v[16][4];
-    if constexpr (BF16) {
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            const uint32_t w[4] = {raw.q[i].x, raw.q[i].y, raw.q[i].z, raw.q[i].w};
-#pragma unroll
-            for (int h = 0; h < 4; ++h) {
-                v[2 * i + h / 2][2 * (h % 2)] = as_f(w[h] << 16);
-                v[2 * i + h / 2][2 * (h % 2) + 1] = as_f(w[h] & 0xFFFF0000u);
-            }
-        }
-    } else {
-#pragma unroll
-        for (int j = 0; j < 16; ++j) {
-            v[j][0] = as_f(raw.q[j].x); v[j][1] = as_f(raw.q[j].y); v[j][2] = as_f(raw.q[j].z); v[j][3] = as_f(raw.q[j].w);
-        }
-    }
-
-    if (NORM && rp.ln_gain) {   // uniform: RMS normalisation ahead of the transform (layout A: elements tid*64 + 4j + e)
-        __shared__ double red_n[W];
-        double ss = 0.0;
-#pragma unroll
-        for (int j = 0; j < 16; ++j)
-#pragma unroll
-            for (int e = 0; e < 4; ++e) ss += (double)v[j][e] * (double)v[j][e];
-        const float rn = rms_factor<W>(ss, red_n, lane, wave, K, rp.ln_eps, few_rows);
-        const float4* gsrc = reinterpret_cast<const float4*>(rp.ln_gain + bigrow_segment<LOG2K>(tid) * 64);
-#pragma unroll
-        for (int j = 0; j < 16; ++j) {
-            const float4 gq = gsrc[j];
-            v[j][0] = (v[j][0] * rn) * gq.x;
-            v[j][1] = (v[j][1] * rn) * gq.y;
-            v[j][2] = (v[j][2] * rn) * gq.z;
-            v[j][3] = (v[j][3] * rn) * gq.w;
-        }
-    }
-
-    auto stages_e = [&]() {   // index bits 0, 1: inside a chunk
-#pragma unroll
-        for (int j = 0; j < 16; ++j) {
-            const float a0 = v[j][0] + v[j][1], a1 = v[j][0] - v[j][1];
-            const float a2 = v[j][2] + v[j][3], a3 = v[j][2] - v[j][3];
-            v[j][0] = a0 + a2; v[j][2] = a0 - a2;
-            v[j][1] = a1 + a3; v[j][3] = a1 - a3;
-        }
-    };
-    auto stages_j = [&](int nstages) {   // the low `nstages` bits of the chunk number, ascending
-#pragma unroll
-        for (int b = 0; b < 4; ++b) {
-            if (b >= nstages) break;
-#pragma unroll
-            for (int j = 0; j < 16; ++j)
-                if (!(j & (1 << b))) {
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        const float a = v[j][e], c = v[j | (1 << b)][e];
-                        v[j][e] = a + c;
-                        v[j | (1 << b)][e] = a - c;
-                    }
-                }
-        }
-    };
-    // index bits 6-9: between lanes (see above); CTRL = the DPP permutation that reaches the partner, `upper` =
-    // this lane's index bit is set
-    auto stage_lane = [&](auto ctrl_tag, bool upper) {
-        constexpr int CTRL = decltype(ctrl_tag)::value;
-        const float c = upper ? -1.0f : 1.0f;
-#pragma unroll
-        for (int j = 0; j < 16; ++j) lane_butterfly4<CTRL>(v[j], c);
-    };
-    auto lds_write = [&](auto layout_tag, uint32_t thread) {
-        using L = decltype(layout_tag);
-        const uint32_t base = swz16(L::qt(thread)) << 4;   // bytes
-#pragma unroll
-        for (int j = 0; j < 16; ++j) {
-            constexpr uint32_t dummy = 0;
-            (void)dummy;
-            float4* dst = reinterpret_cast<float4*>(reinterpret_cast<char*>(row_lds) + (base ^ (swz16(L::qj(j)) << 4)));
-            *dst = make_float4(v[j][0], v[j][1], v[j][2], v[j][3]);
-        }
-    };
-    auto lds_read = [&](auto layout_tag) {
-        using L = decltype(layout_tag);
-        const uint32_t base = swz16(L::qt(tid)) << 4;
-#pragma unroll
-        for (int j = 0; j < 16; ++j) {
-            const float4 t = *reinterpret_cast<const float4*>(reinterpret_cast<const char*>(row_lds) +
-                                                              (base ^ (swz16(L::qj(j)) << 4)));
-            v[j][0] = t.x; v[j][1] = t.y; v[j][2] = t.z; v[j][3] = t.w;
-        }
-    };
-
-    stages_e();
-    stages_j(4);              // index bits 2-5
-    if constexpr (kLaneStages<LOG2K>) {
-        const uint32_t seg = bigrow_segment<LOG2K>(tid);
-        stage_lane(std::integral_constant<int, 0xB1>{}, seg & 1u);    // index bit 6: lane ^ 1 (quad_perm [1,0,3,2])
-        stage_lane(std::integral_constant<int, 0x4E>{}, seg & 2u);    // index bit 7: lane ^ 2 (quad_perm [2,3,0,1])
-        stage_lane(std::integral_constant<int, 0x141>{}, seg & 4u);   // index bit 8: lane ^ 7 (row_half_mirror)
-        stage_lane(std::integral_constant<int, 0x128>{}, seg & 8u);   // index bit 9: lane ^ 8 (row_ror:8)
-        if constexpr (ROWLOOP) __syncthreads();   // after this row's first stages: the wait is mostly over by then
-        lds_write(LA{}, seg);
-    } else {
-        if constexpr (ROWLOOP) __syncthreads();
-        lds_write(LA{}, tid);
-        __syncthreads();
-        lds_read(LB{});
-        stages_j(4);              // index bits 6-9
-        lds_write(LB{}, tid);     // to the very addresses this thread has just read: no barrier needed before it
-    }
-    __syncthreads();
-    lds_read(LC{});
-    before_tail();
-    stages_j(LC::stages());   // index bits 10..m-1
-
-    // c_n = (float)(1/sqrt(K)).  For even log2 K it is a power of two: scaling by it commutes exactly
-    // with every later rounding (max, fp64 sum, the gain product), so it is applied to the row
-    // statistics and folded into the gain instead of costing one multiply per element.
-    const float c_n = (float)(1.0 / sqrt((double)K));
-    // the sign this thread's values carry out of the lane stages: parity of index bits 6-9, which in layout C
-    // are bits 4-7 of q_t(thread); it leaves with the factor below (exactly: a sign flip)
-    const float c_s = (kLaneStages<LOG2K> && (__builtin_popcount((LC::qt(tid) >> 4) & 15u) & 1)) ? -c_n : c_n;
-    constexpr bool FOLD = (LOG2K % 2) == 0 && BITS != 0;
-    if constexpr (!FOLD) {
-#pragma unroll
-        for (int j = 0; j < 16; ++j)
-#pragma unroll
-            for (int e = 0; e < 4; ++e) v[j][e] = v[j][e] * c_s;
-    }
-
-    if constexpr (BITS == 0) {
-        // transform only: `codes` is the output array and `code_offset` its element type
-#pragma unroll
-        for (int j = 0; j < 16; ++j)
-            store_xr<4>(codes, code_offset, row_off + (int64_t)((LC::qt(tid) ^ LC::qj(j)) << 2), v[j]);
-        return;
-    }
-
-    float gain, s_d;
-    if constexpr (BITS == 8) {
-        float m = 0.0f;
-#pragma unroll
-        for (int j = 0; j < 16; ++j)
-#pragma unroll
-            for (int e = 0; e < 4; ++e) m = fmaxf(m, fabsf(v[j][e]));
-        m = wave_max(m, few_rows);
-        if constexpr (W > 1) {
-            if (lane == 0) red_f[wave] = m;
-            __syncthreads();
-            m = red_f[0];
-#pragma unroll
-            for (int w = 1; w < W; ++w) m = fmaxf(m, red_f[w]);
-        }
-        if constexpr (FOLD) m = m * c_n;
-        gain = 127.0f / (m + rp.eps);
-        s_d = m / 127.0f;
-    } else {
-        double s = 0.0;
-#pragma unroll
-        for (int j = 0; j < 16; ++j)
-#pragma unroll
-            for (int e = 0; e < 4; ++e) s += (double)fabsf(v[j][e]);
-        s = wave_sum(s, few_rows);
-        if constexpr (W > 1) {
-            if (lane == 0) red_d[wave] = s;
-            __syncthreads();
-            s = red_d[0];
-#pragma unroll
-            for (int w = 1; w < W; ++w) s += red_d[w];
-        }
-        if constexpr (FOLD) s = s * (double)c_n;
-        const float beta = (float)(s / (double)K);
-        gain = kRoot7 / (beta + rp.eps);
-        s_d = beta / kRoot7;
-    }
-
-    constexpr float lo = BITS == 8 ? -128.0f : -8.0f;
-    constexpr float hi = BITS == 8 ? 127.0f : 7.0f;
-    static_assert(!BF6OUT || BITS == 4 || BITS == 0, "bf6 records carry INT4 codes only");
-    const float magic = kMagic + (float)code_offset;   // byte forms: the low byte of t + magic is code + offset
-    if constexpr (FOLD) gain = gain * c_s;   // (the statistics above took |v| and the positive c_n)
-    int isum = 0;
-    int8_t* out = codes + row_off + (LC::qt(tid) << 2);
-    uint32_t* c24 = reinterpret_cast<uint32_t*>(row_lds);   // BF6OUT: 24 bits of bf6 per chunk, by chunk number
-    const uint32_t cbase = LC::qt(tid);
-    if constexpr (!BF6OUT) {
-#pragma unroll
-        for (int j = 0; j < 16; ++j) {
-            uint32_t packed = 0;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const float t = __builtin_amdgcn_fmed3f(v[j][e] * gain, lo, hi);
-                const uint32_t bits = as_u(t + magic);
-                packed |= (bits & 0xFFu) << (8 * e);
-            }
-            if (code_sum) isum = __builtin_amdgcn_sdot4((int)packed, 0x01010101, isum, false);   // += the 4 stored bytes
-            *reinterpret_cast<uint32_t*>(out + (LC::qj(j) << 2)) = packed;
-        }
-        isum -= 64 * code_offset;
-    } else {
-        // The codes as fp32 integers (round to nearest even by adding and removing 1.5 * 2^23, which
-        // also turns -0 into +0), then the hardware's 32-value fp32 -> bf6 conversion: exact for
-        // integers in [-8, 7].  Its result holds source pair i (one value from each operand) at bits
-        // [12i, 12i+12), so with the even elements of 8 chunks in one operand and the odd ones in the
-        // other, chunk c of the 8 lands in order at bits [24c, 24c+24) of the six result dwords.
-        typedef float v16f __attribute__((ext_vector_type(16)));
-        typedef uint32_t v6u __attribute__((ext_vector_type(6)));
-        float fsum = 0.0f;
-#pragma unroll
-        for (int half = 0; half < 2; ++half) {
-            v16f ev, od;
-#pragma unroll
-            for (int jj = 0; jj < 8; ++jj) {
-                float q[4];
-#pragma unroll
-                for (int e = 0; e < 4; ++e)
-                    q[e] = (__builtin_amdgcn_fmed3f(v[8 * half + jj][e] * gain, lo, hi) + kMagic) - kMagic;
-                ev[2 * jj] = q[0]; od[2 * jj] = q[1];
-                ev[2 * jj + 1] = q[2]; od[2 * jj + 1] = q[3];
-            }
-            if (code_sum) {   // uniform, and off on the forward path: small integers, exact in any order
-#pragma unroll
-                for (int i = 0; i < 16; ++i) fsum += ev[i] + od[i];
-            }
-            const v6u r = __builtin_amdgcn_cvt_scalef32_2xpk16_bf6_f32(ev, od, 1.0f);
-            // one dword per chunk into LDS by chunk number; bits 24-31 of it are not meaningful
-            const uint32_t piece[8] = {r[0], __builtin_amdgcn_alignbit(r[1], r[0], 24),
-                                       __builtin_amdgcn_alignbit(r[2], r[1], 16), r[2] >> 8,
-                                       r[3], __builtin_amdgcn_alignbit(r[4], r[3], 24),
-                                       __builtin_amdgcn_alignbit(r[5], r[4], 16), r[5] >> 8};
-#pragma unroll
-            for (int jj = 0; jj < 8; ++jj) c24[cbase ^ LC::qj(8 * half + jj)] = piece[jj];
-        }
-        isum = (int)fsum;
-        // Regroup through LDS.  Eight consecutive chunks (32 features, 24 bytes: one record) become six dwords,
-        // stored as the record's 16-byte and 8-byte piece by every lane (56 fewer vector instructions per row than
-        // the form below, whose even and odd lanes store different pieces: 2-6 % faster at K <= 8192; at K = 16384
-        // with fp32 rows 5 % faster, and it needs no spill there).  K = 16384 with bf16 rows keeps four chunks (16
-        // features, 12 bytes) per lane and step: there the record form measured 8 % slower (0.125 against 0.116 ms
-        // for 8192 rows) although it executes fewer instructions.
-        __syncthreads();
-        if constexpr (LOG2K < 14 || !BF16) {
-#pragma unroll
-            for (int i = 0; i < 2; ++i) {
-                const uint32_t rec = tid + NT * i;
-                const uint4 c = *reinterpret_cast<const uint4*>(c24 + 8 * rec);
-                const uint4 e = *reinterpret_cast<const uint4*>(c24 + 8 * rec + 4);
-                store_code_record<BLOCKB>(codes, row, K, (int)rec,
-                                  __builtin_amdgcn_perm(c.y, c.x, 0x04020100u),    // x0 x1 x2 y0
-                                  __builtin_amdgcn_perm(c.z, c.y, 0x05040201u),    // y1 y2 z0 z1
-                                  __builtin_amdgcn_perm(c.w, c.z, 0x06050402u),    // z2 w0 w1 w2
-                                  __builtin_amdgcn_perm(e.y, e.x, 0x04020100u),
-                                  __builtin_amdgcn_perm(e.z, e.y, 0x05040201u),
-                                  __builtin_amdgcn_perm(e.w, e.z, 0x06050402u));
-            }
-        } else {
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const uint32_t quad = tid + NT * i;
-                const uint4 c = *reinterpret_cast<const uint4*>(c24 + 4 * quad);
-                store_code_quad<BLOCKB>(codes, row, K, (int)quad,
-                                __builtin_amdgcn_perm(c.y, c.x, 0x04020100u),
-                                __builtin_amdgcn_perm(c.z, c.y, 0x05040201u),
-                                __builtin_amdgcn_perm(c.w, c.z, 0x06050402u));
-            }
-        }
-    }
-    if (code_sum) {   // uniform: the fp6 x fp4 GEMM needs no code sum
-        isum = wave_sum(isum, few_rows);
-        if constexpr (W > 1) {
-            if (lane == 0) red_i[wave] = isum;
-            __syncthreads();
-            isum = 0;
-#pragma unroll
-            for (int w = 0; w < W; ++w) isum += red_i[w];
-        }
-        if (tid == 0) code_sum[row] = isum;
     }
     if (tid == 0) s_dequant[row] = s_d;
 }

@@ -672,6 +672,8 @@ def test_17_to_32_tokens_stream_against_many_rows(hbl, T, K, N):
     (1, 512, 32, 1, True), (3, 1024, 96, 3, True), (4, 2048, 64, 2, True), (2, 2048, 16352, 1, True),
     (1, 512, 16416, 1, True), (4, 1024, 12320, 1, True), (2, 512, 12320, 1, False), (3, 1280, 8224, 1, False),   # 32 rows
     (1, 4096, 96, 1, True), (4, 4096, 64, 1, True), (1, 8192, 160, 1, True), (1, 16384, 96, 1, True),
+    (2, 4096, 96, 1, True), (2, 8192, 96, 3, True), (1, 2048, 64, 1, True), (1, 16256, 64, 1, False), (3, 3968, 96, 1, False),
+    (4, 640, 4096, 1, False), (1, 8192, 8160, 1, False), (2, 4096, 4128, 1, True), (2, 2048, 8224, 1, False),   # rows side by side
 ])
 @pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
 def test_one_launch_small_batches(hbl, T, K, N, groups, hadamard, dtype):
