@@ -25,11 +25,19 @@ __device__ __forceinline__ uint32_t quad_lane(uint32_t v) {   // value of one fi
     return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, CTRL, 0xF, 0xF, false);
 }
 
+// Head states read back leave with the non-temporal hint: written once and not read by the kernel, they need not stay in L2
+// until the launch ends and has to write them back (262144 rows of 128, 4 bits, both launches 30.1 -> 28.8 us; the packed codes
+// with the hint too 33.2: the next launch reads them).
+__device__ __forceinline__ void store_stream(void* dst, uint32_t a, uint32_t b, uint32_t c, uint32_t d) {
+    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+    __builtin_nontemporal_store((u32x4){a, b, c, d}, reinterpret_cast<u32x4*>(dst));
+}
+
 constexpr int kItems = 1;   // 16-byte pieces per thread, all loaded before any arithmetic (2 measured no faster:
                             // the kernel already runs at the rate a plain copy reaches on this chip)
 
 template <int BITS, bool BF16>
-__global__ __launch_bounds__(256) void kv_quant_kernel(const void* __restrict__ x, int64_t threads, int lanes_per_row,
+__global__ __launch_bounds__(256) void kv_quant_kernel(const void* __restrict__ x, int64_t threads, int log2_lanes,
                                                        float eps, uint8_t* __restrict__ packed,
                                                        float* __restrict__ scales) {
     const int64_t t0 = (int64_t)blockIdx.x * (256 * kItems) + threadIdx.x;
@@ -67,12 +75,12 @@ __global__ __launch_bounds__(256) void kv_quant_kernel(const void* __restrict__ 
         float gamma = 0.0f;
 #pragma unroll
         for (int i = 0; i < 8; ++i) gamma = fmaxf(gamma, fabsf(h[i]));
-        for (int m = 1; m < lanes_per_row; m <<= 1) gamma = fmaxf(gamma, __shfl_xor(gamma, m, 64));
+        for (int m = 1; m < (1 << log2_lanes); m <<= 1) gamma = fmaxf(gamma, __shfl_xor(gamma, m, 64));
 
         constexpr int half = 1 << (BITS - 1);
         constexpr float qmax = (float)(half - 1);
         const float s_q = qmax / (gamma + eps);
-        if (live && (t % lanes_per_row) == 0) scales[t / lanes_per_row] = gamma / qmax;
+        if (live && (t & ((1 << log2_lanes) - 1)) == 0) scales[t >> log2_lanes] = gamma / qmax;
 
         // t + (1.5*2^23 + half): the fp32 adder rounds to nearest even and leaves code + half in the low mantissa bits
         uint32_t u[8];
@@ -88,7 +96,7 @@ __global__ __launch_bounds__(256) void kv_quant_kernel(const void* __restrict__ 
             uint32_t w = 0;
 #pragma unroll
             for (int i = 0; i < 8; ++i) w |= u[i] << (4 * i);
-            if (live) reinterpret_cast<uint32_t*>(packed)[t] = w;
+                        if (live) reinterpret_cast<uint32_t*>(packed)[t] = w;
         } else {
             uint32_t w = 0;
 #pragma unroll
@@ -105,7 +113,7 @@ __global__ __launch_bounds__(256) void kv_quant_kernel(const void* __restrict__ 
 template <int BITS, bool BF16OUT>
 __global__ __launch_bounds__(256) void kv_dequant_kernel(const uint8_t* __restrict__ packed,
                                                          const float* __restrict__ scales, int64_t threads,
-                                                         int lanes_per_row, void* __restrict__ out) {
+                                                         int log2_lanes, void* __restrict__ out) {
     const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (t >= threads) return;
     uint32_t u[8];
@@ -132,7 +140,7 @@ __global__ __launch_bounds__(256) void kv_dequant_kernel(const uint8_t* __restri
 #pragma unroll
         for (int i = 0; i < 8; ++i) u[i] = (w >> (3 * i)) & 0x7u;
     }
-    const float scale = scales[t / lanes_per_row];
+    const float scale = scales[t >> log2_lanes];
     constexpr float half = (float)(1 << (BITS - 1));
     float v[8];
 #pragma unroll
@@ -144,10 +152,10 @@ __global__ __launch_bounds__(256) void kv_dequant_kernel(const uint8_t* __restri
 #pragma unroll
         for (int i = 0; i < 4; ++i)
             w[i] = __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2){v[2 * i], v[2 * i + 1]}, bf16x2));
-        reinterpret_cast<uint4*>(out)[t] = make_uint4(w[0], w[1], w[2], w[3]);
+        store_stream(reinterpret_cast<uint4*>(out) + t, w[0], w[1], w[2], w[3]);
     } else {
-        reinterpret_cast<float4*>(out)[2 * t] = make_float4(v[0], v[1], v[2], v[3]);
-        reinterpret_cast<float4*>(out)[2 * t + 1] = make_float4(v[4], v[5], v[6], v[7]);
+        store_stream(reinterpret_cast<uint4*>(out) + 2 * t, as_u(v[0]), as_u(v[1]), as_u(v[2]), as_u(v[3]));
+        store_stream(reinterpret_cast<uint4*>(out) + 2 * t + 1, as_u(v[4]), as_u(v[5]), as_u(v[6]), as_u(v[7]));
     }
 }
 
@@ -163,7 +171,8 @@ int launch_kv_quant(const void* x, int x_dtype, int64_t rows, int64_t d, int bit
     const int64_t threads = rows * (d / 8);
     if (threads == 0) return HBL_OK;
     const dim3 grid((unsigned)((threads + 256 * kItems - 1) / (256 * kItems))), block(256);
-    const int lpr = (int)(d / 8);
+    int lpr = 0;   // log2 of the threads per row (a power of two)
+    while ((8 << lpr) < d) ++lpr;
     uint8_t* out = static_cast<uint8_t*>(packed);
     const bool bf = x_dtype == HBL_BF16;
 #define HBL_KVQ(B)                                                                                               \
@@ -179,7 +188,8 @@ int launch_kv_dequant(const void* packed, const float* scales, int64_t rows, int
     const int64_t threads = rows * (d / 8);
     if (threads == 0) return HBL_OK;
     const dim3 grid((unsigned)((threads + 255) / 256)), block(256);
-    const int lpr = (int)(d / 8);
+    int lpr = 0;   // log2 of the threads per row (a power of two)
+    while ((8 << lpr) < d) ++lpr;
     const uint8_t* in = static_cast<const uint8_t*>(packed);
     const bool bf = out_dtype == HBL_BF16;
 #define HBL_KVD(B)                                                                                              \
