@@ -140,7 +140,10 @@ __global__ __launch_bounds__(64 * fused_waves(LOG2K, PW, RB)) void fused_small_k
     int8_t* const codes = reinterpret_cast<int8_t*>(lds + a.codes_off);
     const RowParams rp{a.eps, nullptr, 0.0f, 1};
     if constexpr (LOG2K == 0) {
-        quant_generic_body<4, BF16, 2, BLOCK, PW, SLOTS>(0, rtid, slot, K, codes + row * kRecordRowBytes, s_d + row, nullptr, rp, kCodesBf6, sub);
+        if (K > 512 * PW)   // uniform
+            quant_generic_body<4, BF16, 2, BLOCK, PW, SLOTS>(0, rtid, slot, K, codes + row * kRecordRowBytes, s_d + row, nullptr, rp, kCodesBf6, sub);
+        else
+            quant_generic_body<4, BF16, 1, BLOCK, PW, SLOTS>(0, rtid, slot, K, codes + row * kRecordRowBytes, s_d + row, nullptr, rp, kCodesBf6, sub);
     } else if constexpr (!LARGE) {
         fwht_quant_body<LOG2K, 1, 4, BF16, true, BLOCK>(0, rtid, slot, codes + row * kRecordRowBytes, s_d + row, nullptr, rp, kCodesBf6);
     } else {

@@ -44,38 +44,70 @@ int launch_one(const void* x, int64_t T, int8_t* codes, float* s_dequant, int32_
     return after_launch();
 }
 
-template <int BITS, bool BF16, int MAXC>
-__global__ __launch_bounds__(256) void quant_generic_kernel(const void* __restrict__ x, int K,
-                                                            int8_t* __restrict__ codes,
-                                                            float* __restrict__ s_dequant,
-                                                            int32_t* __restrict__ code_sum, RowParams rp, int code_offset) {
-    quant_generic_body<BITS, BF16, MAXC>(blockIdx.x, threadIdx.x, x, K, codes, s_dequant, code_sum, rp, code_offset);
+template <int BITS, bool BF16, int MAXC, int NW>
+__global__ __launch_bounds__(64 * NW) void quant_generic_kernel(const void* __restrict__ x, int K,
+                                                               int8_t* __restrict__ codes,
+                                                               float* __restrict__ s_dequant,
+                                                               int32_t* __restrict__ code_sum, RowParams rp, int code_offset) {
+    quant_generic_body<BITS, BF16, MAXC, kRecordBlockBytes, NW>(blockIdx.x, threadIdx.x, x, K, codes, s_dequant, code_sum, rp, code_offset);
 }
 
-template <int BITS, bool BF16>
+template <int BITS, bool BF16, int NW>
 void launch_generic_slots(const void* x, int64_t T, int64_t K, RowParams rp, int8_t* codes, float* s_dequant,
                           int32_t* code_sum, int code_offset, hipStream_t stream) {
-    const dim3 grid((unsigned)T), block(256);
-    const int64_t per_thread = (K / 8 + 255) / 256;   // 8-element chunks per thread
+    const dim3 grid((unsigned)T), block(64 * NW);
 #define HBL_GENERIC(MAXC)                                                                                     \
-    launch_kernel("quant_generic_kernel", (quant_generic_kernel<BITS, BF16, MAXC>), grid, block, 0, stream, x, (int)K, codes, s_dequant, \
-                       code_sum, rp, code_offset)
-    if (per_thread <= 1) HBL_GENERIC(1);
-    else if (per_thread <= 2) HBL_GENERIC(2);
-    else if (per_thread <= 4) HBL_GENERIC(4);
-    else HBL_GENERIC(8);
+    case MAXC:                                                                                                \
+        if constexpr (512 * NW * (MAXC - 1) < 16384)                                                          \
+            launch_kernel("quant_generic_kernel", (quant_generic_kernel<BITS, BF16, MAXC, NW>), grid, block, 0, stream, x, (int)K, \
+                          codes, s_dequant, code_sum, rp, code_offset);                                       \
+        break;
+    switch ((K / 8 + 64 * NW - 1) / (64 * NW)) {   // 8-element chunks per thread
+        HBL_GENERIC(1)
+        HBL_GENERIC(2)
+        HBL_GENERIC(3)
+        HBL_GENERIC(4)
+        HBL_GENERIC(5)
+        HBL_GENERIC(6)
+        HBL_GENERIC(7)
+        HBL_GENERIC(8)
+    }
 #undef HBL_GENERIC
+}
+// Waves per row.  Few rows: many waves of few values finish a row sooner.  Many rows: the reductions, the divisions and the norm's
+// square root are the same work for every wave, so fewer waves of more values do it less often.  Time against four waves (bf16,
+// records; without / with the norm):
+//   64 rows:    16 waves: 3072 0.98 / 1.03  5504 0.95 / 1.01  11008 0.91 / 0.96  16256 0.87 / 0.91;  1 wave: 384 0.98 / 0.94  640 1.07
+//   512 rows:   16 waves: 11008 1.05 / 1.16  16256 0.99 / 1.06;  2 waves: 640 0.99  1920 1.10
+//   1024 rows:  2 waves: 640 0.92 / 0.86  1152 0.94 / 0.89  1920 0.96 / 0.91  3072 0.95 / 0.88;  1 wave: 0.95 / 0.86  0.97 / 0.89  1.03 / 0.94  1.04 / 0.97
+//   3001 rows:  1 wave: 640 0.84 / 0.75  1152 0.87 / 0.77  1920 0.92 / 0.81  3072 0.93 / 0.83 (2 waves 0.93 / 0.86);  2 waves: 5504 1.04 / 0.99
+//   8192 rows:  1 wave: 384 0.60 / 0.50  1152 0.74 / 0.65  3072 0.95 / 0.81;  2 waves: 5504 1.00 / 0.95  8064 1.03 / 1.02
+// (fp32 rows, whose chunks are two loads each: 4096 of 3072 1.02 by one wave, and two as for fewer rows.)
+int generic_waves(int64_t T, int64_t K, bool bf16) {
+    if (K > 4096) return T <= 256 ? 16 : 4;
+    if (K <= 512 || (T >= 2048 && (bf16 || K <= 2048))) return 1;
+    return T >= 1024 ? 2 : 4;
+}
+template <int BITS, bool BF16>
+void launch_generic_waves(const void* x, int64_t T, int64_t K, RowParams rp, int8_t* codes, float* s_dequant,
+                          int32_t* code_sum, int code_offset, hipStream_t stream) {
+    switch (generic_waves(T, K, BF16)) {
+        case 1: return launch_generic_slots<BITS, BF16, 1>(x, T, K, rp, codes, s_dequant, code_sum, code_offset, stream);
+        case 2: return launch_generic_slots<BITS, BF16, 2>(x, T, K, rp, codes, s_dequant, code_sum, code_offset, stream);
+        case 4: return launch_generic_slots<BITS, BF16, 4>(x, T, K, rp, codes, s_dequant, code_sum, code_offset, stream);
+        default: return launch_generic_slots<BITS, BF16, 16>(x, T, K, rp, codes, s_dequant, code_sum, code_offset, stream);
+    }
 }
 
 int launch_generic(const void* x, int x_dtype, int64_t T, int64_t K, int bits, RowParams rp, int8_t* codes,
                    float* s_dequant, int32_t* code_sum, int code_offset, hipStream_t stream) {
     const bool bf = x_dtype == HBL_BF16;
     if (bits == 8) {
-        if (bf) launch_generic_slots<8, true>(x, T, K, rp, codes, s_dequant, code_sum, code_offset, stream);
-        else    launch_generic_slots<8, false>(x, T, K, rp, codes, s_dequant, code_sum, code_offset, stream);
+        if (bf) launch_generic_waves<8, true>(x, T, K, rp, codes, s_dequant, code_sum, code_offset, stream);
+        else    launch_generic_waves<8, false>(x, T, K, rp, codes, s_dequant, code_sum, code_offset, stream);
     } else {
-        if (bf) launch_generic_slots<4, true>(x, T, K, rp, codes, s_dequant, code_sum, code_offset, stream);
-        else    launch_generic_slots<4, false>(x, T, K, rp, codes, s_dequant, code_sum, code_offset, stream);
+        if (bf) launch_generic_waves<4, true>(x, T, K, rp, codes, s_dequant, code_sum, code_offset, stream);
+        else    launch_generic_waves<4, false>(x, T, K, rp, codes, s_dequant, code_sum, code_offset, stream);
     }
     return after_launch();
 }
@@ -180,11 +212,15 @@ __global__ __launch_bounds__(1024) void quant_grouped_kernel(const QuantGroupArg
     const int tid = threadIdx.x;
     const RowParams rp{a.eps, p.ln_gain, p.ln_eps, 1};
     if (!p.hadamard) {
-        if (p.K > 4096) {
-            quant_generic_body<BITS, BF16, 2, kRecordBlockBytes, 16>(row, tid, p.x, p.K, p.codes, p.s_dequant, p.code_sum, rp, p.code_offset);
-        } else if (tid < 256) {
-            quant_generic_body<BITS, BF16, 2>(row, tid, p.x, p.K, p.codes, p.s_dequant, p.code_sum, rp, p.code_offset);
+#define HBL_PLAIN_ROW(MAXC, NW) \
+    quant_generic_body<BITS, BF16, MAXC, kRecordBlockBytes, NW>(row, tid, p.x, p.K, p.codes, p.s_dequant, p.code_sum, rp, p.code_offset)
+        if (p.K > 8192) HBL_PLAIN_ROW(2, 16);
+        else if (p.K > 4096) HBL_PLAIN_ROW(1, 16);
+        else if (tid < 256) {
+            if (p.K > 2048) HBL_PLAIN_ROW(2, 4);
+            else HBL_PLAIN_ROW(1, 4);
         }
+#undef HBL_PLAIN_ROW
         return;
     }
 #define HBL_SMALL_ROW(L2K)                                                                                    \
@@ -277,13 +313,18 @@ int launch_fwht_only(const void* x, int x_dtype, int64_t T, int64_t K, void* out
 // 0.82 to 1.00 for most lengths, but 0.98 to 1.04 for transformed rows of 1024.
 constexpr int64_t kShortReductionRows = 4096;
 
+constexpr int64_t kFewPlainRows = 512;
+
 int launch_fwht_quant(const void* x, int x_dtype, int64_t T, int64_t K, int bits, float eps, bool hadamard,
                       int8_t* codes, float* s_dequant, int32_t* code_sum, int code_offset, hipStream_t stream,
                       const float* ln_gain, float ln_eps) {
     if (T == 0) return HBL_OK;
     if (code_offset == kCodesBf6 && (bits != 4 || K < 512)) return HBL_E_SHAPE;   // records need 8-element chunks
     const RowParams rp = {eps, ln_gain, ln_eps, T <= kShortReductionRows ? 1 : 0};
-    if (!hadamard && !is_pow2(K)) return launch_generic(x, x_dtype, T, K, bits, rp, codes, s_dequant, code_sum, code_offset, stream);
+    // Plain rows that are a power of two have a kernel without any test for the row's end, one or two waves up to 4096; few rows
+    // of 2048 and 4096 are faster by four waves (64 rows 0.87 and 0.91 of the time, 512 rows 0.91 and 0.87; 1024 rows 1.05; INT8
+    // rows of 2048 1.02 to 1.07).
+    if (!hadamard && (!is_pow2(K) || (T <= kFewPlainRows && (K == 4096 || (K == 2048 && bits == 4))))) return launch_generic(x, x_dtype, T, K, bits, rp, codes, s_dequant, code_sum, code_offset, stream);
     if (hadamard) {
         if (K == 2048) return dispatch_bigrow<11>(x, x_dtype, T, bits, rp, codes, s_dequant, code_sum, code_offset, stream);
         if (K == 4096) return dispatch_bigrow<12>(x, x_dtype, T, bits, rp, codes, s_dequant, code_sum, code_offset, stream);

@@ -1039,6 +1039,29 @@ def test_ln_quantiser_rows_walked_by_resident_workgroups(hbl, K, T, dtype):
     assert np.array_equal(sd.cpu().numpy(), s4) and np.array_equal(cs.cpu().numpy(), c4.astype(np.int32).sum(1))
 
 
+@pytest.mark.parametrize("K,T", [(384, 300), (640, 1023), (640, 1024), (1152, 2048), (3072, 2047), (3072, 2048), (4224, 256), (4224, 257),
+                                 (8320, 40), (16256, 257), (2048, 512), (2048, 513), (4096, 512), (4096, 513)])
+@pytest.mark.parametrize("dtype", [synth.BF16, synth.F32])
+def test_plain_rows_on_both_sides_of_the_wave_counts(hbl, K, T, dtype):
+    """Plain rows by 1, 2, 4 and 16 waves, the last chunk slot full or ragged: codes in every form, with the norm and without."""
+    note(f"plain rows K={K} T={T} {dtype}")
+    site = synth.Site("a", T, K, 32, hadamard=False, x_dtype=dtype, outlier_frac=0.01, outlier_scale=30.0, seed=3 * K + T)
+    x = synth.make_x(site)
+    g = ln_gain_for(K, T)
+    xd, gd = dev_x(x), torch.from_numpy(g).cuda()
+    for norm in (False, True):
+        xn = O.rmsnorm(x, g, 1e-6) if norm else x
+        for bits, form in ((4, hbl.CODES_BF6 if K >= 512 else 8), (4, 8), (8, 0)):
+            want, s = O.fwht_quant(xn, bits, hadamard=False, eps=EPS)
+            c, sd, cs = hbl.ln_fwht_quant(xd, gd, 1e-6, bits, False, EPS, code_offset=form) if norm else \
+                hbl.fwht_quant(xd, bits, False, EPS, code_offset=form)
+            assert np.array_equal(sd.cpu().numpy(), s) and np.array_equal(cs.cpu().numpy(), want.astype(np.int32).sum(1))
+            if form == hbl.CODES_BF6:
+                assert np.array_equal(record_bits(c.cpu().numpy(), T, K), record_bits(encode_bf6_records(want.astype(np.int32)), T, K))
+            else:
+                assert np.array_equal(c.cpu().numpy().astype(np.int32) - form, want.astype(np.int32))
+
+
 @pytest.mark.parametrize("K,T", [(2048, 300), (4096, 3), (8192, 256), (8192, 257), (16384, 256), (16384, 257)])
 @pytest.mark.parametrize("dtype", [synth.BF16, synth.F32])
 def test_large_rows_on_both_sides_of_the_split(hbl, K, T, dtype):
