@@ -90,16 +90,11 @@ __device__ __forceinline__ uint32_t ternary_code(float w, float denom, float hal
 // of its own is needed; at most 16 KiB out of L2), then codes = RoundClip(W / (alpha + eps), -1, 1).  The chunks are
 // walked from the end: the memory-side cache still holds the last ones that the sum has read (1 % of the three
 // launches).  4096 x 16384 weights: 55 us = 6.1 TB/s; one weight per step with a division and a byte store was 85 us.
-// VEC: W is 16-byte and codes 4-byte aligned.  stream_codes: the codes leave with the non-temporal hint.  Where W and its codes
-// are more than the memory-side cache holds, they would push out the part of W that the sum has left there: all launches of
-// 4096 x 16384 118.4 -> 114.9 us.  Smaller ones are read by the packer out of that cache: 3072 x 16256 (250 MB) 88.5 -> 89.9 us
-// with the hint, 4096 x 4096 33.9 -> 34.4.
-constexpr int64_t kMemorySideCache = (int64_t)256 << 20;
+// VEC: W is 16-byte and codes 4-byte aligned.
 template <bool VEC>
 __global__ __launch_bounds__(kSumBlock) void ternarize_kernel(const float* __restrict__ W, int64_t count,
                                                               const double* __restrict__ partial, int nparts, float eps,
-                                                              float* __restrict__ alpha, int8_t* __restrict__ codes,
-                                                              int stream_codes) {
+                                                              float* __restrict__ alpha, int8_t* __restrict__ codes) {
     __shared__ double red[kSumBlock / 64];
     double s = 0.0;
     for (int i = threadIdx.x; i < nparts; i += kSumBlock) s += partial[i];
@@ -119,10 +114,7 @@ __global__ __launch_bounds__(kSumBlock) void ternarize_kernel(const float* __res
 #pragma unroll
             for (int e = 0; e < 4; ++e) b[e] = ternary_code(w[i][e], denom, half, divide);
             if constexpr (VEC) {
-                const uint32_t four = b[0] | (b[1] << 8) | (b[2] << 16) | (b[3] << 24);
-                uint32_t* const dst = reinterpret_cast<uint32_t*>(codes) + q;
-                if (stream_codes) __builtin_nontemporal_store(four, dst);   // uniform
-                else *dst = four;
+                reinterpret_cast<uint32_t*>(codes)[q] = b[0] | (b[1] << 8) | (b[2] << 16) | (b[3] << 24);
             } else {
 #pragma unroll
                 for (int e = 0; e < 4; ++e) codes[4 * q + e] = (int8_t)b[e];
@@ -176,7 +168,6 @@ __device__ __forceinline__ uint32_t weight_nibbles(uint32_t c) {
 // Packs eight output rows and adds up their codes.  A wave reads 8 rows x 128 features per load (eight whole
 // 128-byte lines), a lane's 16 codes are one packed dword, and the wave's store is two pieces of 128 bytes of the
 // tile; the waves of the workgroup take the K-blocks in turn.  The row sums sum_k c[o][k] come from the same read.
-// The packed words leave with the non-temporal hint (4096 x 16384 with the launches before it 121.4 -> 118.4 us).
 // Bound by the read of the codes: 16 us for 4096 x 16384 (5.2 TB/s; 8 loads in flight measured the same); with
 // scattered 16-byte loads and a launch of its own for the row sums it was 22 + 13 us.
 constexpr int kPackRows = 8, kPackWaves = 8, kPackAhead = 4;   // rows per workgroup, most waves, loads in flight per wave
@@ -210,7 +201,7 @@ __global__ __launch_bounds__(64 * kPackWaves) void pack_kernel(const int8_t* __r
             // weights 0..7 of the dword at bits 1 and 3 of a nibble, weights 8..15 at bits 0 and 2
             const uint32_t a = weight_nibbles(c[u].x) | (weight_nibbles(c[u].y) << 16);
             const uint32_t b = weight_nibbles(c[u].z) | (weight_nibbles(c[u].w) << 16);
-            if (kb + u * waves < nkb) __builtin_nontemporal_store(a | (b >> 1), dst + (int64_t)(kb + u * waves) * kb_stride);
+            if (kb + u * waves < nkb) dst[(int64_t)(kb + u * waves) * kb_stride] = a | (b >> 1);
         }
     }
 #pragma unroll
@@ -244,9 +235,8 @@ int launch_ternarize(const float* W, int64_t count, float eps, int8_t* codes, fl
     else launch_kernel("abs_sum_partial_kernel", abs_sum_partial_kernel<false>, dim3(nb), dim3(kSumBlock), 0, stream, W, count, partial);
     const int rc = after_launch();
     if (rc != HBL_OK) return rc;
-    const int stream_codes = count * 5 > kMemorySideCache;
-    if (wide) launch_kernel("ternarize_kernel", ternarize_kernel<true>, dim3(nb), dim3(kSumBlock), 0, stream, W, count, partial, nb, eps, alpha, codes, stream_codes);
-    else launch_kernel("ternarize_kernel", ternarize_kernel<false>, dim3(nb), dim3(kSumBlock), 0, stream, W, count, partial, nb, eps, alpha, codes, stream_codes);
+    if (wide) launch_kernel("ternarize_kernel", ternarize_kernel<true>, dim3(nb), dim3(kSumBlock), 0, stream, W, count, partial, nb, eps, alpha, codes);
+    else launch_kernel("ternarize_kernel", ternarize_kernel<false>, dim3(nb), dim3(kSumBlock), 0, stream, W, count, partial, nb, eps, alpha, codes);
     return after_launch();
 }
 

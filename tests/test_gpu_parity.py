@@ -147,16 +147,6 @@ def test_ternarize_chunk_edges_and_alignment(hbl, count, offset):
     assert np.array_equal(codes.cpu().numpy()[offset:], c_ref[0]) and not codes[:offset].any()
 
 
-@pytest.mark.parametrize("count", [(256 << 20) // 5, (256 << 20) // 5 + 1])
-def test_ternarize_on_both_sides_of_the_memory_side_cache(hbl, count):
-    """W and its codes just fill 256 MiB, and one weight more (the codes then leave with the non-temporal hint)."""
-    note(f"ternarize count={count}")
-    W = torch.randn((1, count), device="cuda", generator=torch.Generator(device="cuda").manual_seed(5))
-    codes, alpha = hbl.ternarize_weights_absmean(W, EPS)
-    c_ref, a_ref = O.ternarize_weights_absmean(W.cpu().numpy(), EPS)
-    assert float(alpha) == a_ref and np.array_equal(codes.cpu().numpy(), c_ref)
-
-
 @pytest.mark.parametrize("eps", [EPS, 0.0])
 @pytest.mark.parametrize("v", [1.0, 0.3, 1.7e-5, 3.1e33, 2e-40])
 def test_ternarize_codes_at_the_rounding_boundary(hbl, v, eps):
