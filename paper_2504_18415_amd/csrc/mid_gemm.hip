@@ -36,8 +36,10 @@ struct MidForm {
     static constexpr int KG = KG_, D = D_, NF = NF_, TB = TB_;
     static constexpr bool I8 = I8_;
     static constexpr int BN = 32 * NF, BT = 32 * TB;
-    static constexpr int GW = NF;                                // waves per group
-    static constexpr int NI = NF * TB / GW;                      // 32 x 32 accumulator tiles per wave
+    static constexpr int WI = TB == 2 && !I8 ? 2 : 1;            // weight tiles and ...
+    static constexpr int TI = I8 ? TB : 1;                       // ... token tiles of a wave
+    static constexpr int NI = WI * TI;                           // 32 x 32 accumulator tiles per wave
+    static constexpr int GW = NF * TB / NI;                      // waves per group
     static constexpr int THREADS = 64 * GW * KG;
     static constexpr int CODES = BT * (I8 ? kBK : kRecordRowBytes);   // bytes of a K-block: codes, then weight tiles
     static constexpr int BLOCK = CODES + NF * 1024;
@@ -48,7 +50,7 @@ struct MidForm {
     static constexpr int TPT = BN / 8;                           // threads per token at the store (8 features each)
     static constexpr size_t STAGES_LDS = (size_t)D * STAGE, SUMS_LDS = (size_t)KG * BT * SUMROW;
     static constexpr size_t LDS = STAGES_LDS > SUMS_LDS ? STAGES_LDS : SUMS_LDS;
-    static_assert(D >= 2 && D <= 4 && (NF == 1 || NF == 2 || NF == 4) && TB >= 1 && TB <= 2 && TB <= NF && LDS <= 160 * 1024, "form");
+    static_assert(D >= 2 && D <= 4 && (NF == 1 || NF == 2 || NF == 4) && (TB == 1 || TB == 2 || (TB == 4 && I8)) && TB <= NF && LDS <= 160 * 1024, "form");
     static constexpr int STORES = (BT * TPT + THREADS - 1) / THREADS;   // 16-byte stores per thread
     static int64_t tiles_n(int64_t N) { return (N + BN - 1) / BN; }
     static int64_t tiles_t(int64_t T) { return (T + BT - 1) / BT; }
@@ -141,8 +143,9 @@ __device__ __forceinline__ void mid_gemm_body(const MidProblem& a, int wg, char*
         if (s < stages) issue(s, s);
 
     // operand offsets inside the group's block; accumulator i of this wave: weight tile, token tile
-    auto tile_of = [&](int i) { return TB == 1 || F::I8 ? half : (half & ~1) + i; };
-    auto token_tile_of = [&](int i) { return TB == 1 ? 0 : (F::I8 ? i : half & 1); };
+    constexpr int WI = F::WI, TI = F::TI;
+    auto tile_of = [&](int i) { return half / (TB / TI) * WI + i / TI; };
+    auto token_tile_of = [&](int i) { return half % (TB / TI) * TI + i % TI; };
     const int row = token_tile_of(0) * 32 + (lane & 31);   // of accumulator 0
     int xo_lo[2], xo_hi[2], xo_byte[4];
 #pragma unroll
@@ -172,41 +175,52 @@ __device__ __forceinline__ void mid_gemm_body(const MidProblem& a, int wg, char*
         const char* base = lds + slot * STAGE;
         const bool live = s * KG + group < nkb;   // uniform
         if constexpr (F::I8) {
-            const v4i w = *reinterpret_cast<const v4i*>(base + wo);
-            v4i x[4][NI];
+            v4i w[WI];
+#pragma unroll
+            for (int i = 0; i < WI; ++i) w[i] = *reinterpret_cast<const v4i*>(base + wo + i * 1024);
+            v4i x[4][TI];
 #pragma unroll
             for (int k = 0; k < 4; ++k)
 #pragma unroll
-                for (int i = 0; i < NI; ++i) x[k][i] = *reinterpret_cast<const v4i*>(base + xo_byte[k] + i * 32 * kBK);
+                for (int i = 0; i < TI; ++i) x[k][i] = *reinterpret_cast<const v4i*>(base + xo_byte[k] + i * 32 * kBK);
             if (s + D - 1 < stages) issue(s + D - 1, slot == 0 ? D - 1 : slot - 1);
             if (live) {
 #pragma unroll
                 for (int k = 0; k < 4; ++k) {
-                    const v4i wop = expand_weights_i8((uint32_t)w[k]);
 #pragma unroll
-                    for (int i = 0; i < NI; ++i) acc[i] = __builtin_amdgcn_mfma_i32_32x32x32_i8(wop, x[k][i], acc[i], 0, 0, 0);
+                    for (int n = 0; n < WI; ++n) {
+                        const v4i wop = expand_weights_i8((uint32_t)w[n][k]);
+#pragma unroll
+                        for (int i = 0; i < TI; ++i)
+                            acc[n * TI + i] = __builtin_amdgcn_mfma_i32_32x32x32_i8(wop, x[k][i], acc[n * TI + i], 0, 0, 0);
+                    }
                 }
             }
         } else {
-            v4i w[NI];
-            v8i x[2];
+            v4i w[WI];
+            v8i x[2][TI];
 #pragma unroll
-            for (int i = 0; i < NI; ++i) w[i] = *reinterpret_cast<const v4i*>(base + wo + i * 1024);
+            for (int i = 0; i < WI; ++i) w[i] = *reinterpret_cast<const v4i*>(base + wo + i * 1024);
 #pragma unroll
-            for (int k = 0; k < 2; ++k) {
-                const v4i lo = *reinterpret_cast<const v4i*>(base + xo_lo[k]);
-                const int2 hi = *reinterpret_cast<const int2*>(base + xo_hi[k]);
-                x[k] = v8i{lo[0], lo[1], lo[2], lo[3], hi.x, hi.y, 0, 0};
-            }
+            for (int k = 0; k < 2; ++k)
+#pragma unroll
+                for (int i = 0; i < TI; ++i) {
+                    const v4i lo = *reinterpret_cast<const v4i*>(base + xo_lo[k] + i * 32 * kRecordRowBytes);
+                    const int2 hi = *reinterpret_cast<const int2*>(base + xo_hi[k] + i * 32 * kRecordRowBytes);
+                    x[k][i] = v8i{lo[0], lo[1], lo[2], lo[3], hi.x, hi.y, 0, 0};
+                }
             if (s + D - 1 < stages) issue(s + D - 1, slot == 0 ? D - 1 : slot - 1);
             if (live) {
 #pragma unroll
                 for (int k = 0; k < 2; ++k)
 #pragma unroll
-                    for (int i = 0; i < NI; ++i)
-                        acc[i] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(
-                            fp4_operand((uint32_t)w[i][2 * k], (uint32_t)w[i][2 * k + 1]), x[k], acc[i], 4 /*A: fp4*/,
-                            3 /*B: bf6*/, 0, 0, 0, 0);
+                    for (int n = 0; n < WI; ++n) {
+                        const v8i wop = fp4_operand((uint32_t)w[n][2 * k], (uint32_t)w[n][2 * k + 1]);
+#pragma unroll
+                        for (int i = 0; i < TI; ++i)
+                            acc[n * TI + i] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(wop, x[k][i], acc[n * TI + i], 4 /*A: fp4*/,
+                                                                                              3 /*B: bf6*/, 0, 0, 0, 0);
+                    }
             }
         }
         slot = slot + 1 == D ? 0 : slot + 1;
@@ -294,9 +308,24 @@ int64_t mid_tiles(int64_t T, int64_t N) { return MidForm<4, 2, 2, 2>::tiles_n(N)
 
 constexpr int64_t kMidResident = 512;   // workgroups of 8 waves and up to 80 KiB of LDS that the chip holds at once
 
+// Bytes, more than 512 tiles of 64 x 64: the 128 x 128 tile of the prefill kernel keeps one wave per SIMD, which issues the 15
+// instructions that expand 16 weights at half the rate of two.  While a launch of such tiles fits the chip at once (256) or leaves
+// much of a second round idle (384), 8-wave workgroups of two K groups are faster.  128 x 128 outputs with at most 256 tiles: K =
+// 512 0.95 to 0.97 of the time, 1024 0.93 to 1.00, 2048 0.90 to 1.00, 4096 and more 0.91 to 1.01.  128 x 64 outputs, two workgroups
+// per CU: up to 256 tiles K = 256 0.83 to 0.92, 512 0.87 to 0.95, 1024 0.92 to 0.96, 2048 0.90 to 1.00, above 0.94 to 1.06; 257 to
+// 384 tiles 0.90 to 1.01 at every K (128 x 128 outputs: 1.04 to 1.24).  (2048 x 2048 -> 2048 with the quantiser 19.6 -> 18.6 us, 1536 x
+// 8192 -> 2048 43.6 -> 40.6, 1536 x 1024 -> 3072 15.4 -> 13.9.)  From 385 to 512 tiles both are 1.04 to 1.2 times as slow.  Records expand
+// 16 weights by three instructions: 1.0 to 1.35 there.
+int64_t mid_large_tiles(int64_t T, int64_t N) { return ((N + 127) / 128) * ((T + 127) / 128); }
+
 template <bool I8, bool RAW>
 int launch_form(const MidProblem& a, hipStream_t stream) {
     const int64_t tiles = mid_tiles(a.T, a.N);
+    if constexpr (I8) {
+        if (a.T > 64 && tiles > kMidResident)
+            return a.K > 1024 && mid_large_tiles(a.T, a.N) <= 256 ? launch_cfg<MidForm<2, 3, 4, 4, true>, RAW>(a, stream)
+                                                                  : launch_cfg<MidForm<2, 3, 4, 2, true>, RAW>(a, stream);
+    }
     using Narrow = MidForm<8, 3, 1, 1, I8>;
     if (a.K >= 1024 && Narrow::tiles_n(a.N) * Narrow::tiles_t(a.T) <= 256) return launch_cfg<Narrow, RAW>(a, stream);
     if (tiles <= 128) return a.K < 8192 ? launch_cfg<MidForm<4, 4, 2, 1, I8>, RAW>(a, stream) : launch_cfg<MidForm<8, 3, 2, 1, I8>, RAW>(a, stream);
@@ -356,6 +385,8 @@ bool mid_gemm_preferred(int64_t T, int64_t K, int64_t N, bool records) {
     if (mid_tiles(T, N) <= kMidResident) return true;
     return T <= 64 && (records || K > (T <= 32 || N > 65536 ? 1024 : 384));
 }
+
+bool mid_large_bytes_preferred(int64_t T, int64_t N) { return T > 64 && mid_large_tiles(T, N) <= 384; }
 
 int launch_mid_gemm(const MidProblem& a, bool records, hipStream_t stream) {
     if (records) return a.acc_out ? launch_form<false, true>(a, stream) : launch_form<false, false>(a, stream);

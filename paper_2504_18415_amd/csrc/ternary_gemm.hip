@@ -395,7 +395,7 @@ int launch_ternary_gemm(const int8_t* codes, int code_offset, int64_t T, int64_t
     a.N = (int)N;
     a.rows_per_group = n_scale_groups > 0 ? (int)(N / n_scale_groups) : (int)N;
     a.tiles_n = a.tiles_t = 0;
-    if (tile == kTileAuto && mid_gemm_preferred(T, K, N, false)) {   // too few tiles for the chip
+    if (tile == kTileAuto && (mid_gemm_preferred(T, K, N, false) || mid_large_bytes_preferred(T, N))) {   // too few tiles for the chip
         MidProblem m = {};
         m.codes = a.codes;
         m.packed = a.packed;

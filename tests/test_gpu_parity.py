@@ -789,6 +789,25 @@ def test_prefill_tiles_bf16_outputs(hbl, T, N, groups, bits, K):
     assert torch.equal(y, want)
 
 
+@pytest.mark.parametrize("T,K,N,groups,bits", [(1000, 2176, 2208, 3, 8), (1500, 4224, 2080, 1, 8), (2049, 2048, 1952, 1, 8),
+                                               (1600, 2176, 3040, 5, 8), (3073, 128, 1920, 3, 8), (3073, 128, 1920, 3, 4)])
+def test_large_byte_tiles_of_the_mid_size_kernel(hbl, T, K, N, groups, bits):
+    """INT8 (and INT4 rows shorter than 512) with 145 to 384 tiles of 128 x 128: two K groups per workgroup, 128 x 64 and 128 x 128
+    outputs, odd numbers of K-blocks, ragged edges and scale groups: exact products, scaled and rounded."""
+    note(f"large byte tiles T={T} K={K} N={N} bits={bits}")
+    g = torch.Generator(device="cuda").manual_seed(T + N + K)
+    c = torch.randint(-1, 2, (N, K), dtype=torch.int8, device="cuda", generator=g)
+    x = torch.randn((T, K), device="cuda", generator=g).to(torch.bfloat16)
+    alpha = torch.rand(groups, device="cuda", generator=g) + 0.5
+    with hbl.trace(4) as tr:
+        y = hbl.plain_bitlinear_forward(x, hbl.pack_ternary_2bit(c), N, alpha, bits, EPS)
+        torch.cuda.synchronize()
+    assert tr.launches[-1][0] == "mid_gemm_kernel"
+    codes, sd, _ = hbl.fwht_quant(x, bits, False, EPS)
+    want = (((codes.double() @ c.double().t()).float() * sd[:, None]) * alpha.repeat_interleave(N // groups)[None, :]).to(torch.bfloat16)
+    assert torch.equal(y, want)
+
+
 def test_f6f4_raw_accumulators_extreme_and_split_k_shapes(hbl):
     """|acc| = 8 * 16384 = 2^17 out of the fp6 x fp4 matrix cores as an integer, on mid-size batches for which the forward
     call cuts K over the waves of a workgroup (8 and 4 K groups): raw accumulators against the oracle."""
