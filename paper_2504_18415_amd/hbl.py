@@ -1,4 +1,4 @@
-"""Thin ctypes binding over libhbitlinear.so (include/hbitlinear.h).
+"""Thin binding over libhbitlinear.so (include/hbitlinear.h): ctypes, and csrc/host_call.cpp for the calls that are short.
 
 Argument marshalling only: every step of the path runs in the library's HIP
 kernels.  PyTorch provides device memory (``tensor.data_ptr()``) and the
@@ -40,6 +40,7 @@ ROUTES = ("fused", "stream", "mid", "prefill")
 TILE_SQUARE, TILE_SMALL, TILE_WIDE, TILE_MID = 0, 1, 2, 3
 
 _lib = None
+_call = None   # csrc/host_call.cpp, bound to the loaded library: takes the ordinary calls, or declines (None)
 
 
 class Problem(ctypes.Structure):
@@ -108,8 +109,23 @@ def lib():
         L.hbl_grouped_workspace_bytes.restype = sz
         L.hbl_grouped_workspace_bytes.argtypes = [ctypes.POINTER(Problem), ci]
         L.hbl_bitlinear_forward_grouped.argtypes = [ctypes.POINTER(Problem), ci, f32, vp, sz, vp]
+        _bind_native(L)
         _lib = L
     return _lib
+
+
+def _bind_native(L):
+    """The calls whose time on the host counts are marshalled natively where _host_call.so is built; what it declines, and
+    everything without it, goes the way below.  Both make the same library call."""
+    global _call
+    try:
+        from . import _host_call
+    except ImportError:
+        return
+    _host_call.bind(*[ctypes.cast(f, ctypes.c_void_p).value for f in (
+        L.hbl_hbitlinear_forward, L.hbl_plain_bitlinear_forward, L.hbl_ln_bitlinear_forward, L.hbl_bitlinear_forward_small,
+        L.hbl_workspace_bytes, L.hbl_fwht, L.hbl_kv_quant_absmax, L.hbl_kv_dequant, L.hbl_kv_packed_bytes)])
+    _call = _host_call
 
 
 # torch.cuda.current_stream().cuda_stream builds a Stream object on every call: 2.6 us of the 14 us that a small forward call
@@ -224,6 +240,10 @@ def hbitlinear_forward(x: torch.Tensor, Wq_packed: torch.Tensor, N: int, w_scale
                        eps: float = EPS, y: Optional[torch.Tensor] = None,
                        workspace: Optional[torch.Tensor] = None) -> torch.Tensor:
     """Eq. 7 with the Hadamard transform: x [T,K] -> y bf16 [T,N]."""
+    if _call is not None:
+        r = _call.forward(0, x, Wq_packed, N, w_scales, bits, eps, y, workspace)
+        if r is not None:
+            return r if type(r) is not int else _check(r, "hbitlinear_forward")
     return _forward(lib().hbl_hbitlinear_forward, "hbitlinear_forward", x, Wq_packed, N, w_scales, bits, eps, y,
                     workspace)
 
@@ -232,6 +252,10 @@ def plain_bitlinear_forward(x: torch.Tensor, Wq_packed: torch.Tensor, N: int, w_
                             eps: float = EPS, y: Optional[torch.Tensor] = None,
                             workspace: Optional[torch.Tensor] = None) -> torch.Tensor:
     """Eq. 7 without the transform (W_qkv, W_up/gate)."""
+    if _call is not None:
+        r = _call.forward(1, x, Wq_packed, N, w_scales, bits, eps, y, workspace)
+        if r is not None:
+            return r if type(r) is not int else _check(r, "plain_bitlinear_forward")
     return _forward(lib().hbl_plain_bitlinear_forward, "plain_bitlinear_forward", x, Wq_packed, N, w_scales, bits,
                     eps, y, workspace)
 
@@ -244,6 +268,10 @@ def bitlinear_forward_small(x: torch.Tensor, Wq_packed: torch.Tensor, N: int, w_
                             bits: int = 4, hadamard: bool = True, eps: float = EPS) -> torch.Tensor:
     """The forward call that allocates nothing (T <= 64; intermediates in the library's static device scratch).
     ``y`` bf16 [T,N] is the caller's; calls that may overlap on one GPU race."""
+    if _call is not None:
+        r = _call.small(x, Wq_packed, N, w_scales, y, bits, hadamard, eps)
+        if r is not None:
+            return r if type(r) is not int else _check(r, "bitlinear_forward_small")
     _dev_check(x, Wq_packed, w_scales, y)
     T, K = x.shape
     _check_projection(T, K, N, Wq_packed, w_scales, y)
@@ -419,6 +447,10 @@ def bitlinear_forward_grouped(items, eps: float = EPS, workspace: Optional[torch
 
 def fwht(x: torch.Tensor, out_dtype: Optional[torch.dtype] = None, out: Optional[torch.Tensor] = None) -> torch.Tensor:
     """Eq. 3-4 alone (and the backward pass of Eq. 8 when x holds gradient rows): Hadamard(x) row by row."""
+    if _call is not None and out is None and (out_dtype is None or out_dtype in (torch.float32, torch.bfloat16)):
+        r = _call.fwht(x, out_dtype is torch.bfloat16)
+        if r is not None:
+            return r if type(r) is not int else _check(r, "fwht")
     _dev_check(x, out)
     T, K = x.shape
     if out is None:
@@ -431,6 +463,10 @@ def ln_bitlinear_forward(x: torch.Tensor, ln_gain: torch.Tensor, ln_eps: float, 
                          Wq_packed: torch.Tensor, N: int, w_scales: torch.Tensor, bits: int = 4, eps: float = EPS,
                          y: Optional[torch.Tensor] = None, workspace: Optional[torch.Tensor] = None) -> torch.Tensor:
     """Eq. 7 with its LN (RMS normalisation with gain ``ln_gain`` [K] fp32) fused into the quantiser launch."""
+    if _call is not None:
+        r = _call.ln_forward(x, ln_gain, ln_eps, hadamard, Wq_packed, N, w_scales, bits, eps, y, workspace)
+        if r is not None:
+            return r if type(r) is not int else _check(r, "ln_bitlinear_forward")
     _dev_check(x, ln_gain, Wq_packed, w_scales, y, workspace)
     T, K = x.shape
     _check_projection(T, K, N, Wq_packed, w_scales, y, workspace)
@@ -484,6 +520,10 @@ def forward_route(T: int, K: int, N: int, bits: int = 4, hadamard: bool = True, 
 def kv_quant_absmax(x: torch.Tensor, bits: int, eps: float = EPS, packed: Optional[torch.Tensor] = None,
                     scales: Optional[torch.Tensor] = None):
     """Low-bit head states (Section 3.1, Main Results): x [rows, d] -> (packed uint8 [rows, d*bits/8], scales fp32 [rows])."""
+    if _call is not None and packed is None and scales is None:
+        r = _call.kv_quant(x, bits, eps)
+        if r is not None:
+            return r if type(r) is not int else _check(r, "kv_quant_absmax")
     _dev_check(x)
     rows, d = x.shape
     nbytes = lib().hbl_kv_packed_bytes(rows, d, bits)
@@ -499,6 +539,10 @@ def kv_quant_absmax(x: torch.Tensor, bits: int, eps: float = EPS, packed: Option
 def kv_dequant(packed: torch.Tensor, scales: torch.Tensor, d: int, bits: int, out_dtype=torch.bfloat16,
                out: Optional[torch.Tensor] = None) -> torch.Tensor:
     """Inverse map of :func:`kv_quant_absmax`: -> [rows, d] bf16 or fp32."""
+    if _call is not None and out is None and out_dtype in (torch.bfloat16, torch.float32):
+        r = _call.kv_dequant(packed, scales, d, bits, out_dtype is torch.bfloat16)
+        if r is not None:
+            return r if type(r) is not int else _check(r, "kv_dequant")
     _dev_check(packed, scales)
     rows = scales.shape[0]
     if out is None:

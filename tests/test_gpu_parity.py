@@ -1352,3 +1352,77 @@ def test_binding_rejects_short_buffers_before_the_library_sees_them(hbl):
     with pytest.raises(ValueError):
         hbl.bitlinear_forward_grouped([(x, good, 128, al, 4, True, None)])
     assert hbl.hbitlinear_forward(x, good, 64, al, 4).shape == (4, 64)
+
+
+def test_native_calls_and_the_python_path_agree(hbl, monkeypatch):
+    """The binding's native half takes ordinary calls and declines the rest: same outputs bit for bit, the same exceptions, the
+    current stream, and the Python path for what it declines (subclasses, sizes that are no plain integers)."""
+    note("native calls against the Python path")
+    hbl.lib()
+    native = hbl._call
+    assert native is not None, "_host_call.so is not built"
+    g = torch.Generator(device="cuda").manual_seed(3)
+    T, K, N = 5, 512, 96
+    codes = torch.randint(-1, 2, (N, K), dtype=torch.int8, device="cuda", generator=g)
+    packed, al = hbl.pack_ternary_2bit(codes), torch.rand(3, device="cuda", generator=g) + 0.5
+    gain = torch.rand(K, device="cuda", generator=g)
+    y = torch.empty((T, N), dtype=torch.bfloat16, device="cuda")
+    ws = hbl.alloc_workspace(T, K, N, 8)
+
+    class Sub(torch.Tensor):
+        pass
+
+    def calls(x):
+        yield hbl.hbitlinear_forward(x, packed, N, al, 4, EPS)
+        yield hbl.plain_bitlinear_forward(x, packed, N, al, 8, EPS, y=y, workspace=ws).clone()
+        yield hbl.ln_bitlinear_forward(x, gain, 1e-6, True, packed, N, al, 4, EPS)
+        yield hbl.bitlinear_forward_small(x, packed, N, al, y, 4, False, EPS).clone()
+        yield hbl.fwht(x)
+        yield hbl.fwht(x, out_dtype=torch.bfloat16)
+        p, s = hbl.kv_quant_absmax(x, 4, EPS)
+        yield p
+        yield s
+        yield hbl.kv_dequant(p, s, K, 4)
+        yield hbl.kv_dequant(p, s, K, 4, out_dtype=torch.float32)
+
+    def fails(x):
+        out = []
+        for f in (lambda: hbl.hbitlinear_forward(x.t(), packed, N, al), lambda: hbl.hbitlinear_forward(x, packed[:-16], N, al),
+                  lambda: hbl.plain_bitlinear_forward(x, packed, N + 32, al), lambda: hbl.hbitlinear_forward(x.double(), packed, N, al),
+                  lambda: hbl.hbitlinear_forward(x, packed, N, al, 5), lambda: hbl.hbitlinear_forward(x, packed, N, al, workspace=ws[:256]),
+                  lambda: hbl.hbitlinear_forward(x, packed, N, al, y=y[:, :32]), lambda: hbl.hbitlinear_forward(x[:, :384].contiguous(), packed, N, al),
+                  lambda: hbl.ln_bitlinear_forward(x, gain[:-1], 1e-6, True, packed, N, al), lambda: hbl.hbitlinear_forward(x.cpu(), packed, N, al),
+                  lambda: hbl.kv_quant_absmax(x, 5), lambda: hbl.fwht(x[:, :384].contiguous())):
+            with pytest.raises(Exception) as e:
+                f()
+            out.append((type(e.value), getattr(e.value, "status", None)))
+        return out
+
+    for dtype in (torch.bfloat16, torch.float32):
+        x = torch.randn((T, K), device="cuda", generator=g).to(dtype)
+        got, got_fails = list(calls(x)), fails(x)
+        as_subclass = hbl.hbitlinear_forward(x.as_subclass(Sub), packed, N, al)
+        assert type(as_subclass) is torch.Tensor and torch.equal(as_subclass, got[0])
+        assert torch.equal(hbl.hbitlinear_forward(x, packed, np.int64(N), al), got[0])
+        monkeypatch.setattr(hbl, "_call", None)
+        want, want_fails = list(calls(x)), fails(x)
+        monkeypatch.setattr(hbl, "_call", native)
+        assert got_fails == want_fails
+        for a, b in zip(got, want):
+            assert a.dtype == b.dtype and a.shape == b.shape and torch.equal(a, b)
+    assert native.forward(0, x.t(), packed, N, al, 4, EPS, None, None) is None
+    # the current stream: a busy default stream does not hold the call back, and its result is there on its own stream
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        z = hbl.hbitlinear_forward(x, packed, N, al, 4, EPS)
+    side.synchronize()
+    assert torch.equal(z, got[0])
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        z = hbl.hbitlinear_forward(x, packed, N, al, 4, EPS)
+    for _ in range(3):
+        z.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(z, got[0])
