@@ -20,7 +20,7 @@ OBJ_DIR = os.path.join(CSRC, "_build")
 LIB = os.path.join(PKG, "libhbitlinear.so")
 HOST_CALL = os.path.join(PKG, "_host_call.so")
 SOURCES = ["api.hip", "fwht_quant.hip", "ternary_setup.hip", "ternary_gemm.hip", "ternary_gemm_f6f4.hip", "mid_gemm.hip",
-           "decode_gemm.hip", "fused_small.hip", "kv_quant.hip"]
+           "decode_gemm.hip", "fused_small.hip", "fused_bytes.hip", "kv_quant.hip"]
 
 HIPCC_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",

@@ -107,6 +107,7 @@ void fill_decode_problem(DecodeProblem& dp, const Workspace& ws, int64_t T, int6
 
 Route forward_route(int64_t T, int64_t K, int64_t N, int x_dtype, int bits, bool hadamard, bool norm) {
     if (!norm && fused_small_preferred(T, K, N, x_dtype, bits, hadamard)) return Route::kFused;
+    if (fused_bytes_preferred(T, K, N, bits)) return Route::kFusedBytes;
     // up to 16 tokens: the weight-streaming kernel, unless its plan leaves long serial chains of tiles
     if (decode_stream_preferred(T, K, N, bf6_path_supported(K, bits))) return Route::kStream;
     if (bf6_path_supported(K, bits) && decode_shared_preferred(T, K, N)) return Route::kStream;
@@ -130,6 +131,8 @@ int forward(const void* x, int x_dtype, int64_t T, int64_t K, const void* Wq_pac
     const Route route = forward_route(T, K, N, x_dtype, bits, hadamard, ln_gain != nullptr);
     if (route == Route::kFused)
         return launch_fused_small(x, x_dtype, T, K, Wq_packed, N, w_scales, groups, eps, hadamard, y, s);
+    if (route == Route::kFusedBytes)
+        return launch_fused_bytes(x, x_dtype, T, K, Wq_packed, N, w_scales, groups, bits, eps, hadamard, ln_gain, ln_eps, y, s);
     const Workspace ws = carve_workspace(workspace, T, K, N, with_partial);
     const int code_form = code_form_for(K, bits);
     rc = launch_fwht_quant(x, x_dtype, T, K, bits, eps, hadamard, ws.codes, ws.s_dequant, nullptr, code_form, s, ln_gain,

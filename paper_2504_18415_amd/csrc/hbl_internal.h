@@ -194,6 +194,12 @@ bool fused_small_preferred(int64_t T, int64_t K, int64_t N, int x_dtype, int bit
 int launch_fused_small(const void* x, int x_dtype, int64_t T, int64_t K, const void* packed, int64_t N, const float* w_scales,
                        int64_t groups, float eps, bool hadamard, void* y, hipStream_t stream);
 
+// One-launch form for short rows and up to 16 tokens (fused_bytes.hip).
+bool fused_bytes_preferred(int64_t T, int64_t K, int64_t N, int bits);
+int launch_fused_bytes(const void* x, int x_dtype, int64_t T, int64_t K, const void* packed, int64_t N, const float* w_scales,
+                       int64_t groups, int bits, float eps, bool hadamard, const float* ln_gain, float ln_eps, void* y,
+                       hipStream_t stream);
+
 // ---------------------------------------------------------------------------------------------
 // Grouped small-batch path: up to kMaxGroup independent projections (T <= 64 each) served by one
 // quantiser launch and one GEMM launch (a K range split over workgroups is reduced by the last of them to
@@ -296,6 +302,7 @@ enum class Route : int {
     kStream = 1,    // decode_gemm.hip, after a quantiser launch (as the ones below)
     kMid = 2,       // mid_gemm.hip
     kPrefill = 3,   // ternary_gemm_f6f4.hip / ternary_gemm.hip
+    kFusedBytes = 4,   // fused_bytes.hip: short rows, quantiser and product in one launch
 };
 Route forward_route(int64_t T, int64_t K, int64_t N, int x_dtype, int bits, bool hadamard, bool norm);
 

@@ -584,11 +584,13 @@ __device__ __forceinline__ void quant_generic_body(int64_t row, int tid, const v
 #pragma unroll
             for (int e = 0; e < 8; ++e) m = fmaxf(m, fabsf(v[c][e]));
         m = wave_max(m, few_rows);
-        if (lane == 0) red_f[wave] = m;
-        __syncthreads();
-        m = red_f[0];
+        if constexpr (NW > 1) {
+            if (lane == 0) red_f[wave] = m;
+            __syncthreads();
+            m = red_f[0];
 #pragma unroll
-        for (int w = 1; w < NW; ++w) m = fmaxf(m, red_f[w]);
+            for (int w = 1; w < NW; ++w) m = fmaxf(m, red_f[w]);
+        }
         gain = 127.0f / (m + rp.eps);
         s_d = m / 127.0f;
     } else {
@@ -598,11 +600,13 @@ __device__ __forceinline__ void quant_generic_body(int64_t row, int tid, const v
 #pragma unroll
             for (int e = 0; e < 8; ++e) s += (double)fabsf(v[c][e]);
         s = wave_sum(s, few_rows);
-        if (lane == 0) red_d[wave] = s;
-        __syncthreads();
-        s = red_d[0];
+        if constexpr (NW > 1) {
+            if (lane == 0) red_d[wave] = s;
+            __syncthreads();
+            s = red_d[0];
 #pragma unroll
-        for (int w = 1; w < NW; ++w) s += red_d[w];
+            for (int w = 1; w < NW; ++w) s += red_d[w];
+        }
         const float beta = (float)(s / (double)K);
         gain = kRoot7 / (beta + rp.eps);
         s_d = beta / kRoot7;
@@ -635,14 +639,14 @@ __device__ __forceinline__ void quant_generic_body(int64_t row, int tid, const v
     }
     if (code_sum) {
         isum = wave_sum(isum, few_rows);
-        if (lane == 0) red_i[wave] = isum;
-        __syncthreads();
-        if (tid == 0) {
+        if constexpr (NW > 1) {
+            if (lane == 0) red_i[wave] = isum;
+            __syncthreads();
             isum = 0;
 #pragma unroll
             for (int w = 0; w < NW; ++w) isum += red_i[w];
-            code_sum[row] = isum;
         }
+        if (tid == 0) code_sum[row] = isum;
     }
     if (tid == 0) s_dequant[row] = s_d;
 }

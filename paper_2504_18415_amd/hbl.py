@@ -36,7 +36,7 @@ EXPORTS = [
 ]
 # exports for the test suite only (csrc/hbl_test_exports.h)
 TEST_EXPORTS = ["hbl_test_grouped_plan", "hbl_test_gemm_i32_tile", "hbl_test_forward_route"]
-ROUTES = ("fused", "stream", "mid", "prefill")
+ROUTES = ("fused", "stream", "mid", "prefill", "fused_bytes")
 TILE_SQUARE, TILE_SMALL, TILE_WIDE, TILE_MID = 0, 1, 2, 3
 
 _lib = None

@@ -699,6 +699,45 @@ def test_one_launch_small_batches(hbl, T, K, N, groups, hadamard, dtype):
     assert torch.equal(y[:T], want) and bool((y[T] == 7.0).all())
 
 
+@pytest.mark.parametrize("T,K,N,groups,hadamard,bits,norm", [
+    (1, 128, 32, 1, True, 4, False), (4, 128, 32768, 1, False, 8, False), (5, 256, 96, 3, True, 4, False),
+    (8, 384, 16384, 1, False, 4, False), (9, 512, 8192, 1, True, 4, False), (16, 640, 160, 1, False, 4, False),
+    (16, 1024, 8192, 2, True, 8, False), (1, 1024, 4128, 1, True, 8, False), (4, 896, 96, 1, False, 8, False),
+    (4, 512, 32, 1, False, 4, False), (3, 512, 64, 1, True, 4, True), (2, 768, 96, 3, False, 4, True), (13, 256, 64, 1, True, 8, True), (7, 1024, 32, 1, False, 8, True),
+])
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+def test_one_launch_short_rows(hbl, T, K, N, groups, hadamard, bits, norm, dtype):
+    """Up to 16 short rows in one launch: every number of waves, K-blocks fewer and more than the waves' share, both widths, the
+    norm and the ends of the rule, bit for bit what the two stages give on their own (the quantiser's byte codes, then the
+    product), with codes of an exact product on the host."""
+    note(f"one-launch short rows T={T} K={K} N={N} hadamard={hadamard} INT{bits} norm={norm} {dtype}")
+    assert hbl.forward_route(T, K, N, bits, hadamard, hbl._x_dtype(torch.empty(0, dtype=dtype)), norm) == "fused_bytes"
+    g = torch.Generator(device="cuda").manual_seed(T + K + N)
+    codes = torch.randint(-1, 2, (N, K), dtype=torch.int8, device="cuda", generator=g)
+    x = torch.randn((T, K), device="cuda", generator=g)
+    x[:, 5] *= 40
+    x[T // 2] = 0                                                            # a row of zeros among the others
+    x = x.to(dtype)
+    gain = torch.from_numpy(ln_gain_for(K, K)).cuda()
+    alpha = torch.rand(groups, device="cuda", generator=g) + 0.5
+    packed = hbl.pack_ternary_2bit(codes)
+    y = torch.full((T + 1, N), 7.0, dtype=torch.bfloat16, device="cuda")     # a row that stays as it is
+    with hbl.trace(4) as tr:
+        if norm:
+            hbl.ln_bitlinear_forward(x, gain, EPS, hadamard, packed, N, alpha, bits, EPS, y=y[:T])
+        else:
+            (hbl.hbitlinear_forward if hadamard else hbl.plain_bitlinear_forward)(x, packed, N, alpha, bits, EPS, y=y[:T])
+        torch.cuda.synchronize()
+    assert [name for name, _ in tr.launches] == ["fused_bytes_kernel"]
+    q, sd, cs = hbl.ln_fwht_quant(x, gain, EPS, bits, hadamard, EPS) if norm else hbl.fwht_quant(x, bits, hadamard, EPS)
+    want = hbl.gemm_dequant_bf16(q, sd, cs, packed, N, alpha)
+    assert torch.equal(y[:T], want) and bool((y[T] == 7.0).all())
+    rows = torch.arange(N, device="cuda")[:: max(1, N // 64)]
+    exact = q.cpu().int() @ codes[rows].cpu().int().T
+    scale = sd[:, None] * alpha[rows // (N // groups)][None, :]
+    assert torch.equal(y[:T][:, rows].cpu(), (exact.float() * scale.cpu()).to(torch.bfloat16))
+
+
 @pytest.mark.parametrize("shapes", [
     [(20, 640, 96), (17, 8320, 160), (5, 512, 32), (32, 256, 64)],            # at most 32 tokens, few tiles
     [(40, 640, 96), (64, 8320, 160), (5, 512, 32), (33, 384, 64)],            # more tokens
