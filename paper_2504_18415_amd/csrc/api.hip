@@ -507,14 +507,14 @@ int hbl_gemm_i32_bf6(const void* code_records, int64_t T, int64_t K, const void*
 int hbl_test_gemm_i32_tile(const void* codes, int code_form, int64_t T, int64_t K, const void* Wq_packed, int64_t N,
                            int32_t* acc, int tile, void* stream) {
     if (code_form != HBL_CODES_INT8 && code_form != HBL_CODES_BF6) return HBL_E_BITS;
-    if (tile < kTileSquare || tile > kTileMid) return HBL_E_SHAPE;
+    if (tile < kTileSquare || tile > kTileNarrowDeep || (tile > kTileMid && tile < kTileHalf)) return HBL_E_SHAPE;
     int rc = check_gemm_shape(T, K, N, false);
     if (rc != HBL_OK) return rc;
     if (T <= 64 || (code_form == HBL_CODES_BF6 && K < 512)) return HBL_E_SHAPE;
     if (!codes || !Wq_packed || !acc) return HBL_E_NULL;
     if (!aligned16(codes) || !aligned16(Wq_packed) || !aligned16(acc)) return HBL_E_ALIGN;
     hipStream_t s = static_cast<hipStream_t>(stream);
-    if (tile == kTileMid && code_form != HBL_CODES_BF6) return HBL_E_SHAPE;
+    if ((tile == kTileMid || tile > kTileHalf) && code_form != HBL_CODES_BF6) return HBL_E_SHAPE;
     if (code_form == HBL_CODES_BF6)
         return launch_ternary_gemm_f6f4(static_cast<const int8_t*>(codes), T, K, Wq_packed, N, nullptr, nullptr, 1,
                                         nullptr, s, acc, tile);

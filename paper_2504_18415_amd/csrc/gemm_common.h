@@ -109,6 +109,36 @@ __device__ __forceinline__ uint2 dequant_quad(v4i acc, float sd, float alpha, in
     return dequant_quad_sums(acc, sd, alpha, code_offset, ws);
 }
 
+// Time of a prefill launch by workgroup tile, us: the rounds of workgroups that the busiest CU runs (K-blocks and start-up with
+// output of each), or the tiles that the chip as a whole - its power limit - gets through, whichever is longer, and the launch.
+// The figures are fits to measured times of each tile (the tables of the two kernels); a tile that was measured 2 % faster or
+// less is no reason to leave the widest one.
+struct TileCost {
+    int tile, features, tokens;
+    float round_block, round_rest, chip_block, chip_rest, launch;
+    int64_t tiles(int64_t T, int64_t N) const { return ((N + features - 1) / features) * ((T + tokens - 1) / tokens); }
+    float us(int64_t T, int64_t K, int64_t N) const {
+        const int64_t n = tiles(T, N);
+        const float blocks = (float)(K / 128), rounds = (float)((n + 255) / 256), even = (float)n / 256.0f;
+        const float cu = rounds * (blocks * round_block + round_rest), chip = even * (blocks * chip_block + chip_rest);
+        return (cu > chip ? cu : chip) + launch;
+    }
+};
+// costs[0] is the widest tile.
+template <int COUNT>
+int cheapest_tile(const TileCost (&costs)[COUNT], int64_t T, int64_t K, int64_t N) {
+    int best = costs[0].tile;
+    float least = costs[0].us(T, K, N);
+    for (int i = 1; i < COUNT; ++i) {
+        const float us = 1.02f * costs[i].us(T, K, N);
+        if (us < least) {
+            least = us;
+            best = costs[i].tile;
+        }
+    }
+    return best;
+}
+
 typedef int v8i __attribute__((ext_vector_type(8)));
 // Two packed dwords (32 weights) -> the four fp4 operand registers of a lane.
 __device__ __forceinline__ v8i fp4_operand(uint32_t p0, uint32_t p1) {

@@ -176,6 +176,9 @@ int launch_fwht_only(const void* x, int x_dtype, int64_t T, int64_t K, void* out
 constexpr int kTileAuto = -1, kTileSquare = 0 /*256 x 256*/, kTileSmall = 1 /*128 x 128*/,
               kTileWide = 2 /*512 features x 128 tokens*/, kTileMid = 3 /*mid-size kernel, K cut over the waves*/,
               kTileFewTokens = 4 /*bytes, at most 64 tokens*/;
+// ... of which a CU holds two and more
+constexpr int kTileHalf = 10 /*256 x 128*/, kTileSmallFlat = 11 /*128 x 128, two stages*/,
+              kTileNarrow = 12 /*192 x 128, two stages*/, kTileNarrowDeep = 13 /*192 x 128, four stages*/;   // (11 to 13: records)
 
 // GEMM + epilogue. If acc_out != nullptr the raw int32 accumulators are written
 // (no scales, no code_sum needed); otherwise y (bf16) is written.

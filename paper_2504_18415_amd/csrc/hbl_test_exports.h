@@ -25,8 +25,8 @@ int hbl_test_grouped_plan(const hbl_problem* problems, int n_problems, int* rout
 
 /*
  * Host only: the kernel that a single forward call of this shape ends in, as the dispatch picks it (norm != 0: with the
- * RMS normalisation).  0: one launch for quantiser and product   1: weight streaming   2: mid-size   3: prefill;
- * or a negative status.
+ * RMS normalisation).  0: one launch for quantiser and product   1: weight streaming   2: mid-size   3: prefill
+ * 4: one launch for short rows; or a negative status.
  */
 int hbl_test_forward_route(int64_t T, int64_t K, int64_t N, int x_dtype, int bits, int hadamard, int norm);
 
@@ -38,6 +38,8 @@ int hbl_test_forward_route(int64_t T, int64_t K, int64_t N, int x_dtype, int bit
  *              kernel, code records; K >= 512)
  *   tile       0: 256 x 256   1: 128 x 128   2: 512 features x 128 tokens
  *              3: the mid-size kernel, K cut over the waves of a workgroup (HBL_CODES_BF6 only)
+ *              10: 256 features x 128 tokens   11: 128 x 128, two stages   12, 13: 192 features x 128 tokens, two and four
+ *              stages (11 to 13: HBL_CODES_BF6 only)
  */
 int hbl_test_gemm_i32_tile(const void* codes, int code_form, int64_t T, int64_t K, const void* Wq_packed,
                            int64_t N, int32_t* acc, int tile, void* stream);

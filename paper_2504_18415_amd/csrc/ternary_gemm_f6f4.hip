@@ -25,21 +25,21 @@ namespace {
 using namespace gemm;
 typedef float v16f __attribute__((ext_vector_type(16)));
 
+// At most eight MFMA tiles a wave (128 accumulator registers): two waves per SIMD, and more where they fit.
 // RAW: the accumulators themselves leave the kernel, as int32 [T, N] (acc_out), with no dequantisation: the
 // export the parity tests compare with the integer contraction of Eq. 7 bit for bit.
 template <int WAVES_N, int WAVES_T, int TN, int TT, int NSTAGE, bool RAW = false>
-__global__ __launch_bounds__(64 * WAVES_N * WAVES_T) void ternary_gemm_f6f4_kernel(const GemmArgs a) {
+__global__ __launch_bounds__(64 * WAVES_N * WAVES_T, TN * TT <= 8 ? 2 : 1) void ternary_gemm_f6f4_kernel(const GemmArgs a) {
     constexpr int NW = WAVES_N * WAVES_T;
     constexpr int BN = WAVES_N * TN * 32;
     constexpr int BT = WAVES_T * TT * 32;
     constexpr int XBYTES = BT * kRecordRowBytes;   // code records per stage (0.75 byte per feature)
-    constexpr int WBYTES = (BN / 32) * 1024;       // packed weights per stage
+    constexpr int WL = (BN / 32 + NW - 1) / NW;    // global->LDS copies per wave per stage: weights
+    constexpr int WBYTES = WL * NW * 1024;         // packed weights per stage (room for as many copies from every wave)
     constexpr int STAGE = XBYTES + WBYTES;
     constexpr int XPIECES = XBYTES / 1024;         // 1 KiB pieces of the code panels of a stage
-    constexpr int XL = XPIECES / NW;               // global->LDS copies per wave per stage: codes
-    constexpr int WL = (BN / 32) / NW;             // ... and weights
-    static_assert(BT % kPanelTokens == 0 && XPIECES % NW == 0 && (BN / 32) % NW == 0,
-                  "stage copies must divide evenly over the waves");
+    constexpr int XL = XPIECES / NW;               // ... and codes
+    static_assert(BT % kPanelTokens == 0 && XPIECES % NW == 0, "stage copies must divide evenly over the waves");
     static_assert(NSTAGE >= 2, "need at least double buffering");
     constexpr int PENDING = (NSTAGE - 2) * (XL + WL);
 
@@ -51,10 +51,12 @@ __global__ __launch_bounds__(64 * WAVES_N * WAVES_T) void ternary_gemm_f6f4_kern
     const int wn = wave % WAVES_N;
     const int wt = wave / WAVES_N;
 
-    // each XCD gets a contiguous run of tiles, feature tile fastest (workgroups are dealt round-robin)
+    // each XCD gets a contiguous run of tiles, feature tile fastest (workgroups are dealt round-robin); 1 to 2 % faster than the
+    // plain order also where the runs differ in length by a tile
     int wg = blockIdx.x;
     const int nwg = a.tiles_n * a.tiles_t;
-    if ((nwg & 7) == 0) wg = (wg & 7) * (nwg >> 3) + (wg >> 3);
+    const int xcd = wg & 7, extra = nwg & 7;
+    wg = xcd * (nwg >> 3) + (xcd < extra ? xcd : extra) + (wg >> 3);
     const int tile_n = wg % a.tiles_n;
     const int tile_t = wg / a.tiles_n;
     const int n0 = tile_n * BN;
@@ -189,7 +191,9 @@ __global__ __launch_bounds__(64 * WAVES_N * WAVES_T) void ternary_gemm_f6f4_kern
         constexpr int READS = TN + 2 * TT;
         constexpr int SIDE = XL + WL > READS ? XL + WL : READS;
         constexpr bool FITS = SIDE <= NMF - 2;
-        constexpr int FIRSTV = FITS ? (TN + 2 < NMF - 2 ? TN + 2 : NMF - 2) : 0;
+        // first expansion: after the last packed load, or, with more feature tiles, so early that tile i's (at most one tile
+        // per MFMA) still follows its load, behind MFMA i, by four
+        constexpr int FIRSTV = !FITS ? 0 : TN > 4 ? 4 : TN + 2 < NMF - 2 ? TN + 2 : NMF - 2;
         constexpr int VPER = (TOTAL + (NMF - FIRSTV) - 1) / (NMF - FIRSTV);
         const int nslot = slot + 1 == NSTAGE ? 0 : slot + 1;
         if (!FITS) {
@@ -287,10 +291,9 @@ __global__ __launch_bounds__(64 * WAVES_N * WAVES_T) void ternary_gemm_f6f4_kern
     typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
     typedef float f32x2 __attribute__((ext_vector_type(2)));
     constexpr int ROWB = TN * 64 + 16;       // padded LDS row: 16-byte chunks stay aligned, rows shift by 4 banks
-    constexpr int JG = TT < 2 ? TT : 2;      // token tiles per pass through the LDS
+    constexpr int JG = TT % 2 == 0 && NW * 64 * ROWB <= NSTAGE * STAGE ? 2 : 1;   // token tiles per pass through the LDS
     constexpr int CPR = TN * 4;              // 16-byte chunks per row
-    constexpr int RPI = 64 / CPR;            // rows per read instruction
-    static_assert(NW * JG * 32 * ROWB <= NSTAGE * STAGE && 64 % CPR == 0 && TT % JG == 0, "epilogue staging");
+    static_assert(NW * JG * 32 * ROWB <= NSTAGE * STAGE, "epilogue staging");
     char* obuf = lds + wave * (JG * 32 * ROWB);
 #pragma unroll
     for (int jg = 0; jg < TT; jg += JG) {
@@ -318,9 +321,9 @@ __global__ __launch_bounds__(64 * WAVES_N * WAVES_T) void ternary_gemm_f6f4_kern
         __builtin_amdgcn_sched_barrier(0);
         // a wave's LDS accesses execute in order: no barrier between its own writes and reads
 #pragma unroll
-        for (int r = 0; r < JG * 32; r += RPI) {
-            const int row = r + lane / CPR;
-            const int c = lane % CPR;
+        for (int q = 0; q < JG * 32 * CPR; q += 64) {   // (a multiple of 64 chunks: no lane idle)
+            const int row = (q + lane) / CPR;
+            const int c = (q + lane) % CPR;
             const uint4 val = *reinterpret_cast<const uint4*>(obuf + row * ROWB + c * 16);
             const int t = t0 + (wt * TT + jg + row / 32) * 32 + (row & 31);
             const int n = n0 + wn * TN * 32 + c * 8;
@@ -330,11 +333,37 @@ __global__ __launch_bounds__(64 * WAVES_N * WAVES_T) void ternary_gemm_f6f4_kern
     }
 }
 
+// Workgroup tile of a prefill call.  The wide tile (512 x 128: 28 KB per 128-feature stage through L2 and LDS, 32 for 256 x 256)
+// uses the fewest bytes and vector instructions per MFMA and is the fastest where the launch is long and fills its rounds; but a
+// CU holds one of its workgroups, so that its start-up and its output (7 us a round) run with the matrix cores idle, and a
+// last round with few tiles costs a whole one.  Tiles of half the size and less fit two, three and four times into a CU's
+// registers: one workgroup's output passes under another's products.  Beyond 512 tiles of 128 x 128 the least of the estimates
+// below is taken; 213 sizes there: 0.85 of the time of the wide or square tile with the fewest tiles, none above 1.04.  GEMM,
+// us: T = 7052, K = 768, N = 10336 59.5 -> 45.1; T = 3339, K = 6656, N = 4864 81.6 -> 61.5; T = 4684, K = 512, N = 6816
+// 30.7 -> 17.9; T = 8192, K = 16384, N = 4096 stays at 217.
+constexpr TileCost kTileCosts[] = {{kTileWide, 512, 128, 0.622f, 7.235f, 0.803f, 7.582f, 1.152f},
+                                   {kTileSquare, 256, 256, 0.641f, 6.968f, 0.814f, 7.268f, 1.453f},
+                                   {kTileHalf, 256, 128, 0.383f, 2.236f, 0.459f, 1.666f, 1.660f},
+                                   {kTileNarrow, 192, 128, 0.326f, 0.655f, 0.344f, 1.353f, 3.568f},
+                                   {kTileSmallFlat, 128, 128, 0.232f, 0.742f, 0.250f, 0.816f, 2.215f}};
+int prefill_tile(int64_t T, int64_t K, int64_t N) {
+    const int64_t small = ((N + 127) / 128) * ((T + 127) / 128), narrow = ((N + 191) / 192) * ((T + 127) / 128);
+    if (small > 512) return cheapest_tile(kTileCosts, T, K, N);
+    // At most two workgroups of 128 x 128 a CU.  One: four stages hide the latency of long rows (two of them take 1.3 to 1.4
+    // times as long from K = 6000 on).  Up to 256 tiles of 192 x 128 a CU runs one of these in 0.88 to 0.99 of the time of two
+    // small ones, with four stages in long rows (K = 2688: 0.92 with two stages, 0.94 with four; 3840: 1.07, 0.92).  The
+    // others: two small workgroups side by side hide the latency from each other (two stages 0.95 to 0.98 of four).
+    if (small <= 256) return kTileSmall;
+    if (narrow <= 256) return K <= 3072 ? kTileNarrow : kTileNarrowDeep;
+    return kTileSmallFlat;
+}
+
 template <int WAVES_N, int WAVES_T, int TN, int TT, int NSTAGE, bool RAW = false>
 int launch_cfg(GemmArgs a, hipStream_t stream) {
     constexpr int BN = WAVES_N * TN * 32;
     constexpr int BT = WAVES_T * TT * 32;
-    constexpr size_t lds = (size_t)NSTAGE * (BT * kRecordRowBytes + (BN / 32) * 1024);
+    constexpr int NW = WAVES_N * WAVES_T;
+    constexpr size_t lds = (size_t)NSTAGE * (BT * kRecordRowBytes + (BN / 32 + NW - 1) / NW * NW * 1024);
     a.tiles_n = (a.N + BN - 1) / BN;
     a.tiles_t = (a.T + BT - 1) / BT;
     auto kern = ternary_gemm_f6f4_kernel<WAVES_N, WAVES_T, TN, TT, NSTAGE, RAW>;
@@ -363,16 +392,7 @@ int launch_ternary_gemm_f6f4(const int8_t* code_records, int64_t T, int64_t K, c
     a.N = (int)N;
     a.rows_per_group = n_scale_groups > 0 ? (int)(N / n_scale_groups) : (int)N;
     a.code_offset = 0;      // signed operands: no correction terms
-    // Too few tiles for the chip: the mid-size kernel, which cuts K over the waves of a workgroup.
-    // Workgroup tile: 64 K outputs either way (the 256 accumulator registers of four waves).  512 features x 128
-    // tokens moves 28 KB per 128-feature stage through L2 and LDS (12 KB of codes + 16 KB of packed weights) against
-    // 32 KB for 256 x 256 (24 + 8): measured 4 % faster on the GEMM at N = 4096 and 12288, equal at N = 32768.  The
-    // square tile stays for shapes the wide one pads more; below ~180 tiles (256 CUs) the small tile takes over
-    // (192 big tiles measured 8 % faster than 768 tiles of 128 x 128).
-    const int64_t tiles_sq = (int64_t)((N + 255) / 256) * ((T + 255) / 256);
-    const int64_t tiles_wide = (int64_t)((N + 511) / 512) * ((T + 127) / 128);
-    int cfg = tiles_sq >= 180 ? (tiles_wide <= tiles_sq ? kTileWide : kTileSquare) : kTileSmall;
-    if (mid_gemm_preferred(T, K, N, true)) cfg = kTileMid;
+    int cfg = mid_gemm_preferred(T, K, N, true) ? kTileMid : prefill_tile(T, K, N);   // (too few tiles for the chip: mid-size)
     if (tile != kTileAuto) cfg = tile;   // parity tests name the tile themselves
     const bool raw = acc_out != nullptr;
     switch (cfg) {
@@ -382,6 +402,14 @@ int launch_ternary_gemm_f6f4(const int8_t* code_records, int64_t T, int64_t K, c
             return raw ? launch_cfg<2, 2, 2, 2, 4, true>(a, stream) : launch_cfg<2, 2, 2, 2, 4>(a, stream);
         case kTileWide:     // 512 features x 128 tokens, 4 x 1 waves of 128 x 128
             return raw ? launch_cfg<4, 1, 4, 4, 3, true>(a, stream) : launch_cfg<4, 1, 4, 4, 3>(a, stream);
+        case kTileHalf:     // 256 features x 128 tokens, 2 x 2 waves of 128 x 64
+            return raw ? launch_cfg<2, 2, 4, 2, 3, true>(a, stream) : launch_cfg<2, 2, 4, 2, 3>(a, stream);
+        case kTileSmallFlat:
+            return raw ? launch_cfg<2, 2, 2, 2, 2, true>(a, stream) : launch_cfg<2, 2, 2, 2, 2>(a, stream);
+        case kTileNarrow:   // 192 features x 128 tokens, 2 x 2 waves of 96 x 64
+            return raw ? launch_cfg<2, 2, 3, 2, 2, true>(a, stream) : launch_cfg<2, 2, 3, 2, 2>(a, stream);
+        case kTileNarrowDeep:
+            return raw ? launch_cfg<2, 2, 3, 2, 4, true>(a, stream) : launch_cfg<2, 2, 3, 2, 4>(a, stream);
         case kTileMid: {
             MidProblem m = {};
             m.codes = a.codes;

@@ -38,6 +38,7 @@ EXPORTS = [
 TEST_EXPORTS = ["hbl_test_grouped_plan", "hbl_test_gemm_i32_tile", "hbl_test_forward_route"]
 ROUTES = ("fused", "stream", "mid", "prefill", "fused_bytes")
 TILE_SQUARE, TILE_SMALL, TILE_WIDE, TILE_MID = 0, 1, 2, 3
+TILE_HALF, TILE_SMALL_FLAT, TILE_NARROW, TILE_NARROW_DEEP = 10, 11, 12, 13
 
 _lib = None
 _call = None   # csrc/host_call.cpp, bound to the loaded library: takes the ordinary calls, or declines (None)

@@ -1,3 +1,4 @@
+import gc
 import os
 import sys
 
@@ -26,6 +27,13 @@ def load_golden(name):
                 key, vals = line.split(":", 1)
                 cur[key.strip()] = [float(v) for v in vals.split()]
     return cases
+
+
+@pytest.fixture(scope="module", autouse=True)
+def collected():
+    """A caught exception keeps its frame, and the tensors in it, until a collection: run it here, not at some call of a module
+    that watches the allocator."""
+    gc.collect()
 
 
 @pytest.fixture(scope="session")

@@ -804,6 +804,53 @@ def test_prefill_gemm_tiles_raw_accumulators(hbl, T, K, N):
     assert np.array_equal(hbl.gemm_i32_bf6(rec, packed, N, T, K).cpu().numpy(), want)      # the forward's own choice
 
 
+@pytest.mark.parametrize("T,K,N", [(300, 512, 544), (129, 4096, 96), (260, 640, 1056), (65, 896, 32), (384, 768, 576)])
+def test_half_and_narrow_tiles_raw_accumulators(hbl, T, K, N):
+    """The prefill tiles of which a CU holds two and more, with ragged last tiles either way and fewer K-blocks than a ring has
+    stages: the integer contraction bit for bit, extreme codes included."""
+    note(f"half and narrow tiles T={T} K={K} N={N}")
+    rng = np.random.default_rng(T + K + N)
+    q = rng.integers(-8, 8, (T, K)).astype(np.int8)
+    q[0], q[-1] = -8, 7
+    c = rng.integers(-1, 2, (N, K)).astype(np.int8)
+    c[0], c[-1] = 1, -1
+    want = O.gemm_i32(q, c)
+    packed = hbl.pack_ternary_2bit(torch.from_numpy(c).cuda())
+    rec = torch.from_numpy(encode_bf6_records(q.astype(np.int32)).view(np.int8)).cuda()
+    for tile in (hbl.TILE_HALF, hbl.TILE_SMALL_FLAT, hbl.TILE_NARROW, hbl.TILE_NARROW_DEEP):
+        got = hbl.gemm_i32_tile_for_tests(rec, hbl.CODES_BF6, packed, N, tile, T=T, K=K).cpu().numpy()
+        assert np.array_equal(got, want), f"fp6 x fp4 kernel, tile {tile}"
+
+
+@pytest.mark.parametrize("T,K,N,groups", [
+    (1100, 512, 3936, 3),     # 279 tiles of 128 x 128, 189 of 192 x 128: the narrow tile, two stages
+    (1100, 3200, 3936, 3),    # ... four stages
+    (1900, 512, 3104, 1),     # 375 and 255: the last of them; the small tile from here on
+    (1921, 640, 3264, 3),     # 416 and 272: the small tile, two stages
+    (906, 512, 8384, 2),      # 528: the small tile
+    (2192, 512, 6944, 7),     # 990: half the wide tile
+    (3719, 640, 3232, 1),     # 780: the narrow tile
+    (3990, 2432, 3136, 2),    # 800: the square tile
+    (1677, 1792, 7008, 3),    # 770: the wide tile
+])
+def test_prefill_tile_rule_bf16_outputs(hbl, T, K, N, groups):
+    """Every tile the rule for code records picks, ragged tokens and features, several scale groups: every output bit for bit as
+    the exact product of the codes, scaled and rounded, gives it."""
+    note(f"prefill tile rule T={T} K={K} N={N}")
+    assert hbl.forward_route(T, K, N, 4, hadamard=False) == "prefill"
+    g = torch.Generator(device="cuda").manual_seed(T + N + K)
+    c = torch.randint(-1, 2, (N, K), dtype=torch.int8, device="cuda", generator=g)
+    x = torch.randn((T, K), device="cuda", generator=g).to(torch.bfloat16)
+    alpha = torch.rand(groups, device="cuda", generator=g) + 0.5
+    packed = hbl.pack_ternary_2bit(c)
+    y = torch.full((T + 1, N), 7.0, dtype=torch.bfloat16, device="cuda")     # a row that stays as it is
+    hbl.plain_bitlinear_forward(x, packed, N, alpha, 4, EPS, y=y[:T])
+    q, sd, _ = hbl.fwht_quant(x, 4, False, EPS)
+    exact = q.to(torch.float32) @ c.to(torch.float32).T                      # integers below 2^24
+    want = ((exact * sd[:, None]) * alpha[torch.arange(N, device="cuda") // (N // groups)][None, :]).to(torch.bfloat16)
+    assert torch.equal(y[:T], want) and bool((y[T] == 7.0).all())
+
+
 @pytest.mark.parametrize("T,N,groups", [
     (1000, 2208, 3),      # 560 tiles of 64 x 64, 36 of 256 x 256: 128 x 128
     (3001, 4128, 3),      # 204 of 256 x 256, 216 of 512 x 128: the square tile
