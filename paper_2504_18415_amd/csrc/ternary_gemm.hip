@@ -23,18 +23,18 @@ namespace {
 using namespace gemm;
 typedef int v16i __attribute__((ext_vector_type(16)));
 
+// (at most eight MFMA tiles a wave - 128 accumulator registers: two waves per SIMD, and more where they fit)
 template <int WAVES_N, int WAVES_T, int TN, int TT, int NSTAGE, bool RAW>
-__global__ __launch_bounds__(64 * WAVES_N * WAVES_T) void ternary_gemm_kernel(const GemmArgs a) {
+__global__ __launch_bounds__(64 * WAVES_N * WAVES_T, TN * TT <= 8 ? 2 : 1) void ternary_gemm_kernel(const GemmArgs a) {
     constexpr int NW = WAVES_N * WAVES_T;
     constexpr int BN = WAVES_N * TN * 32;
     constexpr int BT = WAVES_T * TT * 32;
     constexpr int XBYTES = BT * kBK;               // codes per stage
-    constexpr int WBYTES = (BN / 32) * 1024;       // packed weights per stage
+    constexpr int WL = (BN / 32 + NW - 1) / NW;    // global->LDS copies per wave per stage: weights
+    constexpr int WBYTES = WL * NW * 1024;         // packed weights per stage (room for as many copies from every wave)
     constexpr int STAGE = XBYTES + WBYTES;
-    constexpr int XL = (BT / 8) / NW;              // global->LDS instructions per wave per stage: codes
-    constexpr int WL = (BN / 32) / NW;             // ... and weights
+    constexpr int XL = (BT / 8) / NW;              // ... and codes
     static_assert((BT / 8) % NW == 0, "code loads must divide evenly over the waves");
-    static_assert((BN / 32) % NW == 0, "weight loads must divide evenly over the waves");
     static_assert(NSTAGE >= 2, "need at least double buffering");
     // loads of later stages that may stay in flight while stage kb is consumed
     constexpr int PENDING = (NSTAGE - 2) * (XL + WL);
@@ -48,10 +48,11 @@ __global__ __launch_bounds__(64 * WAVES_N * WAVES_T) void ternary_gemm_kernel(co
     const int wt = wave / WAVES_N;
 
     // Workgroups are dealt round-robin over the 8 XCDs; give each XCD a contiguous run of tiles
-    // (feature tile fastest) so that the workgroups sharing an activation panel share an L2.
+    // (feature tile fastest) so that the workgroups sharing an activation panel share an L2.  (The runs may differ by a tile.)
     int wg = blockIdx.x;
     const int nwg = a.tiles_n * a.tiles_t;
-    if ((nwg & 7) == 0) wg = (wg & 7) * (nwg >> 3) + (wg >> 3);
+    const int xcd = wg & 7, extra = nwg & 7;
+    wg = xcd * (nwg >> 3) + (xcd < extra ? xcd : extra) + (wg >> 3);
     const int tile_n = wg % a.tiles_n;
     const int tile_t = wg / a.tiles_n;
     const int n0 = tile_n * BN;
@@ -291,10 +292,9 @@ __global__ __launch_bounds__(64 * WAVES_N * WAVES_T) void ternary_gemm_kernel(co
         // number of such partial-line writes.  So the dequantised tiles go through the wave's share of the
         // LDS and leave as whole rows: TN*64 contiguous bytes per token, 16 bytes per lane.
         constexpr int ROWB = TN * 64 + 16;       // padded LDS row: 16-byte chunks stay aligned, rows shift by 4 banks
-        constexpr int JG = TT < 2 ? TT : 2;      // token tiles per pass through the LDS
+        constexpr int JG = TT % 2 == 0 && NW * 64 * ROWB <= NSTAGE * STAGE ? 2 : 1;   // token tiles per pass through the LDS
         constexpr int CPR = TN * 4;              // 16-byte chunks per row
-        constexpr int RPI = 64 / CPR;            // rows per read instruction
-        static_assert(NW * JG * 32 * ROWB <= NSTAGE * STAGE && 64 % CPR == 0 && TT % JG == 0, "epilogue staging");
+        static_assert(NW * JG * 32 * ROWB <= NSTAGE * STAGE, "epilogue staging");
         char* obuf = lds + wave * (JG * 32 * ROWB);
 #pragma unroll
         for (int jg = 0; jg < TT; jg += JG) {
@@ -325,9 +325,9 @@ __global__ __launch_bounds__(64 * WAVES_N * WAVES_T) void ternary_gemm_kernel(co
             __builtin_amdgcn_sched_barrier(0);
             // a wave's LDS accesses execute in order: no barrier between its own writes and reads
 #pragma unroll
-            for (int r = 0; r < JG * 32; r += RPI) {
-                const int row = r + lane / CPR;
-                const int c = lane % CPR;
+            for (int q = 0; q < JG * 32 * CPR; q += 64) {   // (a multiple of 64 chunks: no lane idle)
+                const int row = (q + lane) / CPR;
+                const int c = (q + lane) % CPR;
                 const uint4 val = *reinterpret_cast<const uint4*>(obuf + row * ROWB + c * 16);
                 const int t = t0 + (wt * TT + jg + row / 32) * 32 + (row & 31);
                 const int n = n0 + wn * TN * 32 + c * 8;
@@ -342,7 +342,8 @@ template <int WAVES_N, int WAVES_T, int TN, int TT, int NSTAGE, bool RAW>
 int launch_cfg(GemmArgs a, hipStream_t stream) {
     constexpr int BN = WAVES_N * TN * 32;
     constexpr int BT = WAVES_T * TT * 32;
-    constexpr size_t lds = (size_t)NSTAGE * (BT * kBK + (BN / 32) * 1024);
+    constexpr int NW = WAVES_N * WAVES_T;
+    constexpr size_t lds = (size_t)NSTAGE * (BT * kBK + (BN / 32 + NW - 1) / NW * NW * 1024);
     a.tiles_n = (a.N + BN - 1) / BN;
     a.tiles_t = (a.T + BT - 1) / BT;
     auto kern = ternary_gemm_kernel<WAVES_N, WAVES_T, TN, TT, NSTAGE, RAW>;
@@ -353,22 +354,28 @@ int launch_cfg(GemmArgs a, hipStream_t stream) {
     return after_launch();
 }
 
+// Workgroup tile (more than 384 tiles of 128 x 128; fewer are the mid-size kernel's): the wide one (512 x 128, 32 KB per stage
+// through L2 and LDS) spends the fewest bytes per product, but a CU holds one of its workgroups, and start-up and output of a
+// round (11 us) pass with the matrix cores idle.  Of 256 x 128 (waves of 64 x 128: half the weight expansion of 128 x 64) a CU
+// holds two, of 128 x 128 with two stages four.  The least estimate is taken; 109 sizes: 0.85 of the time of the former rule
+// (wide or square from 200 tiles of 256 x 256 on, else 128 x 128 with four stages), none above 1.03.  GEMM, us: T = 8192,
+// K = 4096, N = 12288 333 -> 315; T = 2048, K = 8192, N = 11008 175 -> 145; T = 5811, K = 768, N = 10336 74.1 -> 56.9; T = 8192,
+// K = 16384, N = 4096 stays at 387.
+constexpr TileCost kTileCosts[] = {{kTileWide, 512, 128, 1.224f, 10.927f, 0.510f, 4.267f, 0.300f},
+                                   {kTileSquare, 256, 256, 1.260f, 11.200f, 0.530f, 4.400f, 0.300f},
+                                   {kTileHalf, 256, 128, 0.690f, 2.303f, 0.565f, 2.168f, 3.462f},
+                                   {kTileSmall, 128, 128, 0.434f, 0.859f, 0.455f, 1.068f, 3.408f}};
+
 template <bool RAW>
 int choose(const GemmArgs& a, hipStream_t stream, int tile) {
-    const int64_t big_tiles = (int64_t)((a.N + 255) / 256) * ((a.T + 255) / 256);
-    int cfg = kTileSmall;
-    if (big_tiles >= 200) {
-        // 512 features x 128 tokens moves 32 KB per stage (16 codes + 16 weights) against 40 KB for 256 x 256:
-        // 1-3 % faster here (4 % on the fp6 x fp4 kernel); the square tile stays where the wide one pads more
-        const int64_t wide_tiles = (int64_t)((a.N + 511) / 512) * ((a.T + 127) / 128);
-        cfg = wide_tiles <= big_tiles ? kTileWide : kTileSquare;
-    }
+    int cfg = cheapest_tile(kTileCosts, a.T, a.K, a.N);
     if (a.T <= 64) cfg = kTileFewTokens;
     if (tile != kTileAuto) cfg = tile;   // parity tests name the tile themselves
     switch (cfg) {
         case kTileFewTokens:   // 128 features x 32 or 64 tokens, 4 waves of one feature tile
             return a.T <= 32 ? launch_cfg<4, 1, 1, 1, 4, RAW>(a, stream) : launch_cfg<4, 1, 1, 2, 4, RAW>(a, stream);
-        case kTileSmall: return launch_cfg<2, 2, 2, 2, 4, RAW>(a, stream);    // 128 x 128, 4 waves
+        case kTileSmall: return launch_cfg<2, 2, 2, 2, 2, RAW>(a, stream);    // 128 x 128, 4 waves
+        case kTileHalf: return launch_cfg<4, 1, 2, 4, 3, RAW>(a, stream);     // 256 features x 128 tokens, 4 waves of 64 x 128
         case kTileSquare: return launch_cfg<2, 2, 4, 4, 3, RAW>(a, stream);   // 256 x 256, 4 waves of 128 x 128
         case kTileWide: return launch_cfg<4, 1, 4, 4, 3, RAW>(a, stream);     // 512 features x 128 tokens, 4 waves of 128 x 128
         default: return HBL_E_SHAPE;

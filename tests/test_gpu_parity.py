@@ -822,6 +822,31 @@ def test_half_and_narrow_tiles_raw_accumulators(hbl, T, K, N):
         assert np.array_equal(got, want), f"fp6 x fp4 kernel, tile {tile}"
 
 
+@pytest.mark.parametrize("T,K,N,groups,bits", [
+    (663, 128, 8256, 3, 8), (663, 256, 8256, 3, 4),       # 390 tiles of 128 x 128: the small tile; INT4 codes with their offset
+    (1025, 256, 6976, 2, 8), (1025, 384, 6976, 2, 4),     # 495: 256 x 128
+    (908, 2176, 12608, 2, 8),                             # 792: the wide tile
+    (6657, 3968, 2080, 1, 8),                             # 901: the square tile
+])
+def test_prefill_byte_tile_rule(hbl, T, K, N, groups, bits):
+    """Every tile the rule for byte codes picks, ragged tokens and features, several scale groups: the integers through the half
+    tile, and every output bit for bit as the exact product of the codes, scaled and rounded, gives it."""
+    note(f"prefill byte tile rule T={T} K={K} N={N} INT{bits}")
+    assert hbl.forward_route(T, K, N, bits, hadamard=False) == "prefill"
+    g = torch.Generator(device="cuda").manual_seed(T + N + K)
+    c = torch.randint(-1, 2, (N, K), dtype=torch.int8, device="cuda", generator=g)
+    x = torch.randn((T, K), device="cuda", generator=g).to(torch.bfloat16)
+    alpha = torch.rand(groups, device="cuda", generator=g) + 0.5
+    packed = hbl.pack_ternary_2bit(c)
+    y = torch.full((T + 1, N), 7.0, dtype=torch.bfloat16, device="cuda")     # a row that stays as it is
+    hbl.plain_bitlinear_forward(x, packed, N, alpha, bits, EPS, y=y[:T])
+    q, sd, _ = hbl.fwht_quant(x, bits, False, EPS)
+    exact = q.to(torch.float32) @ c.to(torch.float32).T                      # integers below 2^24
+    assert torch.equal(hbl.gemm_i32_tile_for_tests(q, hbl.CODES_INT8, packed, N, hbl.TILE_HALF), exact.to(torch.int32))
+    want = ((exact * sd[:, None]) * alpha[torch.arange(N, device="cuda") // (N // groups)][None, :]).to(torch.bfloat16)
+    assert torch.equal(y[:T], want) and bool((y[T] == 7.0).all())
+
+
 @pytest.mark.parametrize("T,K,N,groups", [
     (1100, 512, 3936, 3),     # 279 tiles of 128 x 128, 189 of 192 x 128: the narrow tile, two stages
     (1100, 3200, 3936, 3),    # ... four stages
