@@ -1,4 +1,4 @@
-// One-launch form of the forward pass for short rows and up to 16 tokens (K <= 1024, both widths, with or without the transform
+// One-launch form of the forward pass for short rows and up to 16 tokens (K <= 2048, both widths, with or without the transform
 // and the norm; fused_small.hip is asked first).
 //
 // Such a projection is two launches of 2.2 to 2.9 us each, nearly all of it start-up and drain, and on the host two launches
@@ -17,7 +17,7 @@ namespace {
 using gemm::lds_dma16;
 using gemm::v4i;
 
-constexpr int kFusedTokens = 16;
+constexpr int kFusedTokens = 16, kFusedLength = 2048;
 
 struct FusedBytesArgs {
     const void* x;
@@ -32,7 +32,7 @@ struct FusedBytesArgs {
 // Bytes of a token's codes in LDS: 16 more than the row, so that 16 tokens' reads start in different banks.
 constexpr int code_row_bytes(int K) { return K + 16; }
 
-// LOG2K: transformed rows of 2^LOG2K (7..10); 0: plain rows of up to 512 * MAXC.  WAVES >= T.
+// LOG2K: transformed rows of 2^LOG2K (7..11); 0: plain rows of up to 512 * MAXC.  WAVES >= T.
 template <int LOG2K, int MAXC, int BITS, bool BF16, int WAVES>
 __global__ __launch_bounds__(64 * WAVES) void fused_bytes_kernel(const FusedBytesArgs a) {
     extern __shared__ __attribute__((aligned(1024))) char lds[];
@@ -87,7 +87,7 @@ __global__ __launch_bounds__(64 * WAVES) void fused_bytes_kernel(const FusedByte
 template <int LOG2K, int MAXC, int BITS, bool BF16, int WAVES>
 int launch_cfg(const FusedBytesArgs& a, hipStream_t stream) {
     const int nkb = a.K / 128;
-    const size_t lds = (size_t)(nkb > WAVES ? nkb : WAVES) * 1024 + (size_t)a.T * code_row_bytes(a.K);   // at most 33 KiB
+    const size_t lds = (size_t)(nkb > WAVES ? nkb : WAVES) * 1024 + (size_t)a.T * code_row_bytes(a.K);   // at most 49 KiB
     launch_kernel("fused_bytes_kernel", (fused_bytes_kernel<LOG2K, MAXC, BITS, BF16, WAVES>), dim3((unsigned)(a.N / 32)), dim3(64 * WAVES), lds,
                   stream, a);
     return after_launch();
@@ -100,12 +100,21 @@ int launch_waves(const FusedBytesArgs& a, hipStream_t stream) {
 }
 template <int BITS, bool BF16>
 int launch_rows(const FusedBytesArgs& a, bool hadamard, hipStream_t stream) {
-    if (!hadamard) return a.K <= 512 ? launch_waves<0, 1, BITS, BF16>(a, stream) : launch_waves<0, 2, BITS, BF16>(a, stream);
+    if (!hadamard) {
+        switch ((a.K + 511) / 512) {
+            case 1: return launch_waves<0, 1, BITS, BF16>(a, stream);
+            case 2: return launch_waves<0, 2, BITS, BF16>(a, stream);
+            case 3: return launch_waves<0, 3, BITS, BF16>(a, stream);
+            case 4: return launch_waves<0, 4, BITS, BF16>(a, stream);
+            default: return HBL_E_SHAPE;
+        }
+    }
     switch (a.K) {
         case 128: return launch_waves<7, 0, BITS, BF16>(a, stream);
         case 256: return launch_waves<8, 0, BITS, BF16>(a, stream);
         case 512: return launch_waves<9, 0, BITS, BF16>(a, stream);
         case 1024: return launch_waves<10, 0, BITS, BF16>(a, stream);
+        case 2048: return launch_waves<11, 0, BITS, BF16>(a, stream);
         default: return HBL_E_SHAPE;
     }
 }
@@ -120,8 +129,13 @@ int launch_rows(const FusedBytesArgs& a, bool hadamard, hipStream_t stream) {
 // 1.12, T = 8, N = 32768 0.80 to 1.41, T = 16, N = 16384 0.75 to 1.31.  Rows of records (INT4, K >= 512) have the faster second
 // launch: four of 1024 against N = 32768 take 6.73 for 6.36, three 5.83 for 6.32.  One to four of them that fused_small.hip
 // takes are its.
-bool fused_bytes_preferred(int64_t T, int64_t K, int64_t N, int bits) {
-    if (T > kFusedTokens || K > 1024) return false;
+// Rows of 1152 to 2048: plain ones 0.46 to 0.98 on the near side (INT8, K = 1536, T = 16, N = 4096 4.11 for 7.79; INT4, K = 1920,
+// T = 8, N = 8192 4.36 for 6.66), beyond it T = 4 1.00 to 1.14 (INT4; INT8 0.71 to 0.81 at N = 32768, taken), T = 8 0.87 to 1.34,
+// T = 16 0.75 to 1.39.  A transform of 2048 in one wave is the longer chain: up to 8 rows and 256 workgroups 0.71 to 0.96,
+// 16 rows 0.95 to 1.30, N = 16384 0.79 to 1.43.
+bool fused_bytes_preferred(int64_t T, int64_t K, int64_t N, int bits, bool hadamard) {
+    if (T > kFusedTokens || K > kFusedLength) return false;
+    if (K > 1024) return hadamard ? T <= 8 && N / 32 <= 256 : N / 32 <= (T <= 4 && bits == 8 ? 1024 : T <= 8 ? 512 : 256);
     const int few = bits == 4 && K >= 512 && T * K >= 4096 ? 3 : 4;
     return N / 32 <= (T <= few ? 1024 : T <= 8 ? 512 : 256);
 }
