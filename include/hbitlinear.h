@@ -284,7 +284,7 @@ int hbl_gemm_i32_bf6(const void* code_records, int64_t T, int64_t K, const void*
  * this call, with code_offset = HBL_CODES_BF6 for INT4 activations with K >= 512 (fp6 x fp4 matrix cores),
  * HBL_CODES_UINT4_PLUS8 for INT4 on shorter rows, HBL_CODES_INT8 for INT8 activations.  Smaller batches give
  * the same results, some by other kernels on the same code forms: up to 32 tokens the weight-streaming
- * kernel, up to 4 with INT4 one launch for both steps.  code_sum is not read (the packed weights are
+ * kernel, up to 4 with INT4 and up to 16 short rows one launch for both steps.  code_sum is not read (the packed weights are
  * signed) and may be NULL.
  */
 int hbl_gemm_dequant_bf16(const int8_t* codes, int code_offset, const float* s_dequant,

@@ -12,7 +12,7 @@
 //   - gain = 127/(gamma+eps) or sqrt7/(beta+eps) with IEEE fp32 division,
 //     code = RoundClip(gain * x_r) with round-half-to-even.
 //
-// Index bits of a row of K = CH*64*R*W elements, low to high:
+// Index bits of a transformed row of K = CH*64*R*W < 2048 elements (from 2048 on: large_rows.h), low to high:
 //   [e: log2 CH in-thread][lane: 6][r: log2 R in-thread chunks][wave: log2 W]
 // so that every global access is one contiguous CH-element piece per lane and
 // the stage order e -> lane -> r -> wave is ascending.  The wave stages swap

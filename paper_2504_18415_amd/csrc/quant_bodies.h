@@ -1,5 +1,6 @@
 // Device bodies of the activation front end (Eq. 3-6): one token row per call, by one or more waves of a workgroup.  The
-// launches of fwht_quant.hip and the one-launch small-batch kernel (fused_small.hip) run the same code.
+// launches of fwht_quant.hip and the one-launch small-batch kernels (fused_small.hip, fused_bytes.hip) run the same code;
+// transformed rows of 2048 and more in launches of their own: large_rows.h.
 #pragma once
 
 #include <type_traits>

@@ -6,7 +6,7 @@
 // MFMA rate per instruction and with far fewer toggling multiplier bits, which matters because the
 // matrix cores are power-limited.  No offset trick is needed here: the operands are signed.
 //
-// Same skeleton as ternary_gemm.hip (256 x 256 tiles, 4 waves of 128 x 128, direct global->LDS copies,
+// Same skeleton as ternary_gemm.hip (four waves, up to 128 x 128 outputs each, direct global->LDS copies,
 // one small piece of side work after every MFMA).  Differences:
 //   - a pipeline stage is still 128 features but only two MFMA K-steps of 64;
 //   - activation codes arrive as the record image of code_records.h: 6 bits per code, a token row of a

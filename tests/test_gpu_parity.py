@@ -879,9 +879,9 @@ def test_prefill_tile_rule_bf16_outputs(hbl, T, K, N, groups):
 
 
 @pytest.mark.parametrize("T,N,groups", [
-    (1000, 2208, 3),      # 560 tiles of 64 x 64, 36 of 256 x 256: 128 x 128
-    (3001, 4128, 3),      # 204 of 256 x 256, 216 of 512 x 128: the square tile
-    (3001, 4576, 11),     # 216 of either: 512 features x 128 tokens
+    (1000, 2208, 3),      # 560 tiles of 64 x 64, 144 of 128 x 128: records 128 x 128, bytes the mid-size kernel's large tile
+    (3001, 4128, 3),      # 792 of 128 x 128: records 128 x 128 with two stages, bytes 256 x 128
+    (3001, 4576, 11),     # 864: the same
 ])
 @pytest.mark.parametrize("bits,K", [(4, 640), (8, 640), (4, 384)])
 def test_prefill_tiles_bf16_outputs(hbl, T, N, groups, bits, K):
