@@ -1,4 +1,4 @@
-// One-launch form of the forward pass for short rows and up to 16 tokens (K <= 2048, both widths, with or without the transform
+// One-launch form of the forward pass for short rows and up to 16 tokens (K <= 3584, both widths, with or without the transform
 // and the norm; fused_small.hip is asked first).
 //
 // Such a projection is two launches of 2.2 to 2.9 us each, nearly all of it start-up and drain, and on the host two launches
@@ -9,6 +9,8 @@
 // Bound: one serial chain - launch, a row's loads, transform and two reductions across the wave, LDS, MFMA, a sum over the waves.
 // 16 fp32 rows of 256 against 256 output rows, transformed: 3.5 us of GPU time for 5.2 with two launches, 5.3 us for 9.3 called
 // one after another from the host.
+#include <atomic>
+
 #include "quant_bodies.h"
 
 namespace hbl {
@@ -17,7 +19,7 @@ namespace {
 using gemm::lds_dma16;
 using gemm::v4i;
 
-constexpr int kFusedTokens = 16, kFusedLength = 2048;
+constexpr int kFusedTokens = 16, kFusedLength = 3584;
 
 struct FusedBytesArgs {
     const void* x;
@@ -87,9 +89,14 @@ __global__ __launch_bounds__(64 * WAVES) void fused_bytes_kernel(const FusedByte
 template <int LOG2K, int MAXC, int BITS, bool BF16, int WAVES>
 int launch_cfg(const FusedBytesArgs& a, hipStream_t stream) {
     const int nkb = a.K / 128;
-    const size_t lds = (size_t)(nkb > WAVES ? nkb : WAVES) * 1024 + (size_t)a.T * code_row_bytes(a.K);   // at most 49 KiB
-    launch_kernel("fused_bytes_kernel", (fused_bytes_kernel<LOG2K, MAXC, BITS, BF16, WAVES>), dim3((unsigned)(a.N / 32)), dim3(64 * WAVES), lds,
-                  stream, a);
+    const size_t lds = (size_t)(nkb > WAVES ? nkb : WAVES) * 1024 + (size_t)a.T * code_row_bytes(a.K);   // at most 85 KiB
+    auto kern = fused_bytes_kernel<LOG2K, MAXC, BITS, BF16, WAVES>;
+    if constexpr (MAXC > 4) {
+        static std::atomic<uint64_t> lds_allowed{0};   // per instantiation: devices already set up
+        if (const int rc = allow_dynamic_lds(kern, (kFusedLength / 128) * 1024 + WAVES * code_row_bytes(kFusedLength), lds_allowed); rc != HBL_OK)
+            return rc;
+    }
+    launch_kernel("fused_bytes_kernel", kern, dim3((unsigned)(a.N / 32)), dim3(64 * WAVES), lds, stream, a);
     return after_launch();
 }
 template <int LOG2K, int MAXC, int BITS, bool BF16>
@@ -106,6 +113,9 @@ int launch_rows(const FusedBytesArgs& a, bool hadamard, hipStream_t stream) {
             case 2: return launch_waves<0, 2, BITS, BF16>(a, stream);
             case 3: return launch_waves<0, 3, BITS, BF16>(a, stream);
             case 4: return launch_waves<0, 4, BITS, BF16>(a, stream);
+            case 5: return launch_waves<0, 5, BITS, BF16>(a, stream);
+            case 6: return launch_waves<0, 6, BITS, BF16>(a, stream);
+            case 7: return launch_waves<0, 7, BITS, BF16>(a, stream);
             default: return HBL_E_SHAPE;
         }
     }
@@ -133,8 +143,12 @@ int launch_rows(const FusedBytesArgs& a, bool hadamard, hipStream_t stream) {
 // T = 8, N = 8192 4.36 for 6.66), beyond it T = 4 1.00 to 1.14 (INT4; INT8 0.71 to 0.81 at N = 32768, taken), T = 8 0.87 to 1.34,
 // T = 16 0.75 to 1.39.  A transform of 2048 in one wave is the longer chain: up to 8 rows and 256 workgroups 0.71 to 0.96,
 // 16 rows 0.95 to 1.30, N = 16384 0.79 to 1.43.
+// Plain rows of 2176 to 3584 (up to 56 values a lane): 0.56 to 0.95 on the near side (INT8, K = 3072, T = 8, N = 8192 4.91 for
+// 7.89; INT4 5.17 for 6.72), beyond it INT4 T = 5 to 8 0.91 to 1.07, T = 16 1.39 to 1.58, INT8 T = 16 1.09 to 1.23.  Rows of 4096:
+// INT4, T = 16 1.05 to 1.13 and spills; they stay two launches.
 bool fused_bytes_preferred(int64_t T, int64_t K, int64_t N, int bits, bool hadamard) {
     if (T > kFusedTokens || K > kFusedLength) return false;
+    if (K > 2048) return !hadamard && N / 32 <= (T <= 8 && bits == 8 ? 512 : 256);
     if (K > 1024) return hadamard ? T <= 8 && N / 32 <= 256 : N / 32 <= (T <= 4 && bits == 8 ? 1024 : T <= 8 ? 512 : 256);
     const int few = bits == 4 && K >= 512 && T * K >= 4096 ? 3 : 4;
     return N / 32 <= (T <= few ? 1024 : T <= 8 ? 512 : 256);

@@ -705,6 +705,8 @@ def test_one_launch_small_batches(hbl, T, K, N, groups, hadamard, dtype):
     (16, 1024, 8192, 2, True, 8, False), (1, 1024, 4128, 1, True, 8, False), (4, 896, 96, 1, False, 8, False),
     (5, 1152, 96, 3, False, 4, False), (16, 1536, 160, 1, False, 8, False), (9, 2048, 8192, 1, False, 4, False),
     (3, 1664, 32768, 1, False, 8, False), (8, 2048, 8192, 1, True, 8, False), (6, 2048, 96, 1, True, 4, True),
+    (16, 3584, 96, 1, False, 4, False), (8, 2560, 16384, 1, False, 8, False), (11, 3072, 8192, 2, False, 8, True),
+    (5, 2176, 8192, 1, False, 4, True), (1, 3456, 96, 3, False, 8, False),
     (4, 512, 32, 1, False, 4, False), (3, 512, 64, 1, True, 4, True), (2, 768, 96, 3, False, 4, True), (13, 256, 64, 1, True, 8, True), (7, 1024, 32, 1, False, 8, True),
 ])
 @pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
