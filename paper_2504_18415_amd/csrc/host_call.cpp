@@ -3,7 +3,7 @@
 // come, and either makes the call and returns its result, returns the library's status (an int) if it is not 0, or returns None
 // without having done anything where an argument is not the ordinary one (another type, layout, device or size than a plain
 // contiguous device tensor that fits): the Python code then takes the call and raises what it raises.
-// (16 x 256 -> 256, fp32, outputs and workspace allocated by the call, calls in a row: 11.9 -> 8.0 us.)
+// (16 x 256 -> 256, fp32, outputs and workspace allocated by the call, calls in a row: 11.9 -> 8.0 us with two launches, 5.3 with one.)
 #define PY_SSIZE_T_CLEAN
 #include <Python.h>
 
@@ -60,15 +60,20 @@ int x_dtype(const at::Tensor& t) {
 }
 void* stream() { return c10::hip::getCurrentHIPStream().stream(); }
 
+// Other threads run during the allocations and the library's call, as they do during torch.empty and a call through ctypes.  An
+// exception (an allocation that fails) passes the destructor, which takes the lock back, on its way to END_HANDLE_TH_ERRORS.
 template <typename Call>
-int without_gil(Call call) {   // other threads run during the library's call, as during one through ctypes
-    int rc;
-    Py_BEGIN_ALLOW_THREADS
-    rc = call();
-    Py_END_ALLOW_THREADS
-    return rc;
+int without_gil(Call call) {
+    struct Released {
+        PyThreadState* const state = PyEval_SaveThread();
+        ~Released() { PyEval_RestoreThread(state); }
+    } released;
+    return call();
 }
+constexpr int kDeclined = 1;   // beside the library's statuses, which are not positive
+
 PyObject* result(int rc, PyObject* given, const at::Tensor& t) {
+    if (rc == kDeclined) return decline();
     if (rc != HBL_OK) return PyLong_FromLong(rc);
     if (given != nullptr && given != Py_None) {
         Py_INCREF(given);
@@ -77,16 +82,27 @@ PyObject* result(int rc, PyObject* given, const at::Tensor& t) {
     return THPVariable_Wrap(t);
 }
 
-// What the projection calls share: x [T, K], packed weights, scales, y (allocated if None).
+// Memory that a call reads (a lazily cloned tensor is read where it is) or writes (its own copy is made here, which may fail).
+const void* input(const at::Tensor& t) { return t.const_data_ptr(); }
+const float* floats(const at::Tensor& t) { return t.const_data_ptr<float>(); }
+
+// What the projection calls share: x [T, K], packed weights, scales, y (allocated if it is not given).
 struct Projection {
     const at::Tensor *x, *packed, *scales;
-    at::Tensor y;
+    at::Tensor y, workspace;
     int64_t T, K, N, bits;
     int dtype;
     float eps;
+    // y and the workspace that were not given; without the interpreter's lock
+    bool allocate(bool with_workspace) {
+        if (!y.defined()) y = at::empty({T, N}, x->options().dtype(at::kBFloat16));
+        if (with_workspace && !workspace.defined())
+            workspace = at::empty({(int64_t)lib.workspace_bytes(T, K, N, (int)bits)}, x->options().dtype(at::kByte));
+        return ordinary(y) && (!with_workspace || ordinary(workspace));
+    }
 };
 bool get_projection(PyObject* x, PyObject* packed, PyObject* n, PyObject* scales, PyObject* bits, PyObject* eps, PyObject* y,
-                    bool may_allocate, Projection& p) {
+                    Projection& p) {
     p.x = tensor(x);
     p.packed = tensor(packed);
     p.scales = tensor(scales);
@@ -102,35 +118,29 @@ bool get_projection(PyObject* x, PyObject* packed, PyObject* n, PyObject* scales
         const at::Tensor* t = tensor(y);
         if (!t || t->scalar_type() != at::kBFloat16 || t->dim() != 2 || t->size(0) != p.T || t->size(1) != p.N) return false;
         p.y = *t;
-        return true;
     }
-    if (!may_allocate) return false;
-    p.y = at::empty({p.T, p.N}, p.x->options().dtype(at::kBFloat16));
-    return ordinary(p.y);
+    return true;
 }
-bool get_workspace(PyObject* o, const Projection& p, at::Tensor& ws) {
-    if (o != Py_None) {
-        const at::Tensor* t = tensor(o);
-        if (!t || t->scalar_type() != at::kByte) return false;
-        ws = *t;
-        return true;
-    }
-    ws = at::empty({(int64_t)lib.workspace_bytes(p.T, p.K, p.N, (int)p.bits)}, p.x->options().dtype(at::kByte));
-    return ordinary(ws);
+bool get_workspace(PyObject* o, Projection& p) {
+    if (o == Py_None) return true;
+    const at::Tensor* t = tensor(o);
+    if (!t || t->scalar_type() != at::kByte) return false;
+    p.workspace = *t;
+    return true;
 }
 
 // forward(plain, x, packed, N, scales, bits, eps, y, workspace)
 PyObject* forward(PyObject*, PyObject* const* a, Py_ssize_t n) {
     HANDLE_TH_ERRORS
     Projection p;
-    at::Tensor ws;
     int64_t plain;
-    if (n != 9 || !get_int(a[0], plain) || !get_projection(a[1], a[2], a[3], a[4], a[5], a[6], a[7], true, p) || !get_workspace(a[8], p, ws))
+    if (n != 9 || !get_int(a[0], plain) || !get_projection(a[1], a[2], a[3], a[4], a[5], a[6], a[7], p) || !get_workspace(a[8], p))
         return decline();
     void* s = stream();
     const int rc = without_gil([&] {
-        return lib.forward[plain != 0](p.x->data_ptr(), p.dtype, p.T, p.K, p.packed->data_ptr(), p.N, p.scales->data_ptr<float>(),
-                                       p.scales->numel(), (int)p.bits, p.eps, p.y.data_ptr(), ws.data_ptr(), ws.numel(), s);
+        if (!p.allocate(true)) return kDeclined;
+        return lib.forward[plain != 0](input(*p.x), p.dtype, p.T, p.K, input(*p.packed), p.N, floats(*p.scales), p.scales->numel(),
+                                       (int)p.bits, p.eps, p.y.data_ptr(), p.workspace.data_ptr(), p.workspace.numel(), s);
     });
     return result(rc, a[7], p.y);
     END_HANDLE_TH_ERRORS
@@ -140,18 +150,18 @@ PyObject* forward(PyObject*, PyObject* const* a, Py_ssize_t n) {
 PyObject* ln_forward(PyObject*, PyObject* const* a, Py_ssize_t n) {
     HANDLE_TH_ERRORS
     Projection p;
-    at::Tensor ws;
     float ln_eps;
     if (n != 11 || !PyBool_Check(a[3]) || !get_float(a[2], ln_eps)) return decline();
     const at::Tensor* gain = tensor(a[1]);
-    if (!gain || gain->scalar_type() != at::kFloat || !get_projection(a[0], a[4], a[5], a[6], a[7], a[8], a[9], true, p) ||
-        gain->numel() != p.K || !get_workspace(a[10], p, ws))
+    if (!gain || gain->scalar_type() != at::kFloat || !get_projection(a[0], a[4], a[5], a[6], a[7], a[8], a[9], p) ||
+        gain->numel() != p.K || !get_workspace(a[10], p))
         return decline();
     void* s = stream();
+    const int hadamard = a[3] == Py_True;
     const int rc = without_gil([&] {
-        return lib.ln_forward(p.x->data_ptr(), p.dtype, p.T, p.K, gain->data_ptr<float>(), ln_eps, a[3] == Py_True, p.packed->data_ptr(),
-                              p.N, p.scales->data_ptr<float>(), p.scales->numel(), (int)p.bits, p.eps, p.y.data_ptr(),
-                              ws.data_ptr(), ws.numel(), s);
+        if (!p.allocate(true)) return kDeclined;
+        return lib.ln_forward(input(*p.x), p.dtype, p.T, p.K, floats(*gain), ln_eps, hadamard, input(*p.packed), p.N, floats(*p.scales),
+                              p.scales->numel(), (int)p.bits, p.eps, p.y.data_ptr(), p.workspace.data_ptr(), p.workspace.numel(), s);
     });
     return result(rc, a[9], p.y);
     END_HANDLE_TH_ERRORS
@@ -161,11 +171,12 @@ PyObject* ln_forward(PyObject*, PyObject* const* a, Py_ssize_t n) {
 PyObject* small(PyObject*, PyObject* const* a, Py_ssize_t n) {
     HANDLE_TH_ERRORS
     Projection p;
-    if (n != 8 || !PyBool_Check(a[6]) || !get_projection(a[0], a[1], a[2], a[3], a[5], a[7], a[4], false, p)) return decline();
+    if (n != 8 || !PyBool_Check(a[6]) || a[4] == Py_None || !get_projection(a[0], a[1], a[2], a[3], a[5], a[7], a[4], p)) return decline();
     void* s = stream();
+    const int hadamard = a[6] == Py_True;
     const int rc = without_gil([&] {
-        return lib.small(p.x->data_ptr(), p.dtype, p.T, p.K, p.packed->data_ptr(), p.N, p.scales->data_ptr<float>(), p.scales->numel(),
-                         (int)p.bits, p.eps, a[6] == Py_True, p.y.data_ptr(), s);
+        return lib.small(input(*p.x), p.dtype, p.T, p.K, input(*p.packed), p.N, floats(*p.scales), p.scales->numel(), (int)p.bits, p.eps,
+                         hadamard, p.y.data_ptr(), s);
     });
     return result(rc, a[4], p.y);
     END_HANDLE_TH_ERRORS
@@ -177,11 +188,13 @@ PyObject* fwht(PyObject*, PyObject* const* a, Py_ssize_t n) {
     if (n != 2 || !PyBool_Check(a[1])) return decline();
     const at::Tensor* x = tensor(a[0]);
     if (!x || x->dim() != 2 || x_dtype(*x) < 0) return decline();
-    const at::Tensor out = at::empty({x->size(0), x->size(1)}, x->options().dtype(a[1] == Py_True ? at::kBFloat16 : at::kFloat));
-    if (!ordinary(out)) return decline();
+    const bool bf16 = a[1] == Py_True;
+    at::Tensor out;
     void* s = stream();
     const int rc = without_gil([&] {
-        return lib.fwht(x->data_ptr(), x_dtype(*x), x->size(0), x->size(1), out.data_ptr(), a[1] == Py_True ? HBL_BF16 : HBL_F32, s);
+        out = at::empty({x->size(0), x->size(1)}, x->options().dtype(bf16 ? at::kBFloat16 : at::kFloat));
+        if (!ordinary(out)) return kDeclined;
+        return lib.fwht(input(*x), x_dtype(*x), x->size(0), x->size(1), out.data_ptr(), bf16 ? HBL_BF16 : HBL_F32, s);
     });
     return result(rc, nullptr, out);
     END_HANDLE_TH_ERRORS
@@ -197,18 +210,20 @@ PyObject* kv_quant(PyObject*, PyObject* const* a, Py_ssize_t n) {
     if (!x || x->dim() != 2 || x_dtype(*x) < 0) return decline();
     const int64_t rows = x->size(0), d = x->size(1);
     if (lib.kv_packed_bytes(rows, d, (int)bits) == 0) return decline();   // (no rows, or a shape that is refused)
-    const at::Tensor packed = at::empty({rows, d * bits / 8}, x->options().dtype(at::kByte));
-    const at::Tensor scales = at::empty({rows}, x->options().dtype(at::kFloat));
-    if (!ordinary(packed) || !ordinary(scales)) return decline();
+    at::Tensor packed, scales;
     void* s = stream();
     const int rc = without_gil([&] {
-        return lib.kv_quant(x->data_ptr(), x_dtype(*x), rows, d, (int)bits, eps, packed.data_ptr(), scales.data_ptr<float>(), s);
+        packed = at::empty({rows, d * bits / 8}, x->options().dtype(at::kByte));
+        scales = at::empty({rows}, x->options().dtype(at::kFloat));
+        if (!ordinary(packed) || !ordinary(scales)) return kDeclined;
+        return lib.kv_quant(input(*x), x_dtype(*x), rows, d, (int)bits, eps, packed.data_ptr(), scales.data_ptr<float>(), s);
     });
-    if (rc != HBL_OK) return PyLong_FromLong(rc);
-    PyObject* both = PyTuple_New(2);
-    if (!both) return nullptr;
-    PyTuple_SET_ITEM(both, 0, THPVariable_Wrap(packed));
-    PyTuple_SET_ITEM(both, 1, THPVariable_Wrap(scales));
+    PyObject* first = result(rc, nullptr, packed);
+    if (rc != HBL_OK || !first) return first;
+    PyObject* second = THPVariable_Wrap(scales);
+    PyObject* both = second ? PyTuple_Pack(2, first, second) : nullptr;
+    Py_DECREF(first);
+    Py_XDECREF(second);
     return both;
     END_HANDLE_TH_ERRORS
 }
@@ -223,12 +238,13 @@ PyObject* kv_dequant(PyObject*, PyObject* const* a, Py_ssize_t n) {
     const int64_t rows = scales->size(0);
     const size_t need = lib.kv_packed_bytes(rows, d, (int)bits);
     if (need == 0 || packed->scalar_type() != at::kByte || (size_t)packed->numel() < need) return decline();
-    const at::Tensor out = at::empty({rows, d}, packed->options().dtype(a[4] == Py_True ? at::kBFloat16 : at::kFloat));
-    if (!ordinary(out)) return decline();
+    const bool bf16 = a[4] == Py_True;
+    at::Tensor out;
     void* s = stream();
     const int rc = without_gil([&] {
-        return lib.kv_dequant(packed->data_ptr(), scales->data_ptr<float>(), rows, d, (int)bits, out.data_ptr(),
-                              a[4] == Py_True ? HBL_BF16 : HBL_F32, s);
+        out = at::empty({rows, d}, packed->options().dtype(bf16 ? at::kBFloat16 : at::kFloat));
+        if (!ordinary(out)) return kDeclined;
+        return lib.kv_dequant(input(*packed), floats(*scales), rows, d, (int)bits, out.data_ptr(), bf16 ? HBL_BF16 : HBL_F32, s);
     });
     return result(rc, nullptr, out);
     END_HANDLE_TH_ERRORS

@@ -1541,3 +1541,31 @@ def test_native_calls_and_the_python_path_agree(hbl, monkeypatch):
         graph.replay()
         torch.cuda.synchronize()
         assert torch.equal(z, got[0])
+
+
+def test_native_calls_and_memory_that_cannot_be_had(hbl):
+    """A lazily cloned output gets memory of its own inside the native call.  Where there is none left the call raises, with the
+    interpreter's lock held again, and the next call works; inputs are read where they are, without a copy."""
+    note("native calls with lazily cloned tensors, memory exhausted")
+    T, K, N = 512, 128, 65536
+    g = torch.Generator(device="cuda").manual_seed(4)
+    packed = hbl.pack_ternary_2bit(torch.randint(-1, 2, (N, K), dtype=torch.int8, device="cuda", generator=g))
+    x, al, ws = torch.randn((T, K), device="cuda", generator=g), torch.ones(1, device="cuda"), hbl.alloc_workspace(T, K, N, 4)
+    want = hbl.hbitlinear_forward(x, packed, N, al, 4, EPS)
+    lazy = torch._lazy_clone(x)
+    assert torch.equal(hbl.hbitlinear_forward(lazy, packed, N, al, 4, EPS), want) and torch._C._is_cow_tensor(lazy)
+    shared = torch.full((T, N), 7.0, dtype=torch.bfloat16, device="cuda")
+    y = torch._lazy_clone(shared)                                            # 64 MiB that are copied when they are written
+    torch.cuda.synchronize()
+    torch.cuda.empty_cache()
+    total = torch.cuda.get_device_properties(0).total_memory
+    torch.cuda.set_per_process_memory_fraction((torch.cuda.memory_reserved() + (8 << 20)) / total)
+    try:
+        with pytest.raises(torch.OutOfMemoryError):
+            hbl.hbitlinear_forward(x, packed, N, al, 4, EPS, y=y, workspace=ws)
+    finally:
+        torch.cuda.set_per_process_memory_fraction(1.0)
+    shared = torch.full((T, N), 7.0, dtype=torch.bfloat16, device="cuda")
+    y = torch._lazy_clone(shared)
+    assert hbl.hbitlinear_forward(x, packed, N, al, 4, EPS, y=y, workspace=ws) is y
+    assert torch.equal(y, want) and bool((shared == 7.0).all())
