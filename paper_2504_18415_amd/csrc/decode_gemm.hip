@@ -416,9 +416,8 @@ int launch_form(const DecodeArgs& planned, int wgs, int counters, hipStream_t st
     }
     constexpr int ROWS = SHARE ? 32 : RQ * 8;
     constexpr size_t lds = (size_t)D * ((SHARE ? 1 : NW) * ROWS * kBK + NW * 1024);
-    auto kern = decode_gemm_kernel<SHARE, RQ, D, NW, BYTES>;
-    static std::atomic<uint64_t> lds_allowed{0};   // per instantiation: devices already set up
-    if (const int rc = allow_dynamic_lds(kern, lds, lds_allowed); rc != HBL_OK) return rc;
+    constexpr auto kern = decode_gemm_kernel<SHARE, RQ, D, NW, BYTES>;
+    if (const int rc = allow_dynamic_lds<kern, lds>(); rc != HBL_OK) return rc;
     launch_kernel("decode_gemm_kernel", kern, dim3((unsigned)wgs), dim3(64 * NW), lds, stream, a);
     return after_launch();
 }

@@ -9,8 +9,6 @@
 // Bound: one serial chain - launch, a row's loads, transform and two reductions across the wave, LDS, MFMA, a sum over the waves.
 // 16 fp32 rows of 256 against 256 output rows, transformed: 3.5 us of GPU time for 5.2 with two launches, 5.3 us for 9.3 called
 // one after another from the host.
-#include <atomic>
-
 #include "quant_bodies.h"
 
 namespace hbl {
@@ -90,12 +88,10 @@ template <int LOG2K, int MAXC, int BITS, bool BF16, int WAVES>
 int launch_cfg(const FusedBytesArgs& a, hipStream_t stream) {
     const int nkb = a.K / 128;
     const size_t lds = (size_t)(nkb > WAVES ? nkb : WAVES) * 1024 + (size_t)a.T * code_row_bytes(a.K);   // at most 85 KiB
-    auto kern = fused_bytes_kernel<LOG2K, MAXC, BITS, BF16, WAVES>;
-    if constexpr (MAXC > 4) {
-        static std::atomic<uint64_t> lds_allowed{0};   // per instantiation: devices already set up
-        if (const int rc = allow_dynamic_lds(kern, (kFusedLength / 128) * 1024 + WAVES * code_row_bytes(kFusedLength), lds_allowed); rc != HBL_OK)
-            return rc;
-    }
+    constexpr auto kern = fused_bytes_kernel<LOG2K, MAXC, BITS, BF16, WAVES>;
+    constexpr int longest = LOG2K ? 1 << LOG2K : 512 * MAXC;   // (16 rows of 2048 are 256 bytes beyond 48 KiB)
+    constexpr size_t most = (longest / 128 > WAVES ? longest / 128 : WAVES) * 1024 + WAVES * code_row_bytes(longest);
+    if (const int rc = allow_dynamic_lds<kern, most>(); rc != HBL_OK) return rc;
     launch_kernel("fused_bytes_kernel", kern, dim3((unsigned)(a.N / 32)), dim3(64 * WAVES), lds, stream, a);
     return after_launch();
 }

@@ -7,8 +7,6 @@
 // transforms and quantises the rows with the code of the quantiser launches - the same row in every workgroup, which costs no
 // time that the weights do not need anyway - into an image of records in LDS, and multiplies from there.  No workgroup waits
 // for another one.
-#include <atomic>
-
 #include "large_rows.h"
 
 namespace hbl {
@@ -227,9 +225,8 @@ template <int LOG2K, int PW, bool BF16, int RB, int RW>
 int launch_cfg(FusedArgs a, const FusedLayout& l, hipStream_t stream) {
     a.codes_off = (uint32_t)l.codes_off;
     a.weights_off = (uint32_t)l.weights_off;
-    auto kern = fused_small_kernel<LOG2K, PW, BF16, RB, RW>;
-    static std::atomic<uint64_t> lds_allowed{0};   // per instantiation: devices already set up
-    if (const int rc = allow_dynamic_lds(kern, kCuLds - 1024, lds_allowed); rc != HBL_OK) return rc;
+    constexpr auto kern = fused_small_kernel<LOG2K, PW, BF16, RB, RW>;
+    if (const int rc = allow_dynamic_lds<kern, kCuLds - 1024>(); rc != HBL_OK) return rc;
     launch_kernel("fused_small_kernel", kern, dim3((unsigned)((a.N + RW - 1) / RW)), dim3(64 * fused_waves(LOG2K, PW, RB)), l.bytes, stream, a);
     return after_launch();
 }

@@ -17,8 +17,6 @@
 // so that every global access is one contiguous CH-element piece per lane and
 // the stage order e -> lane -> r -> wave is ascending.  The wave stages swap
 // the wave bits with the low r bits through LDS once, then run in registers.
-#include <atomic>
-
 #include "large_rows.h"
 
 namespace hbl {
@@ -36,10 +34,9 @@ template <int LOG2K, int W, int BITS, bool BF16, bool HADAMARD>
 int launch_one(const void* x, int64_t T, int8_t* codes, float* s_dequant, int32_t* code_sum, RowParams rp,
                int code_offset, hipStream_t stream) {
     constexpr int K = 1 << LOG2K;
-    const size_t lds = (HADAMARD && W > 1) ? sizeof(float) * K : 0;
-    auto kern = fwht_quant_kernel<LOG2K, W, BITS, BF16, HADAMARD>;
-    static std::atomic<uint64_t> lds_allowed{0};   // per instantiation: devices already set up
-    if (const int rc = allow_dynamic_lds(kern, lds, lds_allowed); rc != HBL_OK) return rc;
+    constexpr size_t lds = (HADAMARD && W > 1) ? sizeof(float) * K : 0;
+    constexpr auto kern = fwht_quant_kernel<LOG2K, W, BITS, BF16, HADAMARD>;
+    if (const int rc = allow_dynamic_lds<kern, lds>(); rc != HBL_OK) return rc;
     launch_kernel("fwht_quant_kernel", kern, dim3((unsigned)T), dim3(64 * W), lds, stream, x, codes, s_dequant, code_sum, rp, code_offset);
     return after_launch();
 }
@@ -137,9 +134,8 @@ int launch_bigrow_form(const void* x, int64_t T, int8_t* codes, float* s_dequant
                        int code_offset, hipStream_t stream) {
     using L = LargeRow<LOG2K, R>;
     constexpr size_t lds = sizeof(float) * L::K;
-    auto kern = fwht_quant_bigrow_kernel<LOG2K, R, BITS, BF16, BF6OUT, NORM>;
-    static std::atomic<uint64_t> lds_allowed{0};   // per instantiation: devices already set up
-    if (const int rc = allow_dynamic_lds(kern, lds, lds_allowed); rc != HBL_OK) return rc;
+    constexpr auto kern = fwht_quant_bigrow_kernel<LOG2K, R, BITS, BF16, BF6OUT, NORM>;
+    if (const int rc = allow_dynamic_lds<kern, lds>(); rc != HBL_OK) return rc;
     constexpr int64_t most = (int64_t)1 << 22;   // rows per launch: a grid has fewer than 2^32 threads
     for (int64_t first = 0; first < T; first += most)
         launch_kernel("fwht_quant_bigrow_kernel", kern, dim3((unsigned)(T - first < most ? T - first : most)), dim3(L::NT), lds, stream,
@@ -271,14 +267,15 @@ int launch_quant_grouped(const QuantGroupArgs& args, int bits, int x_dtype, hipS
     }
     if (rows == 0) return HBL_OK;
     const bool bf = x_dtype == HBL_BF16;
-    auto launch = [&](auto kern) -> int {
-        static std::atomic<uint64_t> lds_allowed{0};   // per instantiation: devices already set up
-        if (const int rc = allow_dynamic_lds(kern, 64 * 1024, lds_allowed); rc != HBL_OK) return rc;
+    auto launch = [&](auto bits_tag, auto bf_tag) -> int {
+        constexpr auto kern = quant_grouped_kernel<decltype(bits_tag)::value, decltype(bf_tag)::value>;
+        if (const int rc = allow_dynamic_lds<kern, 64 * 1024>(); rc != HBL_OK) return rc;
         launch_kernel("quant_grouped_kernel", kern, dim3((unsigned)rows), dim3((unsigned)threads), lds, stream, args);
         return after_launch();
     };
-    if (bits == 8) return bf ? launch(quant_grouped_kernel<8, true>) : launch(quant_grouped_kernel<8, false>);
-    return bf ? launch(quant_grouped_kernel<4, true>) : launch(quant_grouped_kernel<4, false>);
+    using std::integral_constant;
+    if (bits == 8) return bf ? launch(integral_constant<int, 8>{}, std::true_type{}) : launch(integral_constant<int, 8>{}, std::false_type{});
+    return bf ? launch(integral_constant<int, 4>{}, std::true_type{}) : launch(integral_constant<int, 4>{}, std::false_type{});
 }
 
 int launch_fwht_only(const void* x, int x_dtype, int64_t T, int64_t K, void* out, int out_dtype, hipStream_t stream) {

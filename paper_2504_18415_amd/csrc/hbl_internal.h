@@ -50,18 +50,20 @@ inline int after_launch() {
     return e == hipSuccess ? HBL_OK : note_hip_error(e);
 }
 
-// Allow `kern` more than 48 KiB of dynamic LDS.  The attribute belongs to the (function, device) pair: set
-// once per device this process launches on (`done` is the caller's per-instantiation mask of devices, bit =
-// device ordinal mod 64).
-template <typename Kernel>
-inline int allow_dynamic_lds(Kernel kern, size_t bytes, std::atomic<uint64_t>& done) {
-    if (bytes <= 48 * 1024) return HBL_OK;
+// Allow KERN up to BYTES of dynamic LDS where that is more than 48 KiB: a launch asks for the most that it may ever use.  The
+// attribute belongs to the (function, device) pair and is set once per device this process launches on.  The mask of devices
+// (bit = device ordinal mod 64) belongs to this instantiation, and that to the kernel itself: its type would not do, kernels of the
+// same arguments share it.
+template <auto KERN, size_t BYTES>
+inline int allow_dynamic_lds() {
+    if constexpr (BYTES <= 48 * 1024) return HBL_OK;
+    static std::atomic<uint64_t> done{0};
     int dev = 0;
     hipError_t e = hipGetDevice(&dev);
     if (e != hipSuccess) return note_hip_error(e);
     const uint64_t bit = 1ull << (dev & 63);
     if (done.load(std::memory_order_acquire) & bit) return HBL_OK;
-    e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+    e = hipFuncSetAttribute(reinterpret_cast<const void*>(KERN), hipFuncAttributeMaxDynamicSharedMemorySize, (int)BYTES);
     if (e != hipSuccess) return note_hip_error(e);
     done.fetch_or(bit, std::memory_order_release);
     return HBL_OK;

@@ -14,7 +14,6 @@
 // 22.6 -> 11.9, 17 x 4096 -> 4096 12.0 -> 8.9, 32 x 4096 -> 32768 14.9 -> 13.4 (beyond that many rows: decode_shared_preferred).
 // INT8 activations: 64 x 16384 -> 4096 24.4 -> 16.9, 24 x 8192 -> 3072 15.2 -> 11.2, 97 x 11008 -> 4096 33.7 -> 16.8, 128 x
 // 4096 -> 4096 24.4 -> 11.9, 300 x 8192 -> 3072 34.9 -> 22.1 us.
-#include <atomic>
 #include <type_traits>
 
 #include "gemm_common.h"
@@ -284,9 +283,8 @@ template <typename F, bool RAW>
 int launch_cfg(MidProblem a, hipStream_t stream) {
     a.tiles_n = (int)F::tiles_n(a.N);
     a.tiles_t = (int)F::tiles_t(a.T);
-    auto kern = mid_gemm_kernel<F, RAW>;
-    static std::atomic<uint64_t> lds_allowed{0};   // per instantiation: devices already set up
-    if (const int rc = allow_dynamic_lds(kern, F::LDS, lds_allowed); rc != HBL_OK) return rc;
+    constexpr auto kern = mid_gemm_kernel<F, RAW>;
+    if (const int rc = allow_dynamic_lds<kern, F::LDS>(); rc != HBL_OK) return rc;
     launch_kernel("mid_gemm_kernel", kern, dim3((unsigned)(a.tiles_n * a.tiles_t)), dim3(F::THREADS), F::LDS, stream, a);
     return after_launch();
 }
@@ -349,9 +347,8 @@ int launch_grouped_forms(MidArgs& args, hipStream_t stream) {
         wgs += p.tiles_n * p.tiles_t;
     }
     constexpr size_t lds = FA::LDS > FB::LDS ? FA::LDS : FB::LDS;
-    auto kern = mid_gemm_grouped_kernel<FA, FB>;
-    static std::atomic<uint64_t> lds_allowed{0};   // per instantiation: devices already set up
-    if (const int rc = allow_dynamic_lds(kern, lds, lds_allowed); rc != HBL_OK) return rc;
+    constexpr auto kern = mid_gemm_grouped_kernel<FA, FB>;
+    if (const int rc = allow_dynamic_lds<kern, lds>(); rc != HBL_OK) return rc;
     launch_kernel("mid_gemm_grouped_kernel", kern, dim3((unsigned)wgs), dim3(FA::THREADS), lds, stream, args);
     return after_launch();
 }

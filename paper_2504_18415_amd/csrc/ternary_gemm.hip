@@ -12,7 +12,6 @@
 // correction left is for an offset on the stored codes (INT4 codes travel as q + 8): offset * sum_k c[o][k],
 // removed in the epilogue in int32.  Both operands are staged through LDS with direct global->LDS 16-byte
 // loads, NSTAGE deep: codes into an XOR-swizzled [token][128 B] layout, weights tile by tile.
-#include <atomic>
 #include <type_traits>
 
 #include "gemm_common.h"
@@ -346,9 +345,8 @@ int launch_cfg(GemmArgs a, hipStream_t stream) {
     constexpr size_t lds = (size_t)NSTAGE * (BT * kBK + (BN / 32 + NW - 1) / NW * NW * 1024);
     a.tiles_n = (a.N + BN - 1) / BN;
     a.tiles_t = (a.T + BT - 1) / BT;
-    auto kern = ternary_gemm_kernel<WAVES_N, WAVES_T, TN, TT, NSTAGE, RAW>;
-    static std::atomic<uint64_t> lds_allowed{0};   // per instantiation: devices already set up
-    if (const int rc = allow_dynamic_lds(kern, lds, lds_allowed); rc != HBL_OK) return rc;
+    constexpr auto kern = ternary_gemm_kernel<WAVES_N, WAVES_T, TN, TT, NSTAGE, RAW>;
+    if (const int rc = allow_dynamic_lds<kern, lds>(); rc != HBL_OK) return rc;
     launch_kernel("ternary_gemm_kernel", kern, dim3((unsigned)(a.tiles_n * a.tiles_t)), dim3(64 * WAVES_N * WAVES_T), lds,
                        stream, a);
     return after_launch();

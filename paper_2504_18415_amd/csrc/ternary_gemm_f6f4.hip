@@ -14,7 +14,6 @@
 //     as it is (twelve 1 KiB pieces), and an operand is one 16-byte + one 8-byte LDS read;
 //   - the packed weights (sign / magnitude bit pairs) become fp4 operands with two AND and one shift per
 //     dword: two operand registers of eight fp4 values each.
-#include <atomic>
 #include <type_traits>
 
 #include "gemm_common.h"
@@ -366,9 +365,8 @@ int launch_cfg(GemmArgs a, hipStream_t stream) {
     constexpr size_t lds = (size_t)NSTAGE * (BT * kRecordRowBytes + (BN / 32 + NW - 1) / NW * NW * 1024);
     a.tiles_n = (a.N + BN - 1) / BN;
     a.tiles_t = (a.T + BT - 1) / BT;
-    auto kern = ternary_gemm_f6f4_kernel<WAVES_N, WAVES_T, TN, TT, NSTAGE, RAW>;
-    static std::atomic<uint64_t> lds_allowed{0};   // per instantiation: devices already set up
-    if (const int rc = allow_dynamic_lds(kern, lds, lds_allowed); rc != HBL_OK) return rc;
+    constexpr auto kern = ternary_gemm_f6f4_kernel<WAVES_N, WAVES_T, TN, TT, NSTAGE, RAW>;
+    if (const int rc = allow_dynamic_lds<kern, lds>(); rc != HBL_OK) return rc;
     launch_kernel("ternary_gemm_f6f4_kernel", kern, dim3((unsigned)(a.tiles_n * a.tiles_t)), dim3(64 * WAVES_N * WAVES_T), lds,
                        stream, a);
     return after_launch();

@@ -1066,6 +1066,19 @@ def test_grouped_quantiser_workgroup_sizes(hbl, bits, lengths):
 
 
 @pytest.mark.parametrize("bits", [4, 8])
+@pytest.mark.parametrize("dtype", [synth.BF16, synth.F32])
+def test_kernels_with_more_than_48_kib_of_lds(hbl, bits, dtype):
+    """Each of the grouped quantisers on rows of 64 KiB, and 16 rows of 2048 in one launch (256 bytes beyond 48 KiB)."""
+    note(f"more than 48 KiB of LDS bits={bits} {dtype}")
+    sites = [synth.Site(f"l{i}", T, K, 64, hadamard=h, x_dtype=dtype, seed=70 + i, outlier_frac=0.01, outlier_scale=30.0)
+             for i, (T, K, h) in enumerate([(3, 16384, True), (2, 640, False)])]
+    run_group(hbl, sites, [bits] * len(sites))
+    site = synth.Site("l", 16, 2048, 96, hadamard=False, x_dtype=dtype, seed=72, outlier_frac=0.01, outlier_scale=30.0)
+    assert hbl.forward_route(16, 2048, 96, bits, False) == "fused_bytes"
+    run_site(hbl, site, bits)
+
+
+@pytest.mark.parametrize("bits", [4, 8])
 @pytest.mark.parametrize("T", [5, 16, 33, 48, 64])
 def test_grouped_short_and_odd_k(hbl, bits, T):
     """K ranges of 1, 3, 4, 5 and 9 blocks: shorter than the copy ring of the weight-streaming kernel (up to 16 tokens),
