@@ -111,7 +111,8 @@ Route forward_route(int64_t T, int64_t K, int64_t N, int x_dtype, int bits, bool
     // up to 16 tokens: the weight-streaming kernel, unless its plan leaves long serial chains of tiles
     if (decode_stream_preferred(T, K, N, bf6_path_supported(K, bits))) return Route::kStream;
     if (bf6_path_supported(K, bits) && decode_shared_preferred(T, K, N)) return Route::kStream;
-    return mid_gemm_preferred(T, K, N, bf6_path_supported(K, bits)) ? Route::kMid : Route::kPrefill;
+    const int tile = bf6_path_supported(K, bits) ? records_tile(T, K, N) : bytes_tile(T, K, N);
+    return tile == kTileMid ? Route::kMid : Route::kPrefill;
 }
 
 namespace {
@@ -415,6 +416,14 @@ int hbl_test_forward_route(int64_t T, int64_t K, int64_t N, int x_dtype, int bit
     if (rc != HBL_OK) return rc;
     if (T < 1) return HBL_E_SHAPE;
     return (int)forward_route(T, K, N, x_dtype, bits, hadamard != 0, norm != 0);
+}
+
+int hbl_test_gemm_tile(int64_t T, int64_t K, int64_t N, int code_form) {
+    if (code_form != HBL_CODES_INT8 && code_form != HBL_CODES_UINT4_PLUS8 && code_form != HBL_CODES_BF6) return HBL_E_BITS;
+    const int rc = check_gemm_shape(T, K, N, false);
+    if (rc != HBL_OK) return rc;
+    if (T < 1 || (code_form == HBL_CODES_BF6 && K < 512)) return HBL_E_SHAPE;
+    return code_form == HBL_CODES_BF6 ? records_tile(T, K, N) : bytes_tile(T, K, N);
 }
 
 size_t hbl_code_bytes(int64_t T, int64_t K, int code_form) {

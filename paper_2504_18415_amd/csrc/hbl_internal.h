@@ -182,6 +182,10 @@ constexpr int kTileAuto = -1, kTileSquare = 0 /*256 x 256*/, kTileSmall = 1 /*12
 constexpr int kTileHalf = 10 /*256 x 128*/, kTileSmallFlat = 11 /*128 x 128, two stages*/,
               kTileNarrow = 12 /*192 x 128, two stages*/, kTileNarrowDeep = 13 /*192 x 128, four stages*/;   // (11 to 13: records)
 
+// The tile that a launch of either kernel takes for a shape (kTileMid: the mid-size kernel does the work).
+int bytes_tile(int64_t T, int64_t K, int64_t N);     // ternary_gemm.hip
+int records_tile(int64_t T, int64_t K, int64_t N);   // ternary_gemm_f6f4.hip
+
 // GEMM + epilogue. If acc_out != nullptr the raw int32 accumulators are written
 // (no scales, no code_sum needed); otherwise y (bf16) is written.
 int launch_ternary_gemm(const int8_t* codes, int code_offset, int64_t T, int64_t K, const void* packed, int64_t N,

@@ -31,6 +31,12 @@ int hbl_test_grouped_plan(const hbl_problem* problems, int n_problems, int* rout
 int hbl_test_forward_route(int64_t T, int64_t K, int64_t N, int x_dtype, int bits, int hadamard, int norm);
 
 /*
+ * Host only: the tile (numbers below; 4: 128 features x 32 or 64 tokens) that the GEMM on codes of this form takes, in the
+ * stage-level calls and in forward calls that end in the mid-size (3) or a prefill kernel; or a negative status.
+ */
+int hbl_test_gemm_tile(int64_t T, int64_t K, int64_t N, int code_form);
+
+/*
  * The integer contraction of Eq. 7 through one named workgroup tile of a prefill GEMM kernel (T > 64):
  * acc[t][o] = sum_k q[t][k] c[o][k] as int32 [T, N], on a shape of the caller's choice - the forward
  * calls pick the tile from the shape, so most tiles would otherwise be reachable at benchmark sizes only.

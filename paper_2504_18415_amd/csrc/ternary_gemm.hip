@@ -365,11 +365,8 @@ constexpr TileCost kTileCosts[] = {{kTileWide, 512, 128, 1.224f, 10.927f, 0.510f
                                    {kTileSmall, 128, 128, 0.434f, 0.859f, 0.455f, 1.068f, 3.408f}};
 
 template <bool RAW>
-int choose(const GemmArgs& a, hipStream_t stream, int tile) {
-    int cfg = cheapest_tile(kTileCosts, a.T, a.K, a.N);
-    if (a.T <= 64) cfg = kTileFewTokens;
-    if (tile != kTileAuto) cfg = tile;   // parity tests name the tile themselves
-    switch (cfg) {
+int launch_tile(const GemmArgs& a, hipStream_t stream, int tile) {
+    switch (tile) {
         case kTileFewTokens:   // 128 features x 32 or 64 tokens, 4 waves of one feature tile
             return a.T <= 32 ? launch_cfg<4, 1, 1, 1, 4, RAW>(a, stream) : launch_cfg<4, 1, 1, 2, 4, RAW>(a, stream);
         case kTileSmall: return launch_cfg<2, 2, 2, 2, 2, RAW>(a, stream);    // 128 x 128, 4 waves
@@ -381,6 +378,11 @@ int choose(const GemmArgs& a, hipStream_t stream, int tile) {
 }
 
 }  // namespace
+
+int bytes_tile(int64_t T, int64_t K, int64_t N) {
+    if (mid_gemm_preferred(T, K, N, false) || mid_large_bytes_preferred(T, N)) return kTileMid;   // too few tiles for the chip
+    return T <= 64 ? kTileFewTokens : cheapest_tile(kTileCosts, T, K, N);
+}
 
 int launch_ternary_gemm(const int8_t* codes, int code_offset, int64_t T, int64_t K, const void* packed, int64_t N,
                         const float* s_dequant, const float* w_scales,
@@ -400,7 +402,8 @@ int launch_ternary_gemm(const int8_t* codes, int code_offset, int64_t T, int64_t
     a.N = (int)N;
     a.rows_per_group = n_scale_groups > 0 ? (int)(N / n_scale_groups) : (int)N;
     a.tiles_n = a.tiles_t = 0;
-    if (tile == kTileAuto && (mid_gemm_preferred(T, K, N, false) || mid_large_bytes_preferred(T, N))) {   // too few tiles for the chip
+    if (tile == kTileAuto) tile = bytes_tile(T, K, N);   // (parity tests name the tile themselves)
+    if (tile == kTileMid) {
         MidProblem m = {};
         m.codes = a.codes;
         m.packed = a.packed;
@@ -416,7 +419,7 @@ int launch_ternary_gemm(const int8_t* codes, int code_offset, int64_t T, int64_t
         m.w_row_sum = a.w_row_sum;
         return launch_mid_gemm(m, false, stream);
     }
-    return acc_out ? choose<true>(a, stream, tile) : choose<false>(a, stream, tile);
+    return acc_out ? launch_tile<true>(a, stream, tile) : launch_tile<false>(a, stream, tile);
 }
 
 }  // namespace hbl

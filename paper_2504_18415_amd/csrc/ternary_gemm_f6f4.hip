@@ -374,6 +374,10 @@ int launch_cfg(GemmArgs a, hipStream_t stream) {
 
 }  // namespace
 
+int records_tile(int64_t T, int64_t K, int64_t N) {
+    return mid_gemm_preferred(T, K, N, true) ? kTileMid : prefill_tile(T, K, N);   // (too few tiles for the chip: mid-size)
+}
+
 int launch_ternary_gemm_f6f4(const int8_t* code_records, int64_t T, int64_t K, const void* packed, int64_t N,
                              const float* s_dequant, const float* w_scales, int64_t n_scale_groups, void* y_bf16,
                              hipStream_t stream, int32_t* acc_out, int tile) {
@@ -390,10 +394,9 @@ int launch_ternary_gemm_f6f4(const int8_t* code_records, int64_t T, int64_t K, c
     a.N = (int)N;
     a.rows_per_group = n_scale_groups > 0 ? (int)(N / n_scale_groups) : (int)N;
     a.code_offset = 0;      // signed operands: no correction terms
-    int cfg = mid_gemm_preferred(T, K, N, true) ? kTileMid : prefill_tile(T, K, N);   // (too few tiles for the chip: mid-size)
-    if (tile != kTileAuto) cfg = tile;   // parity tests name the tile themselves
+    if (tile == kTileAuto) tile = records_tile(T, K, N);   // (parity tests name the tile themselves)
     const bool raw = acc_out != nullptr;
-    switch (cfg) {
+    switch (tile) {
         case kTileSquare:   // 256 x 256, 2 x 2 waves of 128 x 128
             return raw ? launch_cfg<2, 2, 4, 4, 3, true>(a, stream) : launch_cfg<2, 2, 4, 4, 3>(a, stream);
         case kTileSmall:    // 128 x 128

@@ -35,9 +35,9 @@ EXPORTS = [
     "hbl_code_bytes", "hbl_bitlinear_forward_small",
 ]
 # exports for the test suite only (csrc/hbl_test_exports.h)
-TEST_EXPORTS = ["hbl_test_grouped_plan", "hbl_test_gemm_i32_tile", "hbl_test_forward_route"]
+TEST_EXPORTS = ["hbl_test_grouped_plan", "hbl_test_gemm_i32_tile", "hbl_test_forward_route", "hbl_test_gemm_tile"]
 ROUTES = ("fused", "stream", "mid", "prefill", "fused_bytes")
-TILE_SQUARE, TILE_SMALL, TILE_WIDE, TILE_MID = 0, 1, 2, 3
+TILE_SQUARE, TILE_SMALL, TILE_WIDE, TILE_MID, TILE_FEW_TOKENS = 0, 1, 2, 3, 4
 TILE_HALF, TILE_SMALL_FLAT, TILE_NARROW, TILE_NARROW_DEEP = 10, 11, 12, 13
 
 _lib = None
@@ -99,6 +99,7 @@ def lib():
         L.hbl_test_grouped_plan.argtypes = [ctypes.POINTER(Problem), ci, ip, ip, ip, ip]
         L.hbl_test_gemm_i32_tile.argtypes = [vp, ci, i64, i64, vp, i64, vp, ci, vp]
         L.hbl_test_forward_route.argtypes = [i64, i64, i64, ci, ci, ci, ci]
+        L.hbl_test_gemm_tile.argtypes = [i64, i64, i64, ci]
         L.hbl_gemm_i32_bf6.argtypes = [vp, i64, i64, vp, i64, vp, vp, sz, vp]
         L.hbl_bitlinear_forward_small.argtypes = [vp, ci, i64, i64, vp, i64, vp, i64, ci, f32, ci, vp, vp]
         L.hbl_code_bytes.restype = sz
@@ -516,6 +517,14 @@ def forward_route(T: int, K: int, N: int, bits: int = 4, hadamard: bool = True, 
     if rc < 0:
         raise HblError(rc, "forward_route")
     return ROUTES[rc]
+
+
+def gemm_tile(T: int, K: int, N: int, code_form: int) -> int:
+    """Host-only: the tile (``TILE_*``) that the GEMM takes for codes of this form, beyond the streaming kernel's range."""
+    rc = lib().hbl_test_gemm_tile(T, K, N, code_form)
+    if rc < 0:
+        raise HblError(rc, "gemm_tile")
+    return rc
 
 
 def kv_quant_absmax(x: torch.Tensor, bits: int, eps: float = EPS, packed: Optional[torch.Tensor] = None,

@@ -246,6 +246,22 @@ def test_routes_of_17_to_64_tokens_against_many_output_rows(L):
     assert route(33, 512, 131072, 4) == route(64, 4096, 131072, 4) == "mid"
 
 
+def test_route_names_the_kernel_that_runs_for_large_byte_tiles(L):
+    """Bytes of more than 64 tokens: up to 384 tiles of 128 x 128 they are the mid-size kernel's, and the route says so."""
+    from paper_2504_18415_amd import hbl
+    for bits, K, form in ((8, 2048, hbl.CODES_INT8), (8, 640, hbl.CODES_INT8), (4, 384, hbl.CODES_UINT4_PLUS8)):
+        for T, N in ((2048, 2048), (1000, 2208), (1536, 4096), (100, 32768)):          # 256, 144, 384, 256 tiles
+            assert hbl.forward_route(T, K, N, bits, hadamard=False) == "mid", (T, K, N, bits)
+            assert hbl.gemm_tile(T, K, N, form) == hbl.TILE_MID
+        for T, N in ((1537, 4096), (1536, 4128), (663, 8256)):                         # 416, 396, 390
+            assert hbl.forward_route(T, K, N, bits, hadamard=False) == "prefill", (T, K, N, bits)
+            assert hbl.gemm_tile(T, K, N, form) not in (hbl.TILE_MID, hbl.TILE_FEW_TOKENS)
+    assert hbl.forward_route(2048, 2048, 2048, 4, hadamard=False) == "prefill"         # records: prefill tiles
+    for T, K, N, form in ((0, 512, 64, hbl.CODES_INT8), (4, 384, 64, hbl.CODES_BF6), (4, 100, 64, hbl.CODES_INT8)):
+        with pytest.raises(hbl.HblError):
+            hbl.gemm_tile(T, K, N, form)
+
+
 def test_kv_quant_argument_errors_before_any_launch(L):
     from paper_2504_18415_amd import hbl
     E = {n: getattr(hbl, n) for n in ("E_NULL", "E_SHAPE", "E_BITS", "E_DTYPE", "E_ALIGN")}

@@ -891,7 +891,8 @@ def test_prefill_tiles_bf16_outputs(hbl, T, N, groups, bits, K):
     bytes, and bytes with the INT4 offset that the row sums take out: every output bit for bit as the exact product of
     the codes, scaled and rounded, gives it."""
     note(f"prefill tiles, bf16 outputs T={T} N={N} K={K} bits={bits}")
-    assert hbl.forward_route(T, K, N, bits, hadamard=False) == "prefill"
+    mid = (bits == 8 or K < 512) and T == 1000                                   # bytes, few tiles: the mid-size kernel's
+    assert hbl.forward_route(T, K, N, bits, hadamard=False) == ("mid" if mid else "prefill")
     g = torch.Generator(device="cuda").manual_seed(T + N + K)
     c = torch.randint(-1, 2, (N, K), dtype=torch.int8, device="cuda", generator=g)
     x = torch.randn((T, K), device="cuda", generator=g)
