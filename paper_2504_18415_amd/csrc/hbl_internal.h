@@ -293,8 +293,8 @@ struct MidArgs {
     MidProblem p[kMaxGroup];
 };
 bool mid_gemm_preferred(int64_t T, int64_t K, int64_t N, bool records);
-// Whether bytes beyond its range take its 128 x 64 or 128 x 128 tiles instead of the prefill kernel's 128 x 128 ones.
-bool mid_large_bytes_preferred(int64_t T, int64_t N);
+// Whether bytes beyond its range take its 128 x 64 or 128 x 128 tiles instead of a prefill kernel's.
+bool mid_large_bytes_preferred(int64_t T, int64_t K, int64_t N);
 int launch_mid_gemm(const MidProblem& a, bool records, hipStream_t stream);
 // Whether a group takes that kernel (more than 16 tokens somewhere).
 bool mid_group_preferred(const DecodeProblem* p, int n);

@@ -306,14 +306,17 @@ int64_t mid_tiles(int64_t T, int64_t N) { return MidForm<4, 2, 2, 2>::tiles_n(N)
 
 constexpr int64_t kMidResident = 512;   // workgroups of 8 waves and up to 80 KiB of LDS that the chip holds at once
 
-// Bytes, more than 512 tiles of 64 x 64: the 128 x 128 tile of the prefill kernel keeps one wave per SIMD, which issues the 15
-// instructions that expand 16 weights at half the rate of two.  While a launch of such tiles fits the chip at once (256) or leaves
-// much of a second round idle (384), 8-wave workgroups of two K groups are faster.  128 x 128 outputs with at most 256 tiles: K =
-// 512 0.95 to 0.97 of the time, 1024 0.93 to 1.00, 2048 0.90 to 1.00, 4096 and more 0.91 to 1.01.  128 x 64 outputs, two workgroups
-// per CU: up to 256 tiles K = 256 0.83 to 0.92, 512 0.87 to 0.95, 1024 0.92 to 0.96, 2048 0.90 to 1.00, above 0.94 to 1.06; 257 to
-// 384 tiles 0.90 to 1.01 at every K (128 x 128 outputs: 1.04 to 1.24).  (2048 x 2048 -> 2048 with the quantiser 19.6 -> 18.6 us, 1536 x
-// 8192 -> 2048 43.6 -> 40.6, 1536 x 1024 -> 3072 15.4 -> 13.9.)  From 385 to 512 tiles both are 1.04 to 1.2 times as slow.  Records expand
-// 16 weights by three instructions: 1.0 to 1.35 there.
+// Bytes, more than 512 tiles of 64 x 64: 8-wave workgroups of two K groups on 128 x 64 outputs, of which a CU holds two, or 128 x
+// 128 ones, one a CU.  The prefill kernel's 128 x 128 tile issues the 15 instructions that expand 16 weights from four waves; where a
+// launch is one round, two waves a SIMD of one tile hide it better.  Time of the GEMM, 1100 sizes, against that tile (two stages) and
+// the 256 x 128 one (H):
+//   all 128 x 64 tiles resident at once (512; at most 256 of 128 x 128 are): K up to 1024 0.93 to 0.99 of the small tile, 2048 0.95,
+//     4096 0.92, 8192 0.90, H 1.3 to 1.5 times as slow.  Rows beyond 1024: 128 x 128 outputs, 0.91 to 1.01 of 128 x 64
+//   more, up to 384 tiles of 128 x 128: K = 128 1.10 to 1.15 of the small tile, 256 1.04, 384 1.03, 512 0.95, 768 0.97, 1024 0.97 (H
+//     1.03), 1152 to 1536 0.98 to 1.03 of H, 2048 1.04, 3072 1.06, 4096 1.09, 8192 1.2
+//   385 to 512: 1.04 to 1.34 of the better of the two
+// (2048 x 2048 -> 2048 with the quantiser 19.6 -> 18.6 us, 1536 x 1024 -> 3072 15.4 -> 13.9.)  Records expand 16 weights by three
+// instructions: 1.0 to 1.35 there.
 int64_t mid_large_tiles(int64_t T, int64_t N) { return ((N + 127) / 128) * ((T + 127) / 128); }
 
 template <bool I8, bool RAW>
@@ -383,7 +386,11 @@ bool mid_gemm_preferred(int64_t T, int64_t K, int64_t N, bool records) {
     return T <= 64 && (records || K > (T <= 32 || N > 65536 ? 1024 : 384));
 }
 
-bool mid_large_bytes_preferred(int64_t T, int64_t N) { return T > 64 && mid_large_tiles(T, N) <= 384; }
+bool mid_large_bytes_preferred(int64_t T, int64_t K, int64_t N) {
+    if (T <= 64) return false;
+    return MidForm<2, 3, 4, 2, true>::tiles_n(N) * MidForm<2, 3, 4, 2, true>::tiles_t(T) <= 512 ||
+           (K >= 512 && K <= 1536 && mid_large_tiles(T, N) <= 384);
+}
 
 int launch_mid_gemm(const MidProblem& a, bool records, hipStream_t stream) {
     if (records) return a.acc_out ? launch_form<false, true>(a, stream) : launch_form<false, false>(a, stream);

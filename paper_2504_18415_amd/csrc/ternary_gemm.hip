@@ -352,13 +352,17 @@ int launch_cfg(GemmArgs a, hipStream_t stream) {
     return after_launch();
 }
 
-// Workgroup tile (more than 384 tiles of 128 x 128; fewer are the mid-size kernel's): the wide one (512 x 128, 32 KB per stage
+// Workgroup tile (few tiles are the mid-size kernel's): the wide one (512 x 128, 32 KB per stage
 // through L2 and LDS) spends the fewest bytes per product, but a CU holds one of its workgroups, and start-up and output of a
 // round (11 us) pass with the matrix cores idle.  Of 256 x 128 (waves of 64 x 128: half the weight expansion of 128 x 64) a CU
-// holds two, of 128 x 128 with two stages four.  The least estimate is taken; 109 sizes: 0.85 of the time of the former rule
-// (wide or square from 200 tiles of 256 x 256 on, else 128 x 128 with four stages), none above 1.03.  GEMM, us: T = 8192,
-// K = 4096, N = 12288 333 -> 315; T = 2048, K = 8192, N = 11008 175 -> 145; T = 5811, K = 768, N = 10336 74.1 -> 56.9; T = 8192,
-// K = 16384, N = 4096 stays at 387.
+// holds two, of 128 x 128 with two stages three.  Short rows take the small tile: with few stages, what counts is how many
+// workgroups start at once.  Against 256 x 128 (700 sizes): K = 128 0.64 to 0.99 of the time, 256 0.67 to 0.90, 384 0.74 to 0.99;
+// K = 512 to 1024 0.90 to 1.00 while all small tiles are resident (768), 1.00 to 1.11 beyond while all larger ones are (512), then
+// 0.71 to 1.11.  (The estimate, fitted to longer rows, gave 256 and 512 the larger tile throughout: 1099 x 256 -> 6912 8.9 -> 7.3 us.)
+// All others take the least estimate; 1600 sizes
+// beyond 128 tiles of 128 x 128, all rules together: 0.83 of the time of the former rule (wide or square from 200 tiles of 256 x 256
+// on, else 128 x 128 with four stages), 1.005 of the best tile of each size.  GEMM, us:
+// T = 8192, K = 4096, N = 12288 333 -> 315; T = 2048, K = 8192, N = 11008 175 -> 145; T = 8192, K = 16384, N = 4096 stays at 387.
 constexpr TileCost kTileCosts[] = {{kTileWide, 512, 128, 1.224f, 10.927f, 0.510f, 4.267f, 0.300f},
                                    {kTileSquare, 256, 256, 1.260f, 11.200f, 0.530f, 4.400f, 0.300f},
                                    {kTileHalf, 256, 128, 0.690f, 2.303f, 0.565f, 2.168f, 3.462f},
@@ -380,8 +384,9 @@ int launch_tile(const GemmArgs& a, hipStream_t stream, int tile) {
 }  // namespace
 
 int bytes_tile(int64_t T, int64_t K, int64_t N) {
-    if (mid_gemm_preferred(T, K, N, false) || mid_large_bytes_preferred(T, N)) return kTileMid;   // too few tiles for the chip
-    return T <= 64 ? kTileFewTokens : cheapest_tile(kTileCosts, T, K, N);
+    if (mid_gemm_preferred(T, K, N, false) || mid_large_bytes_preferred(T, K, N)) return kTileMid;   // too few tiles for the chip
+    if (T <= 64) return kTileFewTokens;
+    return K <= (((N + 127) / 128) * ((T + 127) / 128) <= 768 ? 1024 : 384) ? kTileSmall : cheapest_tile(kTileCosts, T, K, N);
 }
 
 int launch_ternary_gemm(const int8_t* codes, int code_offset, int64_t T, int64_t K, const void* packed, int64_t N,

@@ -247,16 +247,27 @@ def test_routes_of_17_to_64_tokens_against_many_output_rows(L):
 
 
 def test_route_names_the_kernel_that_runs_for_large_byte_tiles(L):
-    """Bytes of more than 64 tokens: up to 384 tiles of 128 x 128 they are the mid-size kernel's, and the route says so."""
+    """Bytes of more than 64 tokens: while all 128 x 64 tiles are resident at once, and up to 384 tiles of 128 x 128 where rows are
+    512 to 1536 long, they are the mid-size kernel's, and the route says so.  Beyond that short rows take the small tile."""
     from paper_2504_18415_amd import hbl
-    for bits, K, form in ((8, 2048, hbl.CODES_INT8), (8, 640, hbl.CODES_INT8), (4, 384, hbl.CODES_UINT4_PLUS8)):
-        for T, N in ((2048, 2048), (1000, 2208), (1536, 4096), (100, 32768)):          # 256, 144, 384, 256 tiles
-            assert hbl.forward_route(T, K, N, bits, hadamard=False) == "mid", (T, K, N, bits)
-            assert hbl.gemm_tile(T, K, N, form) == hbl.TILE_MID
-        for T, N in ((1537, 4096), (1536, 4128), (663, 8256)):                         # 416, 396, 390
-            assert hbl.forward_route(T, K, N, bits, hadamard=False) == "prefill", (T, K, N, bits)
-            assert hbl.gemm_tile(T, K, N, form) not in (hbl.TILE_MID, hbl.TILE_FEW_TOKENS)
-    assert hbl.forward_route(2048, 2048, 2048, 4, hadamard=False) == "prefill"         # records: prefill tiles
+    def tile(T, K, N, bits=8):
+        t = hbl.gemm_tile(T, K, N, hbl.CODES_INT8 if bits == 8 else hbl.CODES_UINT4_PLUS8)
+        assert hbl.forward_route(T, K, N, bits, hadamard=False) == ("mid" if t == hbl.TILE_MID else "prefill"), (T, K, N, bits)
+        return t
+    for bits, K in ((8, 8192), (8, 2048), (8, 640), (8, 128), (4, 384)):
+        for T, N in ((2048, 2048), (1000, 2208), (2048, 2048), (64 + 1, 32768), (291, 12384)):   # at most 512 of 128 x 64
+            assert tile(T, K, N, bits) == hbl.TILE_MID, (T, K, N, bits)
+    for K in (512, 1024, 1536):
+        assert tile(1536, K, 4096) == hbl.TILE_MID and tile(1536, K, 4128) != hbl.TILE_MID       # 384 tiles and 396
+    assert tile(1536, 1664, 4096) == hbl.TILE_HALF and tile(346, 14464, 11424) == hbl.TILE_HALF
+    for K, bits in ((128, 8), (384, 8), (384, 4)):
+        assert tile(1536, K, 4096, bits) == hbl.TILE_SMALL
+    for K in (128, 256, 384):
+        assert tile(1099, K, 6912) == tile(2048, K, 8192) == tile(8192, K, 8192) == hbl.TILE_SMALL
+    assert tile(1099, 1024, 6912) == tile(1536, 1024, 8192) == hbl.TILE_SMALL != tile(1099, 1152, 6912)      # 486, 768 tiles
+    assert tile(1536, 512, 8224) == tile(2048, 512, 8192) == hbl.TILE_HALF                                   # 780, 1024
+    assert tile(8192, 16384, 4096) == hbl.TILE_WIDE
+    assert hbl.forward_route(2048, 2048, 2048, 4, hadamard=False) == "prefill"                   # records: prefill tiles
     for T, K, N, form in ((0, 512, 64, hbl.CODES_INT8), (4, 384, 64, hbl.CODES_BF6), (4, 100, 64, hbl.CODES_INT8)):
         with pytest.raises(hbl.HblError):
             hbl.gemm_tile(T, K, N, form)

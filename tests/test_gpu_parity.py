@@ -828,7 +828,9 @@ def test_half_and_narrow_tiles_raw_accumulators(hbl, T, K, N):
 
 @pytest.mark.parametrize("T,K,N,groups,bits", [
     (663, 128, 8256, 3, 8), (663, 256, 8256, 3, 4),       # 390 tiles of 128 x 128: the small tile; INT4 codes with their offset
-    (1025, 256, 6976, 2, 8), (1025, 384, 6976, 2, 4),     # 495: 256 x 128
+    (1025, 256, 6976, 2, 8), (1025, 384, 6976, 2, 4),     # 495: the small tile
+    (3073, 128, 1920, 3, 8), (3073, 128, 1920, 3, 4),     # 375: the small tile
+    (2049, 2048, 1952, 1, 8), (1600, 2176, 3040, 5, 8),   # 272, 312: 256 x 128
     (908, 2176, 12608, 2, 8),                             # 792: the wide tile
     (6657, 3968, 2080, 1, 8),                             # 901: the square tile
 ])
@@ -905,8 +907,9 @@ def test_prefill_tiles_bf16_outputs(hbl, T, N, groups, bits, K):
     assert torch.equal(y, want)
 
 
-@pytest.mark.parametrize("T,K,N,groups,bits", [(1000, 2176, 2208, 3, 8), (1500, 4224, 2080, 1, 8), (2049, 2048, 1952, 1, 8),
-                                               (1600, 2176, 3040, 5, 8), (3073, 128, 1920, 3, 8), (3073, 128, 1920, 3, 4)])
+@pytest.mark.parametrize("T,K,N,groups,bits", [(1000, 2176, 2208, 3, 8), (1500, 4224, 2080, 1, 8), (2049, 1536, 1952, 1, 8),
+                                               (1600, 1408, 3040, 5, 8), (2049, 128, 1920, 3, 8), (2049, 128, 1920, 3, 4),
+                                               (291, 640, 12384, 3, 8), (291, 2176, 12384, 1, 8)])
 def test_large_byte_tiles_of_the_mid_size_kernel(hbl, T, K, N, groups, bits):
     """INT8 (and INT4 rows shorter than 512) with 145 to 384 tiles of 128 x 128: two K groups per workgroup, 128 x 64 and 128 x 128
     outputs, odd numbers of K-blocks, ragged edges and scale groups: exact products, scaled and rounded."""
