@@ -47,11 +47,14 @@ __global__ __launch_bounds__(64 * WAVES_N * WAVES_T, TN * TT <= 8 ? 2 : 1) void 
     const int wt = wave / WAVES_N;
 
     // Workgroups are dealt round-robin over the 8 XCDs; give each XCD a contiguous run of tiles
-    // (feature tile fastest) so that the workgroups sharing an activation panel share an L2.  (The runs may differ by a tile.)
+    // (feature tile fastest) so that the workgroups sharing an activation panel share an L2.  Where the runs would differ by a
+    // tile and the codes (T K bytes) are not the larger operand (weights N K / 4), or rows are of one or two stages, the plain
+    // order is the better one.  (720 sizes of 128 x 128 and 256 x 128 tiles, time against the better order of each: K up to 256 runs
+    // 1.02 to 1.04, plain 1.003; K above, runs 1.003 and plain 1.011, by this rule 1.002.  1724 x 128 -> 15968 17.6 -> 15.3 us.)
     int wg = blockIdx.x;
     const int nwg = a.tiles_n * a.tiles_t;
     const int xcd = wg & 7, extra = nwg & 7;
-    wg = xcd * (nwg >> 3) + (xcd < extra ? xcd : extra) + (wg >> 3);
+    if (extra == 0 || (a.K > 256 && 4 * (int64_t)a.T > a.N)) wg = xcd * (nwg >> 3) + (xcd < extra ? xcd : extra) + (wg >> 3);
     const int tile_n = wg % a.tiles_n;
     const int tile_t = wg / a.tiles_n;
     const int n0 = tile_n * BN;
