@@ -193,15 +193,22 @@ int dispatch(const void* x, int x_dtype, int64_t T, int bits, RowParams rp, bool
 }
 
 // Rows of several projections in one grid (small-batch path): workgroup -> (problem, row), then the body the stand-alone launch
-// would run for that problem (16 values per thread for large transformed rows).  A body that needs fewer threads than the
-// workgroup has runs on the first waves only; the other waves end at once, and a workgroup barrier waits only for waves
-// that have not ended.
-constexpr int grouped_row_threads(int64_t K, bool hadamard) {
+// would run for that problem.  A body that needs fewer threads than the workgroup has runs on the first waves only; the other
+// waves end at once, and a workgroup barrier waits only for waves that have not ended.
+// MANY: more than 256 rows of more than 4096 features, so that a CU gets more than one of them: fewer waves of more values, as in the
+// stand-alone launches - 32 values a thread for transformed rows of 8192 and 16384, four waves (eight beyond 8192) for plain rows.
+// Time against the other form, whole calls (bf16 and fp32, with the norm and without): 257 to 512 plain rows of 4224 to 8192
+// 0.82 to 0.99, of 11008 to 16384 0.87 to 1.01; transformed rows of 16384 INT4 0.88 to 0.95, INT8 0.97 to 1.02, of 8192 0.96 to 1.03.
+// Up to 256 such rows 0.95 to 1.03; with short rows beside them up to 1.07.
+constexpr int64_t kManyGroupedRows = 256;
+
+constexpr int grouped_row_threads(int64_t K, bool hadamard, bool many) {
+    if (many) return K <= 8192 ? 256 : 512;
     return K <= 4096 ? 256 : (hadamard && K == 8192 ? 512 : 1024);
 }
 
-template <int BITS, bool BF16>
-__global__ __launch_bounds__(1024) void quant_grouped_kernel(const QuantGroupArgs a) {
+template <int BITS, bool BF16, bool MANY>
+__global__ __launch_bounds__(MANY ? 512 : 1024, 4) void quant_grouped_kernel(const QuantGroupArgs a) {
     extern __shared__ __attribute__((aligned(16))) float row_lds[];
     const QuantProblem p = a.p[group_index_of(a.row_begin, a.n, (int)blockIdx.x)];
     const int64_t row = (int)blockIdx.x - p.row_begin;
@@ -210,9 +217,23 @@ __global__ __launch_bounds__(1024) void quant_grouped_kernel(const QuantGroupArg
     if (!p.hadamard) {
 #define HBL_PLAIN_ROW(MAXC, NW) \
     quant_generic_body<BITS, BF16, MAXC, kRecordBlockBytes, NW>(row, tid, p.x, p.K, p.codes, p.s_dequant, p.code_sum, rp, p.code_offset)
-        if (p.K > 8192) HBL_PLAIN_ROW(2, 16);
-        else if (p.K > 4096) HBL_PLAIN_ROW(1, 16);
-        else if (tid < 256) {
+        if (p.K > 8192) {
+            if constexpr (MANY) {
+                if (p.K > 12288) HBL_PLAIN_ROW(4, 8);
+                else HBL_PLAIN_ROW(3, 8);
+            } else {
+                HBL_PLAIN_ROW(2, 16);
+            }
+        } else if (p.K > 4096) {
+            if constexpr (MANY) {
+                if (tid < 256) {
+                    if (p.K > 6144) HBL_PLAIN_ROW(4, 4);
+                    else HBL_PLAIN_ROW(3, 4);
+                }
+            } else {
+                HBL_PLAIN_ROW(1, 16);
+            }
+        } else if (tid < 256) {
             if (p.K > 2048) HBL_PLAIN_ROW(2, 4);
             else HBL_PLAIN_ROW(1, 4);
         }
@@ -224,18 +245,18 @@ __global__ __launch_bounds__(1024) void quant_grouped_kernel(const QuantGroupArg
         if (tid < 64)                                                                                         \
             fwht_quant_body<L2K, 1, BITS, BF16, true>(row, tid, p.x, p.codes, p.s_dequant, p.code_sum, rp, p.code_offset); \
         return;
-#define HBL_BIG_ROW(L2K)                                                                                      \
+#define HBL_BIG_ROW(L2K, R)                                                                                   \
     case 1 << L2K:                                                                                            \
-        if (tid < LargeRow<L2K, 4>::NT) {                                                                     \
-            LargeRowRaw<4, BF16> raw;                                                                         \
-            large_row_load<L2K, 4, BF16>(p.x, row, tid, raw);                                                 \
+        if (tid < LargeRow<L2K, R>::NT) {                                                                     \
+            LargeRowRaw<R, BF16> raw;                                                                         \
+            large_row_load<L2K, R, BF16>(p.x, row, tid, raw);                                                 \
             if constexpr (BITS == 4) {                                                                        \
                 if (p.code_offset == kCodesBf6) {                                                             \
-                    large_row_body<L2K, 4, 4, BF16, true, true>(row, tid, raw, row_lds, p.codes, p.s_dequant, p.code_sum, rp, 8); \
+                    large_row_body<L2K, R, 4, BF16, true, true>(row, tid, raw, row_lds, p.codes, p.s_dequant, p.code_sum, rp, 8); \
                     return;                                                                                   \
                 }                                                                                             \
             }                                                                                                 \
-            large_row_body<L2K, 4, BITS, BF16, false, true>(row, tid, raw, row_lds, p.codes, p.s_dequant, p.code_sum, rp, p.code_offset); \
+            large_row_body<L2K, R, BITS, BF16, false, true>(row, tid, raw, row_lds, p.codes, p.s_dequant, p.code_sum, rp, p.code_offset); \
         }                                                                                                     \
         return;
     switch (p.K) {
@@ -243,39 +264,49 @@ __global__ __launch_bounds__(1024) void quant_grouped_kernel(const QuantGroupArg
         HBL_SMALL_ROW(8)
         HBL_SMALL_ROW(9)
         HBL_SMALL_ROW(10)
-        HBL_BIG_ROW(11)
-        HBL_BIG_ROW(12)
-        HBL_BIG_ROW(13)
-        HBL_BIG_ROW(14)
+        HBL_BIG_ROW(11, 4)
+        HBL_BIG_ROW(12, 4)
+        HBL_BIG_ROW(13, (MANY ? 5 : 4))
+        HBL_BIG_ROW(14, (MANY ? 5 : 4))
         default: return;
     }
 #undef HBL_SMALL_ROW
 #undef HBL_BIG_ROW
 }
 
+template <int BITS, bool BF16, bool MANY>
+int launch_grouped_kernel(const QuantGroupArgs& args, int rows, int threads, size_t lds, hipStream_t stream) {
+    constexpr auto kern = quant_grouped_kernel<BITS, BF16, MANY>;
+    if (const int rc = allow_dynamic_lds<kern, 64 * 1024>(); rc != HBL_OK) return rc;
+    launch_kernel("quant_grouped_kernel", kern, dim3((unsigned)rows), dim3((unsigned)threads), lds, stream, args);
+    return after_launch();
+}
+template <int BITS, bool BF16>
+int launch_grouped_rows(const QuantGroupArgs& args, hipStream_t stream) {
+    int rows = 0, large = 0, threads = 256;
+    size_t lds = 0;
+    for (int i = 0; i < args.n; ++i) {
+        rows += args.p[i].T;
+        if (args.p[i].K > 4096) large += args.p[i].T;
+    }
+    const bool many = large > kManyGroupedRows;
+    for (int i = 0; i < args.n; ++i) {
+        const QuantProblem& p = args.p[i];
+        if (p.hadamard && p.K >= 2048 && sizeof(float) * (size_t)p.K > lds) lds = sizeof(float) * (size_t)p.K;
+        const int need = grouped_row_threads(p.K, p.hadamard != 0, many);
+        if (need > threads) threads = need;
+    }
+    if (rows == 0) return HBL_OK;
+    return many ? launch_grouped_kernel<BITS, BF16, true>(args, rows, threads, lds, stream)
+                : launch_grouped_kernel<BITS, BF16, false>(args, rows, threads, lds, stream);
+}
+
 }  // namespace
 
 int launch_quant_grouped(const QuantGroupArgs& args, int bits, int x_dtype, hipStream_t stream) {
-    int rows = 0;
-    size_t lds = 0;
-    int threads = 256;
-    for (int i = 0; i < args.n; ++i) {
-        const QuantProblem& p = args.p[i];
-        rows += p.T;
-        if (p.hadamard && p.K >= 2048 && sizeof(float) * (size_t)p.K > lds) lds = sizeof(float) * (size_t)p.K;
-        if (grouped_row_threads(p.K, p.hadamard != 0) > threads) threads = grouped_row_threads(p.K, p.hadamard != 0);
-    }
-    if (rows == 0) return HBL_OK;
     const bool bf = x_dtype == HBL_BF16;
-    auto launch = [&](auto bits_tag, auto bf_tag) -> int {
-        constexpr auto kern = quant_grouped_kernel<decltype(bits_tag)::value, decltype(bf_tag)::value>;
-        if (const int rc = allow_dynamic_lds<kern, 64 * 1024>(); rc != HBL_OK) return rc;
-        launch_kernel("quant_grouped_kernel", kern, dim3((unsigned)rows), dim3((unsigned)threads), lds, stream, args);
-        return after_launch();
-    };
-    using std::integral_constant;
-    if (bits == 8) return bf ? launch(integral_constant<int, 8>{}, std::true_type{}) : launch(integral_constant<int, 8>{}, std::false_type{});
-    return bf ? launch(integral_constant<int, 4>{}, std::true_type{}) : launch(integral_constant<int, 4>{}, std::false_type{});
+    if (bits == 8) return bf ? launch_grouped_rows<8, true>(args, stream) : launch_grouped_rows<8, false>(args, stream);
+    return bf ? launch_grouped_rows<4, true>(args, stream) : launch_grouped_rows<4, false>(args, stream);
 }
 
 int launch_fwht_only(const void* x, int x_dtype, int64_t T, int64_t K, void* out, int out_dtype, hipStream_t stream) {

@@ -1070,6 +1070,32 @@ def test_grouped_quantiser_workgroup_sizes(hbl, bits, lengths):
 
 
 @pytest.mark.parametrize("bits", [4, 8])
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("lengths", [((8192, True),) * 5, ((16384, True),) * 5, ((4224, False), (6144, False), (6272, False), (8192, False), (4352, False)),
+                                     ((8320, False), (12288, False), (12416, False), (16384, False), (11008, False)),
+                                     ((16384, True), (8192, True), (640, False), (5504, False), (2048, True), (16256, False), (11008, False), (128, True))])
+def test_grouped_quantiser_beyond_256_large_rows(hbl, lengths, dtype, bits):
+    """More than 256 rows above 4096 features in one grouped launch - 32 values a thread, four and eight waves a row, every number of
+    slots, shorter rows beside them - bit for bit the outputs of the same group of few rows, with the norm and without."""
+    note(f"grouped quantiser, many rows {lengths} {dtype} bits={bits}")
+    g = torch.Generator(device="cuda").manual_seed(len(lengths) + lengths[0][0])
+    T, N, one = 64, 64, torch.ones(1, device="cuda")
+    items = []
+    for i, (K, hadamard) in enumerate(lengths):
+        packed = hbl.pack_ternary_2bit(torch.randint(-1, 2, (N, K), dtype=torch.int8, device="cuda", generator=g))
+        x = torch.randn((T, K), device="cuda", generator=g)
+        x[:, 7] *= 40
+        norm = (torch.rand(K, device="cuda", generator=g) + 0.5, 1e-6) if i % 2 else ()
+        items.append((x.to(dtype), packed, N, one, bits, hadamard, None, *norm))
+    assert sum(T for K, _ in lengths if K > 4096) > 256
+    ys = hbl.bitlinear_forward_grouped(items, EPS)
+    for it, y in zip(items, ys):
+        for t in range(0, T, 16):
+            few = (it[0][t:t + 16], *it[1:])
+            assert torch.equal(hbl.bitlinear_forward_grouped([few], EPS)[0], y[t:t + 16]), (it[0].shape, it[5])
+
+
+@pytest.mark.parametrize("bits", [4, 8])
 @pytest.mark.parametrize("dtype", [synth.BF16, synth.F32])
 def test_kernels_with_more_than_48_kib_of_lds(hbl, bits, dtype):
     """Each of the grouped quantisers on rows of 64 KiB, and 16 rows of 2048 in one launch (256 bytes beyond 48 KiB)."""
