@@ -293,11 +293,12 @@ __device__ __forceinline__ void large_row_body(int64_t row, uint32_t tid, const 
             if (code_sum) isum += (int)(bits - as_u(magic));
         }
         __syncthreads();
-        // (non-temporal, as the transform's outputs: 8192 rows of 16384 82.5 -> 76.6 us, 1024 of 16384 13.6 -> 11.9; the records,
-        // whose pieces are no whole lines, gain nothing that way and the GEMM behind them ran 10 % slower)
+        // (Plain stores: the GEMM reads the codes next.  With the non-temporal hint the launch alone is 5 to 12 % faster - 8192 rows of
+        // 16384 82.5 -> 76.6 us - but the call is not: 0.98 to 1.02 with it from 1024 output rows on, 1.02 to 1.34 below - 64 rows of
+        // 16384 against 32 output rows 13.7 -> 18.4.  Only 6 to 8 MiB of codes gain, 1 to 7 %.)
 #pragma unroll
         for (int i = 0; i < E / 16; ++i)
-            store_stream16(codes + row * K + (tid + NT * i) * 16, reinterpret_cast<const uint4*>(row_lds)[L::slot((tid + NT * i) * 16) >> 4]);
+            *reinterpret_cast<uint4*>(codes + row * K + (tid + NT * i) * 16) = reinterpret_cast<const uint4*>(row_lds)[L::slot((tid + NT * i) * 16) >> 4];
     } else {
         // The codes as fp32 integers (adding and removing 1.5 * 2^23 also turns -0 into +0) have at most four significant bits:
         // the upper half of the register is the same number in bf16.  It goes to LDS by feature, and the thread of a record
