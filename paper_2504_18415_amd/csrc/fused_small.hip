@@ -243,15 +243,18 @@ int launch_cfg(FusedArgs a, const FusedLayout& l, hipStream_t stream) {
 //     8192  1: 0.72-0.96
 //   32 rows, plain:  one token 3: 0.78-0.87 and 4: 0.83-0.99 (64 rows: 0.79-0.94);  two tokens 1: 0.66-0.80  1.5: 0.76-0.92 (64 rows:
 //     0.75-0.91);  three 1: 0.70-0.89  2: 0.92-1.04 (512: 1.12);  four 1: 0.81-0.91  1.5: 1.04-1.20
+//   one plain token beyond 4096:  up to 8192 features by eight waves, 16 rows 1: 0.50-0.56, 32 rows 1: 0.49-0.63  2: 0.60-0.77 (two of
+//     16 waves do not share a CU: 1 x 4224 -> 16384 6.6 us with them, 5.4 by eight, 8.9 by two launches);  above, 16 rows 1: 0.49-0.58
+//     2 (bf16 rows of at most 9728 have room for two): 0.83-0.92
 //   64 rows, plain:  two tokens 1: 0.75-0.91  2: 0.88-0.98 (512: 1.07);  three 1.5: 1.09-1.32;  four 1: 1.06-1.31
 // Four plain rows of at most 512 features (0.89-0.95), and 32 rows for four of at most 1024 (0.82-0.87), are left to the two
 // launches: less than a microsecond, and more than one workgroup per CU is a loss from there on.
 // (1 x 4096 -> 4096 transformed 6.3 us by two launches, 4.3 by one; 1 x 16384 -> 4096 9.9 and 7.5; 4 x 2048 -> 2048 6.3 and 4.6.)
 int most_workgroups_per_cu(int64_t T, int64_t K, bool hadamard, int rw) {
-    if (rw == 16) return hadamard || T < 4 || K > 512 ? 1 : 0;
+    if (rw == 16) return T == 1 && !hadamard && K > 8192 ? 2 : (hadamard || T < 4 || K > 512 ? 1 : 0);
     if (rw == 64) return T == 1 ? 4 : (T == 2 ? (K < 1024 ? 1 : 2) : 0);   // (plain rows only)
     if (!hadamard) {
-        if (T == 1) return K <= 4096 ? 3 : 1;
+        if (T == 1) return K <= 4096 ? 3 : 2;
         if (T == 3) return K >= 1024 ? 2 : 1;
         return T == 2 || K > 1024 ? 1 : 0;
     }
@@ -271,7 +274,7 @@ FusedPlan fused_plan(int64_t T, int64_t K, int64_t N, int x_dtype, bool hadamard
     if (hadamard) {
         while ((1 << p.log2k) < K) ++p.log2k;
     } else {
-        p.pw = K <= 4096 ? 4 : 16;
+        p.pw = K <= 4096 ? 4 : K <= 8192 ? 8 : 16;
     }
     if (T > kFusedRows || (T > 1 && K > (hadamard && T == 2 ? 8192 : 4096))) return p;
     p.rb = T == 1 ? 1 : (fused_row_waves(p.log2k, p.pw) > 1 ? (int)T : kFusedRows);
@@ -317,7 +320,9 @@ int launch_tokens(const FusedArgs& a, const FusedPlan& p, hipStream_t stream) {
 template <bool BF16>
 int launch_kind(const FusedArgs& a, const FusedPlan& p, hipStream_t stream) {
     switch (p.log2k) {
-        case 0: return p.pw == 4 ? launch_tokens<0, 4, BF16>(a, p, stream) : launch_tokens<0, 16, BF16>(a, p, stream);
+        case 0:
+            if (p.pw == 8) return launch_rows<0, 8, BF16, 1>(a, p, stream);
+            return p.pw == 4 ? launch_tokens<0, 4, BF16>(a, p, stream) : launch_tokens<0, 16, BF16>(a, p, stream);
         case 9: return launch_tokens<9, 0, BF16>(a, p, stream);
         case 10: return launch_tokens<10, 0, BF16>(a, p, stream);
         case 11: return launch_tokens<11, 0, BF16>(a, p, stream);

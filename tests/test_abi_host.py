@@ -218,6 +218,18 @@ def test_one_launch_only_where_it_is_no_slower(L):
         hbl.forward_route(0, 4096, 4096)
 
 
+def test_one_plain_token_of_more_than_4096_features(L):
+    """Rows of up to 8192 by eight waves, two workgroups of 32 output rows a CU; longer ones by sixteen, 16 rows, two where LDS has
+    room for them."""
+    from paper_2504_18415_amd import hbl
+    route = lambda K, N, dt=hbl.BF16: hbl.forward_route(1, K, N, 4, False, dt)
+    for dt in (hbl.BF16, hbl.F32):
+        assert route(4224, 16384, dt) == "fused" and route(4224, 16416, dt) == "stream"
+        assert route(5376, 12288, dt) == route(8192, 8192, dt) == "fused" and route(8192, 8224, dt) == "stream"
+        assert route(11008, 4096, dt) == route(16256, 4096, dt) == "fused" and route(11008, 4128, dt) != "fused"
+    assert route(8320, 8192) == "fused" and route(8320, 8224) != "fused" and route(8320, 4128, hbl.F32) != "fused"
+
+
 def test_single_calls_of_up_to_16_tokens_stream_or_not(L):
     """Long K ranges that few waves share: the mid-size kernel up to 128 workgroups of the streaming one, where it is the
     faster; beyond them records stream, bytes from 192 on."""

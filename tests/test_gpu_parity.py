@@ -699,6 +699,29 @@ def test_one_launch_small_batches(hbl, T, K, N, groups, hadamard, dtype):
     assert torch.equal(y[:T], want) and bool((y[T] == 7.0).all())
 
 
+@pytest.mark.parametrize("K,N,groups", [(4224, 96, 3), (4224, 16352, 1), (5120, 4128, 1), (6272, 8224, 1), (8192, 8192, 2), (8064, 64, 1),
+                                        (8320, 8160, 1), (9728, 4128, 3)])
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+def test_one_launch_one_long_plain_row(hbl, K, N, groups, dtype):
+    """One plain row of more than 4096 features by eight and by sixteen waves, one and two slots a thread, full and ragged, 16 and 32
+    output rows a workgroup, one and two workgroups a CU: bit for bit what the two stages give."""
+    note(f"one long plain row K={K} N={N} {dtype}")
+    if hbl.forward_route(1, K, N, 4, False, hbl._x_dtype(torch.empty(0, dtype=dtype))) != "fused":
+        assert dtype == torch.float32 and K > 6144 and N > 4096        # (an fp32 row leaves no room for two workgroups)
+        return
+    g = torch.Generator(device="cuda").manual_seed(K + N)
+    packed = hbl.pack_ternary_2bit(torch.randint(-1, 2, (N, K), dtype=torch.int8, device="cuda", generator=g))
+    x = torch.randn((1, K), device="cuda", generator=g)
+    x[:, 5] *= 40
+    x = x.to(dtype)
+    alpha = torch.rand(groups, device="cuda", generator=g) + 0.5
+    y = torch.full((2, N), 7.0, dtype=torch.bfloat16, device="cuda")         # a row that stays as it is
+    hbl.plain_bitlinear_forward(x, packed, N, alpha, 4, EPS, y=y[:1])
+    q, sd, cs = hbl.fwht_quant(x, 4, False, EPS, code_offset=hbl.CODES_BF6)
+    want = hbl.gemm_dequant_bf16(q, sd, cs, packed, N, alpha, code_offset=hbl.CODES_BF6, K=K)
+    assert torch.equal(y[:1], want) and bool((y[1] == 7.0).all())
+
+
 @pytest.mark.parametrize("T,K,N,groups,hadamard,bits,norm", [
     (1, 128, 32, 1, True, 4, False), (4, 128, 32768, 1, False, 8, False), (5, 256, 96, 3, True, 4, False),
     (8, 384, 16384, 1, False, 4, False), (9, 512, 8192, 1, True, 4, False), (16, 640, 160, 1, False, 4, False),
