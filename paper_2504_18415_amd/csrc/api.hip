@@ -107,7 +107,7 @@ void fill_decode_problem(DecodeProblem& dp, const Workspace& ws, int64_t T, int6
 
 Route forward_route(int64_t T, int64_t K, int64_t N, int x_dtype, int bits, bool hadamard, bool norm) {
     if (!norm && fused_small_preferred(T, K, N, x_dtype, bits, hadamard)) return Route::kFused;
-    if (fused_bytes_preferred(T, K, N, bits, hadamard)) return Route::kFusedBytes;
+    if (fused_bytes_preferred(T, K, N, bits, hadamard, norm)) return Route::kFusedBytes;
     // up to 16 tokens: the weight-streaming kernel, unless its plan leaves long serial chains of tiles
     if (decode_stream_preferred(T, K, N, bf6_path_supported(K, bits))) return Route::kStream;
     if (bf6_path_supported(K, bits) && decode_shared_preferred(T, K, N)) return Route::kStream;

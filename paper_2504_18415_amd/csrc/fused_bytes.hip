@@ -142,12 +142,21 @@ int launch_rows(const FusedBytesArgs& a, bool hadamard, hipStream_t stream) {
 // Plain rows of 2176 to 3584 (up to 56 values a lane): 0.56 to 0.95 on the near side (INT8, K = 3072, T = 8, N = 8192 4.91 for
 // 7.89; INT4 5.17 for 6.72), beyond it INT4 T = 5 to 8 0.91 to 1.07, T = 16 1.39 to 1.58, INT8 T = 16 1.09 to 1.23.  Rows of 4096:
 // INT4, T = 16 1.05 to 1.13 and spills; they stay two launches.
-bool fused_bytes_preferred(int64_t T, int64_t K, int64_t N, int bits, bool hadamard) {
+// The norm (double-precision squares, a reduction and the gains' loads) is repeated in every workgroup too.  With it, 2800 sizes: INT4
+// by values in all rows, 16 x 1536 0.80 to 0.88, 12 x 2560 0.89 to 0.96;  up to 4096 output rows and 8192, 9 x 3584 0.95 to 0.98 and 1.02,
+// 16 x 2048 0.97 to 1.02 and 1.06, 12 x 3072 0.94 to 0.98 and 1.03, 16 x 3072 1.02 to 1.11 and 1.15;  five to eight rows against 8224 to 16384 output rows, INT4: 1536 0.85 to 0.96, 2048 1.00 to 1.15,
+// transformed 1024 7 x 0.97, 8 x 1.03, INT8: 8 x 2560 0.93 to 0.97, 8 x 3072 1.00 to 1.03, 8 x 3584 1.04 to 1.08;  transformed rows of
+// 2048, INT4, five to eight: up to 4096 output rows 0.95 to 1.00, 8192 1.02 to 1.05.
+bool fused_bytes_preferred(int64_t T, int64_t K, int64_t N, int bits, bool hadamard, bool norm) {
     if (T > kFusedTokens || K > kFusedLength) return false;
-    if (K > 2048) return !hadamard && N / 32 <= (T <= 8 && bits == 8 ? 512 : 256);
-    if (K > 1024) return hadamard ? T <= 8 && N / 32 <= 256 : N / 32 <= (T <= 4 && bits == 8 ? 1024 : T <= 8 ? 512 : 256);
-    const int few = bits == 4 && K >= 512 && T * K >= 4096 ? 3 : 4;
-    return N / 32 <= (T <= few ? 1024 : T <= 8 ? 512 : 256);
+    const int64_t values = T * K;
+    if (norm && bits == 4 && (values > (N > 4096 ? 31744 : 36864) || (hadamard && K > 1024 && T > 4 && N > 4096))) return false;
+    const bool heavy = norm && (bits == 8 ? values > 23552 : K > 1536 || (hadamard && values > 7168));
+    const int64_t eight = heavy ? 256 : 512;   // workgroups for five to eight rows
+    if (K > 2048) return !hadamard && N / 32 <= (T <= 8 && bits == 8 ? eight : 256);
+    if (K > 1024) return hadamard ? T <= 8 && N / 32 <= 256 : N / 32 <= (T <= 4 ? (bits == 8 ? 1024 : 512) : T <= 8 ? eight : 256);
+    const int few = bits == 4 && K >= 512 && values >= 4096 ? 3 : 4;
+    return N / 32 <= (T <= few ? 1024 : T <= 4 ? 512 : T <= 8 ? eight : 256);
 }
 
 int launch_fused_bytes(const void* x, int x_dtype, int64_t T, int64_t K, const void* packed, int64_t N, const float* w_scales,

@@ -204,7 +204,7 @@ int launch_fused_small(const void* x, int x_dtype, int64_t T, int64_t K, const v
                        int64_t groups, float eps, bool hadamard, void* y, hipStream_t stream);
 
 // One-launch form for short rows and up to 16 tokens (fused_bytes.hip).
-bool fused_bytes_preferred(int64_t T, int64_t K, int64_t N, int bits, bool hadamard);
+bool fused_bytes_preferred(int64_t T, int64_t K, int64_t N, int bits, bool hadamard, bool norm);
 int launch_fused_bytes(const void* x, int x_dtype, int64_t T, int64_t K, const void* packed, int64_t N, const float* w_scales,
                        int64_t groups, int bits, float eps, bool hadamard, const float* ln_gain, float ln_eps, void* y,
                        hipStream_t stream);

@@ -218,6 +218,22 @@ def test_one_launch_only_where_it_is_no_slower(L):
         hbl.forward_route(0, 4096, 4096)
 
 
+def test_one_launch_for_short_rows_with_the_norm(L):
+    """With the norm every workgroup repeats more, so its lines lie closer; without it they are where they were."""
+    from paper_2504_18415_amd import hbl
+    one = lambda T, K, N, bits, had, norm: hbl.forward_route(T, K, N, bits, had, hbl.BF16, norm) == "fused_bytes"
+    for norm in (False, True):                                     # the same on both
+        for T, K, N, bits, had in ((16, 1920, 8192, 4, False), (12, 2560, 8192, 4, False), (9, 3456, 8192, 4, False), (8, 1536, 16384, 4, False),
+                                   (8, 2048, 8192, 4, False), (7, 1024, 16384, 4, True), (12, 3072, 4096, 4, False), (8, 2048, 4096, 4, True), (16, 3584, 8192, 8, False),
+                                   (8, 2944, 16384, 8, False), (5, 3584, 16384, 8, False), (3, 1024, 32768, 4, True), (16, 1024, 8192, 8, True),
+                                   (4, 2048, 16384, 4, False)):
+            if norm or not (T <= 4 and bits == 4):                 # (without the norm those are fused_small.hip's or two launches)
+                assert one(T, K, N, bits, had, norm), (T, K, N, bits, had, norm)
+    for T, K, N, bits, had in ((16, 2048, 4128, 4, False), (12, 2688, 4128, 4, False), (9, 3584, 4128, 4, False), (16, 2432, 32, 4, False), (8, 1664, 8224, 4, False),
+                               (8, 1024, 8224, 4, True), (5, 2048, 4128, 4, True), (8, 3072, 8224, 8, False)):   # up to 1.21 times the two launches
+        assert one(T, K, N, bits, had, False) and not one(T, K, N, bits, had, True), (T, K, N, bits, had)
+
+
 def test_one_plain_token_of_more_than_4096_features(L):
     """Rows of up to 8192 by eight waves, two workgroups of 32 output rows a CU; longer ones by sixteen, 16 rows, two where LDS has
     room for them."""
