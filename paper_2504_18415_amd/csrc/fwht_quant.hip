@@ -79,16 +79,26 @@ void launch_generic_slots(const void* x, int64_t T, int64_t K, RowParams rp, int
 //   1024 rows:  2 waves: 640 0.92 / 0.86  1152 0.94 / 0.89  1920 0.96 / 0.91  3072 0.95 / 0.88;  1 wave: 0.95 / 0.86  0.97 / 0.89  1.03 / 0.94  1.04 / 0.97
 //   3001 rows:  1 wave: 640 0.84 / 0.75  1152 0.87 / 0.77  1920 0.92 / 0.81  3072 0.93 / 0.83 (2 waves 0.93 / 0.86);  2 waves: 5504 1.04 / 0.99
 //   8192 rows:  1 wave: 384 0.60 / 0.50  1152 0.74 / 0.65  3072 0.95 / 0.81;  2 waves: 5504 1.00 / 0.95  8064 1.03 / 1.02
-// (fp32 rows, whose chunks are two loads each: 4096 of 3072 1.02 by one wave, and two as for fewer rows.)
-int generic_waves(int64_t T, int64_t K, bool bf16) {
+// Long rows and a finer look at the number of rows (2100 sizes; mean over 3 lengths each):
+//   INT4, 2048 to 2500 rows: 1792 to 3072 1 wave 0.97 to 1.05 (2 waves 0.93 to 0.98), 3200 to 3584 0.98 to 1.09 (0.98 to 1.02),
+//     3712 to 3968 1.03 to 1.14 (1.00 to 1.03);  2600 rows and more: 1792 to 3072 0.83 to 0.98, 3200 and above 0.98 to 1.10 (0.96 to 1.03)
+//   INT4, 1024 to 2000 rows, 2 waves: up to 3072 0.92 to 1.04, 3200 and above 0.98 to 1.12
+//   INT8 bf16 0.82 to 1.03 by 1 wave, from 2048 rows on, and by 2 waves before;  fp32, 3200 and above, 1.00 to 1.06
+//   with the norm, from 2048 rows on, 1 wave: INT8 0.60 to 1.00;  INT4 up to 3584 0.65 to 0.99, above 0.92 to 1.05 (2 waves 0.90 to 0.98)
+//   INT4, fp32 rows, whose chunks are two loads each, 1792 to 3072: 2 waves 0.92 to 1.00, 1.03 at 8192 rows
+template <int BITS>
+int generic_waves(int64_t T, int64_t K, bool bf16, bool norm) {
     if (K > 4096) return T <= 256 ? 16 : 4;
-    if (K <= 512 || (T >= 2048 && (bf16 || K <= 2048))) return 1;
+    if (K <= 512) return 1;
+    const bool records = BITS == 4 && !norm;   // (few other instructions to share, and more of them per value)
+    if (!norm && K > 3072 && (BITS == 4 || !bf16)) return 4;
+    if (T >= (records && K > 1536 ? 2560 : 2048) && (bf16 || K <= (records ? 1536 : 2048))) return BITS == 4 && K > 3584 ? 2 : 1;
     return T >= 1024 ? 2 : 4;
 }
 template <int BITS, bool BF16>
 void launch_generic_waves(const void* x, int64_t T, int64_t K, RowParams rp, int8_t* codes, float* s_dequant,
                           int32_t* code_sum, int code_offset, hipStream_t stream) {
-    switch (generic_waves(T, K, BF16)) {
+    switch (generic_waves<BITS>(T, K, BF16, rp.ln_gain != nullptr)) {
         case 1: return launch_generic_slots<BITS, BF16, 1>(x, T, K, rp, codes, s_dequant, code_sum, code_offset, stream);
         case 2: return launch_generic_slots<BITS, BF16, 2>(x, T, K, rp, codes, s_dequant, code_sum, code_offset, stream);
         case 4: return launch_generic_slots<BITS, BF16, 4>(x, T, K, rp, codes, s_dequant, code_sum, code_offset, stream);

@@ -1252,6 +1252,13 @@ def test_plain_rows_on_both_sides_of_the_wave_counts(hbl, K, T, dtype):
                 assert np.array_equal(c.cpu().numpy().astype(np.int32) - form, want.astype(np.int32))
 
 
+@pytest.mark.parametrize("K,T,dtype", [(1664, 2559, synth.BF16), (1664, 2560, synth.BF16), (1664, 2048, synth.F32), (1536, 2048, synth.F32),
+                                       (1664, 4097, synth.F32), (3200, 1024, synth.BF16), (3200, 2048, synth.BF16), (3712, 2048, synth.BF16)])
+def test_plain_rows_where_the_wave_count_changes_with_the_norm(hbl, K, T, dtype):
+    """The same at the lines that differ with the norm, the type and the length."""
+    test_plain_rows_on_both_sides_of_the_wave_counts(hbl, K, T, dtype)
+
+
 @pytest.mark.parametrize("K,T", [(2048, 300), (4096, 3), (8192, 256), (8192, 257), (16384, 256), (16384, 257)])
 @pytest.mark.parametrize("dtype", [synth.BF16, synth.F32])
 def test_large_rows_on_both_sides_of_the_split(hbl, K, T, dtype):
