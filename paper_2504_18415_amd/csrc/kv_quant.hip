@@ -25,9 +25,11 @@ __device__ __forceinline__ uint32_t quad_lane(uint32_t v) {   // value of one fi
     return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, CTRL, 0xF, 0xF, false);
 }
 
-// Head states read back leave with the non-temporal hint: written once and not read by the kernel, they need not stay in L2
-// until the launch ends and has to write them back (262144 rows of 128, 4 bits, both launches 30.1 -> 28.8 us; the packed codes
-// with the hint too 33.2: the next launch reads them).
+// Head states read back as bf16 leave with the non-temporal hint: written once and not read by the kernel, they need not stay in
+// L2 until the launch ends and has to write them back (262144 rows of 128, 4 bits, both launches 30.1 -> 28.8 us; the packed codes
+// with the hint too 33.2: the next launch reads them).  Not so fp32: a thread's 32 bytes leave by two instructions, each of which
+// covers half of every line, and without L2 to join them the launch takes up to 1.9 times as long (229272 rows of 128, 4 bits, 22.3
+// -> 41.9 us).
 __device__ __forceinline__ void store_stream(void* dst, uint32_t a, uint32_t b, uint32_t c, uint32_t d) {
     typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
     __builtin_nontemporal_store((u32x4){a, b, c, d}, reinterpret_cast<u32x4*>(dst));
@@ -154,8 +156,8 @@ __global__ __launch_bounds__(256) void kv_dequant_kernel(const uint8_t* __restri
             w[i] = __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2){v[2 * i], v[2 * i + 1]}, bf16x2));
         store_stream(reinterpret_cast<uint4*>(out) + t, w[0], w[1], w[2], w[3]);
     } else {
-        store_stream(reinterpret_cast<uint4*>(out) + 2 * t, as_u(v[0]), as_u(v[1]), as_u(v[2]), as_u(v[3]));
-        store_stream(reinterpret_cast<uint4*>(out) + 2 * t + 1, as_u(v[4]), as_u(v[5]), as_u(v[6]), as_u(v[7]));
+        reinterpret_cast<float4*>(out)[2 * t] = make_float4(v[0], v[1], v[2], v[3]);
+        reinterpret_cast<float4*>(out)[2 * t + 1] = make_float4(v[4], v[5], v[6], v[7]);
     }
 }
 
