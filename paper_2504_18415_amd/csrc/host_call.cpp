@@ -279,4 +279,11 @@ PyModuleDef module = {PyModuleDef_HEAD_INIT, "_host_call", nullptr, -1, methods,
 
 }  // namespace
 
-PyMODINIT_FUNC PyInit__host_call() { return PyModule_Create(&module); }
+PyMODINIT_FUNC PyInit__host_call() {
+    PyObject* m = PyModule_Create(&module);
+    if (m && PyModule_AddStringConstant(m, "built_for", HBL_BUILT_FOR) < 0) {   // torch's version
+        Py_DECREF(m);
+        return nullptr;
+    }
+    return m;
+}

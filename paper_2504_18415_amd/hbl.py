@@ -117,12 +117,14 @@ def lib():
 
 
 def _bind_native(L):
-    """The calls whose time on the host counts are marshalled natively where _host_call.so is built; what it declines, and
-    everything without it, goes the way below.  Both make the same library call."""
+    """The calls whose time on the host counts are marshalled natively where the module _host_call is built, for this torch; what
+    it declines, and everything without it, goes the way below.  Both make the same library call."""
     global _call
     try:
         from . import _host_call
     except ImportError:
+        return
+    if _host_call.built_for != torch.__version__:
         return
     _host_call.bind(*[ctypes.cast(f, ctypes.c_void_p).value for f in (
         L.hbl_hbitlinear_forward, L.hbl_plain_bitlinear_forward, L.hbl_ln_bitlinear_forward, L.hbl_bitlinear_forward_small,

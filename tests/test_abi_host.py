@@ -149,6 +149,68 @@ def test_binding_fails_loudly_without_library(monkeypatch, tmp_path):
         hbl.lib()
 
 
+@pytest.fixture()
+def build_in(monkeypatch, tmp_path):
+    """The build with its outputs under tmp_path and compilers that only write their output file; returns (module, commands run)."""
+    from paper_2504_18415_amd import build
+    ran = []
+
+    def run(cmd, verbose):
+        ran.append(cmd)
+        with open(cmd[cmd.index("-o") + 1], "w") as f:
+            f.write("built")
+    monkeypatch.setattr(build, "PKG", str(tmp_path))
+    monkeypatch.setattr(build, "OBJ_DIR", str(tmp_path / "_build"))
+    monkeypatch.setattr(build, "LIB", str(tmp_path / "libhbitlinear.so"))
+    monkeypatch.setattr(build, "HOST_CALL", str(tmp_path / os.path.basename(build.HOST_CALL)))
+    monkeypatch.setattr(build, "_run", run)
+    return build, ran
+
+
+def test_library_is_built_without_the_native_half(build_in, monkeypatch, tmp_path, capsys):
+    """The module is optional: where it cannot be compiled the library is linked all the same, and no module of another build stays."""
+    build, ran = build_in
+    run = build._run
+
+    def without_gxx(cmd, verbose):
+        if any("host_call" in word for word in cmd):
+            raise RuntimeError("no compiler")
+        run(cmd, verbose)
+    monkeypatch.setattr(build, "_run", without_gxx)
+    for old in ("_host_call.so", os.path.basename(build.HOST_CALL)):
+        (tmp_path / old).write_text("of another build")
+    assert build.build_library() == build.LIB and os.path.exists(build.LIB)
+    assert not [f for f in os.listdir(tmp_path) if "host_call" in f] and "no compiler" in capsys.readouterr().err
+    monkeypatch.setattr(build, "_host_call_command", lambda out: (_ for _ in ()).throw(ImportError("no torch")))
+    os.remove(build.LIB)
+    assert build.build_library(incremental=True) == build.LIB and os.path.exists(build.LIB)
+
+
+def test_native_half_is_built_again_for_another_torch(build_in, monkeypatch):
+    build, ran = build_in
+    hosts = lambda: sum(any("host_call" in word for word in cmd) for cmd in ran)
+    build.build_library()
+    assert hosts() == 1 and open(build.HOST_CALL).read() == "built"
+    build.build_library(incremental=True)
+    assert hosts() == 1                                                          # nothing changed
+    import torch
+    monkeypatch.setattr(torch, "__version__", "0.0.0+another")
+    build.build_library(incremental=True)
+    assert hosts() == 2
+    assert "cpython" in os.path.basename(build.HOST_CALL)                        # and another Python does not see this file
+
+
+def test_native_half_of_another_torch_is_not_used(L, monkeypatch):
+    from paper_2504_18415_amd import hbl, _host_call
+    monkeypatch.setattr(hbl, "_call", None)
+    monkeypatch.setattr(_host_call, "built_for", "0.0.0+another")
+    hbl._bind_native(L)
+    assert hbl._call is None
+    monkeypatch.undo()
+    hbl._bind_native(L)
+    assert hbl._call is _host_call
+
+
 def test_outputs_are_plain_tensors_whatever_the_input_is(L, monkeypatch):
     """Outputs that the binding allocates: plain tensors, also for a Parameter or another subclass."""
     torch = pytest.importorskip("torch")
