@@ -183,6 +183,12 @@ def _check_projection(T, K, N, Wq_packed, w_scales, y, workspace=None):
         raise ValueError("workspace must be a uint8 tensor")
 
 
+def _check_bytes(t, what, nbytes):
+    """Memory that a kernel reads or writes whole: a short buffer would make it go out of bounds on the device."""
+    if t.numel() * t.element_size() < nbytes:
+        raise ValueError(f"{what} needs {nbytes} bytes (got {t.dtype} {tuple(t.shape)})")
+
+
 def ternarize_weights_absmean(W: torch.Tensor, eps: float = EPS) -> Tuple[torch.Tensor, torch.Tensor]:
     """Eq. 1.  W [N,K] fp32 (device) -> (codes int8 [N,K], alpha fp32 [1]) on the device."""
     _dev_check(W)
@@ -459,6 +465,8 @@ def fwht(x: torch.Tensor, out_dtype: Optional[torch.dtype] = None, out: Optional
     T, K = x.shape
     if out is None:
         out = torch.empty((T, K), dtype=out_dtype or torch.float32, device=x.device)
+    else:
+        _check_bytes(out, "out", T * K * out.element_size())
     _check(lib().hbl_fwht(_ptr(x), _x_dtype(x), T, K, _ptr(out), _x_dtype(out), _stream()), "fwht")
     return out
 
@@ -536,13 +544,17 @@ def kv_quant_absmax(x: torch.Tensor, bits: int, eps: float = EPS, packed: Option
         r = _call.kv_quant(x, bits, eps)
         if r is not None:
             return r if type(r) is not int else _check(r, "kv_quant_absmax")
-    _dev_check(x)
+    _dev_check(x, packed, scales)
     rows, d = x.shape
     nbytes = lib().hbl_kv_packed_bytes(rows, d, bits)
     if packed is None:
         packed = torch.empty((rows, d * bits // 8) if nbytes or rows == 0 else (0,), dtype=torch.uint8, device=x.device)
+    else:
+        _check_bytes(packed, "packed", nbytes)
     if scales is None:
         scales = torch.empty(rows, dtype=torch.float32, device=x.device)
+    else:
+        _check_bytes(scales, "scales", 4 * rows)
     _check(lib().hbl_kv_quant_absmax(_ptr(x), _x_dtype(x), rows, d, bits, eps, _ptr(packed), _ptr(scales), _stream()),
            "kv_quant_absmax")
     return packed, scales
@@ -555,10 +567,13 @@ def kv_dequant(packed: torch.Tensor, scales: torch.Tensor, d: int, bits: int, ou
         r = _call.kv_dequant(packed, scales, d, bits, out_dtype is torch.bfloat16)
         if r is not None:
             return r if type(r) is not int else _check(r, "kv_dequant")
-    _dev_check(packed, scales)
+    _dev_check(packed, scales, out)
     rows = scales.shape[0]
+    _check_bytes(packed, "packed", lib().hbl_kv_packed_bytes(rows, d, bits))
+    _check_bytes(scales, "scales", 4 * rows)
     if out is None:
         out = torch.empty((rows, d), dtype=out_dtype, device=packed.device)
+    _check_bytes(out, "out", rows * d * (2 if out.dtype == torch.bfloat16 else 4))   # (any other type takes fp32)
     _check(lib().hbl_kv_dequant(_ptr(packed), _ptr(scales), rows, d, bits, _ptr(out),
                                 BF16 if out.dtype == torch.bfloat16 else F32, _stream()), "kv_dequant")
     return out

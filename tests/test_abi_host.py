@@ -211,6 +211,31 @@ def test_native_half_of_another_torch_is_not_used(L, monkeypatch):
     assert hbl._call is _host_call
 
 
+def test_short_arrays_never_reach_the_library(L, monkeypatch):
+    """Head states and transform into callers' arrays: what would be read or written out of range is refused before any launch."""
+    import torch
+    from paper_2504_18415_amd import hbl
+
+    class NoLaunch:
+        hbl_kv_packed_bytes = L.hbl_kv_packed_bytes
+
+        def __getattr__(self, name):
+            raise AssertionError(name + " was called")
+    monkeypatch.setattr(hbl, "_lib", NoLaunch())
+    monkeypatch.setattr(hbl, "_call", None)
+    monkeypatch.setattr(hbl, "_dev_check", lambda *ts: None)                    # (CPU tensors stand in for device ones)
+    x = torch.zeros(4, 64)
+    packed, scales = torch.zeros(4, 32, dtype=torch.uint8), torch.zeros(4)
+    for call in (lambda: hbl.kv_dequant(packed, scales, 64, 4, out_dtype=torch.float16),          # two bytes where four are written
+                 lambda: hbl.kv_dequant(packed, scales, 64, 4, out=torch.zeros(4, 32)), lambda: hbl.kv_dequant(packed[:3], scales, 64, 4),
+                 lambda: hbl.kv_dequant(packed, scales, 128, 4), lambda: hbl.kv_dequant(packed, scales.to(torch.bfloat16), 64, 4),
+                 lambda: hbl.kv_quant_absmax(x, 4, packed=packed[:3], scales=scales), lambda: hbl.kv_quant_absmax(x, 8, packed=packed),
+                 lambda: hbl.kv_quant_absmax(x, 4, scales=scales[:3]), lambda: hbl.kv_quant_absmax(x, 4, scales=scales.to(torch.bfloat16)),
+                 lambda: hbl.fwht(torch.zeros(4, 128), out=torch.zeros(3, 128))):
+        with pytest.raises(ValueError):
+            call()
+
+
 def test_outputs_are_plain_tensors_whatever_the_input_is(L, monkeypatch):
     """Outputs that the binding allocates: plain tensors, also for a Parameter or another subclass."""
     torch = pytest.importorskip("torch")
