@@ -12,11 +12,10 @@
 //   - gain = 127/(gamma+eps) or sqrt7/(beta+eps) with IEEE fp32 division,
 //     code = RoundClip(gain * x_r) with round-half-to-even.
 //
-// Index bits of a transformed row of K = CH*64*R*W < 2048 elements (from 2048 on: large_rows.h), low to high:
-//   [e: log2 CH in-thread][lane: 6][r: log2 R in-thread chunks][wave: log2 W]
+// Index bits of a transformed row of K = CH*64*R < 2048 elements, by one wave (from 2048 on: large_rows.h), low to high:
+//   [e: log2 CH in-thread][lane: 6][r: log2 R in-thread chunks]
 // so that every global access is one contiguous CH-element piece per lane and
-// the stage order e -> lane -> r -> wave is ascending.  The wave stages swap
-// the wave bits with the low r bits through LDS once, then run in registers.
+// the stage order e -> lane -> r is ascending.
 #include "large_rows.h"
 
 namespace hbl {
@@ -33,11 +32,8 @@ __global__ __launch_bounds__(64 * W) void fwht_quant_kernel(const void* __restri
 template <int LOG2K, int W, int BITS, bool BF16, bool HADAMARD>
 int launch_one(const void* x, int64_t T, int8_t* codes, float* s_dequant, int32_t* code_sum, RowParams rp,
                int code_offset, hipStream_t stream) {
-    constexpr int K = 1 << LOG2K;
-    constexpr size_t lds = (HADAMARD && W > 1) ? sizeof(float) * K : 0;
-    constexpr auto kern = fwht_quant_kernel<LOG2K, W, BITS, BF16, HADAMARD>;
-    if (const int rc = allow_dynamic_lds<kern, lds>(); rc != HBL_OK) return rc;
-    launch_kernel("fwht_quant_kernel", kern, dim3((unsigned)T), dim3(64 * W), lds, stream, x, codes, s_dequant, code_sum, rp, code_offset);
+    launch_kernel("fwht_quant_kernel", (fwht_quant_kernel<LOG2K, W, BITS, BF16, HADAMARD>), dim3((unsigned)T), dim3(64 * W), 0, stream, x,
+                  codes, s_dequant, code_sum, rp, code_offset);
     return after_launch();
 }
 

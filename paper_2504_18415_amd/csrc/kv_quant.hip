@@ -49,7 +49,7 @@ __global__ __launch_bounds__(256) void kv_quant_kernel(const void* __restrict__ 
         const int64_t t = t0 + 256 * k;
 #pragma unroll
         for (int q = 0; q < (BF16 ? 1 : 2); ++q) raw[k][q] = make_uint4(0, 0, 0, 0);
-        if (t < threads) {   // whole rows (and whole quads) are live or not: lanes_per_row divides 64
+        if (t < threads) {   // whole rows (and whole quads) are live or not: a row is a power of two of lanes
             if constexpr (BF16) {
                 raw[k][0] = reinterpret_cast<const uint4*>(x)[t];
             } else {
@@ -98,7 +98,7 @@ __global__ __launch_bounds__(256) void kv_quant_kernel(const void* __restrict__ 
             uint32_t w = 0;
 #pragma unroll
             for (int i = 0; i < 8; ++i) w |= u[i] << (4 * i);
-                        if (live) reinterpret_cast<uint32_t*>(packed)[t] = w;
+            if (live) reinterpret_cast<uint32_t*>(packed)[t] = w;
         } else {
             uint32_t w = 0;
 #pragma unroll

@@ -292,7 +292,7 @@ __device__ __forceinline__ void store_xr(void* out, int out_dtype, int64_t elem,
     }
 }
 
-// One token row per workgroup of 64*W threads; `row` and `tid` come from the caller so that the grouped
+// One token row per workgroup of 64*W threads (transformed rows: W = 1); `row` and `tid` come from the caller so that the grouped
 // launch (several projections' rows in one grid) can run the same body.
 template <int LOG2K, int W, int BITS, bool BF16, bool HADAMARD, int BLOCKB = kRecordBlockBytes>
 __device__ __forceinline__ void fwht_quant_body(int64_t row, int tid, const void* __restrict__ x,
@@ -304,12 +304,11 @@ __device__ __forceinline__ void fwht_quant_body(int64_t row, int tid, const void
     constexpr int E = K / NT;            // elements per thread
     constexpr int CH = E < 8 ? E : 8;    // contiguous elements per chunk
     constexpr int R = E / CH;            // chunks per thread
-    static_assert(E >= 1 && R >= 1 && (W == 1 || R >= W), "unsupported split");
+    static_assert(E >= 1 && R >= 1 && (W == 1 || !HADAMARD), "transformed rows belong to one wave");
 
     __shared__ double red_d[W];
     __shared__ float red_f[W];
     __shared__ int red_i[W];
-    extern __shared__ float exch[];      // K floats when HADAMARD && W > 1
 
     const int lane = tid & 63;
     const int wave = tid >> 6;
@@ -339,8 +338,6 @@ __device__ __forceinline__ void fwht_quant_body(int64_t row, int tid, const void
             for (int e = 0; e < CH; ++e) v[r][e] = (v[r][e] * rn) * gv[e];
         }
     }
-
-    bool exchanged = false;  // register slot r holds chunk g = wave*R + r until the LDS exchange
 
     if constexpr (HADAMARD) {
         // e bits
@@ -375,41 +372,6 @@ __device__ __forceinline__ void fwht_quant_body(int64_t row, int tid, const void
                         v[r + h][e] = a - b;
                     }
                 }
-        // wave bits: trade them for the low log2(W) bits of r through LDS
-        if constexpr (W > 1) {
-#pragma unroll
-            for (int r = 0; r < R; ++r) {
-                float* dst = exch + ((wave * R + r) * 64 + lane) * CH;
-#pragma unroll
-                for (int e = 0; e < CH; e += 4)
-                    *reinterpret_cast<float4*>(dst + e) = make_float4(v[r][e], v[r][e + 1], v[r][e + 2], v[r][e + 3]);
-            }
-            __syncthreads();
-            // slot j = r_hi*W + w2 now holds chunk g = w2*R + r_hi*W + wave
-#pragma unroll
-            for (int j = 0; j < R; ++j) {
-                const int w2 = j % W, r_hi = j / W;
-                const float* src = exch + ((w2 * R + r_hi * W + wave) * 64 + lane) * CH;
-#pragma unroll
-                for (int e = 0; e < CH; e += 4) {
-                    const float4 t = *reinterpret_cast<const float4*>(src + e);
-                    v[j][e] = t.x; v[j][e + 1] = t.y; v[j][e + 2] = t.z; v[j][e + 3] = t.w;
-                }
-            }
-            exchanged = true;
-#pragma unroll
-            for (int h = 1; h < W; h <<= 1)
-#pragma unroll
-                for (int j = 0; j < R; ++j)
-                    if ((j & h) == 0) {
-#pragma unroll
-                        for (int e = 0; e < CH; ++e) {
-                            const float a = v[j][e], b = v[j + h][e];
-                            v[j][e] = a + b;
-                            v[j + h][e] = a - b;
-                        }
-                    }
-        }
         // 1/sqrt(K), with the sign the lane stages left on this lane's values: (-1)^(set bits among position bits 0-3)
         const float c_n = (__builtin_popcount(pos & 15) & 1) ? -(float)(1.0 / sqrt((double)K)) : (float)(1.0 / sqrt((double)K));
 #pragma unroll
@@ -424,8 +386,7 @@ __device__ __forceinline__ void fwht_quant_body(int64_t row, int tid, const void
         static_assert(CH >= 2, "transform-only rows hold at least two elements per lane");
 #pragma unroll
         for (int r = 0; r < R; ++r) {
-            const int g = exchanged ? (r % W) * R + (r / W) * W + wave : wave * R + r;
-            store_xr<CH>(codes, code_offset, row_off + (int64_t)(g * 64 + pos) * CH, v[r]);
+            store_xr<CH>(codes, code_offset, row_off + (int64_t)((wave * R + r) * 64 + pos) * CH, v[r]);
         }
         return;
     }
@@ -492,13 +453,7 @@ __device__ __forceinline__ void fwht_quant_body(int64_t row, int tid, const void
 #pragma unroll
             for (int p = 0; p < (CH + 3) / 4; ++p) isum = __builtin_amdgcn_sdot4((int)packed[p], 0x01010101, isum, false);
         }
-        int g;
-        if (exchanged) {
-            const int w2 = r % W, r_hi = r / W;
-            g = w2 * R + r_hi * W + wave;
-        } else {
-            g = wave * R + r;
-        }
+        const int g = wave * R + r;
         int8_t* dst = codes + row_off + (int64_t)(g * 64 + pos) * CH;
         if constexpr (CH == 8) {
             if (bf6) bf6_store_pair<BLOCKB>(codes, row, K, g * 64 + pos, bf6_pack4(packed[0]), bf6_pack4(packed[1]));

@@ -190,9 +190,7 @@ __global__ __launch_bounds__(64 * WAVES_N * WAVES_T, TN * TT <= 8 ? 2 : 1) void 
         constexpr int READS = TN + 2 * TT;
         constexpr int SIDE = XL + WL > READS ? XL + WL : READS;
         constexpr bool FITS = SIDE <= NMF - 2;
-        // first expansion: after the last packed load, or, with more feature tiles, so early that tile i's (at most one tile
-        // per MFMA) still follows its load, behind MFMA i, by four
-        constexpr int FIRSTV = !FITS ? 0 : TN > 4 ? 4 : TN + 2 < NMF - 2 ? TN + 2 : NMF - 2;
+        constexpr int FIRSTV = !FITS ? 0 : TN + 2 < NMF - 2 ? TN + 2 : NMF - 2;   // first expansion: after the last packed load
         constexpr int VPER = (TOTAL + (NMF - FIRSTV) - 1) / (NMF - FIRSTV);
         const int nslot = slot + 1 == NSTAGE ? 0 : slot + 1;
         if (!FITS) {
