@@ -388,6 +388,19 @@ def test_route_names_the_kernel_that_runs_for_large_byte_tiles(L):
             hbl.gemm_tile(T, K, N, form)
 
 
+def test_tiles_of_code_records(L):
+    """At most two small workgroups a CU: one tile of 128 x 128 with four stages, then 192 x 128 with two or four, then 128 x 128 with
+    two; beyond that the least estimate, on both sides of where it changes."""
+    from paper_2504_18415_amd import hbl
+    tile = lambda T, K, N: hbl.gemm_tile(T, K, N, hbl.CODES_BF6)
+    assert tile(1000, 640, 2080) == hbl.TILE_SMALL and tile(512, 640, 2048) == hbl.TILE_MID
+    assert tile(2048, 640, 2048) == hbl.TILE_SMALL and tile(2049, 640, 2048) == hbl.TILE_NARROW                # 256 tiles and 272
+    assert tile(2049, 3072, 2048) == hbl.TILE_NARROW and tile(2049, 3200, 2048) == hbl.TILE_NARROW_DEEP
+    assert tile(2048, 640, 3072) == hbl.TILE_NARROW and tile(2048, 640, 3104) == hbl.TILE_SMALL_FLAT           # 256 of 192 x 128, 272
+    assert tile(2048, 512, 4096) == hbl.TILE_SMALL_FLAT and tile(4096, 512, 4096) == hbl.TILE_HALF             # 512, 1024
+    assert tile(8192, 16384, 4096) == tile(8192, 4096, 12288) == hbl.TILE_WIDE
+
+
 def test_kv_quant_argument_errors_before_any_launch(L):
     from paper_2504_18415_amd import hbl
     E = {n: getattr(hbl, n) for n in ("E_NULL", "E_SHAPE", "E_BITS", "E_DTYPE", "E_ALIGN")}

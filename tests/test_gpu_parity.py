@@ -849,19 +849,21 @@ def test_half_and_narrow_tiles_raw_accumulators(hbl, T, K, N):
         assert np.array_equal(got, want), f"fp6 x fp4 kernel, tile {tile}"
 
 
-@pytest.mark.parametrize("T,K,N,groups,bits", [
-    (663, 128, 8256, 3, 8), (663, 256, 8256, 3, 4),       # 390 tiles of 128 x 128: the small tile; INT4 codes with their offset
-    (1025, 256, 6976, 2, 8), (1025, 384, 6976, 2, 4),     # 495: the small tile
-    (3073, 128, 1920, 3, 8), (3073, 128, 1920, 3, 4),     # 375: the small tile
-    (2049, 2048, 1952, 1, 8), (1600, 2176, 3040, 5, 8),   # 272, 312: 256 x 128
-    (908, 2176, 12608, 2, 8),                             # 792: the wide tile
-    (6657, 3968, 2080, 1, 8),                             # 901: the square tile
+@pytest.mark.parametrize("T,K,N,groups,bits,tile", [
+    (663, 128, 8256, 3, 8, "SMALL"), (663, 256, 8256, 3, 4, "SMALL"),       # 390 tiles of 128 x 128; INT4 codes with their offset
+    (1025, 256, 6976, 2, 8, "SMALL"), (1025, 384, 6976, 2, 4, "SMALL"),     # 495
+    (3073, 128, 1920, 3, 8, "SMALL"), (3073, 128, 1920, 3, 4, "SMALL"),     # 375
+    (2049, 2048, 1952, 1, 8, "HALF"), (1600, 2176, 3040, 5, 8, "HALF"),     # 272, 312
+    (1025, 512, 11296, 1, 8, "HALF"),                                       # 801: ragged last tiles either way
+    (908, 2176, 12608, 2, 8, "WIDE"),                                       # 792
+    (6657, 3968, 2080, 1, 8, "SQUARE"),                                     # 901
 ])
-def test_prefill_byte_tile_rule(hbl, T, K, N, groups, bits):
+def test_prefill_byte_tile_rule(hbl, T, K, N, groups, bits, tile):
     """Every tile the rule for byte codes picks, ragged tokens and features, several scale groups: the integers through the half
     tile, and every output bit for bit as the exact product of the codes, scaled and rounded, gives it."""
-    note(f"prefill byte tile rule T={T} K={K} N={N} INT{bits}")
+    note(f"prefill byte tile rule T={T} K={K} N={N} INT{bits} {tile}")
     assert hbl.forward_route(T, K, N, bits, hadamard=False) == "prefill"
+    assert hbl.gemm_tile(T, K, N, hbl.CODES_INT8 if bits == 8 else hbl.CODES_UINT4_PLUS8) == getattr(hbl, "TILE_" + tile)
     g = torch.Generator(device="cuda").manual_seed(T + N + K)
     c = torch.randint(-1, 2, (N, K), dtype=torch.int8, device="cuda", generator=g)
     x = torch.randn((T, K), device="cuda", generator=g).to(torch.bfloat16)
@@ -876,22 +878,24 @@ def test_prefill_byte_tile_rule(hbl, T, K, N, groups, bits):
     assert torch.equal(y[:T], want) and bool((y[T] == 7.0).all())
 
 
-@pytest.mark.parametrize("T,K,N,groups", [
-    (1100, 512, 3936, 3),     # 279 tiles of 128 x 128, 189 of 192 x 128: the narrow tile, two stages
-    (1100, 3200, 3936, 3),    # ... four stages
-    (1900, 512, 3104, 1),     # 375 and 255: the last of them; the small tile from here on
-    (1921, 640, 3264, 3),     # 416 and 272: the small tile, two stages
-    (906, 512, 8384, 2),      # 528: the small tile
-    (2192, 512, 6944, 7),     # 990: half the wide tile
-    (3719, 640, 3232, 1),     # 780: the narrow tile
-    (3990, 2432, 3136, 2),    # 800: the square tile
-    (1677, 1792, 7008, 3),    # 770: the wide tile
+@pytest.mark.parametrize("T,K,N,groups,tile", [
+    (1000, 640, 2208, 3, "SMALL"),           # 144 tiles of 128 x 128, four stages
+    (1100, 512, 3936, 3, "NARROW"),          # 279, 189 of 192 x 128: two stages
+    (1100, 3200, 3936, 3, "NARROW_DEEP"),    # ... four stages
+    (1900, 512, 3104, 1, "NARROW"),          # 375 and 255: the last of them; the small tile from here on
+    (1921, 640, 3264, 3, "SMALL_FLAT"),      # 416 and 272: two stages
+    (906, 512, 8384, 2, "SMALL_FLAT"),       # 528
+    (2192, 512, 6944, 7, "HALF"),            # 990: half the wide tile
+    (3719, 640, 3232, 1, "NARROW"),          # 780
+    (3990, 2432, 3136, 2, "SQUARE"),         # 800
+    (1677, 1792, 7008, 3, "WIDE"),           # 770
 ])
-def test_prefill_tile_rule_bf16_outputs(hbl, T, K, N, groups):
+def test_prefill_tile_rule_bf16_outputs(hbl, T, K, N, groups, tile):
     """Every tile the rule for code records picks, ragged tokens and features, several scale groups: every output bit for bit as
     the exact product of the codes, scaled and rounded, gives it."""
-    note(f"prefill tile rule T={T} K={K} N={N}")
+    note(f"prefill tile rule T={T} K={K} N={N} {tile}")
     assert hbl.forward_route(T, K, N, 4, hadamard=False) == "prefill"
+    assert hbl.gemm_tile(T, K, N, hbl.CODES_BF6) == getattr(hbl, "TILE_" + tile)
     g = torch.Generator(device="cuda").manual_seed(T + N + K)
     c = torch.randint(-1, 2, (N, K), dtype=torch.int8, device="cuda", generator=g)
     x = torch.randn((T, K), device="cuda", generator=g).to(torch.bfloat16)
@@ -1599,13 +1603,45 @@ def test_native_calls_and_the_python_path_agree(hbl, monkeypatch):
         for a, b in zip(got, want):
             assert a.dtype == b.dtype and a.shape == b.shape and torch.equal(a, b)
     assert native.forward(0, x.t(), packed, N, al, 4, EPS, None, None) is None
+    # nothing to do: no rows, no head rows
+    empty = x[:0]
+    for call in (native, None):
+        monkeypatch.setattr(hbl, "_call", call)
+        assert hbl.hbitlinear_forward(empty, packed, N, al, 4, EPS).shape == (0, N)
+        assert hbl.ln_bitlinear_forward(empty, gain, 1e-6, True, packed, N, al, 4, EPS).shape == (0, N)
+        assert hbl.bitlinear_forward_small(empty, packed, N, al, y[:0], 4, True, EPS).shape == (0, N)
+        assert hbl.fwht(empty).shape == (0, K) and hbl.fwht(empty, out_dtype=torch.bfloat16).dtype == torch.bfloat16
+        p, s = hbl.kv_quant_absmax(empty, 4, EPS)
+        assert p.shape == (0, K // 2) and s.shape == (0,) and hbl.kv_dequant(p, s, K, 4).shape == (0, K)
+    monkeypatch.setattr(hbl, "_call", native)
     # the current stream: a busy default stream does not hold the call back, and its result is there on its own stream
-    side = torch.cuda.Stream()
-    side.wait_stream(torch.cuda.current_stream())
+    side, done = torch.cuda.Stream(), torch.cuda.Event()
+    torch.cuda.synchronize()
+    torch.cuda._sleep(50_000_000)                                            # half a second at 100 MHz, 25 ms at 2 GHz
+    done.record()
     with torch.cuda.stream(side):
         z = hbl.hbitlinear_forward(x, packed, N, al, 4, EPS)
+        same = (z == got[0]).all()
     side.synchronize()
-    assert torch.equal(z, got[0])
+    assert not done.query(), "the call waited for the default stream"
+    with torch.cuda.stream(side):
+        assert bool(same)
+    torch.cuda.synchronize()
+    # two threads, each on a stream and on rows of its own
+    import threading
+    inputs, outputs = [x, -2 * x], [None, None]
+    def work(i):
+        with torch.cuda.stream(torch.cuda.Stream()):
+            outputs[i] = [hbl.hbitlinear_forward(inputs[i], packed, N, al, 4, EPS) for _ in range(50)]
+            torch.cuda.current_stream().synchronize()
+    threads = [threading.Thread(target=work, args=(i,)) for i in range(2)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert all(torch.equal(o, got[0]) for o in outputs[0])
+    want = hbl.hbitlinear_forward(inputs[1], packed, N, al, 4, EPS)
+    assert all(torch.equal(o, want) for o in outputs[1])
     graph = torch.cuda.CUDAGraph()
     with torch.cuda.graph(graph):
         z = hbl.hbitlinear_forward(x, packed, N, al, 4, EPS)
