@@ -110,7 +110,8 @@ __device__ __forceinline__ uint2 dequant_quad(v4i acc, float sd, float alpha, in
 }
 
 // Time of a prefill launch by workgroup tile, us: the rounds of workgroups that the busiest CU runs (K-blocks and start-up with
-// output of each), or the tiles that the chip as a whole - its power limit - gets through, whichever is longer, and the launch.
+// output of each), or the tiles that the chip as a whole gets through (its power, where rounds are full and rows long), whichever
+// is longer, and the launch.
 // The figures are fits to measured times of each tile (the tables of the two kernels); a tile that was measured 2 % faster or
 // less is no reason to leave the widest one.
 struct TileCost {

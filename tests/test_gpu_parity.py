@@ -938,8 +938,8 @@ def test_prefill_tiles_bf16_outputs(hbl, T, N, groups, bits, K):
                                                (1600, 1408, 3040, 5, 8), (2049, 128, 1920, 3, 8), (2049, 128, 1920, 3, 4),
                                                (291, 640, 12384, 3, 8), (291, 2176, 12384, 1, 8)])
 def test_large_byte_tiles_of_the_mid_size_kernel(hbl, T, K, N, groups, bits):
-    """INT8 (and INT4 rows shorter than 512) with 145 to 384 tiles of 128 x 128: two K groups per workgroup, 128 x 64 and 128 x 128
-    outputs, odd numbers of K-blocks, ragged edges and scale groups: exact products, scaled and rounded."""
+    """INT8 (and INT4 rows shorter than 512) while all tiles of 128 x 64 are resident, and K = 512 to 1536 up to 384 tiles of 128 x 128:
+    two K groups per workgroup, 128 x 64 and 128 x 128 outputs, odd numbers of K-blocks, ragged edges and scale groups: exact products, scaled and rounded."""
     note(f"large byte tiles T={T} K={K} N={N} bits={bits}")
     g = torch.Generator(device="cuda").manual_seed(T + N + K)
     c = torch.randint(-1, 2, (N, K), dtype=torch.int8, device="cuda", generator=g)
